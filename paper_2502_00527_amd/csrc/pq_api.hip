@@ -45,6 +45,8 @@ ChunkPlan plan_chunks(int32_t n_seqs, int32_t n_kv_heads, int32_t max_seq_len) {
   ChunkPlan p;
   p.pages_per_chunk = ppc;
   p.n_chunks = static_cast<int32_t>((max_pages + ppc - 1) / ppc);
+  p.n_big = p.n_chunks;
+  p.pages_small = ppc;
   return p;
 }
 

@@ -3,8 +3,7 @@
 #include <algorithm>
 #include <mutex>
 
-#include "pq_decode_kernels.hpp"
-#include "pq_decode_roles.hpp"
+#include "pq_decode_matrix.hpp"
 
 // Scratch of pq_decode_attention_static: partials and arrival words live here instead of in a
 // caller-supplied workspace.  One copy per GPU, at its own address on each.
@@ -25,7 +24,7 @@ constexpr int kMergeSlices = kMergeThreads / 32;
 __global__ __launch_bounds__(kMergeThreads) void pq_decode_merge_kernel(
     const float* __restrict__ ws_acc, const float* __restrict__ ws_ml,
     const int32_t* __restrict__ seq_lens, float* __restrict__ out, int32_t n_q_heads,
-    int32_t max_seq_len, int32_t pages_per_chunk, int32_t n_chunks) {
+    int32_t max_seq_len, int32_t pages_per_chunk, int32_t n_chunks, int32_t n_big, int32_t pages_small) {
   __shared__ float4 part_o[kMergeSlices][32];
   __shared__ float part_l[kMergeSlices];
   __shared__ float wave_max[kMergeThreads / 64];
@@ -38,7 +37,7 @@ __global__ __launch_bounds__(kMergeThreads) void pq_decode_merge_kernel(
     return;
   }
   const int n_pages = (L + kGroup - 1) / kGroup;
-  const int nc = (n_pages + pages_per_chunk - 1) / pages_per_chunk;
+  const int nc = chunks_of_pages(n_pages, pages_per_chunk, n_big, pages_small);
   const float2* ml = reinterpret_cast<const float2*>(ws_ml) + oh * n_chunks;
   const float4* ac = reinterpret_cast<const float4*>(ws_acc + oh * n_chunks * kHeadDim) + quad;
 
@@ -82,8 +81,8 @@ __global__ __launch_bounds__(kMergeThreads) void pq_decode_merge_kernel(
   }
 }
 
-// Score-only kernels: uniform angle grid -> lanes are tokens (pq_score_tokens_kernel); grouped
-// quantizer -> the attention kernels' lane layout with a table per page (pq_score_keys_kernel).
+// Score-only kernels: the grouped quantizer has one of its own (a table per page); on the uniform grid
+// up to 4 query heads are served by the kernel whose lanes are tokens, 5 to 8 by the matrix kernel.
 template <int G, int RB, int TB, bool GA>
 void launch_scores_one(const DecodeArgs& a, dim3 grid, hipStream_t st) {
   if constexpr (GA) hipLaunchKernelGGL((pq_score_keys_kernel<G, RB, TB, true>), grid, dim3(kThreads), 0, st, a);
@@ -110,63 +109,54 @@ bool launch_scores_rt(int rt, int G, const DecodeArgs& a, dim3 grid, hipStream_t
     default: return false;
   }
 }
-bool launch_scores(int rt, bool grouped, int G, const DecodeArgs& a, dim3 grid, hipStream_t st) {
-  return grouped ? launch_scores_rt<true>(rt, G, a, grid, st) : launch_scores_rt<false>(rt, G, a, grid, st);
-}
 
-// Which attention kernel a launch gets.  The role-specialised kernel, whose work-groups share
-// the launch's pages out evenly and merge in the kernel, serves fp16 values with the uniform
-// angle grid when there is work for at least 256 work-groups; smaller launches stay with the
-// kernel whose four wavefronts share a chunk's pages four ways (measured: 9 against 12 us for one
-// head over 4096 tokens).
+// The name an attention launch of the uniform angle grid runs under: "roles" from 256 work-groups
+// on, "partials" below (and with quantized values at more than two query heads per KV head, and with
+// the grouped quantizer, which has a kernel of its own).
 enum class AttentionKernel { kPartials, kRoles };
 constexpr int kComputeUnits = 256;           // MI355X
+constexpr int kResidentGroups = 2 * kComputeUnits;   // work-groups of the attention and score kernels
 
-#ifndef PQ_BALANCED_MIN_PAGES
-#define PQ_BALANCED_MIN_PAGES 4
-#endif
-#ifndef PQ_BALANCED_GROUPS
-#define PQ_BALANCED_GROUPS (kComputeUnits * role_groups_per_cu(4))
-#endif
-constexpr int kBalancedMinPages = PQ_BALANCED_MIN_PAGES;   // smallest share of a work-group: two pages per wavefront pair
-#ifndef PQ_BALANCED_UNIT_COST
-#define PQ_BALANCED_UNIT_COST 2
-#endif
-constexpr int kBalancedUnitCost = PQ_BALANCED_UNIT_COST;   // pages' worth of time to start on a (sequence, KV head)
-#ifndef PQ_BALANCED_XCD_SKEW
-#define PQ_BALANCED_XCD_SKEW 30
-#endif
-constexpr int kBalancedXcdSkewPermille = PQ_BALANCED_XCD_SKEW;   // even-numbered work-groups (even XCDs) take 3 % more, odd ones 3 % less
-constexpr int kBalancedMaxSeqs = 4096;       // every work-group scans all sequence lengths
-
-// Work-groups of a balanced launch: all that are resident at once (3 per compute unit), fewer if
-// the shape cannot have kBalancedMinPages pages for each.
-int balanced_groups(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len, int per_cu = role_groups_per_cu(4)) {
+// Work-groups of four pages each that the shape could have, as far as 768 (the workspace's size is
+// stated in them).
+constexpr int64_t kCountedGroups = 768;
+int64_t four_page_groups(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len) {
   const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
   const int64_t bound = static_cast<int64_t>(n_seqs) * l->n_kv_heads * max_pages;   // pages x KV heads, at most
-  const int64_t resident = std::min<int64_t>(PQ_BALANCED_GROUPS, static_cast<int64_t>(kComputeUnits) * per_cu);
-  return static_cast<int>(std::min<int64_t>(resident, (bound + kBalancedMinPages - 1) / kBalancedMinPages));
+  return std::min<int64_t>(kCountedGroups, (bound + 3) / 4);
+}
+
+// Uniform angle grid, and pages enough for at least 256 work-groups.
+bool large_uniform_launch(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len) {
+  return l->angle_quantizer == PQ_ANGLE_UNIFORM && n_seqs <= 4096 && four_page_groups(l, n_seqs, max_seq_len) >= kComputeUnits;
 }
 
 AttentionKernel choose_attention_kernel(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads,
                                         int32_t max_seq_len) {
-  const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
-  const int64_t bound = static_cast<int64_t>(n_seqs) * l->n_kv_heads * (max_pages + kBalancedUnitCost);
-  // Quantized values make the launch arithmetic-bound, and with 4 query heads per KV head the
-  // value wavefront's unpacking and dot products are the longer side of every step of the
-  // specialised kernel: wavefronts that all score and aggregate use the four SIMDs evenly
-  // (measured at the GQA shape, 4-bit values: 147 against 166 us; with 2 heads per KV head the
-  // specialised kernel wins, 127 against 147 us).
-  const bool roles_fit = v_bits == 16 || n_q_heads / l->n_kv_heads <= 2;
-  if (l->angle_quantizer == PQ_ANGLE_UNIFORM && roles_fit && n_seqs <= kBalancedMaxSeqs &&
-      bound < (int64_t{1} << 31) && balanced_groups(l, n_seqs, max_seq_len) >= 256)
-    return AttentionKernel::kRoles;
-  return AttentionKernel::kPartials;
+  const bool name_fits = v_bits == 16 || n_q_heads / l->n_kv_heads <= 2;
+  return name_fits && large_uniform_launch(l, n_seqs, max_seq_len) ? AttentionKernel::kRoles : AttentionKernel::kPartials;
 }
 
-// The caller's workspace holds either the chunk partials of a grid launch ([seq][q head][chunk])
-// or, for a balanced launch, one partial per segment slot ([slot][head of the group], slots =
-// work-groups + units) and the units' arrival words.  Its size covers both.
+bool launch_attention(int w, int v_bits, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st) {
+  switch (v_bits) {
+    case 16: return launch_attention_matrix_v16(w, roles, a, grid, st);
+    case 4: return launch_attention_matrix_v4(w, roles, a, grid, st);
+    case 2: return launch_attention_matrix_v2(w, roles, a, grid, st);
+    default: return false;
+  }
+}
+
+// Index of a bit allocation in the key-side tables of its symbol width (pq_decode_matrix.hpp).
+int key_table_index(const pq_layout* l) {
+  const int w = l->r_bits + l->t_bits;
+  for (int i = 0; i < 3; ++i)
+    if (kTableRadiusBits[w == 8][i] == l->r_bits) return i;
+  return 0;                                  // not reached: layout_supported() admits what is built
+}
+
+// The caller's workspace: the chunks' partials and the units' arrival words.  Its size is that of
+// the chunk plan of plan_chunks() or of one partial for each of four_page_groups() + units, whichever
+// is larger; plan_uniform() keeps within it.
 struct Workspace {
   float* acc;
   float* ml;
@@ -176,21 +166,78 @@ struct Workspace {
 
 size_t round256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
 
-Workspace carve_workspace(void* base, const pq_layout* l, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
+size_t workspace_slots(const pq_layout* l, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
   const ChunkPlan plan = plan_chunks(n_seqs, l->n_kv_heads, max_seq_len);
   const size_t units = static_cast<size_t>(n_seqs) * l->n_kv_heads;
-  const size_t grid_slots = static_cast<size_t>(n_seqs) * n_q_heads * plan.n_chunks;
-  const size_t balanced_slots = (static_cast<size_t>(balanced_groups(l, n_seqs, max_seq_len)) + units) * (n_q_heads / l->n_kv_heads);
-  const size_t slots = std::max(grid_slots, balanced_slots);
+  const size_t chunk_slots = static_cast<size_t>(n_seqs) * n_q_heads * plan.n_chunks;
+  return std::max(chunk_slots, (static_cast<size_t>(four_page_groups(l, n_seqs, max_seq_len)) + units) * (n_q_heads / l->n_kv_heads));
+}
+
+Workspace carve_workspace(void* base, const pq_layout* l, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
+  const size_t slots = workspace_slots(l, n_seqs, n_q_heads, max_seq_len);
   const size_t acc_bytes = round256(slots * kHeadDim * sizeof(float));
   const size_t ml_bytes = round256(slots * 2 * sizeof(float));
   Workspace w;
   w.acc = static_cast<float*>(base);
   w.ml = reinterpret_cast<float*>(static_cast<uint8_t*>(base) + acc_bytes);
   w.arrivals = reinterpret_cast<uint64_t*>(static_cast<uint8_t*>(base) + acc_bytes + ml_bytes);
-  const size_t words = units + static_cast<size_t>(balanced_groups(l, n_seqs, max_seq_len)) + units;   // per unit, per segment slot
+  const size_t units = static_cast<size_t>(n_seqs) * l->n_kv_heads;
+  const size_t words = units + static_cast<size_t>(four_page_groups(l, n_seqs, max_seq_len)) + units;
   w.bytes = acc_bytes + ml_bytes + round256(words * sizeof(uint64_t));
   return w;
+}
+
+// Chunk plan of the uniform angle grid's attention kernel.  Two work-groups are resident on a compute
+// unit, and starting and ending one costs about as much as streaming 8 pages: chunks are as long as
+// they can be without leaving compute units idle at the end.  `share` is a resident work-group's part
+// of the launch if every sequence has max_seq_len tokens.  Measured (pages per chunk: microseconds;
+// "48 + 16": 48, the last quarter in chunks of 16):
+//   up to 16 pages a share   248 units x 2 .. 24 pages   8: 51, 16: 44, 24: 47;  8 x 1024  8: 64, 16: 61, 24: 68
+//   fp16 values              256 x 64      24: 110, 32: 110, 44: 107.5, 64: 110;  128 x 256  32: 210, 44: 212, 64: 208
+//                            512 x 8 .. 128  24: 240, 44: 238, 64: 239, 64 + 24: 233
+//   quantized values         256 x 4 .. 64   16: 54, 24: 43.4, 24 + 8: 44, 32: 55;  128 x 256  32: 131, 64: 126, 48 + 16: 125
+// (With fp16 values a work-group that is left alone streams faster; with quantized ones it does not.)
+// The two-stage entry points, whose second one does not know the values' width, use the fp16 plan.
+ChunkPlan plan_uniform(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
+  const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
+  const int64_t units = static_cast<int64_t>(n_seqs) * l->n_kv_heads;
+  const int64_t share = (units * max_pages + kResidentGroups - 1) / kResidentGroups;
+  auto whole_rounds = [](int64_t pages) { return (pages + kMatWaves - 1) / kMatWaves * kMatWaves; };
+  int64_t big, small, n_big = 0;
+  if (max_pages < 2 * kMatWaves) {
+    big = small = max_pages;                             // less than two pages a wavefront: one chunk, nothing to merge
+  } else if (share <= 16) {
+    big = small = share <= 4 ? 4 : share <= 8 ? 8 : 16;
+  } else if (v_bits == 16 && share <= 64) {
+    big = small = std::min<int64_t>(64, whole_rounds(share * 4 / 3));
+  } else {
+    big = std::min<int64_t>(64, whole_rounds(share * 3 / 4));
+    small = std::max<int64_t>(8, std::min<int64_t>(24, whole_rounds(share / 4)));
+    n_big = std::max<int64_t>(1, max_pages * 4 / 5 / big);
+  }
+  // as many partials as the workspace holds (its own plan has max_pages / 32 chunks or more)
+  const int64_t most = static_cast<int64_t>(workspace_slots(l, n_seqs, n_q_heads, max_seq_len)) / (static_cast<int64_t>(n_seqs) * n_q_heads);
+  auto chunks = [&] {
+    const int64_t first = std::min(n_big, (max_pages + big - 1) / big), rest = max_pages - n_big * big;
+    return first + (rest > 0 ? (rest + small - 1) / small : 0);
+  };
+  while (chunks() > most && small < max_pages) {
+    small += 4;
+    if (small > big) {
+      big = small;
+      n_big = 0;
+    }
+  }
+  ChunkPlan p;
+  p.pages_per_chunk = static_cast<int32_t>(big);
+  p.pages_small = static_cast<int32_t>(small);
+  p.n_chunks = static_cast<int32_t>(chunks());
+  p.n_big = static_cast<int32_t>(n_big == 0 && big == small ? p.n_chunks : n_big);
+  return p;
+}
+ChunkPlan plan_attention(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
+  return l->angle_quantizer == PQ_ANGLE_UNIFORM ? plan_uniform(l, v_bits, n_seqs, n_q_heads, max_seq_len)
+                                                : plan_chunks(n_seqs, l->n_kv_heads, max_seq_len);
 }
 
 // cos / sin of the centre of every angle bin of the uniform grid over [-pi, pi) (Section 3.2
@@ -255,25 +302,56 @@ namespace {
 
 // Chunks of the score-only kernels: equal chunks of whole rounds of the 4 wavefronts, enough of
 // them for `groups_per_cu` resident work-groups on each compute unit (4 with the token-lane
-// kernel, 2 with the grouped quantizer's), at least 4 pages each.
+// kernel, 2 with the others), at least 4 pages each.
 ChunkPlan plan_score_chunks(int32_t n_seqs, int32_t n_kv_heads, int32_t max_seq_len, int groups_per_cu) {
   const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
   const int64_t units = static_cast<int64_t>(n_seqs) * n_kv_heads;
-  const int64_t want = int64_t{256} * groups_per_cu;
+  const int64_t want = int64_t{kComputeUnits} * groups_per_cu;
   const int64_t per_unit = std::max<int64_t>(1, (want + units - 1) / units);            // chunks per (sequence, KV head)
   int64_t ppc = std::max<int64_t>(4, (max_pages + per_unit - 1) / per_unit);
   ppc = (ppc + 3) & ~int64_t{3};
   ChunkPlan p;
   p.pages_per_chunk = static_cast<int32_t>(std::min<int64_t>(ppc, 256));                 // a wavefront keeps 64 page ids
-  p.n_chunks = static_cast<int32_t>((max_pages + p.pages_per_chunk - 1) / p.pages_per_chunk);
+  p.n_chunks = p.n_big = static_cast<int32_t>((max_pages + p.pages_per_chunk - 1) / p.pages_per_chunk);
+  p.pages_small = p.pages_per_chunk;
   return p;
 }
 
-// Whether pq_decode_attention shares this launch out evenly and merges inside the attention kernel
-// (true), or launches one work-group per chunk and the merge kernel after it.
+// The raw scores of a launch, pass by pass over the query heads of a KV head; `a` is complete but for
+// what depends on the pass and the chunks.  Scores come from here whoever asks for them, so that
+// they are the same bit for bit: on the uniform grid the attention kernel does not store its own.
+int launch_scores(const pq_layout* layout, DecodeArgs a, hipStream_t stream) {
+  const bool grouped = layout->angle_quantizer == PQ_ANGLE_GROUPED;
+  const int rt = layout->r_bits * 10 + layout->t_bits;
+  // the token-lane kernel addresses 4 score rows with 32-bit byte offsets
+  const bool tokens_fit = a.scores_stride < (int64_t{1} << 28);
+  hipError_t e = hipSuccess;
+  for (int head0 = 0; head0 < a.group_total && e == hipSuccess;) {
+    const int left = a.group_total - head0;
+    const bool matrix = !grouped && (left > 4 || !tokens_fit);
+    const int G = matrix ? std::min(left, kMaxHeads) : (left >= 4 ? 4 : (left >= 2 ? 2 : 1));
+    const ChunkPlan plan = plan_score_chunks(a.n_seqs, a.n_kv_heads, a.max_seq_len, grouped || matrix ? 2 : 4);
+    if (plan.n_chunks > 65535) return PQ_ERR_UNSUPPORTED;   // grid.z
+    a.pages_per_chunk = plan.pages_per_chunk;
+    a.n_chunks = plan.n_chunks;
+    a.head0 = head0;
+    a.n_heads = G;
+    const dim3 grid(a.n_kv_heads, a.n_seqs, plan.n_chunks);
+    const bool found = matrix ? launch_scores_matrix(layout->r_bits + layout->t_bits, a, grid, stream)
+                              : (grouped ? launch_scores_rt<true>(rt, G, a, grid, stream) : launch_scores_rt<false>(rt, G, a, grid, stream));
+    if (!found) return PQ_ERR_UNSUPPORTED;   // not reached: layout_supported() admits what is built
+    e = hipGetLastError();
+    head0 += G;
+  }
+  return e == hipSuccess ? PQ_OK : record_hip_error(e);
+}
+
+// Whether one kernel does all of pq_decode_attention (true), or the merge kernel follows: the
+// sequences are one chunk long, or a large launch has few enough chunks per unit.
 bool merges_in_kernel(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
-  if (choose_attention_kernel(l, v_bits, n_seqs, n_q_heads, max_seq_len) != AttentionKernel::kRoles) return false;
-  return static_cast<int64_t>(n_seqs) * l->n_kv_heads * kArriveFan >= balanced_groups(l, n_seqs, max_seq_len);
+  if (l->angle_quantizer != PQ_ANGLE_UNIFORM) return false;
+  const int n_chunks = plan_uniform(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
+  return n_chunks == 1 || (n_chunks <= kMergeFan && large_uniform_launch(l, n_seqs, max_seq_len));
 }
 
 // Everything the decode entry points have in common: argument checks, kernel arguments, and the
@@ -308,7 +386,7 @@ int decode_launch(const pq_layout* layout, const void* q, pq_dtype q_dtype, int3
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return PQ_ERR_WORKSPACE;
   const Workspace ws = carve_workspace(workspace, layout, n_seqs, n_q_heads, max_seq_len);
   if (workspace_bytes < ws.bytes) return PQ_ERR_WORKSPACE;
-  const ChunkPlan plan = plan_chunks(n_seqs, layout->n_kv_heads, max_seq_len);
+  const ChunkPlan plan = plan_attention(layout, out != nullptr ? v_bits : 16, n_seqs, n_q_heads, max_seq_len);
 
   DecodeArgs a = {};
   a.q = q;
@@ -325,9 +403,6 @@ int decode_launch(const pq_layout* layout, const void* q, pq_dtype q_dtype, int3
   a.ws_ml = ws.ml;
   a.out = out;
   a.arrivals = ws.arrivals;
-  a.min_pages = kBalancedMinPages;
-  a.unit_cost = kBalancedUnitCost;
-  a.xcd_skew_permille = kBalancedXcdSkewPermille;
   a.scores_stride = scores_stride;
   a.n_pool_pages = n_pool_pages;
   a.n_kv_heads = layout->n_kv_heads;
@@ -336,6 +411,8 @@ int decode_launch(const pq_layout* layout, const void* q, pq_dtype q_dtype, int3
   a.max_seq_len = max_seq_len;
   a.pages_per_chunk = plan.pages_per_chunk;
   a.n_chunks = plan.n_chunks;
+  a.n_big = plan.n_big;
+  a.pages_small = plan.pages_small;
   a.q_is_f32 = q_dtype == PQ_F32 ? 1 : 0;
   a.scale_log2 = static_cast<float>(static_cast<double>(sm_scale) * 1.4426950408889634074);
   fill_angle_tables(a, layout->t_bits);
@@ -343,39 +420,33 @@ int decode_launch(const pq_layout* layout, const void* q, pq_dtype q_dtype, int3
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const int group_total = n_q_heads / layout->n_kv_heads;
   a.group_total = group_total;
-  // The role-specialised kernel shares a launch out evenly and merges in the kernel, except when
-  // the units are few and each would be shared by more work-groups than one arrival word takes
-  // well (one long sequence), or when only the partials are asked for: then one work-group per
-  // chunk, and the merge kernel.
   const bool roles = choose_attention_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len) == AttentionKernel::kRoles;
-  const int n_balanced = balanced_groups(layout, n_seqs, max_seq_len);
-  const bool balanced = out != nullptr && merges_in_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len);
-  a.grid_mode = balanced ? 0 : 1;
+  const bool merged = out != nullptr && merges_in_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len);
+  a.merge_in_kernel = merged ? 1 : 0;
   const dim3 grid(layout->n_kv_heads, n_seqs, plan.n_chunks);
+  a.table_index = key_table_index(layout);
+  if (scores && !grouped) {
+    const int ss = launch_scores(layout, a, stream);
+    if (ss != PQ_OK) return ss;
+  }
   hipError_t e = hipSuccess;
-  // A kernel instance serves 8, 4, 2 or 1 query heads of a KV head; other groups take several
-  // passes over the cache (6 = 4 + 2, 12 = 8 + 4, ...).
+  // A pass over the cache serves up to 8 query heads of a KV head; with the grouped quantizer 4, 2 or 1.
   for (int head0 = 0; head0 < group_total && e == hipSuccess;) {
     const int left = group_total - head0;
-    // 8 heads at a time where there is a kernel for it: the role-specialised one, fp16 values
-    const int G = (left >= 8 && roles && v_bits == 16) ? 8 : (left >= 4 ? 4 : (left >= 2 ? 2 : 1));
+    const int G = grouped ? (left >= 4 ? 4 : (left >= 2 ? 2 : 1)) : std::min(left, kMaxHeads);
     a.head0 = head0;
-    bool found;
-    if (roles) {
-      found = a.grid_mode ? launch_attention_roles_grid(rt, G, v_bits, a, static_cast<int>(grid.x * grid.y * grid.z), stream)
-                          : launch_attention_roles(rt, G, v_bits, a, std::min(n_balanced, balanced_groups(layout, n_seqs, max_seq_len, role_groups_per_cu(G))), stream);
-    } else {
-      found = grouped ? launch_attention_partials_ga(rt, G, v_bits, a, grid, stream)
-                      : launch_attention_partials(rt, G, v_bits, a, grid, stream);
-    }
+    a.n_heads = G;
+    const bool found = grouped ? launch_attention_partials_ga(rt, G, v_bits, a, grid, stream)
+                               : launch_attention(layout->r_bits + layout->t_bits, v_bits, roles, a, grid, stream);
     if (!found) return PQ_ERR_UNSUPPORTED;   // not reached: layout_supported() admits what is built
     e = hipGetLastError();
     head0 += G;
   }
   if (e != hipSuccess) return record_hip_error(e);
-  if (out != nullptr && a.grid_mode) {
+  if (out != nullptr && !merged) {
     hipLaunchKernelGGL(pq_decode_merge_kernel, dim3(n_q_heads, n_seqs), dim3(kMergeThreads), 0, stream, ws.acc,
-                       ws.ml, seq_lens, out, n_q_heads, max_seq_len, plan.pages_per_chunk, plan.n_chunks);
+                       ws.ml, seq_lens, out, n_q_heads, max_seq_len, plan.pages_per_chunk, plan.n_chunks, plan.n_big,
+                       plan.pages_small);
     e = hipGetLastError();
     if (e != hipSuccess) return record_hip_error(e);
   }
@@ -418,13 +489,14 @@ extern "C" int pq_decode_merge(const pq_layout* layout, int32_t n_seqs, int32_t 
   const int st = check_decode_shape(layout, n_seqs, n_q_heads, max_seq_len);
   if (st != PQ_OK) return st;
   if (!seq_lens || !out) return PQ_ERR_INVALID_ARG;
-  const ChunkPlan plan = plan_chunks(n_seqs, layout->n_kv_heads, max_seq_len);
+  const ChunkPlan plan = plan_attention(layout, 16, n_seqs, n_q_heads, max_seq_len);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return PQ_ERR_WORKSPACE;
   const Workspace ws = carve_workspace(const_cast<void*>(workspace), layout, n_seqs, n_q_heads, max_seq_len);
   if (workspace_bytes < ws.bytes) return PQ_ERR_WORKSPACE;
   hipLaunchKernelGGL(pq_decode_merge_kernel, dim3(n_q_heads, n_seqs), dim3(kMergeThreads), 0,
                      static_cast<hipStream_t>(hip_stream), ws.acc, ws.ml, seq_lens, out, n_q_heads,
-                     max_seq_len, plan.pages_per_chunk, plan.n_chunks);
+                     max_seq_len, plan.pages_per_chunk, plan.n_chunks, plan.n_big,
+                       plan.pages_small);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return record_hip_error(e);
   return PQ_OK;
@@ -481,13 +553,7 @@ extern "C" int pq_score_keys(const pq_layout* layout, const void* q, pq_dtype q_
     return PQ_ERR_INVALID_ARG;
   if ((reinterpret_cast<uintptr_t>(block_table) | reinterpret_cast<uintptr_t>(seq_lens) | reinterpret_cast<uintptr_t>(scores)) & 3u)
     return PQ_ERR_INVALID_ARG;
-  if (scores_stride >= (int64_t{1} << 28)) return PQ_ERR_UNSUPPORTED;   // 4 score rows are addressed with 32-bit byte offsets
-  const bool grouped = layout->angle_quantizer == PQ_ANGLE_GROUPED;
-#ifndef PQ_SCORE_GROUPS_PER_CU
-#define PQ_SCORE_GROUPS_PER_CU 4
-#endif
-  const ChunkPlan plan = plan_score_chunks(n_seqs, layout->n_kv_heads, max_seq_len, grouped ? 2 : PQ_SCORE_GROUPS_PER_CU);
-  if (plan.n_chunks > 65535) return PQ_ERR_UNSUPPORTED;   // grid.z
+  if (scores_stride >= (int64_t{1} << 28)) return PQ_ERR_UNSUPPORTED;
   DecodeArgs a = {};
   a.q = q;
   a.q_is_f32 = q_dtype == PQ_F32 ? 1 : 0;
@@ -504,23 +570,8 @@ extern "C" int pq_score_keys(const pq_layout* layout, const void* q, pq_dtype q_
   a.n_q_heads = n_q_heads;
   a.max_pages_per_seq = max_pages_per_seq;
   a.max_seq_len = max_seq_len;
-  a.pages_per_chunk = plan.pages_per_chunk;
-  a.n_chunks = plan.n_chunks;
   fill_angle_tables(a, layout->t_bits);
-  const dim3 grid(layout->n_kv_heads, n_seqs, plan.n_chunks);
-  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const int group_total = n_q_heads / layout->n_kv_heads;
-  hipError_t e = hipSuccess;
-  a.group_total = group_total;
-  for (int head0 = 0; head0 < group_total && e == hipSuccess;) {
-    const int left = group_total - head0;
-    const int G = left >= 4 ? 4 : (left >= 2 ? 2 : 1);
-    a.head0 = head0;
-    if (!launch_scores(layout->r_bits * 10 + layout->t_bits, grouped, G, a, grid, stream))
-      return PQ_ERR_UNSUPPORTED;           // not reached: layout_supported() admits what is built
-    e = hipGetLastError();
-    head0 += G;
-  }
-  if (e != hipSuccess) return record_hip_error(e);
-  return PQ_OK;
+  a.group_total = n_q_heads / layout->n_kv_heads;
+  a.table_index = key_table_index(layout);
+  return launch_scores(layout, a, static_cast<hipStream_t>(hip_stream));
 }

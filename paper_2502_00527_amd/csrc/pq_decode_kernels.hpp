@@ -63,26 +63,27 @@ struct DecodeArgs {
   const int32_t* seq_lens;
   int32_t n_seqs;
   float* scores;
-  float* ws_acc;            // [seq][q_head][chunk][128]; balanced launches: [slot][head of the group][128]
-  float* ws_ml;             // [seq][q_head][chunk][2] = (m in log2 units, l); balanced: [slot][head of the group][2]
-  // launches whose work-groups share the pages out evenly and merge in the kernel (pq_decode_sched.hpp)
+  float* ws_acc;            // [seq][q_head][chunk][128]
+  float* ws_ml;             // [seq][q_head][chunk][2] = (m in log2 units, l)
+  // launches that merge in the kernel (pq_decode_sched.hpp)
   float* out;               // [seq][q_head][128]
-  uint64_t* arrivals;       // one arrival word per (sequence, KV head), then one per segment slot
-  int32_t min_pages;        // smallest share of a work-group, in pages
-  int32_t unit_cost;        // what starting on a (sequence, KV head) costs a work-group, in pages
-  int32_t xcd_skew_permille;  // how much more than the average share an even-numbered work-group takes
+  uint64_t* arrivals;       // one arrival word per (sequence, KV head)
+  int32_t merge_in_kernel;
   int32_t q_is_f32;         // the query is fp32 (else fp16)
-  int32_t grid_mode;        // role-specialised kernel: one work-group per (KV head, sequence, chunk) instead
   int64_t scores_stride;
   int64_t n_pool_pages;
   int32_t n_kv_heads;
   int32_t n_q_heads;
   int32_t group_total;      // query heads per KV head (any value); one launch covers G of them ...
   int32_t head0;            // ... starting at this head of the group
+  int32_t n_heads;          // G, where it is not a template parameter (pq_decode_matrix.hpp: 1 .. 8)
+  int32_t table_index;      // bit allocation among those of the symbol width (pq_decode_matrix.hpp)
   int32_t max_pages_per_seq;
   int32_t max_seq_len;
   int32_t pages_per_chunk;
   int32_t n_chunks;
+  int32_t n_big;            // chunks from here on are pages_small long (pq_decode_matrix.hpp)
+  int32_t pages_small;
   float scale_log2;         // sm_scale * log2(e)
   float cos_tab[kMaxAngleBins];
   float sin_tab[kMaxAngleBins];
@@ -96,6 +97,13 @@ bool launch_attention_partials(int rt, int G, int v_bits, const DecodeArgs& a, d
 bool launch_attention_partials_ga(int rt, int G, int v_bits, const DecodeArgs& a, dim3 grid, hipStream_t st);
 
 namespace {
+
+// Chunks a sequence of n_pages pages has, when the first n_big are `big` pages long and the others `small`.
+__device__ __forceinline__ int chunks_of_pages(int n_pages, int big, int n_big, int small) {
+  const int first = min((n_pages + big - 1) / big, n_big);
+  const int rest = n_pages - n_big * big;
+  return first + (rest > 0 ? (rest + small - 1) / small : 0);
+}
 
 __device__ __forceinline__ uint32_t f2u(float x) { return __float_as_uint(x); }
 __device__ __forceinline__ float u2f(uint32_t x) { return __uint_as_float(x); }

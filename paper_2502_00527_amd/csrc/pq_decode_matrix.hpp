@@ -1,0 +1,913 @@
+// Attention and score-only kernels of the uniform angle grid, on the matrix cores.
+//
+// Scores.  A key pair is reconstructed as rho~ (cos theta~, sin theta~), rho~ = s (c + 1/2) + z
+// (Section 3.2), and the score is sum over pairs of q . k~.  Written with the four products
+//     q_x s, q_y s, q_x z, q_y z          (per pair and page: the query side)
+//     c' cos, c' sin, cos, sin, c' = c + 1/2   (a function of the packed symbol alone: the key side)
+// it is a contraction over 4 terms a pair.  The key side is a table of 2^(r+t) symbols that does not
+// depend on the query, the page or the head: 16 bytes a symbol, each of the four numbers as two
+// fp16 (high part, low part: 22 bits and more), and one 128-bit LDS read of it IS an operand of
+// v_mfma_f32_16x16x32_f16 -- lane (token, pair block), 8 of the 32 products summed.  The query
+// side fills the other operand: 16 columns = 8 query heads x {high, low} fp16 part of the
+// products, so a product of an fp16 query and an fp16 parameter (22 bits) enters exactly, and
+// any group of 1 to 8 query heads costs the same.  Accumulation is fp32, restarted every 4
+// instructions (16 pairs) to keep the partial sums small: measured against float64 the scores
+// are as close as those of one fp32 multiply-add per pair.
+//
+// Values.  The accumulator layout of the scores -- lane (column, four consecutive tokens) -- is
+// the operand layout of the next product: probabilities go from score to value product in
+// registers, as high and low fp16 parts in the columns that held the query's parts (22 bits; the
+// row sums of both parts are added at the end).  fp16 value rows are transposed pairwise with
+// v_perm_b32; quantized values need no conversion at all (a masked code is an fp16 denormal).
+//
+// What bounds it.  Per page (128 tokens of one KV head) a wavefront issues about 420 vector
+// instructions for the scores (128 table addresses, 250 for the query side), 350 for the softmax
+// and 190 for the values, and 160 matrix instructions (640 cycles per page and compute unit); one
+// multiply-add per (head, pair, token) and (head, dim, token) on the vector unit took 2200.  With
+// fp16 values a page is 41 KB, 3600 cycles of a compute unit's share of HBM: memory-bound.  With
+// quantized values the page is 11 - 17 KB and vector issue is about as long as the stream.
+//
+// The table is kept 16 times in LDS, copy l in the 16-byte column l of a 256-byte row, and lane l
+// reads copy l % 16: reads of 16 lanes touch every bank once whatever the symbols are.  64 KB for
+// 8-bit symbols, 16 KB for 6-bit ones: two work-groups per compute unit.
+#pragma once
+#include "pq_decode_sched.hpp"
+
+namespace pq {
+
+// Launchers (pq_decode_matrix.hip, one per value width).  `w` = r + t; a.n_heads query heads (1 .. 8) from a.head0 on.
+// `roles` picks the name the launch runs under.  They return
+// false, and launch nothing, for a width without a kernel; launch errors are left to hipGetLastError().
+bool launch_attention_matrix_v16(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st);
+bool launch_attention_matrix_v4(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st);
+bool launch_attention_matrix_v2(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st);
+bool launch_scores_matrix(int w, const DecodeArgs& a, dim3 grid, hipStream_t st);
+
+namespace {
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+constexpr int kMatWaves = 4;
+constexpr int kMatThreads = kMatWaves * 64;
+constexpr int kScoreWaves = 4;
+constexpr int kMaxHeads = 8;            // query heads of one pass: columns h (high part) and 8 + h (low part)
+
+// ---- key-side table ---------------------------------------------------------------------------
+// Entry of symbol (a << r) | c: fp16 {c' cos, c' sin, cos, sin} high parts, then their low parts,
+// all scaled by 2^kTableShift (keeps the low parts out of the denormal range; c' <= 31.5).
+constexpr int kTableShift = 10;
+
+constexpr uint16_t half_bits(double v) {          // nearest fp16, ties to even; |v| < 65504
+  const uint16_t sign = v < 0 ? 0x8000u : 0u;
+  if (v < 0) v = -v;
+  int e = -14;                                     // quantum 2^(e - 10): fixed below 2^-14
+  double quantum = 1.0 / 16777216.0;
+  while (v >= quantum * 2048.0) {
+    quantum *= 2.0;
+    ++e;
+  }
+  const double n = v / quantum;
+  int64_t k = static_cast<int64_t>(n);
+  const double rest = n - static_cast<double>(k);
+  if (rest > 0.5 || (rest == 0.5 && (k & 1))) ++k;
+  // k quanta: 1024 <= k <= 2048 in the normal range (2048 carries into the exponent field by itself)
+  return static_cast<uint16_t>(sign | (k < 1024 ? k : ((static_cast<int64_t>(e) + 14) << 10) + k));
+}
+constexpr double half_value(uint16_t b) {
+  const int e = (b >> 10) & 31;
+  double v = e == 0 ? (b & 1023) / 1024.0 : 1.0 + (b & 1023) / 1024.0;
+  for (int i = e == 0 ? 1 : e; i < 15; ++i) v *= 0.5;
+  for (int i = 15; i < e; ++i) v *= 2.0;
+  return (b & 0x8000) ? -v : v;
+}
+constexpr double cos_series(double x) {            // |x| <= pi
+  double term = 1.0, sum = 1.0;
+  for (int k = 1; k <= 15; ++k) {
+    term *= -x * x / ((2.0 * k - 1.0) * (2.0 * k));
+    sum += term;
+  }
+  return sum;
+}
+template <int W>
+struct KeyTables {
+  uint32_t word[3][1 << W][4];
+};
+// the bit allocations of a width, in table order
+constexpr int kTableRadiusBits[2][3] = {{3, 4, 2}, {4, 5, 3}};       // W = 6: (3,3) (4,2) (2,4); W = 8: (4,4) (5,3) (3,5)
+template <int W>
+constexpr KeyTables<W> make_key_tables() {
+  constexpr double kPi = 3.14159265358979323846;
+  KeyTables<W> t = {};
+  for (int i = 0; i < 3; ++i) {
+    const int rb = kTableRadiusBits[W == 8][i], tb = W - rb;
+    for (int a = 0; a < (1 << tb); ++a) {
+      const double th = -kPi + (a + 0.5) * (2.0 * kPi / (1 << tb));
+      // sin from the cosine of the angle a quarter turn back, kept within [-pi, pi]
+      const double cs = cos_series(th), sn = th >= -kPi / 2 ? cos_series(th - kPi / 2) : -cos_series(th + kPi / 2);
+      for (int c = 0; c < (1 << rb); ++c) {
+        const double scale = 1 << kTableShift;
+        const double x[4] = {(c + 0.5) * cs * scale, (c + 0.5) * sn * scale, cs * scale, sn * scale};
+        uint16_t h[8] = {};
+        for (int k = 0; k < 4; ++k) {
+          h[k] = half_bits(x[k]);
+          h[4 + k] = half_bits(x[k] - half_value(h[k]));
+        }
+        for (int k = 0; k < 4; ++k) t.word[i][(a << rb) | c][k] = h[2 * k] | (static_cast<uint32_t>(h[2 * k + 1]) << 16);
+      }
+    }
+  }
+  return t;
+}
+__device__ const KeyTables<8> key_tables8 = make_key_tables<8>();
+__device__ const KeyTables<6> key_tables6 = make_key_tables<6>();
+
+constexpr int kTableRow = 256;           // bytes of a symbol in LDS: 16 copies of its entry
+template <int W>
+__device__ __forceinline__ const uint4* key_table(int index) {
+  if constexpr (W == 8) return reinterpret_cast<const uint4*>(&key_tables8.word[index][0][0]);
+  else return reinterpret_cast<const uint4*>(&key_tables6.word[index][0][0]);
+}
+// Fills the LDS table; a work-group barrier must follow before it is read.
+template <int W, int NT>
+__device__ __forceinline__ void fill_key_table(uint8_t* lut, const uint4* src, int tid) {
+  constexpr int kSlots = (1 << W) * 16;              // 16-byte slot: symbol at / 16, copy at % 16
+#pragma unroll
+  for (int i = 0; i < (kSlots + NT - 1) / NT; ++i) {
+    const int at = i * NT + tid;
+    if (kSlots % NT == 0 || at < kSlots) reinterpret_cast<uint4*>(lut)[at] = src[at >> 4];
+  }
+}
+
+// ---- query side -------------------------------------------------------------------------------
+// Columns of the query operand.  NH = 8 (5 to 8 query heads): column = 8 part + head.  NH = 4 (1 to
+// 4 heads): column = 8 part + 4 half + head, where half 0 carries the pairs of the first two steps of
+// every four and half 1 the others (zeros elsewhere) -- the partial sums of a column are half as long.
+template <int NH>
+__device__ __forceinline__ int column_head(int col) { return col & (NH - 1); }
+
+// The pass's query in LDS, [pair][column] with 8 bytes an entry: q = (q_x, q_y) as fp16, and
+//   fp16 queries: q again in low-part columns, 0 in high-part ones;
+//   fp32 queries: what q's rounding to fp16 left over, in low-part columns, 0 in high-part ones.
+// Each head is scaled by a power of two so that its largest element is in [2^9, 2^10): with
+// parameters scaled below 2^5 the products stay inside fp16, and fp16 queries lose nothing unless
+// an element is 2^-23 of the head's largest.  The 16 pairs of a block are followed by 128 bytes of
+// padding (the four lane rows read four blocks at once).
+constexpr int kQueryTop = 9, kParamTop = 4;
+constexpr int kQueryBlock = 16 * 16 * 8 + 128;
+struct QueryShared {
+  __attribute__((aligned(16))) uint8_t pairs[kBlocks * kQueryBlock];
+};
+struct QueryFetch {
+  float v[4];
+};
+// thread = (head tid / 32, dims 4 (tid % 32) ..+3); heads from n_heads on are zero
+__device__ __forceinline__ QueryFetch fetch_query_heads(const DecodeArgs& a, bool q32, int64_t q_at, int tid) {
+  QueryFetch f = {};
+  const int h = tid >> 5;
+  if (h < a.n_heads) {
+    const int64_t at = q_at + h * kHeadDim + (tid & 31) * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      f.v[e] = q32 ? static_cast<const float*>(a.q)[at + e] : __half2float(static_cast<const __half*>(a.q)[at + e]);
+  }
+  return f;
+}
+// `shifts`: the power of two each head was multiplied with
+template <int NH, bool Q32>
+__device__ __forceinline__ void store_query_heads(QueryShared& q, int* shifts, const QueryFetch& f, float sign, int tid) {
+  uint32_t top = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) top = max(top, f2u(f.v[e]) & 0x7fffffffu);
+#pragma unroll
+  for (int d = 16; d >= 1; d >>= 1) top = max(top, static_cast<uint32_t>(__shfl_xor(static_cast<int>(top), d)));
+  const int shift = min(kQueryTop + 127 - static_cast<int>(top >> 23), 126);
+  const int h = tid >> 5, dim = (tid & 31) * 4;
+  if (h >= NH) return;                               // (also the wavefronts beyond the fourth)
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int j = (dim + e) & (kPairs - 1), comp = (dim + e) >> 6, kk = j & 15;
+    _Float16* const at = reinterpret_cast<_Float16*>(q.pairs + (j >> 4) * kQueryBlock + kk * 128 + comp * 2);
+    const float x = sign * __builtin_ldexpf(f.v[e], shift);
+    const _Float16 hi = static_cast<_Float16>(x);
+    const _Float16 rest = Q32 ? static_cast<_Float16>(x - static_cast<float>(hi)) : hi;
+    const _Float16 none = static_cast<_Float16>(0.f);
+#pragma unroll
+    for (int half = 0; half < 8 / NH; ++half) {
+      const bool here = NH == 8 || ((kk >> 1) & 1) == half;
+      _Float16* const high = at + (half * NH + h) * 4;
+      _Float16* const low = high + 8 * 4;
+      high[0] = low[0] = here ? hi : none;
+      high[2] = none;
+      low[2] = here ? rest : none;
+    }
+  }
+  if ((tid & 31) == 0) shifts[h] = shift;
+}
+
+__device__ __forceinline__ f16x2 to_half2(float x, float y) { return __builtin_convertvector((f32x2{x, y}), f16x2); }
+__device__ __forceinline__ uint32_t h2u(f16x2 h) {
+  uint32_t u;
+  __builtin_memcpy(&u, &h, 4);
+  return u;
+}
+__device__ __forceinline__ f16x2 u2h(uint32_t u) {
+  f16x2 h;
+  __builtin_memcpy(&h, &u, 4);
+  return h;
+}
+// fp16 pair of (x0, x1) in the lanes of high-part columns (minus_low = 0), of what the high parts
+// leave over in those of low-part columns (minus_low = -1)
+__device__ __forceinline__ uint32_t split_pair(float x0, float x1, float minus_low) {
+  const f16x2 h = to_half2(x0, x1);
+  return h2u(to_half2(fmaf(static_cast<float>(h.x), minus_low, x0), fmaf(static_cast<float>(h.y), minus_low, x1)));
+}
+__device__ __forceinline__ f16x8 as_operand(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  const u32x4 v = {a, b, c, d};
+  f16x8 r;
+  __builtin_memcpy(&r, &v, 16);
+  return r;
+}
+__device__ __forceinline__ f16x8 as_operand(const uint4& v) { return as_operand(v.x, v.y, v.z, v.w); }
+
+// Maximum over the wavefront, as a scalar.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+  auto dpp = [](uint32_t v, auto ctrl) {
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  x = max(x, dpp(x, std::integral_constant<int, 0xB1>{}));
+  x = max(x, dpp(x, std::integral_constant<int, 0x4E>{}));
+  x = max(x, dpp(x, std::integral_constant<int, 0x141>{}));
+  x = max(x, dpp(x, std::integral_constant<int, 0x140>{}));
+  auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = max(r[0], r[1]);
+  auto s = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return static_cast<uint32_t>(uni(static_cast<int>(max(s[0], s[1]))));
+}
+
+// A page's radius parameters, one pair a lane, scaled by the power of two 2^k that brings the
+// largest into [2^4, 2^5) (as far as 2^15 goes); sets k.  Negative or non-finite words -- the encoder
+// writes neither -- scale like numbers just above the largest finite one.
+__device__ __forceinline__ uint32_t scale_page_params(uint32_t par, int& k) {
+  const uint32_t e = wave_max_u32(max(par & 0xffffu, par >> 16)) >> 10;   // biased exponent (and sign)
+  k = max(-12, min(15, kParamTop + 15 - static_cast<int>(e)));
+  return h2u(u2h(par) * u2h(static_cast<uint32_t>((k + 15) << 10) * 0x10001u));
+}
+
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
+// ---- scores of a page ---------------------------------------------------------------------------
+// Which tokens of a page are batch t of 16, matrix row m (a result lane of row r holds m = 4 r .. 4 r + 3):
+// the order the values of the same lane come in.
+enum class TokenOrder {
+  kRows,       // fp16 values, four consecutive rows a load: token 16 ((t + rot) % 8) + 4 (m % 4) + m / 4
+  kPlain,      // 4-bit values (units of 4 tokens), scores alone: token 16 ((t + rot) % 8) + m
+  kUnits8      // 2-bit values (units of 8 tokens): token 32 (t / 2) + 8 (m / 4) + 4 (t % 2) + m % 4
+};
+constexpr TokenOrder token_order(int v_bits) {
+  return v_bits == 16 ? TokenOrder::kRows : (v_bits == 4 ? TokenOrder::kPlain : TokenOrder::kUnits8);
+}
+template <TokenOrder O>
+__device__ __forceinline__ int batch_token(int t, int rot) {     // wavefront-uniform part
+  return O == TokenOrder::kUnits8 ? 32 * (t >> 1) + 4 * (t & 1) : 16 * ((t + rot) & 7);
+}
+template <TokenOrder O>
+__device__ __forceinline__ int row_token(int m) {                // part of the matrix row
+  return O == TokenOrder::kRows ? 4 * (m & 3) + (m >> 2) : (O == TokenOrder::kPlain ? m : 8 * (m >> 2) + (m & 3));
+}
+
+// One wavefront's key codes and parameters of a page, and the walk over them.  Operand lane =
+// (token row l % 16, pair block l / 16), pair 16 (l / 16) + kk in step kk; result lane = (column
+// l % 16, tokens 4 (l / 16) .. + 3).  The table reads run 4 or 8 instructions ahead (8 where there are registers for it); as a unit is used
+// for the last time it is refilled with the next page's.
+//
+// kChain: steps after which the accumulators restart (16: never).  The instruction rounds once per
+// pair, at the size of the running sum.  Error of a score against float64, 8 x 32K keys with
+// outlier channels, as part of the scores' 2-norm (one fp32 multiply-add per pair: 9.3e-8):
+// NH = 4 (whose columns carry half of the pairs each) with chains of 4: 9.5e-8, NH = 8 with 4:
+// 1.05e-7, with 2: 9.5e-8.  The attention kernel takes 4 (its output's error, 4e-7 - 7e-7, is that of
+// the exponentials) and none with quantized values (1e-5); the score-only kernel 2.
+// kAhead: half-steps (4 table reads each) between a read and its use.  kSets: 1 = a unit is refilled
+// with the next page's after its last use (something else follows the walk and hides the load), 2 = the
+// next page's units are loaded into a second set as the walk starts.
+template <int W, TokenOrder O, int NH, bool Q32, int kAhead, int kSets, int kChain>
+struct ScoreWalk {
+  static constexpr int UB = 2 * W;
+  static_assert(16 % kChain == 0, "steps of a chain");
+  Unit<W / 2> cu[kSets][8];
+  uint32_t par;                                 // {fp16 s, fp16 z} of pair `lane`
+  f32x4 s[8], d[4], done[4];                    // sums, the chain under way, the chain before it
+  f32x4 entry[kAhead + 1][4];
+  u32x2 qv[2];                                  // query and scaled parameters of two steps: fetched early enough that
+  uint32_t sz[2];                               // waiting for them does not wait for the table reads under way
+  // Order of the half-steps: a chain's steps first for one half of the batches, then for the other, so
+  // that four accumulators serve a chain; without restarts simply step by step.
+  static constexpr int kOps = kChain == 16 ? 1 : kChain;   // query operands kept
+  uint32_t q_op[kOps][2];
+  uint32_t lane_lut, q_addr, par_put, par_get, voff_codes, low_mask;
+  float minus_low;
+
+  __device__ __forceinline__ void init(const uint8_t* lut, const QueryShared& q, const uint32_t* params, int lane) {
+    const int row = lane >> 4, col = lane & 15;
+    lane_lut = lds_addr(lut) + col * 16;
+    q_addr = lds_addr(q.pairs) + row * kQueryBlock + col * 8;
+    par_put = lds_addr(params) + lane * 4;
+    par_get = lds_addr(params) + row * 64;
+    voff_codes = (row * kGroup + row_token<O>(col)) * UB;
+    minus_low = col >= 8 ? -1.f : 0.f;
+    low_mask = col >= 8 ? 0xffffffffu : 0u;
+  }
+  __device__ __forceinline__ void load_unit_of(int set, int t, __amdgpu_buffer_rsrc_t rc, int rot) {
+    cu[set][t] = load_unit<W>(rc, voff_codes, static_cast<uint32_t>(batch_token<O>(t, rot)) * UB);
+  }
+  __device__ __forceinline__ void load_params(__amdgpu_buffer_rsrc_t rp, int lane) { par = buf_load4<kAuxCached>(rp, lane * 4, 0); }
+
+  template <int KK>
+  __device__ __forceinline__ f32x4 lookup(const Unit<W / 2>& u) const {
+    uint32_t addr;
+    if constexpr (W == 8) {
+      // byte 0 from the lane's column, byte 1 from the symbol; the table starts at LDS address 0
+      addr = __builtin_amdgcn_perm(u.d[KK >> 2], lane_lut, 0x0c0c0000u | ((4u + (KK & 3)) << 8));
+    } else {
+      constexpr int bit = KK * W, wi = bit >> 5, sh = bit & 31;
+      uint32_t src = u.d[wi];
+      int off = sh;
+      if constexpr (sh + W > 32) {
+        src = __builtin_amdgcn_alignbit(u.d[wi + 1], u.d[wi], sh);
+        off = 0;
+      }
+      uint32_t sym;
+      asm("v_bfe_u32 %0, %1, %2, %3" : "=v"(sym) : "v"(src), "n"(off), "n"(W));
+      asm("v_lshl_add_u32 %0, %1, 8, %2" : "=v"(addr) : "v"(sym), "v"(lane_lut));
+    }
+    return *(const PQ_LDS f32x4*)static_cast<uintptr_t>(addr);
+  }
+  __device__ __forceinline__ void fetch_q(int kk) {
+    qv[kk & 1] = *(const PQ_LDS u32x2*)static_cast<uintptr_t>(q_addr + kk * 128);
+    sz[kk & 1] = *(const PQ_LDS uint32_t*)static_cast<uintptr_t>(par_get + kk * 4);
+  }
+  // The step's query operand: q s and q z rounded to fp16 in high-part columns, what the rounding
+  // left over -- exact for fp16 queries -- in low-part ones.
+  __device__ __forceinline__ void make_query_operand(int kk) {
+    const f16x2 p = u2h(sz[kk & 1]);
+    const f16x2 s_ = {p.x, p.x}, z_ = {p.y, p.y};
+    const u32x2 v = qv[kk & 1];
+    const f16x2 q = u2h(v.x), ql = Q32 ? u2h(v.x & low_mask) : u2h(v.y);
+    f16x2 ys = __builtin_elementwise_fma(q, s_, -(ql * s_));
+    f16x2 yz = __builtin_elementwise_fma(q, z_, -(ql * z_));
+    if constexpr (Q32) {
+      ys = __builtin_elementwise_fma(u2h(v.y), s_, ys);
+      yz = __builtin_elementwise_fma(u2h(v.y), z_, yz);
+    }
+    q_op[kk % kOps][0] = h2u(ys);
+    q_op[kk % kOps][1] = h2u(yz);
+  }
+  // Half-step H: batches 4 half ..+3 of pair step kk.
+  static constexpr int step_of(int H) { return H / (2 * kOps) * kOps + H % kOps; }
+  static constexpr int half_of(int H) { return H / kOps % 2; }
+  static constexpr bool ends_chain(int H) { return H >= 0 && step_of(H) >= kChain && step_of(H) % kChain == kChain - 1; }
+  template <int P, int H>
+  __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rc_nxt, int rot_nxt) {
+    if constexpr (H < 32) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int t = half_of(H) * 4 + j;
+        entry[H % (kAhead + 1)][j] = lookup<step_of(H)>(cu[P][t]);
+        if constexpr (step_of(H) == (kSets == 2 ? 0 : 15)) load_unit_of(kSets == 2 ? 1 - P : P, t, rc_nxt, rot_nxt);
+      }
+    }
+  }
+  template <int P, int H>
+  __device__ __forceinline__ void steps(__amdgpu_buffer_rsrc_t rc_nxt, int rot_nxt) {
+    if constexpr (H < 32) {
+      constexpr int kk = step_of(H), half = half_of(H);
+      issue<P, H + kAhead>(rc_nxt, rot_nxt);
+      const uint32_t b0 = q_op[kk % kOps][0], b1 = q_op[kk % kOps][1];
+      const f16x8 q8 = as_operand(b0, b1, b0, b1);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int t = half * 4 + j;
+        f16x8 k_op;
+        __builtin_memcpy(&k_op, &entry[H % (kAhead + 1)][j], 16);
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (kk < kChain) {
+          s[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(k_op, q8, kk == 0 ? zero : s[t], 0, 0, 0);
+        } else {
+          d[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(k_op, q8, kk % kChain == 0 ? zero : d[j], 0, 0, 0);
+        }
+      }
+      // a finished chain is added a half-step later, when its results are there
+      if constexpr (ends_chain(H - 1)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[half_of(H - 1) * 4 + j] += done[j];
+      }
+      if constexpr (ends_chain(H)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) done[j] = d[j];
+      }
+      // the step's operand has been used for the last time: make that of the same step of the next chain
+      if constexpr (half == 1 && kk + kOps < 16) {
+        make_query_operand(kk + kOps);
+        if constexpr (kk + kOps + 2 < 16) fetch_q(kk + kOps + 2);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      steps<P, H + 1>(rc_nxt, rot_nxt);
+    }
+  }
+  // Scores of the page in cu[P] / par, summed over the columns of a head (and left in all of them), scaled
+  // by 2^(k + the head's query shift + kTableShift); returns k.  cu (set P, or the other of two) and par then
+  // hold the next page.
+  template <int P>
+  __device__ __forceinline__ int run(__amdgpu_buffer_rsrc_t rc_nxt, __amdgpu_buffer_rsrc_t rp_nxt, int rot_nxt, int lane) {
+    issue<P, 0>(rc_nxt, rot_nxt);
+    int k;
+    *(PQ_LDS uint32_t*)static_cast<uintptr_t>(par_put) = scale_page_params(par, k);
+    load_params(rp_nxt, lane);
+    wave_lds_sync();
+    fetch_q(0);
+    fetch_q(1);
+#pragma unroll
+    for (int kk = 0; kk < kOps; ++kk) {
+      make_query_operand(kk);
+      fetch_q(kk + 2);
+    }
+    if constexpr (kAhead == 2) issue<P, 1>(rc_nxt, rot_nxt);
+    static_assert(kAhead == 1 || kAhead == 2, "reads issued before the first half-step");
+    __builtin_amdgcn_sched_barrier(0);
+    steps<P, 0>(rc_nxt, rot_nxt);
+    if constexpr (kChain < 16) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s[4 + j] += done[j];
+    }
+    fold();
+    wave_lds_sync();
+    return k;
+  }
+  __device__ __forceinline__ void fold() {
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if constexpr (NH == 4) s[t][i] += dpp_of<0x124>(s[t][i]);          // row_ror:4: the other half's column
+        s[t][i] += dpp_of<0x128>(s[t][i]);                                 // row_ror:8: the other part's
+      }
+  }
+  // Scores of the residual group (un-quantized fp16 keys, rows past nv_res read as zero): a key row
+  // is an operand as it lies in memory, 32 dims per instruction; same scaling with k = 0, table
+  // shift 0.
+  __device__ __forceinline__ void residual(const __half* rows, int nv_res, int rot, int lane) {
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(rows, static_cast<uint32_t>(nv_res) * (kHeadDim * 2));
+    const int row = lane >> 4, col = lane & 15;
+    f16x8 q8[4];
+#pragma unroll
+    for (int kd = 0; kd < 4; ++kd) {
+      // dims 32 kd + 8 row .. + 7: one coordinate of 8 consecutive pairs; the query in high-part
+      // columns, what its rounding to fp16 left over in low-part ones
+      const int j0 = 32 * (kd & 1) + 8 * row;
+      const uint32_t at = q_addr - row * kQueryBlock + (j0 >> 4) * kQueryBlock + (j0 & 15) * 128;
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        uint32_t x[2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+          const u32x2 v = *(const PQ_LDS u32x2*)static_cast<uintptr_t>(at + (2 * e + o) * 128);
+          const uint32_t pick = (v.x & ~low_mask) | (Q32 ? v.y : 0u);
+          x[o] = (kd >> 1) ? pick >> 16 : pick & 0xffffu;
+        }
+        w[e] = x[0] | (x[1] << 16);
+      }
+      q8[kd] = as_operand(w[0], w[1], w[2], w[3]);
+    }
+    const uint32_t voff = row_token<O>(col) * (kHeadDim * 2) + row * 16;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const uint32_t soff = static_cast<uint32_t>(batch_token<O>(t, rot)) * (kHeadDim * 2);
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      f32x4 lo = zero, hi = zero;
+#pragma unroll
+      for (int kd = 0; kd < 4; ++kd) {
+        const f16x8 k_op = as_operand(buf_load16<kAuxCached>(rs, voff, soff + kd * 64));
+        if (kd < 2) lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(k_op, q8[kd], lo, 0, 0, 0);
+        else hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(k_op, q8[kd], hi, 0, 0, 0);
+      }
+      s[t] = lo + hi;
+      if (t & 1) __builtin_amdgcn_sched_barrier(0);
+    }
+    fold();
+  }
+};
+
+// Pool pages of the pages a wavefront handles in a chunk (chunk pages wave, wave + NW, ...), read one by
+// one through the scalar cache, a page ahead of their use.  Entries of the table row are read
+// without knowing the sequence's length; `get` masks the pages past the wavefront's last one, and
+// block-table entries outside the pool.
+template <int NW>
+struct PageIds {
+  const PQ_CONST int32_t* table;   // block-table row of the sequence, at the wavefront's first page
+  int64_t n_pool_pages;
+  int n_row;                       // entries of the row that belong to the wavefront from there on
+  int n_p;                         // pages of the wavefront in this chunk
+  int ahead;                       // entry of the page that get() is asked for next
+  __device__ __forceinline__ void fetch(int k) { ahead = k < n_row ? table[NW * k] : -1; }
+  __device__ __forceinline__ void start(const DecodeArgs& a, int seq, int first_page) {
+    table = reinterpret_cast<const PQ_CONST int32_t*>(
+        reinterpret_cast<uintptr_t>(a.block_table + static_cast<int64_t>(seq) * a.max_pages_per_seq + first_page));
+    n_pool_pages = a.n_pool_pages;
+    n_row = first_page < a.max_pages_per_seq ? (a.max_pages_per_seq - first_page + NW - 1) / NW : 0;
+    fetch(0);
+  }
+  // id of the wavefront's k-th page, k = 0, 1, 2, ...; -1 if masked or past its last page
+  __device__ __forceinline__ int get(int k) {
+    const int id = ahead;
+    fetch(k + 1);
+    return k < n_p && id >= 0 && id < n_pool_pages ? id : -1;
+  }
+};
+// Lane number, computed where it is asked for (two instructions): cheaper than a register through
+// the page loop.
+__device__ __forceinline__ int lane_id() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(l));
+  return l;
+}
+
+// Two work-groups share a compute unit, a wavefront of each a SIMD: they take the higher issue
+// priority in turns, page by page, so that one's matrix instructions meet the other's vector work.
+__device__ __forceinline__ int priority_turn() {
+  return static_cast<int>(((blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) / 256u) & 1u);
+}
+__device__ __forceinline__ void alternate_priority(int turn) {
+  if (turn & 1) __builtin_amdgcn_s_setprio(1);
+  else __builtin_amdgcn_s_setprio(0);
+}
+
+// What an accumulator of dim k (of the lane's 8) is multiplied with at the end with quantized values: a
+// code was masked in place as an fp16 denormal, code * 2^(position - 24).  Fields are moved up to
+// bits 4 .. 9 first: the matrix unit aligns products by their operands' exponent fields, and the
+// low bits of products with denormals further down are lost (measured: 2e-4 of the output with
+// fields at bit 0, 1e-6 at bits 4 and up).
+template <int VB>
+__device__ __forceinline__ constexpr float code_unscale(int k) {
+  constexpr int kAt2[8] = {4, 6, 8, 6, 8, 4, 6, 8};
+  const int at = VB == 4 ? ((k & 3) == 1 ? 4 : 6) : kAt2[k];
+  return static_cast<float>(1 << (24 - at));
+}
+
+// ---- attention ----------------------------------------------------------------------------------
+template <int W, int VB, int NH, bool Q32>
+__device__ __forceinline__ void attention_body(const DecodeArgs& a) {
+  constexpr int UB = 2 * W;
+  constexpr bool kQuantV = VB != 16;
+  constexpr TokenOrder kOrder = token_order(VB);
+  constexpr int kChain = kQuantV ? 16 : 4;
+  constexpr uint32_t kCodesBytes = kBlocks * kGroup * UB;
+  // Probabilities are exp2(score - m + kProbShift) with m the running maximum rounded up to a whole
+  // number (rescaling factors are then exact powers of two): with fp16 values in [0, 16], so that the
+  // low part's fp16 quantum stays out of the way; with quantized values they meet the token's scale
+  // before they are split, and stay in [0, 1].
+  constexpr float kProbShift = kQuantV ? 0.f : 4.f;
+  constexpr int kVLoads = kQuantV ? kGroup * kHeadDim * VB / 8 / 1024 : 32;   // 1 KB wavefront loads per page of values
+
+  struct Shared {
+    __attribute__((aligned(16))) uint8_t lut[(1 << W) * kTableRow];      // first: at LDS address 0
+    union {
+      QueryShared q;
+      __attribute__((aligned(16))) float red[2][NH][kHeadDim];           // end of the chunk; also lent to the merge
+      float lent[kFinishLdsFloats];
+    };
+    __attribute__((aligned(16))) uint32_t params[kMatWaves][kPairs];
+    __attribute__((aligned(16))) uint32_t vpar[kQuantV ? kMatWaves : 1][kQuantV ? kGroup : 1];
+    float red_ml[kMatWaves][NH][3];                                      // m, l, sum of p * zero-point
+    int q_shift[kMaxHeads];
+    int stage;
+  };
+  __shared__ Shared sh;
+  static_assert(sizeof(Shared) <= 80 * 1024, "two work-groups per compute unit");
+
+  const int kvh = blockIdx.x, seq = blockIdx.y, chunk = blockIdx.z;
+  const int tid = threadIdx.x;
+  const int wave = uni(tid >> 6);
+  const int lane = tid & 63;
+  const int big = min(chunk, a.n_big);
+  const int page0 = big * a.pages_per_chunk + (chunk - big) * a.pages_small;
+  // what does not depend on the sequence's length is fetched along with it
+  const QueryFetch qf = fetch_query_heads(a, Q32, (static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0) * kHeadDim, tid);
+  PageIds<kMatWaves> pids;
+  pids.start(a, seq, page0 + wave);
+  const int L = uni(clamped_len(a, seq));
+  const int n_pages = pages_of_len(L);
+  if (page0 >= n_pages) {
+    // nothing here; a sequence without pages gets its zero rows from its first work-group
+    if (a.merge_in_kernel && chunk == 0 && tid < a.n_heads * 32) {
+      const int64_t head_row = static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0;
+      reinterpret_cast<float4*>(a.out + head_row * kHeadDim)[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    return;
+  }
+  const int npg = min(chunk < a.n_big ? a.pages_per_chunk : a.pages_small, n_pages - page0);
+  const float sign = a.scale_log2 < 0.f ? -1.f : 1.f, scale_abs = fabsf(a.scale_log2);
+  const int row = lane >> 4, col = lane & 15;
+  const int head = column_head<NH>(col);
+  const int n_w = npg > wave ? (npg - wave + kMatWaves - 1) / kMatWaves : 0;   // chunk pages wave, wave + 4, ...
+  const int res_page = (a.residual != nullptr && (L % kGroup) != 0) ? L / kGroup : -1;
+  pids.n_p = n_w;
+
+  const uint32_t voff_values = lane * 16;     // 16 lanes a token row (fp16) or a block of units (quantized)
+  auto page_setup = [&](int k, __amdgpu_buffer_rsrc_t& rc, __amdgpu_buffer_rsrc_t& rp, __amdgpu_buffer_rsrc_t& rv,
+                        __amdgpu_buffer_rsrc_t& rvp, int& nv, int& rot) {
+    const int pid = pids.get(k);
+    const bool ok = pid >= 0;
+    const int64_t ph = ok ? static_cast<int64_t>(pid) * a.n_kv_heads + kvh : 0;
+    const int page = page0 + wave + kMatWaves * k;
+    nv = ok ? min(kGroup, L - page * kGroup) : 0;
+    // pages and heads are a power-of-two number of bytes apart: wavefronts that walk them in the
+    // same order keep hitting the same memory channels together, so the order is rotated
+    rot = (ok && !kQuantV) ? (pid * 13 + kvh * 5) & 7 : 0;
+    const bool packed = ok && page != res_page;                        // the residual group has no codes yet
+    rc = make_rsrc(a.codes + ph * kCodesBytes, packed ? kCodesBytes : 0u);
+    rp = make_rsrc(a.params + ph * kPairs, packed ? kPairs * 4u : 0u);
+    if constexpr (kQuantV) {
+      // whole units are read; codes of slots past the sequence end are finite by construction
+      // and meet a zero probability.  Their parameters could be anything: bounded by nv.
+      rv = make_rsrc(reinterpret_cast<const uint8_t*>(a.values) + ph * (kGroup * kHeadDim * VB / 8),
+                     nv > 0 ? kGroup * kHeadDim * VB / 8 : 0u);
+      rvp = make_rsrc(a.v_params + ph * kGroup, static_cast<uint32_t>(nv) * 4u);
+    } else {
+      rv = make_rsrc(a.values + ph * (kGroup * kHeadDim), static_cast<uint32_t>(nv) * (kHeadDim * 2));
+      rvp = rv;
+    }
+  };
+  __amdgpu_buffer_rsrc_t rc_cur, rp_cur, rv_cur, rvp_cur, rc_nxt, rp_nxt, rv_nxt, rvp_nxt;
+  int nv_cur, nv_nxt, rot_cur, rot_nxt;
+  ScoreWalk<W, kOrder, NH, Q32, kQuantV ? 2 : 1, 1, kChain> w;
+  w.init(sh.lut, sh.q, sh.params[wave], lane);
+  uint4 vr[kQuantV ? 1 : 4][8];                                        // fp16 values: four groups of 8 rows (32 tokens)
+  uint4 vq[kQuantV ? kVLoads : 1];                                     // quantized values: the page's units
+  u32x2 vpar = {0u, 0u};                                               // (scale, zero) of tokens 2 lane, 2 lane + 1
+  // rows of value group g: batches 2g, 2g + 1, tokens 4 i + row of each
+  auto load_rows = [&](uint4 (&dst)[8], __amdgpu_buffer_rsrc_t rv, int g, int rot) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        dst[4 * b + i] = buf_load16<kAuxStream>(rv, voff_values, static_cast<uint32_t>((2 * g + b + rot) & 7) * 4096u + i * 1024u);
+  };
+  page_setup(0, rc_cur, rp_cur, rv_cur, rvp_cur, nv_cur, rot_cur);
+  w.load_params(rp_cur, lane);
+#pragma unroll
+  for (int t = 0; t < 8; ++t) w.load_unit_of(0, t, rc_cur, rot_cur);
+  if constexpr (kQuantV) {
+    vpar = __builtin_amdgcn_raw_buffer_load_b64(rvp_cur, lane * 8, 0, kAuxCached);
+#pragma unroll
+    for (int k = 0; k < kVLoads; ++k) vq[k] = buf_load16<kAuxStream>(rv_cur, voff_values, k * 1024);
+  } else {
+    load_rows(vr[0], rv_cur, 0, rot_cur);
+    load_rows(vr[1], rv_cur, 1, rot_cur);
+  }
+  fill_key_table<W, kMatThreads>(sh.lut, key_table<W>(a.table_index), tid);           // while the first page is under way
+  store_query_heads<NH, Q32>(sh.q, sh.q_shift, qf, sign, tid);
+  __syncthreads();
+
+  // per lane: column (head, part), running maximum, sums over the lane's tokens
+  // (fp16 values: the sums of p come from the matrix unit like one more dim, l_acc)
+  float m_run = kNegInf, l_run = 0.f, z_run = 0.f;
+  f32x4 l_acc = {0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[8];                                                        // dim 8 col + e; columns 4 row .. + 3
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const int turn = priority_turn();
+  for (int it = 0; it < n_w; ++it) {
+    const int pi = page0 + wave + kMatWaves * it;
+    if constexpr (kQuantV) alternate_priority(turn + it);             // (costs 1 % where memory is the bound)
+    page_setup(it + 1, rc_nxt, rp_nxt, rv_nxt, rvp_nxt, nv_nxt, rot_nxt);
+    // lane constants of the score walk, derived anew for each page: the value phase needs their registers
+    const int lane = lane_id(), col = lane & 15;
+    w.init(sh.lut, sh.q, sh.params[wave], lane);
+    const int q_shift = sh.q_shift[column_head<NH>(col)];
+    if constexpr (kQuantV) {
+      *(PQ_LDS u32x2*)static_cast<uintptr_t>(lds_addr(sh.vpar[wave]) + lane * 8) = vpar;
+      vpar = __builtin_amdgcn_raw_buffer_load_b64(rvp_nxt, lane * 8, 0, kAuxCached);
+    }
+    int down = w.template run<0>(rc_nxt, rp_nxt, rot_nxt, lane) + kTableShift + q_shift;
+    if (pi == res_page) {
+      w.residual(a.residual + (static_cast<int64_t>(seq) * a.n_kv_heads + kvh) * (kGroup * kHeadDim), L - res_page * kGroup,
+                 rot_cur, lane_id());
+      down = q_shift;
+    }
+    // the groups the score walk had no registers for
+    if constexpr (!kQuantV) load_rows(vr[2], rv_cur, 2, rot_cur);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- online softmax (log2 domain) over the lane's 32 tokens ----
+    // above zero, so that masked scores (-inf) stay masked whatever the scale is
+    const float mult = fmaxf(__builtin_ldexpf(scale_abs, -down), 1.17549435e-38f);
+    if (nv_cur < kGroup) {
+      const int row = lane_id() >> 4;
+      int nv = uni(nv_cur);
+      asm volatile("" : "+s"(nv));                                     // 32 conditions: not worth keeping in registers
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (batch_token<kOrder>(t, rot_cur) + row_token<kOrder>(4 * row + i) >= nv) w.s[t][i] = kNegInf;
+    }
+    float pm = fmaxf(w.s[0][0], w.s[0][1]);
+    pm = max3(pm, w.s[0][2], w.s[0][3]);
+#pragma unroll
+    for (int t = 1; t < 8; ++t) {
+      pm = max3(pm, w.s[t][0], w.s[t][1]);
+      pm = max3(pm, w.s[t][2], w.s[t][3]);
+    }
+    {
+      auto r = __builtin_amdgcn_permlane16_swap(f2u(pm), f2u(pm), false, false);
+      pm = fmaxf(u2f(r[0]), u2f(r[1]));
+      auto q = __builtin_amdgcn_permlane32_swap(f2u(pm), f2u(pm), false, false);
+      pm = fmaxf(u2f(q[0]), u2f(q[1]));
+    }
+    const float m_new = fmaxf(m_run, __builtin_ceilf(pm * mult));
+    const bool dead = !(m_new > kNegInf);                              // nothing valid seen so far
+    if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+      const float alpha = dead ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first page
+      if constexpr (kQuantV) {
+        l_run *= alpha;
+        z_run *= alpha;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float al = __shfl(alpha, (NH == 8 ? 4 * ((lane_id() >> 4) & 1) : 0) + i);   // head of accumulator row i
+        if constexpr (!kQuantV) l_acc[i] *= al;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e][i] *= al;
+      }
+      m_run = m_new;
+    }
+    const float off = dead ? 0.f : kProbShift - m_run;
+    uint32_t p_op[8][2];                                               // batch t: fp16 pairs of tokens 4 row + (0, 1), (2, 3)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      float p[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(w.s[t][i], mult, off));
+      if constexpr (kQuantV) {
+        l_run += (p[0] + p[1]) + (p[2] + p[3]);
+        // V~ = code * s + z (Section 2): fold s into the probability, collect p * z
+        const u32x4 vp = *(const PQ_LDS u32x4*)static_cast<uintptr_t>(
+            lds_addr(sh.vpar[wave]) + (batch_token<kOrder>(t, 0) + row_token<kOrder>(4 * row)) * 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const f16x2 sz = u2h(vp[i]);
+          z_run = fmaf(p[i], static_cast<float>(sz.y), z_run);
+          p[i] = fmaf(p[i], static_cast<float>(sz.x), 0.f);
+        }
+      }
+      if constexpr (!kQuantV) {
+        if (t == 7) load_rows(vr[3], rv_cur, 3, rot_cur);
+      }
+      p_op[t][0] = split_pair(p[0], p[1], w.minus_low);
+      p_op[t][1] = split_pair(p[2], p[3], w.minus_low);
+    }
+
+    // ---- values: acc += P^T V, 32 tokens (batches 2g, 2g + 1) per instruction ----
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f16x8 pa = as_operand(p_op[2 * g][0], p_op[2 * g][1], p_op[2 * g + 1][0], p_op[2 * g + 1][1]);
+      if constexpr (VB == 16) {
+        constexpr uint32_t kOnes = 0x3c003c00u;
+        l_acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa, as_operand(kOnes, kOnes, kOnes, kOnes), l_acc, 0, 0, 0);
+        uint4(&v)[8] = vr[g];
+        const uint32_t wv[4][8] = {{v[0].x, v[1].x, v[2].x, v[3].x, v[4].x, v[5].x, v[6].x, v[7].x},
+                                   {v[0].y, v[1].y, v[2].y, v[3].y, v[4].y, v[5].y, v[6].y, v[7].y},
+                                   {v[0].z, v[1].z, v[2].z, v[3].z, v[4].z, v[5].z, v[6].z, v[7].z},
+                                   {v[0].w, v[1].w, v[2].w, v[3].w, v[4].w, v[5].w, v[6].w, v[7].w}};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          uint32_t lo[4], hi[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            lo[k] = __builtin_amdgcn_perm(wv[e][2 * k + 1], wv[e][2 * k], 0x05040100u);   // dim 2e of a token pair
+            hi[k] = __builtin_amdgcn_perm(wv[e][2 * k + 1], wv[e][2 * k], 0x07060302u);   // dim 2e + 1
+          }
+          acc[2 * e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa, as_operand(lo[0], lo[1], lo[2], lo[3]), acc[2 * e], 0, 0, 0);
+          acc[2 * e + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa, as_operand(hi[0], hi[1], hi[2], hi[3]), acc[2 * e + 1], 0, 0, 0);
+        }
+        if (g < 2) load_rows(vr[g], rv_nxt, g, rot_nxt);
+        __builtin_amdgcn_sched_barrier(0);
+      } else if constexpr (VB == 4) {
+        // units 2g, 2g + 1 = the tokens of batches 2g, 2g + 1: words (token pair, dim half)
+        const uint32_t u[2][4] = {{vq[2 * g].x, vq[2 * g].y, vq[2 * g].z, vq[2 * g].w},
+                                  {vq[2 * g + 1].x, vq[2 * g + 1].y, vq[2 * g + 1].z, vq[2 * g + 1].w}};
+#pragma unroll
+        for (int dh = 0; dh < 2; ++dh) {
+          const uint32_t x[4] = {u[0][dh], u[0][2 + dh], u[1][dh], u[1][2 + dh]};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            uint32_t f[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              f[j] = (k == 0 ? x[j] << 6 : (k == 1 ? x[j] : x[j] >> (4 * k - 6))) & (k == 1 ? 0x00f000f0u : 0x03c003c0u);
+            acc[4 * dh + k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa, as_operand(f[0], f[1], f[2], f[3]), acc[4 * dh + k], 0, 0, 0);
+          }
+        }
+        vq[2 * g] = buf_load16<kAuxStream>(rv_nxt, voff_values, (2 * g) * 1024);
+        vq[2 * g + 1] = buf_load16<kAuxStream>(rv_nxt, voff_values, (2 * g + 1) * 1024);
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        static_assert(VB == 2, "value bits");
+        // unit g = 32 tokens: words are token pairs with all 8 dims
+        const uint32_t x[4] = {vq[g].x, vq[g].y, vq[g].z, vq[g].w};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          constexpr uint32_t kMask[8] = {0x00300030u, 0x00c000c0u, 0x03000300u, 0x00c000c0u,
+                                         0x03000300u, 0x00300030u, 0x00c000c0u, 0x03000300u};
+          uint32_t f[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) f[j] = (k < 3 ? x[j] << 4 : (k < 5 ? x[j] : x[j] >> 6)) & kMask[k];
+          acc[k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa, as_operand(f[0], f[1], f[2], f[3]), acc[k], 0, 0, 0);
+        }
+        vq[g] = buf_load16<kAuxStream>(rv_nxt, voff_values, g * 1024);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    rc_cur = rc_nxt; rp_cur = rp_nxt; rv_cur = rv_nxt; rvp_cur = rvp_nxt; nv_cur = nv_nxt; rot_cur = rot_nxt;
+  }
+
+  // ---- fold the four wavefronts: maxima and sums through LDS, accumulators in two rounds ----
+  {
+    const int lane = lane_id(), row = lane >> 4, col = lane & 15;
+    const int acc_head = NH == 8 ? 4 * (row & 1) : 0;                  // head of accumulator row i: acc_head + i
+    // columns 0 .. NH - 1 are the heads' high parts; accumulator rows: high part + low part
+    const float l_tot = kQuantV ? sum_rows(l_run) : 0.f;
+    const float z_tot = kQuantV ? sum_rows(z_run) : 0.f;
+    if (lane < NH) {
+      sh.red_ml[wave][lane][0] = m_run;
+      if constexpr (kQuantV) sh.red_ml[wave][lane][1] = l_tot;
+      sh.red_ml[wave][lane][2] = z_tot;
+    }
+    if constexpr (!kQuantV) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float l = tsum32(l_acc[i], l_acc[i]);
+        if (col == 0 && row < NH / 4) sh.red_ml[wave][4 * row + i][1] = l;
+      }
+    }
+    __syncthreads();
+    float wgt[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int h = acc_head + i;
+      const float M = fmaxf(fmaxf(sh.red_ml[0][h][0], sh.red_ml[1][h][0]), fmaxf(sh.red_ml[2][h][0], sh.red_ml[3][h][0]));
+      wgt[i] = M > kNegInf ? __builtin_amdgcn_exp2f(sh.red_ml[wave][h][0] - M) : 0.f;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        acc[e][i] = tsum32(acc[e][i], acc[e][i]) * wgt[i];
+        if constexpr (kQuantV) acc[e][i] *= code_unscale<VB>(e);
+      }
+    if (wave < 2 && row < NH / 4) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        f32x4* const dst = reinterpret_cast<f32x4*>(&sh.red[wave][4 * row + i][col * 8]);
+        dst[0] = f32x4{acc[0][i], acc[1][i], acc[2][i], acc[3][i]};
+        dst[1] = f32x4{acc[4][i], acc[5][i], acc[6][i], acc[7][i]};
+      }
+    }
+    __syncthreads();
+    if (wave >= 2 && row < NH / 4) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        f32x4* const dst = reinterpret_cast<f32x4*>(&sh.red[wave - 2][4 * row + i][col * 8]);
+        dst[0] += f32x4{acc[0][i], acc[1][i], acc[2][i], acc[3][i]};
+        dst[1] += f32x4{acc[4][i], acc[5][i], acc[6][i], acc[7][i]};
+      }
+    }
+    __syncthreads();
+  }
+
+  finish_chunk<NH>(a, seq, kvh, chunk, chunks_of_pages(n_pages, a.pages_per_chunk, a.n_big, a.pages_small), wave * 64 + lane_id(), [&](int h, int quad, float& M, float& l) {
+    M = fmaxf(fmaxf(sh.red_ml[0][h][0], sh.red_ml[1][h][0]), fmaxf(sh.red_ml[2][h][0], sh.red_ml[3][h][0]));
+    f32x4 o = *reinterpret_cast<const f32x4*>(&sh.red[0][h][quad * 4]) + *reinterpret_cast<const f32x4*>(&sh.red[1][h][quad * 4]);
+    l = 0.f;
+    if (M > kNegInf) {
+      float zp = 0.f;                                                  // zero-point term: the same for every dim
+#pragma unroll
+      for (int v = 0; v < kMatWaves; ++v) {
+        const float wg = __builtin_amdgcn_exp2f(sh.red_ml[v][h][0] - M);
+        l = fmaf(wg, sh.red_ml[v][h][1], l);
+        zp = fmaf(wg, sh.red_ml[v][h][2], zp);
+      }
+      if constexpr (kQuantV) o += zp;
+    }
+    return o;
+  }, sh.lent, &sh.stage);
+}
+
+}  // namespace
+}  // namespace pq

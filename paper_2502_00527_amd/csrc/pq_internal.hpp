@@ -28,6 +28,10 @@ bool layout_supported(const pq_layout* l);
 struct ChunkPlan {
   int32_t pages_per_chunk;
   int32_t n_chunks;   // per sequence, for max_seq_len
+  // chunks from number n_big on are pages_small long (attention kernel of the uniform grid; otherwise
+  // n_big is n_chunks)
+  int32_t n_big;
+  int32_t pages_small;
 };
 ChunkPlan plan_chunks(int32_t n_seqs, int32_t n_kv_heads, int32_t max_seq_len);
 
