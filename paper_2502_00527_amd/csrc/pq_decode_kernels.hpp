@@ -8,12 +8,11 @@
 // pulled out of the token loop.  Softmax and the fp16 value aggregation that
 // consume the scores are fused behind it (standard attention, Section 2).
 //
-// This header holds what the decode kernels share (streaming loads, table builds, pair steps,
-// value steps, residual keys) and two of the kernels: pq_decode_partials_kernel, whose
-// wavefronts alternate between a score and a value phase, and the score-only kernels.  The
-// attention kernel that serves large launches, with wavefronts specialised by role, is in
-// pq_decode_roles.hpp; how a launch is shared out and merged inside the kernel is in
-// pq_decode_sched.hpp.
+// This header holds what the vector-unit kernels share (streaming loads, table builds, pair steps,
+// value steps, residual keys) and the kernels themselves: pq_decode_partials_kernel, whose
+// wavefronts alternate between a score and a value phase and which serves the grouped angle
+// quantizer, and the score-only kernels of both quantizers.  Attention over the uniform angle grid is on
+// the matrix cores (pq_decode_matrix.hpp).
 //
 // Mapping to the machine in the attention kernels.  A work-group is 4 wavefronts; the table of
 // all query heads that share the KV head lives in LDS with the heads interleaved (one 16-byte
@@ -89,11 +88,9 @@ struct DecodeArgs {
   float sin_tab[kMaxAngleBins];
 };
 
-// Launchers of the instantiation units (rt = 10 r + t).  They return false, and launch nothing,
-// if there is no kernel for the combination; launch errors are left to hipGetLastError().
-// pq_decode_partials.hip / pq_decode_partials_ga.hip: the attention kernel whose wavefronts
-// alternate between a score and a value phase, uniform angle grid / grouped angle quantizer.
-bool launch_attention_partials(int rt, int G, int v_bits, const DecodeArgs& a, dim3 grid, hipStream_t st);
+// Launcher of the grouped quantizer's attention kernels (rt = 10 r + t; pq_decode_partials_ga.hip).
+// Returns false, and launches nothing, if there is no kernel for the combination; launch errors are
+// left to hipGetLastError().
 bool launch_attention_partials_ga(int rt, int G, int v_bits, const DecodeArgs& a, dim3 grid, hipStream_t st);
 
 namespace {
@@ -134,44 +131,21 @@ __device__ __forceinline__ float row_sum(float x) {
   x += __shfl_xor(x, 2);
   return x + __shfl_xor(x, 1);
 }
-// Maximum / sum over all 64 lanes, result in every lane: inside a row of 16 by DPP (lane ^ 1,
-// lane ^ 2, mirror within 8, mirror within 16), across the rows by the two lane-swap instructions.
+// A DPP move within a row of 16 lanes.
 template <int CTRL>
 __device__ __forceinline__ float dpp_of(float x) {
   return u2f(static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(f2u(x)), CTRL, 0xf, 0xf, true)));
 }
-__device__ __forceinline__ float wave_max(float x) {
-  x = fmaxf(x, dpp_of<0xB1>(x));      // quad_perm(1,0,3,2)
-  x = fmaxf(x, dpp_of<0x4E>(x));      // quad_perm(2,3,0,1)
-  x = fmaxf(x, dpp_of<0x141>(x));     // row_half_mirror
-  x = fmaxf(x, dpp_of<0x140>(x));     // row_mirror
-  auto r = __builtin_amdgcn_permlane16_swap(f2u(x), f2u(x), false, false);
-  x = fmaxf(u2f(r[0]), u2f(r[1]));
-  auto q = __builtin_amdgcn_permlane32_swap(f2u(x), f2u(x), false, false);
-  return fmaxf(u2f(q[0]), u2f(q[1]));
-}
-__device__ __forceinline__ float wave_sum_f(float x) {
-  x += dpp_of<0xB1>(x);
-  x += dpp_of<0x4E>(x);
-  x += dpp_of<0x141>(x);
-  x += dpp_of<0x140>(x);
-  return sum_rows(x);
-}
-
 // Sum of the four 16-lane rows' partial scores: with 4 query heads row h ends with head h's
-// score (transposing fold), with 2 heads rows 0-1 / 2-3, with 1 head every row; with 8 heads row h
-// ends with the scores of heads h and h + 4 (two transposing folds).
+// score (transposing fold), with 2 heads rows 0-1 / 2-3, with 1 head every row.
 template <int G>
 struct Folded {
-  float v[G == 8 ? 2 : 1];
+  float v[1];
 };
 template <int G>
 __device__ __forceinline__ Folded<G> fold_rows(const float (&part)[G]) {
   Folded<G> f;
-  if constexpr (G == 8) {
-    f.v[0] = tsum16(tsum32(part[0], part[2]), tsum32(part[1], part[3]));
-    f.v[1] = tsum16(tsum32(part[4], part[6]), tsum32(part[5], part[7]));
-  } else if constexpr (G == 4) {
+  if constexpr (G == 4) {
     f.v[0] = tsum16(tsum32(part[0], part[2]), tsum32(part[1], part[3]));
   } else if constexpr (G == 2) {
     const float b = tsum32(part[0], part[1]);
@@ -273,18 +247,11 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const PQ_LDS uint8_t*)p));
 }
 
-// The G heads' values of one 16-byte entry; 8 heads are kept as two tables of 4-head entries, the
-// second one HALF bytes after the first, so that an entry's offset is the same in both.
-template <int G, int HALF = 0>
+// The G heads' values of one 16-byte entry.
+template <int G>
 __device__ __forceinline__ Heads<G> lut_read(uint32_t addr) {
   Heads<G> t;
-  if constexpr (G == 8) {
-    static_assert(HALF > 0, "distance of the second table");
-    const f32x4 f = *(const PQ_LDS f32x4*)static_cast<uintptr_t>(addr);
-    const f32x4 g = *(const PQ_LDS f32x4*)static_cast<uintptr_t>(addr + HALF);
-    t.v[0] = f.x; t.v[1] = f.y; t.v[2] = f.z; t.v[3] = f.w;
-    t.v[4] = g.x; t.v[5] = g.y; t.v[6] = g.z; t.v[7] = g.w;
-  } else if constexpr (G == 4) {
+  if constexpr (G == 4) {
     const f32x4 f = *(const PQ_LDS f32x4*)static_cast<uintptr_t>(addr);
     t.v[0] = f.x; t.v[1] = f.y; t.v[2] = f.z; t.v[3] = f.w;
   } else if constexpr (G == 2) {
@@ -364,7 +331,7 @@ __device__ __forceinline__ void score_steps(const Unit<(RB + TB) / 2>& u, uint32
     uint32_t addr;
     pair_fields<RB, TB, K>(u, lut_row0, c, addr);
     const float rho = fmaf(c, sf[K], zz[K]);
-    const Heads<G> t = lut_read<G, kPairs * ROW>(addr + K * ROW);
+    const Heads<G> t = lut_read<G>(addr + K * ROW);
 #pragma unroll
     for (int h = 0; h < G; ++h) part[h] = fmaf(rho, t.v[h], part[h]);
     score_steps<G, RB, TB, K + 1>(u, lut_row0, sf, zz, part);
@@ -403,8 +370,8 @@ __device__ __forceinline__ void dense_steps(const uint4 (&kx)[2], const uint4 (&
         const __half2 hv = *reinterpret_cast<const __half2*>(&w4[e]);
         const float k0 = __low2float(hv), k1 = __high2float(hv);
         const int dim = half * kPairs + v * 8 + 2 * e;            // relative to 16 * row
-        const Heads<G> q0 = lut_read<G, kHeadDim * 16>(qs_row + dim * 16);
-        const Heads<G> q1 = lut_read<G, kHeadDim * 16>(qs_row + (dim + 1) * 16);
+        const Heads<G> q0 = lut_read<G>(qs_row + dim * 16);
+        const Heads<G> q1 = lut_read<G>(qs_row + (dim + 1) * 16);
 #pragma unroll
         for (int h = 0; h < G; ++h) part[h] = fmaf(k1, q1.v[h], fmaf(k0, q0.v[h], part[h]));
       }
@@ -474,45 +441,6 @@ __device__ __forceinline__ uint32_t pack_with_neighbour(float x) {
       __builtin_amdgcn_update_dpp(0, static_cast<int>(f2u(x)), 0xB1 /* quad_perm(1,0,3,2) */, 0xf, 0xf, true)));
   const __half2 h = __floats2half2_rn(x, other);
   return *reinterpret_cast<const uint32_t*>(&h);
-}
-
-// The same with the lane four further on in its row of 16 (lane + 4): called where the lanes col
-// and col + 4 hold the probabilities of tokens n and n + 4; the lanes with (col & 4) == 0 store.
-__device__ __forceinline__ uint32_t pack_with_lane4(float x) {
-  const float other = u2f(static_cast<uint32_t>(
-      __builtin_amdgcn_update_dpp(0, static_cast<int>(f2u(x)), 0x104 /* row_shl:4 */, 0xf, 0xf, true)));
-  const __half2 h = __floats2half2_rn(x, other);
-  return *reinterpret_cast<const uint32_t*>(&h);
-}
-
-// fp16 values with 8 query heads: acc[h][0..7] += p_h[token] * V[token][this lane's 8 dims] for the
-// 4 value rows in `vv`, the (it0 + i)-th 1 KB loads of the page in its rotated order (rot even),
-// i.e. tokens 4 * ((it0 + i + rot) % 32) + row.  Rows i = 0, 1 and i = 2, 3 are token pairs
-// (n, n + 4): their values are interleaved dim by dim (v_perm_b32) into fp16 pairs and meet the
-// probability pairs [pair 4 * (load / 2) + row][8 heads] at `prob` in one v_dot2_f32_f16 per
-// head and dim -- half the instructions of one multiply-add per token.
-__device__ __forceinline__ void consume_values_pairs(const uint4 (&vv)[4], int it0, uint32_t prob, int rot, int row,
-                                                     float (&acc)[8][8]) {
-#pragma unroll
-  for (int i = 0; i < 4; i += 2) {
-    const uint32_t load = static_cast<uint32_t>((it0 + i + rot) & 31);
-    const uint32_t pa = prob + ((4u * (load >> 1) + static_cast<uint32_t>(row)) * 8u) * 4u;
-    const Pairs<4> p0 = pairs_read<4>(pa), p1 = pairs_read<4>(pa + 16);
-    const uint32_t wa[4] = {vv[i].x, vv[i].y, vv[i].z, vv[i].w};
-    const uint32_t wb[4] = {vv[i + 1].x, vv[i + 1].y, vv[i + 1].z, vv[i + 1].w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint32_t lo = __builtin_amdgcn_perm(wb[e], wa[e], 0x05040100u);   // dim 2e of tokens n, n + 4
-      const uint32_t hi = __builtin_amdgcn_perm(wb[e], wa[e], 0x07060302u);   // dim 2e + 1
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        acc[h][2 * e] = dot2(p0.v[h], lo, acc[h][2 * e]);
-        acc[h][2 * e + 1] = dot2(p0.v[h], hi, acc[h][2 * e + 1]);
-        acc[h + 4][2 * e] = dot2(p1.v[h], lo, acc[h + 4][2 * e]);
-        acc[h + 4][2 * e + 1] = dot2(p1.v[h], hi, acc[h + 4][2 * e + 1]);
-      }
-    }
-  }
 }
 
 // Power of two an accumulator of dim k (of the lane's 8) is multiplied with at the end: undoes
@@ -585,9 +513,8 @@ __device__ __forceinline__ QueryRegs<G> fetch_query(const QT* qb, const DecodeAr
 template <int G>
 __device__ __forceinline__ void store_query_lds(float (*q_lds)[4], float2* trig, const QueryRegs<G>& r, int tid) {
   if (tid < kHeadDim) {
-    // heads 4-7 (G = 8) make a second [dim][4] table behind the first
 #pragma unroll
-    for (int h = 0; h < (G == 8 ? 8 : 4); ++h) q_lds[(h >> 2) * kHeadDim + tid][h & 3] = h < G ? r.q[h < G ? h : 0] : 0.f;
+    for (int h = 0; h < 4; ++h) q_lds[tid][h] = h < G ? r.q[h < G ? h : 0] : 0.f;
   } else if (tid < kHeadDim + kMaxAngleBins) {
     trig[tid - kHeadDim] = r.cs;
   }
@@ -701,7 +628,7 @@ __device__ __forceinline__ void build_group_table(uint32_t lut_w, uint32_t tpar,
 }
 
 // ---- score phase with lanes as tokens (uniform angle grid) ---------------------------------
-// Used by the score-only kernel and the role-specialised attention kernel.  (In the attention
+// Used by the score-only kernel.  (In the attention
 // kernel below, whose wavefronts alternate between scoring and aggregating, it measured the same
 // as the lane layout that kernel has -- 158 against 157 us with 4-bit values at the GQA shape --
 // and was not taken over.)  The lanes of a wavefront are 64 consecutive TOKENS of
@@ -759,7 +686,7 @@ struct PageWalk {
       constexpr int b = block_of(S), half = (S / 16) % 2, K = S % 16;
       uint32_t addr;
       pair_fields<RB, TB, K>(cu[half * kBlocks + b], lut_base, c[S % kRing], addr);
-      t[S % kRing] = lut_read<G, kPairs * ROW>(addr + (b * kPairsPerUnit + K) * ROW);
+      t[S % kRing] = lut_read<G>(addr + (b * kPairsPerUnit + K) * ROW);
       if constexpr (K == 15) cu[half * kBlocks + b] = load_unit<W>(rc_nxt, voff_codes, unit_at(half, b));
     }
   }
@@ -806,118 +733,6 @@ struct PageWalk {
     for (int half = 0; half < 2; ++half)
 #pragma unroll
       for (int h = 0; h < G; ++h) asm volatile("" : "+v"(score[half][h]));
-  }
-};
-
-// Online softmax (log2 domain) of a score wavefront whose lanes are tokens: the lane holds the raw
-// scores of tokens `lane` and 64 + `lane` of a page for all G heads (PageWalk::score), so a head's
-// maximum is a wavefront-wide reduction and its running maximum and rescaling factor are
-// uniform; the denominators stay per-lane partial sums until the end.  A page's probabilities go
-// to LDS at `pw` in the layout the value steps read:
-//   fp16 values, G <= 4 : fp32 [token][G]
-//   fp16 values, G == 8 : fp16 pairs of tokens (n, n + 4), [pair = 8 (n / 16) + n % 4 + 4 ((n % 16) / 8)][8]
-//   quantized values    : fp16 pairs of tokens (2m, 2m + 1) with the token's scale folded in, [m][G]
-// and the heads' rescaling factors to `alpha_out[0 .. G)`.
-template <int G, int VB>
-struct LaneSoftmax {
-  static constexpr bool kQuantV = VB != 16;
-  static constexpr bool kPairs16 = kQuantV || G == 8;       // probabilities leave as fp16 pairs
-  float m_run[G], l_run[G], z_run[kQuantV ? G : 1];
-
-  __device__ __forceinline__ void reset() {
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      m_run[h] = kNegInf;
-      l_run[h] = 0.f;
-      if constexpr (kQuantV) z_run[h] = 0.f;
-    }
-  }
-  // score[half][h]: raw scores; nv: valid tokens of the page; vpar[half]: {fp16 scale, fp16 zero} of
-  // the lane's tokens (quantized values).  `is_residual`: the page is the residual group, whose
-  // scores [token][G] are taken from LDS at `res_sc` instead.  `out_rows`: where to store raw scores
-  // (row of head 0 at the page's first token, rows `stride` apart), or null.
-  __device__ __forceinline__ void page(const float (&score)[2][G], int nv, float scale_log2, const uint32_t (&vpar)[2],
-                                       bool is_residual, uint32_t res_sc, float* out_rows, int64_t stride, uint32_t pw,
-                                       float* alpha_out, int lane) {
-    const int col = lane & 15;
-    float al[G];
-    uint32_t packed[kPairs16 ? 2 : 1][G];
-    float pf[kPairs16 ? 1 : 2][G];
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      float sc[2];
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const int tok = half * 64 + lane;
-        sc[half] = score[half][h];
-        if (is_residual) sc[half] = *(const PQ_LDS float*)static_cast<uintptr_t>(res_sc + (tok * G + h) * 4);
-        if (out_rows != nullptr) {
-          if (tok < nv) out_rows[h * stride + tok] = sc[half];
-        }
-        sc[half] = (tok < nv) ? sc[half] * scale_log2 : kNegInf;
-      }
-      const float pm = wave_max(fmaxf(sc[0], sc[1]));
-      const float m_new = fmaxf(m_run[h], pm);
-      const bool dead = !(m_new > kNegInf);                          // nothing valid seen so far
-      const float alpha = dead ? 1.f : __builtin_amdgcn_exp2f(m_run[h] - m_new);   // 0 on the first page
-      float psum = 0.f, zsum = 0.f;
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const float pr = dead ? 0.f : __builtin_amdgcn_exp2f(sc[half] - m_new);
-        psum += pr;
-        if constexpr (kQuantV) {
-          // V~ = code * s + z (Section 2): fold s into the probability, collect p * z
-          const __half2 sz = *reinterpret_cast<const __half2*>(&vpar[half]);
-          zsum = fmaf(pr, __high2float(sz), zsum);
-          packed[half][h] = pack_with_neighbour(pr * __low2float(sz));
-        } else if constexpr (G == 8) {
-          packed[half][h] = pack_with_lane4(pr);
-        } else {
-          pf[half][h] = pr;
-        }
-      }
-      if constexpr (kQuantV) z_run[h] = fmaf(z_run[h], alpha, zsum);
-      l_run[h] = fmaf(l_run[h], alpha, psum);
-      m_run[h] = m_new;
-      al[h] = alpha;
-    }
-    // the lane's probabilities, all heads of a token (pair) side by side
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const int tok = half * 64 + lane;
-      if constexpr (kQuantV) {
-        if ((lane & 1) == 0) {
-#pragma unroll
-          for (int h = 0; h < G; ++h) *(PQ_LDS uint32_t*)static_cast<uintptr_t>(pw + ((tok >> 1) * G + h) * 4) = packed[half][h];
-        }
-      } else if constexpr (G == 8) {
-        if ((col & 4) == 0) {
-          const int pidx = (tok >> 4) * 8 + (col & 3) + ((col >> 3) << 2);
-#pragma unroll
-          for (int h = 0; h < G; ++h) *(PQ_LDS uint32_t*)static_cast<uintptr_t>(pw + (pidx * G + h) * 4) = packed[half][h];
-        }
-      } else {
-#pragma unroll
-        for (int h = 0; h < G; ++h) *(PQ_LDS float*)static_cast<uintptr_t>(pw + (tok * G + h) * 4) = pf[half][h];
-      }
-    }
-    if (lane == 0) {
-#pragma unroll
-      for (int h = 0; h < G; ++h) alpha_out[h] = al[h];
-    }
-  }
-  // (m, l, sum of p * zero-point) of head h over everything this wavefront has seen, to ml[h][0..2]
-  __device__ __forceinline__ void finish(float (*ml)[3], int lane) {
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const float l_tot = wave_sum_f(l_run[h]);
-      const float z_tot = kQuantV ? wave_sum_f(z_run[kQuantV ? h : 0]) : 0.f;
-      if (lane == 0) {
-        ml[h][0] = m_run[h];
-        ml[h][1] = l_tot;
-        ml[h][2] = z_tot;
-      }
-    }
   }
 };
 
@@ -1094,8 +909,8 @@ __global__ PQ_KERNEL_ATTR void pq_decode_partials_kernel(const DecodeArgs a) {
   }
 
   // Two work-groups share a compute unit, and the SIMD favours the older wavefront among equal
-  // priorities: the two take the higher priority in turns, page by page (see rotate_priority in
-  // pq_decode_roles.hpp for the same effect there).
+  // priorities: the two take the higher priority in turns, page by page (among wavefronts of equal
+  // priority the SIMD favours the oldest, and the launch waits for the slowest).
   const unsigned launch_index = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
   const bool shares_cu = gridDim.x * gridDim.y * gridDim.z > 256u;
   const int turn0 = static_cast<int>((launch_index / 256u) & 1u);
