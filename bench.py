@@ -264,9 +264,9 @@ def main() -> int:
     t_start = time.perf_counter()
     ms_step = time_region(step, args.steps, torch)
     wall = time.perf_counter() - t_start
-    # the dominant kernel alone, same launch configuration, same stream, same clock state.  The
-    # role-specialised kernel merges inside the kernel: the step IS that one kernel, timed again
-    # here in a region of its own; the other kernels are followed by a separate merge kernel.
+    # the dominant kernel alone, same launch configuration, same stream, same clock state.  Where the
+    # launch merges in the kernel the step IS that one kernel, timed again here in a region of its
+    # own; otherwise a separate merge kernel follows.
     kernel = pq.pq_decode_kernel_name(cache.layout, wl.n_seqs, wl.n_q_heads, cache.max_seq_len, args.v_bits)
     one_kernel_step = pq.pq_decode_merges_in_kernel(cache.layout, wl.n_seqs, wl.n_q_heads, cache.max_seq_len, args.v_bits)
     ms_partials = time_region(step if one_kernel_step else partials_only, args.steps, torch)

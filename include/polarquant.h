@@ -169,10 +169,9 @@ int pq_encode_values(const pq_layout* layout, int32_t v_bits, const void* values
  *
  *   q             device [n_seqs][n_q_heads][d], post-RoPE, q_dtype PQ_F16 or PQ_F32.
  *                 Query head h reads KV head h / (n_q_heads / n_kv_heads); the ratio may be
- *                 1 .. 16.  Kernels serve 8, 4, 2 or 1 query heads per pass over the cache (8
- *                 with fp16 values, in launches large enough for the role-specialised kernel,
- *                 see pq_decode_kernel_name), so a ratio of 1, 2, 4 (or 8) reads the cache once,
- *                 6 = 4 + 2 twice, 12 = 8 + 4 twice, ...
+ *                 1 .. 16.  A pass over the cache serves up to 8 query heads (with the grouped
+ *                 angle quantizer 4, 2 or 1), so a ratio of 1 .. 8 reads the cache once,
+ *                 12 = 8 + 4 twice, ...
  *   block_table   device int32 [n_seqs][max_pages_per_seq]: page of tokens
  *                 [i*g, (i+1)*g) of each sequence; entries past a sequence's last page
  *                 are ignored

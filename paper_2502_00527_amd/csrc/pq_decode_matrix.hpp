@@ -20,12 +20,14 @@
 // row sums of both parts are added at the end).  fp16 value rows are transposed pairwise with
 // v_perm_b32; quantized values need no conversion at all (a masked code is an fp16 denormal).
 //
-// What bounds it.  Per page (128 tokens of one KV head) a wavefront issues about 420 vector
-// instructions for the scores (128 table addresses, 250 for the query side), 350 for the softmax
-// and 190 for the values, and 160 matrix instructions (640 cycles per page and compute unit); one
-// multiply-add per (head, pair, token) and (head, dim, token) on the vector unit took 2200.  With
-// fp16 values a page is 41 KB, 3600 cycles of a compute unit's share of HBM: memory-bound.  With
-// quantized values the page is 11 - 17 KB and vector issue is about as long as the stream.
+// What bounds it.  Per page (128 tokens of one KV head) a wavefront issues about 1030 vector
+// instructions with fp16 values, 1100 with 4-bit ones -- 128 table addresses, 100 for the query side,
+// 190 for the sums, 300 for the softmax, 130 - 220 for the values -- and 160 matrix instructions (640
+// cycles per page and compute unit); one multiply-add per (head, pair, token) and (head, dim, token)
+// on the vector unit took 2200.  With fp16 values a page is 41 KB, 3600 cycles of a compute unit's
+// share of HBM: memory-bound (16 x 32K tokens, 4 query heads per KV head: 209 us, 6.5 TB/s; 216 us
+// before).  With quantized values the page is 11 - 17 KB and vector issue is the longer side
+// (4-bit values at the same shape: 147 -> 126 us).
 //
 // The table is kept 16 times in LDS, copy l in the 16-byte column l of a 256-byte row, and lane l
 // reads copy l % 16: reads of 16 lanes touch every bank once whatever the symbols are.  64 KB for
