@@ -16,7 +16,7 @@
 //
 // Values.  The accumulator layout of the scores -- lane (column, four consecutive tokens) -- is
 // the operand layout of the next product: probabilities go from score to value product in
-// registers, as high and low fp16 parts in the columns that held the query's parts (22 bits; the
+// registers, as high and low fp16 parts in the columns that held the query's parts (split_pair; the
 // row sums of both parts are added at the end).  fp16 value rows are transposed pairwise with
 // v_perm_b32; quantized values need no conversion at all (a masked code is an fp16 denormal).
 //
@@ -218,11 +218,26 @@ __device__ __forceinline__ f16x2 u2h(uint32_t u) {
   __builtin_memcpy(&h, &u, 4);
   return h;
 }
-// fp16 pair of (x0, x1) in the lanes of high-part columns (minus_low = 0), of what the high parts
-// leave over in those of low-part columns (minus_low = -1)
-__device__ __forceinline__ uint32_t split_pair(float x0, float x1, float minus_low) {
+// A probability's fp16 parts, of x in [0, 2^kProbTop]: the nearest fp16 in the lanes of high-part
+// columns (part = {0, 1}), 2^kLowShift times what that leaves over -- at most 2^(kProbTop - 12) -- in
+// those of low-part ones (part = {-1, 2^kLowShift}).  An accumulator row of low parts is scaled back
+// when a chunk ends.  The two carry 22 bits of x until the high part is below fp16's normal range, a
+// bit less for every power of two below that: a token keeps 22 bits of its weight down to 2^-22 of
+// the largest, and vanishes at 2^-47.  (Where the output hangs on weights of 2^-25 beside an
+// attention sink its error is 4e-7 so, 5e-7 with fp32 weights, and was 3.3e-3 with both parts on one
+// scale and the largest at 2^4.)  kProbTop is no larger because it is added to the exponent before
+// the exponential, whose argument is rounded at that size (at 15: error 5.8e-7 where 8 shows 5.6e-7).
+constexpr int kProbTop = 8;
+constexpr int kLowShift = 15;
+__device__ __forceinline__ f16x2 split_part(bool low, float unit) {
+  return low ? f16x2{static_cast<_Float16>(-1.f), static_cast<_Float16>(unit)} : f16x2{static_cast<_Float16>(0.f), static_cast<_Float16>(1.f)};
+}
+__device__ __forceinline__ uint32_t split_pair(float x0, float x1, f16x2 part) {
   const f16x2 h = to_half2(x0, x1);
-  return h2u(to_half2(fmaf(static_cast<float>(h.x), minus_low, x0), fmaf(static_cast<float>(h.y), minus_low, x1)));
+  const float minus_low = static_cast<float>(part.x), unit = static_cast<float>(part.y);
+  const f16x2 r = {static_cast<_Float16>(fmaf(fmaf(static_cast<float>(h.x), minus_low, x0), unit, 0.f)),
+                   static_cast<_Float16>(fmaf(fmaf(static_cast<float>(h.y), minus_low, x1), unit, 0.f))};
+  return h2u(r);
 }
 __device__ __forceinline__ f16x8 as_operand(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
   const u32x4 v = {a, b, c, d};
@@ -311,7 +326,6 @@ struct ScoreWalk {
   static constexpr int kOps = kChain == 16 ? 1 : kChain;   // query operands kept
   uint32_t q_op[kOps][2];
   uint32_t lane_lut, q_addr, par_put, par_get, voff_codes, low_mask;
-  float minus_low;
 
   __device__ __forceinline__ void init(const uint8_t* lut, const QueryShared& q, const uint32_t* params, int lane) {
     const int row = lane >> 4, col = lane & 15;
@@ -320,7 +334,6 @@ struct ScoreWalk {
     par_put = lds_addr(params) + lane * 4;
     par_get = lds_addr(params) + row * 64;
     voff_codes = (row * kGroup + row_token<O>(col)) * UB;
-    minus_low = col >= 8 ? -1.f : 0.f;
     low_mask = col >= 8 ? 0xffffffffu : 0u;
   }
   __device__ __forceinline__ void load_unit_of(int set, int t, __amdgpu_buffer_rsrc_t rc, int rot) {
@@ -569,10 +582,11 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   constexpr int kChain = kQuantV ? 16 : 4;
   constexpr uint32_t kCodesBytes = kBlocks * kGroup * UB;
   // Probabilities are exp2(score - m + kProbShift) with m the running maximum rounded up to a whole
-  // number (rescaling factors are then exact powers of two): with fp16 values in [0, 16], so that the
-  // low part's fp16 quantum stays out of the way; with quantized values they meet the token's scale
-  // before they are split, and stay in [0, 1].
-  constexpr float kProbShift = kQuantV ? 0.f : 4.f;
+  // number (rescaling factors are then exact powers of two): with fp16 values in [0, 2^kProbTop];
+  // with quantized values they meet the token's scale before they are split, and
+  // stay in [0, 1].
+  constexpr float kProbShift = kQuantV ? 0.f : static_cast<float>(kProbTop);
+  constexpr float kLowUnit = kQuantV ? 1.f : static_cast<float>(1 << kLowShift);
   constexpr int kVLoads = kQuantV ? kGroup * kHeadDim * VB / 8 / 1024 : 32;   // 1 KB wavefront loads per page of values
 
   struct Shared {
@@ -750,6 +764,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       m_run = m_new;
     }
     const float off = dead ? 0.f : kProbShift - m_run;
+    const f16x2 part = split_part(lane_id() & 8, kLowUnit);
     uint32_t p_op[8][2];                                               // batch t: fp16 pairs of tokens 4 row + (0, 1), (2, 3)
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
@@ -771,8 +786,8 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       if constexpr (!kQuantV) {
         if (t == 7) load_rows(vr[3], rv_cur, 3, rot_cur);
       }
-      p_op[t][0] = split_pair(p[0], p[1], w.minus_low);
-      p_op[t][1] = split_pair(p[2], p[3], w.minus_low);
+      p_op[t][0] = split_pair(p[0], p[1], part);
+      p_op[t][1] = split_pair(p[2], p[3], part);
     }
 
     // ---- values: acc += P^T V, 32 tokens (batches 2g, 2g + 1) per instruction ----
@@ -843,6 +858,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   {
     const int lane = lane_id(), row = lane >> 4, col = lane & 15;
     const int acc_head = NH == 8 ? 4 * (row & 1) : 0;                  // head of accumulator row i: acc_head + i
+    const float back = row >= 2 ? 1.f / kLowUnit : 1.f;                // rows of low parts
     // columns 0 .. NH - 1 are the heads' high parts; accumulator rows: high part + low part
     const float l_tot = kQuantV ? sum_rows(l_run) : 0.f;
     const float z_tot = kQuantV ? sum_rows(z_run) : 0.f;
@@ -854,7 +870,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     if constexpr (!kQuantV) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float l = tsum32(l_acc[i], l_acc[i]);
+        const float l = tsum32(l_acc[i] * back, l_acc[i] * back);
         if (col == 0 && row < NH / 4) sh.red_ml[wave][4 * row + i][1] = l;
       }
     }
@@ -870,7 +886,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     for (int e = 0; e < 8; ++e)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        acc[e][i] = tsum32(acc[e][i], acc[e][i]) * wgt[i];
+        acc[e][i] = tsum32(acc[e][i] * back, acc[e][i] * back) * wgt[i];
         if constexpr (kQuantV) acc[e][i] *= code_unscale<VB>(e);
       }
     if (wave < 2 && row < NH / 4) {
