@@ -666,7 +666,9 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   uint4 vq[kQuantV ? kVLoads : 1];                                     // quantized values: the page's units
   u32x2 vpar = {0u, 0u};                                               // (scale, zero) of tokens 2 lane, 2 lane + 1
   // rows of value group g: batches 2g, 2g + 1, tokens 4 i + row of each
-  auto load_rows = [&](uint4 (&dst)[8], __amdgpu_buffer_rsrc_t rv, int g, int rot) {
+  auto load_rows = [&](uint4 (&dst)[8], __amdgpu_buffer_rsrc_t rv, int g, int rot_of_page) {
+    int rot = uni(rot_of_page);
+    asm volatile("" : "+s"(rot));      // offsets stay scalar, whatever else is derived from the rotation (else a loop per load)
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
