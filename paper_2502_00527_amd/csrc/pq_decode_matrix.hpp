@@ -226,11 +226,14 @@ __device__ __forceinline__ f16x2 u2h(uint32_t u) {
 // the largest, and vanishes at 2^-47.  (Where the output hangs on weights of 2^-25 beside an
 // attention sink its error is 4e-7 so, 5e-7 with fp32 weights, and was 3.3e-3 with both parts on one
 // scale and the largest at 2^4.)  kProbTop is no larger because it is added to the exponent before
-// the exponential, whose argument is rounded at that size (at 15: error 5.8e-7 where 8 shows 5.6e-7).
-constexpr int kProbTop = 8;
+// the exponential, whose argument is rounded at that size (at 15: error 5.8e-7 where 8 shows 5.6e-7);
+// and one less than a power of two: where scores are so large that the sum is rounded to a multiple
+// of it, the weights still end at 2^8.
+constexpr int kProbTop = 7;
 constexpr int kLowShift = 15;
-__device__ __forceinline__ f16x2 split_part(bool low, float unit) {
-  return low ? f16x2{static_cast<_Float16>(-1.f), static_cast<_Float16>(unit)} : f16x2{static_cast<_Float16>(0.f), static_cast<_Float16>(1.f)};
+constexpr int kScaleTop = 3;
+__device__ __forceinline__ f16x2 split_part(bool low) {
+  return low ? f16x2{static_cast<_Float16>(-1.f), static_cast<_Float16>(1 << kLowShift)} : f16x2{static_cast<_Float16>(0.f), static_cast<_Float16>(1.f)};
 }
 __device__ __forceinline__ uint32_t split_pair(float x0, float x1, f16x2 part) {
   const f16x2 h = to_half2(x0, x1);
@@ -581,12 +584,11 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   constexpr TokenOrder kOrder = token_order(VB);
   constexpr int kChain = kQuantV ? 16 : 4;
   constexpr uint32_t kCodesBytes = kBlocks * kGroup * UB;
-  // Probabilities are exp2(score - m + kProbShift) with m the running maximum rounded up to a whole
-  // number (rescaling factors are then exact powers of two): with fp16 values in [0, 2^kProbTop];
-  // with quantized values they meet the token's scale before they are split, and
-  // stay in [0, 1].
-  constexpr float kProbShift = kQuantV ? 0.f : static_cast<float>(kProbTop);
-  constexpr float kLowUnit = kQuantV ? 1.f : static_cast<float>(1 << kLowShift);
+  // Probabilities are exp2(score - m + kProbTop) with m the running maximum rounded up to a whole
+  // number (rescaling factors are then exact powers of two).  With quantized values they meet the
+  // token's scale before they are split; scales are taken times 2^s_exp, which brings the largest that
+  // the wavefront has seen into [2^3, 2^4), so that what is split stays below 2^12 and keeps its bits
+  // whatever the values' size (it is 2^-10: error 3e-6 so, 4e-3 with the scales as they are).
   constexpr int kVLoads = kQuantV ? kGroup * kHeadDim * VB / 8 / 1024 : 32;   // 1 KB wavefront loads per page of values
 
   struct Shared {
@@ -694,6 +696,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   // per lane: column (head, part), running maximum, sums over the lane's tokens
   // (fp16 values: the sums of p come from the matrix unit like one more dim, l_acc)
   float m_run = kNegInf, l_run = 0.f, z_run = 0.f;
+  int s_exp = 15;                                                      // (as far as fp16 goes)
   f32x4 l_acc = {0.f, 0.f, 0.f, 0.f};
   f32x4 acc[8];                                                        // dim 8 col + e; columns 4 row .. + 3
 #pragma unroll
@@ -708,8 +711,12 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     const int lane = lane_id(), col = lane & 15;
     w.init(sh.lut, sh.q, sh.params[wave], lane);
     const int q_shift = sh.q_shift[column_head<NH>(col)];
+    const int s_exp_before = s_exp;
     if constexpr (kQuantV) {
-      *(PQ_LDS u32x2*)static_cast<uintptr_t>(lds_addr(sh.vpar[wave]) + lane * 8) = vpar;
+      const int e = static_cast<int>(wave_max_u32(max(vpar.x & 0xffffu, vpar.y & 0xffffu)) >> 10);   // of the page's largest scale
+      s_exp = max(-12, min(s_exp, kScaleTop + 15 - e));
+      const f16x2 factor = u2h(static_cast<uint32_t>((s_exp + 15) << 10) | 0x3c000000u);              // {2^s_exp, 1}
+      *(PQ_LDS u32x2*)static_cast<uintptr_t>(lds_addr(sh.vpar[wave]) + lane * 8) = u32x2{h2u(u2h(vpar.x) * factor), h2u(u2h(vpar.y) * factor)};
       vpar = __builtin_amdgcn_raw_buffer_load_b64(rvp_nxt, lane * 8, 0, kAuxCached);
     }
     int down = w.template run<0>(rc_nxt, rp_nxt, rot_nxt, lane) + kTableShift + q_shift;
@@ -750,7 +757,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     }
     const float m_new = fmaxf(m_run, __builtin_ceilf(pm * mult));
     const bool dead = !(m_new > kNegInf);                              // nothing valid seen so far
-    if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+    if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0 || s_exp != s_exp_before) {
       const float alpha = dead ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first page
       if constexpr (kQuantV) {
         l_run *= alpha;
@@ -758,15 +765,16 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float al = __shfl(alpha, (NH == 8 ? 4 * ((lane_id() >> 4) & 1) : 0) + i);   // head of accumulator row i
+        float al = __shfl(alpha, (NH == 8 ? 4 * ((lane_id() >> 4) & 1) : 0) + i);   // head of accumulator row i
         if constexpr (!kQuantV) l_acc[i] *= al;
+        else al = __builtin_ldexpf(al, s_exp - s_exp_before);
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e][i] *= al;
       }
       m_run = m_new;
     }
-    const float off = dead ? 0.f : kProbShift - m_run;
-    const f16x2 part = split_part(lane_id() & 8, kLowUnit);
+    const float off = dead ? 0.f : static_cast<float>(kProbTop) - m_run;
+    const f16x2 part = split_part(lane_id() & 8);
     uint32_t p_op[8][2];                                               // batch t: fp16 pairs of tokens 4 row + (0, 1), (2, 3)
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
@@ -775,7 +783,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(w.s[t][i], mult, off));
       if constexpr (kQuantV) {
         l_run += (p[0] + p[1]) + (p[2] + p[3]);
-        // V~ = code * s + z (Section 2): fold s into the probability, collect p * z
+        // V~ = code * s + z (Section 2): fold s (times 2^s_exp) into the probability, collect p * z
         const u32x4 vp = *(const PQ_LDS u32x4*)static_cast<uintptr_t>(
             lds_addr(sh.vpar[wave]) + (batch_token<kOrder>(t, 0) + row_token<kOrder>(4 * row)) * 4);
 #pragma unroll
@@ -860,7 +868,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   {
     const int lane = lane_id(), row = lane >> 4, col = lane & 15;
     const int acc_head = NH == 8 ? 4 * (row & 1) : 0;                  // head of accumulator row i: acc_head + i
-    const float back = row >= 2 ? 1.f / kLowUnit : 1.f;                // rows of low parts
+    const float back = row >= 2 ? 1.f / (1 << kLowShift) : 1.f;                // rows of low parts
     // columns 0 .. NH - 1 are the heads' high parts; accumulator rows: high part + low part
     const float l_tot = kQuantV ? sum_rows(l_run) : 0.f;
     const float z_tot = kQuantV ? sum_rows(z_run) : 0.f;
@@ -883,6 +891,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       const int h = acc_head + i;
       const float M = fmaxf(fmaxf(sh.red_ml[0][h][0], sh.red_ml[1][h][0]), fmaxf(sh.red_ml[2][h][0], sh.red_ml[3][h][0]));
       wgt[i] = M > kNegInf ? __builtin_amdgcn_exp2f(sh.red_ml[wave][h][0] - M) : 0.f;
+      if constexpr (kQuantV) wgt[i] = __builtin_ldexpf(wgt[i], -s_exp);
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e)

@@ -36,3 +36,42 @@ def test_attention_sinks(group, logit, v_bits):
     err = relative_error(cache.attention(), want)
     print(f"[precision] sinks group {group} logit {logit} v{v_bits}: {err:.2e}", flush=True)
     assert err <= 4e-6
+
+
+@pytest.mark.parametrize("v_bits", [16, 4, 2])
+@pytest.mark.parametrize("exponent", [8, -4, -7, -10])
+@pytest.mark.parametrize("sharpness", [0.4, 1.0, 3.0])
+def test_values_of_any_size(sharpness, exponent, v_bits):
+    """Values times a power of two give outputs times it: scales of 2^-10 are no harder than scales of 1.
+    With quantized values out = sum p (code s) + sum p z cancels (|z| is up to 100 times a flat softmax's
+    output), and fp32 sums of both parts leave up to 100 * 2^-22."""
+    from packed import Packed, relative_error
+
+    heads, length, group = 2, 3000, 4
+    keys, values = _random(5, length, heads, 128), _random(6, length, heads, 128) * 2.0 ** exponent
+    q = _random(7, 1, heads * group, 128) * sharpness
+    cache = Packed([keys.astype(np.float16)], [values], q.astype(np.float16), v_bits=v_bits)
+    err = relative_error(cache.attention(), cache.exact()[1])
+    print(f"[precision] values 2^{exponent} sharpness {sharpness} v{v_bits}: {err:.2e}", flush=True)
+    assert err <= (2e-6 if v_bits == 16 else 2.4e-5)
+
+
+@pytest.mark.parametrize("v_bits", [16, 4, 2])
+@pytest.mark.parametrize("order", [1, -1])
+def test_values_of_all_sizes_at_once(order, v_bits):
+    """Sizes of 2^-12 to 2^10 from page to page, growing and shrinking along the context, with the weights
+    on the small ones; two tokens of a page differ by 2^8."""
+    from packed import Packed, relative_error
+
+    heads, length, group = 2, 2900, 4
+    keys, values = _random(8, length, heads, 128), _random(9, length, heads, 128)
+    size = np.linspace(-12, 10, length)[::order][:, None, None]
+    values *= np.exp2(np.round(size)) * np.where(np.arange(length) % 2, 1.0, 2.0 ** -8)[:, None, None]
+    direction = _random(10, heads, 128)
+    direction /= np.linalg.norm(direction, axis=-1, keepdims=True)
+    keys -= direction * size * np.log(2.0) * 2.0                                    # weight ~ 1 / size
+    q = _random(11, 1, heads, group, 128) * 0.3 + direction[:, None] * np.sqrt(128.0) * 0.5
+    cache = Packed([keys.astype(np.float16)], [values], q.reshape(1, -1, 128).astype(np.float16), v_bits=v_bits)
+    err = relative_error(cache.attention(), cache.exact()[1])
+    print(f"[precision] values of all sizes order {order} v{v_bits}: {err:.2e}", flush=True)
+    assert err <= (4e-6 if v_bits == 16 else 2.4e-5)
