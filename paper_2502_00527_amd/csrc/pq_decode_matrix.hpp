@@ -231,6 +231,14 @@ __device__ __forceinline__ f16x2 u2h(uint32_t u) {
 // of it, the weights still end at 2^8.
 constexpr int kProbTop = 7;
 constexpr int kLowShift = 15;
+// Sum of an accumulator's two parts, one in lanes 0 - 31, the other (already scaled back) in lanes
+// 32 - 63.  Where a value is infinite the high part is what the product is; a low part may be zero or
+// negative there.
+__device__ __forceinline__ float sum_parts(float x) {
+  auto r = __builtin_amdgcn_permlane32_swap(f2u(x), f2u(x), false, false);
+  const float high = u2f(r[0]), low = u2f(r[1]);
+  return __builtin_isinf(high) ? high : high + low;
+}
 constexpr int kScaleTop = 3;
 __device__ __forceinline__ f16x2 split_part(bool low) {
   return low ? f16x2{static_cast<_Float16>(-1.f), static_cast<_Float16>(1 << kLowShift)} : f16x2{static_cast<_Float16>(0.f), static_cast<_Float16>(1.f)};
@@ -897,7 +905,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     for (int e = 0; e < 8; ++e)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        acc[e][i] = tsum32(acc[e][i] * back, acc[e][i] * back) * wgt[i];
+        acc[e][i] = sum_parts(acc[e][i] * back) * wgt[i];
         if constexpr (kQuantV) acc[e][i] *= code_unscale<VB>(e);
       }
     if (wave < 2 && row < NH / 4) {

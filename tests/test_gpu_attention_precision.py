@@ -75,3 +75,18 @@ def test_values_of_all_sizes_at_once(order, v_bits):
     err = relative_error(cache.attention(), cache.exact()[1])
     print(f"[precision] values of all sizes order {order} v{v_bits}: {err:.2e}", flush=True)
     assert err <= (4e-6 if v_bits == 16 else 2.4e-5)
+
+
+@pytest.mark.parametrize("group", [1, 4, 8])
+def test_infinite_value_elements(group):
+    """A value element that is infinite makes that element of the output infinite, and no other."""
+    from packed import Packed
+
+    heads, length = 2, 700
+    keys, values = _random(12, length, heads, 128), _random(13, length, heads, 128)
+    values[3, 0, 5], values[200, 0, 17], values[650, 1, 40] = np.inf, -np.inf, np.inf
+    cache = Packed([keys.astype(np.float16)], [values], _random(14, 1, heads * group, 128).astype(np.float16))
+    got, want = cache.attention().cpu().double(), cache.exact()[1]
+    assert int(torch.isinf(want).sum()) == 3 * group
+    assert torch.equal(torch.isinf(got), torch.isinf(want)) and torch.equal(got[torch.isinf(want)], want[torch.isinf(want)])
+    assert float((got - want)[torch.isfinite(want)].abs().max()) <= 1e-5
