@@ -81,8 +81,8 @@ __global__ __launch_bounds__(kMergeThreads) void pq_decode_merge_kernel(
   }
 }
 
-// Score-only kernels: the grouped quantizer has one of its own (a table per page); on the uniform grid
-// up to 4 query heads are served by the kernel whose lanes are tokens, 5 to 8 by the matrix kernel.
+// Score-only kernels: the kernel whose lanes are tokens on the uniform grid; the grouped quantizer has
+// one of its own (a table per page).
 template <int G, int RB, int TB, bool GA>
 void launch_scores_one(const DecodeArgs& a, dim3 grid, hipStream_t st) {
   if constexpr (GA) hipLaunchKernelGGL((pq_score_keys_kernel<G, RB, TB, true>), grid, dim3(kThreads), 0, st, a);
@@ -323,22 +323,20 @@ ChunkPlan plan_score_chunks(int32_t n_seqs, int32_t n_kv_heads, int32_t max_seq_
 int launch_scores(const pq_layout* layout, DecodeArgs a, hipStream_t stream) {
   const bool grouped = layout->angle_quantizer == PQ_ANGLE_GROUPED;
   const int rt = layout->r_bits * 10 + layout->t_bits;
-  // the token-lane kernel addresses 4 score rows with 32-bit byte offsets
-  const bool tokens_fit = a.scores_stride < (int64_t{1} << 28);
+  // the token-lane kernel addresses the score rows of a pass with 32-bit byte offsets from the first
+  const int most = grouped || a.scores_stride < (int64_t{1} << 28) ? 4 : 1;
+  const ChunkPlan plan = plan_score_chunks(a.n_seqs, a.n_kv_heads, a.max_seq_len, grouped ? 2 : 4);
+  if (plan.n_chunks > 65535) return PQ_ERR_UNSUPPORTED;   // grid.z
+  a.pages_per_chunk = plan.pages_per_chunk;
+  a.n_chunks = plan.n_chunks;
+  const dim3 grid(a.n_kv_heads, a.n_seqs, plan.n_chunks);
   hipError_t e = hipSuccess;
   for (int head0 = 0; head0 < a.group_total && e == hipSuccess;) {
     const int left = a.group_total - head0;
-    const bool matrix = !grouped && (left > 4 || !tokens_fit);
-    const int G = matrix ? std::min(left, kMaxHeads) : (left >= 4 ? 4 : (left >= 2 ? 2 : 1));
-    const ChunkPlan plan = plan_score_chunks(a.n_seqs, a.n_kv_heads, a.max_seq_len, grouped || matrix ? 2 : 4);
-    if (plan.n_chunks > 65535) return PQ_ERR_UNSUPPORTED;   // grid.z
-    a.pages_per_chunk = plan.pages_per_chunk;
-    a.n_chunks = plan.n_chunks;
+    const int G = std::min(most, left >= 4 ? 4 : (left >= 2 ? 2 : 1));
     a.head0 = head0;
     a.n_heads = G;
-    const dim3 grid(a.n_kv_heads, a.n_seqs, plan.n_chunks);
-    const bool found = matrix ? launch_scores_matrix(layout->r_bits + layout->t_bits, a, grid, stream)
-                              : (grouped ? launch_scores_rt<true>(rt, G, a, grid, stream) : launch_scores_rt<false>(rt, G, a, grid, stream));
+    const bool found = grouped ? launch_scores_rt<true>(rt, G, a, grid, stream) : launch_scores_rt<false>(rt, G, a, grid, stream);
     if (!found) return PQ_ERR_UNSUPPORTED;   // not reached: layout_supported() admits what is built
     e = hipGetLastError();
     head0 += G;

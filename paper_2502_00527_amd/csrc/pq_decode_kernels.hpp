@@ -1284,22 +1284,23 @@ void pq_score_tokens_kernel(const DecodeArgs a) {
 
   float* const out_rows = a.scores + (static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0) * a.scores_stride;
 
-  // the G heads' rows of scores through one descriptor (the host keeps 4 rows under 4 GiB): a
+  // the G heads' rows of a page's scores through one descriptor (the host keeps 4 rows under 4 GiB): a
   // lane's offset is its token, the head's row the scalar offset
   const uint32_t row_bytes = static_cast<uint32_t>(a.scores_stride) * 4u;
-  const __amdgpu_buffer_rsrc_t rs_out = make_rsrc(out_rows, static_cast<uint32_t>(G - 1) * row_bytes + static_cast<uint32_t>(L) * 4u);
   w.lut_base = lds_addr(lut);
   for (int i = 0; i < n_w; ++i) {
     const int pi = page0 + wave + kWaves * i;
     page_setup(i + 1, rc_nxt, pp_nxt, nv_nxt);
     w.run(rc_nxt, pp_nxt);
+    const __amdgpu_buffer_rsrc_t rs_out = make_rsrc(out_rows + static_cast<int64_t>(pi) * kGroup,
+                                                    static_cast<uint32_t>(G - 1) * row_bytes + kGroup * 4u);
     // Unconditional stores (a conditional one would let the compiler move the page's arithmetic
     // behind the condition, away from its table reads): what must not be stored -- tokens past the
     // sequence end, a page without scores of its own -- gets an offset outside the descriptor.
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       const bool valid = pi != res_page && half * 64 + lane < nv_cur;
-      const uint32_t vo = valid ? (static_cast<uint32_t>(pi) * kGroup + half * 64 + lane) * 4u : 0xffffffffu;
+      const uint32_t vo = valid ? (half * 64 + lane) * 4u : 0xffffffffu;
 #pragma unroll
       for (int h = 0; h < G; ++h) __builtin_amdgcn_raw_buffer_store_b32(f2u(w.score[half][h]), rs_out, vo, h * row_bytes, kAuxStream);
     }

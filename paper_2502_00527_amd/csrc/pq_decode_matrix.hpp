@@ -1,4 +1,4 @@
-// Attention and score-only kernels of the uniform angle grid, on the matrix cores.
+// Attention kernel of the uniform angle grid, on the matrix cores.
 //
 // Scores.  A key pair is reconstructed as rho~ (cos theta~, sin theta~), rho~ = s (c + 1/2) + z
 // (Section 3.2), and the score is sum over pairs of q . k~.  Written with the four products
@@ -43,16 +43,13 @@ namespace pq {
 bool launch_attention_matrix_v16(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st);
 bool launch_attention_matrix_v4(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st);
 bool launch_attention_matrix_v2(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st);
-bool launch_scores_matrix(int w, const DecodeArgs& a, dim3 grid, hipStream_t st);
 
 namespace {
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kMatWaves = 4;
 constexpr int kMatThreads = kMatWaves * 64;
-constexpr int kScoreWaves = 4;
 constexpr int kMaxHeads = 8;            // query heads of one pass: columns h (high part) and 8 + h (low part)
 
 // ---- key-side table ---------------------------------------------------------------------------
@@ -293,7 +290,7 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
 // the order the values of the same lane come in.
 enum class TokenOrder {
   kRows,       // fp16 values, four consecutive rows a load: token 16 ((t + rot) % 8) + 4 (m % 4) + m / 4
-  kPlain,      // 4-bit values (units of 4 tokens), scores alone: token 16 ((t + rot) % 8) + m
+  kPlain,      // 4-bit values (units of 4 tokens): token 16 ((t + rot) % 8) + m
   kUnits8      // 2-bit values (units of 8 tokens): token 32 (t / 2) + 8 (m / 4) + 4 (t % 2) + m % 4
 };
 constexpr TokenOrder token_order(int v_bits) {
@@ -317,16 +314,15 @@ __device__ __forceinline__ int row_token(int m) {                // part of the 
 // pair, at the size of the running sum.  Error of a score against float64, 8 x 32K keys with
 // outlier channels, as part of the scores' 2-norm (one fp32 multiply-add per pair: 9.3e-8):
 // NH = 4 (whose columns carry half of the pairs each) with chains of 4: 9.5e-8, NH = 8 with 4:
-// 1.05e-7, with 2: 9.5e-8.  The attention kernel takes 4 (its output's error, 4e-7 - 7e-7, is that of
-// the exponentials) and none with quantized values (1e-5); the score-only kernel 2.
-// kAhead: half-steps (4 table reads each) between a read and its use.  kSets: 1 = a unit is refilled
-// with the next page's after its last use (something else follows the walk and hides the load), 2 = the
-// next page's units are loaded into a second set as the walk starts.
-template <int W, TokenOrder O, int NH, bool Q32, int kAhead, int kSets, int kChain>
+// 1.05e-7, with 2: 9.5e-8.  The kernel takes 4 (its output's error, 4e-7 - 7e-7, is that of the
+// exponentials) and none with quantized values (1e-5).  Raw scores that are handed out come from the
+// token-lane kernel: fp32 queries and 5 to 8 heads would have 1.2e-7 from here where it has 9.2e-8.
+// kAhead: half-steps (4 table reads each) between a read and its use.
+template <int W, TokenOrder O, int NH, bool Q32, int kAhead, int kChain>
 struct ScoreWalk {
   static constexpr int UB = 2 * W;
   static_assert(16 % kChain == 0, "steps of a chain");
-  Unit<W / 2> cu[kSets][8];
+  Unit<W / 2> cu[8];
   uint32_t par;                                 // {fp16 s, fp16 z} of pair `lane`
   f32x4 s[8], d[4], done[4];                    // sums, the chain under way, the chain before it
   f32x4 entry[kAhead + 1][4];
@@ -347,8 +343,8 @@ struct ScoreWalk {
     voff_codes = (row * kGroup + row_token<O>(col)) * UB;
     low_mask = col >= 8 ? 0xffffffffu : 0u;
   }
-  __device__ __forceinline__ void load_unit_of(int set, int t, __amdgpu_buffer_rsrc_t rc, int rot) {
-    cu[set][t] = load_unit<W>(rc, voff_codes, static_cast<uint32_t>(batch_token<O>(t, rot)) * UB);
+  __device__ __forceinline__ void load_unit_of(int t, __amdgpu_buffer_rsrc_t rc, int rot) {
+    cu[t] = load_unit<W>(rc, voff_codes, static_cast<uint32_t>(batch_token<O>(t, rot)) * UB);
   }
   __device__ __forceinline__ void load_params(__amdgpu_buffer_rsrc_t rp, int lane) { par = buf_load4<kAuxCached>(rp, lane * 4, 0); }
 
@@ -396,22 +392,22 @@ struct ScoreWalk {
   static constexpr int step_of(int H) { return H / (2 * kOps) * kOps + H % kOps; }
   static constexpr int half_of(int H) { return H / kOps % 2; }
   static constexpr bool ends_chain(int H) { return H >= 0 && step_of(H) >= kChain && step_of(H) % kChain == kChain - 1; }
-  template <int P, int H>
+  template <int H>
   __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rc_nxt, int rot_nxt) {
     if constexpr (H < 32) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int t = half_of(H) * 4 + j;
-        entry[H % (kAhead + 1)][j] = lookup<step_of(H)>(cu[P][t]);
-        if constexpr (step_of(H) == (kSets == 2 ? 0 : 15)) load_unit_of(kSets == 2 ? 1 - P : P, t, rc_nxt, rot_nxt);
+        entry[H % (kAhead + 1)][j] = lookup<step_of(H)>(cu[t]);
+        if constexpr (step_of(H) == 15) load_unit_of(t, rc_nxt, rot_nxt);
       }
     }
   }
-  template <int P, int H>
+  template <int H>
   __device__ __forceinline__ void steps(__amdgpu_buffer_rsrc_t rc_nxt, int rot_nxt) {
     if constexpr (H < 32) {
       constexpr int kk = step_of(H), half = half_of(H);
-      issue<P, H + kAhead>(rc_nxt, rot_nxt);
+      issue<H + kAhead>(rc_nxt, rot_nxt);
       const uint32_t b0 = q_op[kk % kOps][0], b1 = q_op[kk % kOps][1];
       const f16x8 q8 = as_operand(b0, b1, b0, b1);
 #pragma unroll
@@ -441,15 +437,13 @@ struct ScoreWalk {
         if constexpr (kk + kOps + 2 < 16) fetch_q(kk + kOps + 2);
       }
       __builtin_amdgcn_sched_barrier(0);
-      steps<P, H + 1>(rc_nxt, rot_nxt);
+      steps<H + 1>(rc_nxt, rot_nxt);
     }
   }
-  // Scores of the page in cu[P] / par, summed over the columns of a head (and left in all of them), scaled
-  // by 2^(k + the head's query shift + kTableShift); returns k.  cu (set P, or the other of two) and par then
-  // hold the next page.
-  template <int P>
+  // Scores of the page in cu / par, summed over the columns of a head (and left in all of them), scaled
+  // by 2^(k + the head's query shift + kTableShift); returns k.  cu and par then hold the next page.
   __device__ __forceinline__ int run(__amdgpu_buffer_rsrc_t rc_nxt, __amdgpu_buffer_rsrc_t rp_nxt, int rot_nxt, int lane) {
-    issue<P, 0>(rc_nxt, rot_nxt);
+    issue<0>(rc_nxt, rot_nxt);
     int k;
     *(PQ_LDS uint32_t*)static_cast<uintptr_t>(par_put) = scale_page_params(par, k);
     load_params(rp_nxt, lane);
@@ -461,10 +455,10 @@ struct ScoreWalk {
       make_query_operand(kk);
       fetch_q(kk + 2);
     }
-    if constexpr (kAhead == 2) issue<P, 1>(rc_nxt, rot_nxt);
+    if constexpr (kAhead == 2) issue<1>(rc_nxt, rot_nxt);
     static_assert(kAhead == 1 || kAhead == 2, "reads issued before the first half-step");
     __builtin_amdgcn_sched_barrier(0);
-    steps<P, 0>(rc_nxt, rot_nxt);
+    steps<0>(rc_nxt, rot_nxt);
     if constexpr (kChain < 16) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) s[4 + j] += done[j];
@@ -670,7 +664,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   };
   __amdgpu_buffer_rsrc_t rc_cur, rp_cur, rv_cur, rvp_cur, rc_nxt, rp_nxt, rv_nxt, rvp_nxt;
   int nv_cur, nv_nxt, rot_cur, rot_nxt;
-  ScoreWalk<W, kOrder, NH, Q32, kQuantV ? 2 : 1, 1, kChain> w;
+  ScoreWalk<W, kOrder, NH, Q32, kQuantV ? 2 : 1, kChain> w;
   w.init(sh.lut, sh.q, sh.params[wave], lane);
   uint4 vr[kQuantV ? 1 : 4][8];                                        // fp16 values: four groups of 8 rows (32 tokens)
   uint4 vq[kQuantV ? kVLoads : 1];                                     // quantized values: the page's units
@@ -688,7 +682,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   page_setup(0, rc_cur, rp_cur, rv_cur, rvp_cur, nv_cur, rot_cur);
   w.load_params(rp_cur, lane);
 #pragma unroll
-  for (int t = 0; t < 8; ++t) w.load_unit_of(0, t, rc_cur, rot_cur);
+  for (int t = 0; t < 8; ++t) w.load_unit_of(t, rc_cur, rot_cur);
   if constexpr (kQuantV) {
     vpar = __builtin_amdgcn_raw_buffer_load_b64(rvp_cur, lane * 8, 0, kAuxCached);
 #pragma unroll
@@ -727,7 +721,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       *(PQ_LDS u32x2*)static_cast<uintptr_t>(lds_addr(sh.vpar[wave]) + lane * 8) = u32x2{h2u(u2h(vpar.x) * factor), h2u(u2h(vpar.y) * factor)};
       vpar = __builtin_amdgcn_raw_buffer_load_b64(rvp_nxt, lane * 8, 0, kAuxCached);
     }
-    int down = w.template run<0>(rc_nxt, rp_nxt, rot_nxt, lane) + kTableShift + q_shift;
+    int down = w.run(rc_nxt, rp_nxt, rot_nxt, lane) + kTableShift + q_shift;
     if (pi == res_page) {
       w.residual(a.residual + (static_cast<int64_t>(seq) * a.n_kv_heads + kvh) * (kGroup * kHeadDim), L - res_page * kGroup,
                  rot_cur, lane_id());

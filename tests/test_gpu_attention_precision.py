@@ -90,3 +90,45 @@ def test_infinite_value_elements(group):
     assert int(torch.isinf(want).sum()) == 3 * group
     assert torch.equal(torch.isinf(got), torch.isinf(want)) and torch.equal(got[torch.isinf(want)], want[torch.isinf(want)])
     assert float((got - want)[torch.isfinite(want)].abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("group", [1, 4, 5, 8])
+@pytest.mark.parametrize("radius", [1.0, 400.0, 30000.0])
+def test_raw_scores_carry_fp32(radius, group, dtype):
+    """Raw scores are fp32 multiply-adds, whatever the query group, and whatever the size of one pair's
+    radius beside the others' (the query is zero there): 9.2e-8 of the scores' 2-norm; the same through
+    pq_decode_attention."""
+    from packed import Packed, relative_error
+
+    heads, length = 2, 1300
+    keys = _random(15, length, heads, 128)
+    keys[..., 5], keys[..., 69] = radius, 0.0
+    q = _random(16, 1, heads * group, 128)
+    q[..., 5] = q[..., 69] = 0.0
+    cache = Packed([keys.astype(dtype)], [_random(17, length, heads, 128)], q.astype(dtype))
+    want = cache.exact()[0][0]
+    got = cache.scores()
+    err = relative_error(got[0], want)
+    print(f"[precision] scores radius {radius} group {group} {dtype.__name__}: {err:.2e}", flush=True)
+    assert err <= 1.05e-7
+    through_attention = torch.full_like(got, float("nan"))
+    cache.attention(through_attention)
+    assert torch.equal(through_attention, got)
+
+
+@pytest.mark.parametrize("group", [2, 8])
+def test_score_rows_a_gibibyte_apart(group):
+    """pq_decode_attention takes any scores_stride; rows further apart than 32-bit offsets of 4 rows reach
+    are written one at a time."""
+    from packed import Packed
+
+    length = 300
+    cache = Packed([_random(18, length, 1, 128).astype(np.float16)], [_random(19, length, 1, 128)],
+                   _random(20, 1, group, 128).astype(np.float16))
+    near = torch.full((1, group, length), float("nan"), device="cuda:0")
+    want = cache.attention(near)
+    far = torch.full((1, group, (1 << 28) + 3), float("nan"), device="cuda:0")
+    assert torch.equal(cache.attention(far), want)
+    assert torch.equal(far[..., :length], near)
+    assert bool(torch.isnan(far[..., length:]).all())
