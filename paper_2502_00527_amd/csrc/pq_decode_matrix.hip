@@ -10,6 +10,7 @@
 #ifndef PQ_MATRIX_VB
 #define PQ_MATRIX_VB 16
 #define PQ_MATRIX_LAUNCH launch_attention_matrix_v16
+#define PQ_GIVEN_LAUNCH launch_attention_given_v16
 #endif
 
 namespace pq {
@@ -22,6 +23,15 @@ template <int W, int VB, int NH, bool Q32>
 __global__ PQ_MATRIX_ATTR void pq_decode_roles_kernel(const DecodeArgs a) { attention_body<W, VB, NH, Q32>(a); }
 template <int W, int VB, int NH, bool Q32>
 __global__ PQ_MATRIX_ATTR void pq_decode_partials_kernel(const DecodeArgs a) { attention_body<W, VB, NH, Q32>(a); }
+
+// The same over scores that have been computed already: a call that asks for its raw scores gets them
+// from the score-only kernel, and the softmax reads them back.  Bound by HBM: 272 bytes a token and KV
+// head instead of the codes' 64 + 256.  Both launches, 16 x 32K tokens, 4 query heads per KV head:
+// 260 us; with the whole attention kernel behind the score-only one 287; 8 x 8K, one head per KV head
+// 123 against 145; 16 x 16K, 4-bit values 86 against 116.  The values' rows go four consecutive ones
+// to a lane row, so that a lane's four scores are one load (four loads: 8 heads 7 us slower).
+template <int VB, int NH>
+__global__ PQ_MATRIX_ATTR void pq_decode_given_kernel(const DecodeArgs a) { attention_body<6, VB, NH, false, true>(a); }
 
 template <int W, int VB, int NH, bool Q32>
 void launch_one(bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st) {
@@ -47,6 +57,10 @@ bool launch_w(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st)
 
 bool PQ_MATRIX_LAUNCH(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st) {
   return matrix::launch_w<PQ_MATRIX_VB>(w, roles, a, grid, st);
+}
+void PQ_GIVEN_LAUNCH(const DecodeArgs& a, dim3 grid, hipStream_t st) {
+  if (a.n_heads <= 4) hipLaunchKernelGGL((matrix::pq_decode_given_kernel<PQ_MATRIX_VB, 4>), grid, dim3(kMatThreads), 0, st, a);
+  else hipLaunchKernelGGL((matrix::pq_decode_given_kernel<PQ_MATRIX_VB, 8>), grid, dim3(kMatThreads), 0, st, a);
 }
 
 }  // namespace pq
