@@ -152,10 +152,14 @@ __device__ __forceinline__ int column_head(int col) { return col & (NH - 1); }
 // The pass's query in LDS, [pair][column] with 8 bytes an entry: q = (q_x, q_y) as fp16, and
 //   fp16 queries: q again in low-part columns, 0 in high-part ones;
 //   fp32 queries: what q's rounding to fp16 left over, in low-part columns, 0 in high-part ones.
-// Each head is scaled by a power of two so that its largest element is in [2^9, 2^10): with
-// parameters scaled below 2^5 the products stay inside fp16, and fp16 queries lose nothing unless
-// an element is 2^-23 of the head's largest.  The 16 pairs of a block are followed by 128 bytes of
-// padding (the four lane rows read four blocks at once).
+// Powers of two keep the products inside fp16 and lose nothing: each head is scaled so that its
+// largest element is in [2^9, 2^10), then each pair so that this holds for the pair's largest element
+// of any head, and the pair's radius parameters are scaled the other way -- what then is below fp16's
+// normal range is the parameter of a pair whose products are 2^-18 of the page's largest, or an
+// element 2^-23 of what another head has in the same pair.  (With the heads' scale alone a page with
+// a radius of 30000 beside ones of 0.3, in a pair where the query is small, had an error of 9.3e-5; so,
+// and with fp32 arithmetic, 1.6e-7.)  The 16 pairs of a block are followed by 128 bytes of padding
+// (the four lane rows read four blocks at once).
 constexpr int kQueryTop = 9, kParamTop = 4;
 constexpr int kQueryBlock = 16 * 16 * 8 + 128;
 struct QueryShared {
@@ -176,9 +180,11 @@ __device__ __forceinline__ QueryFetch fetch_query_heads(const DecodeArgs& a, boo
   }
   return f;
 }
-// `shifts`: the power of two each head was multiplied with
+// `shifts`: the power of two each head was multiplied with; `pair_down`: what the parameters of each
+// pair are to be multiplied with.  `exponents` is scratch.  Holds one work-group barrier.
 template <int NH, bool Q32>
-__device__ __forceinline__ void store_query_heads(QueryShared& q, int* shifts, const QueryFetch& f, float sign, int tid) {
+__device__ __forceinline__ void store_query_heads(QueryShared& q, int* shifts, float* pair_down, uint16_t (*exponents)[kHeadDim],
+                                                  const QueryFetch& f, float sign, int tid) {
   uint32_t top = 0;
 #pragma unroll
   for (int e = 0; e < 4; ++e) top = max(top, f2u(f.v[e]) & 0x7fffffffu);
@@ -186,12 +192,27 @@ __device__ __forceinline__ void store_query_heads(QueryShared& q, int* shifts, c
   for (int d = 16; d >= 1; d >>= 1) top = max(top, static_cast<uint32_t>(__shfl_xor(static_cast<int>(top), d)));
   const int shift = min(kQueryTop + 127 - static_cast<int>(top >> 23), 126);
   const int h = tid >> 5, dim = (tid & 31) * 4;
-  if (h >= NH) return;                               // (also the wavefronts beyond the fourth)
+  // exponents after the head's scale, the largest 64 + kQueryTop
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (h < NH) exponents[h][dim + e] = static_cast<uint16_t>(max(0, static_cast<int>((f2u(f.v[e]) & 0x7fffffffu) >> 23) + shift - 127 + 64));
+  __syncthreads();
+  if (h >= NH) return;
+  int up[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int j = (dim + e) & (kPairs - 1);
+    int most = 0;
+#pragma unroll
+    for (int o = 0; o < NH; ++o) most = max(most, max(static_cast<int>(exponents[o][j]), static_cast<int>(exponents[o][j + kPairs])));
+    up[e] = most == 0 ? 0 : 64 + kQueryTop - most;
+    if (h == 0 && dim + e < kPairs) pair_down[j] = most == 0 ? 0.f : __builtin_ldexpf(1.f, -up[e]);   // (not in any product: no say in the page's scale)
+  }
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const int j = (dim + e) & (kPairs - 1), comp = (dim + e) >> 6, kk = j & 15;
     _Float16* const at = reinterpret_cast<_Float16*>(q.pairs + (j >> 4) * kQueryBlock + kk * 128 + comp * 2);
-    const float x = sign * __builtin_ldexpf(f.v[e], shift);
+    const float x = sign * __builtin_ldexpf(f.v[e], shift + up[e]);
     const _Float16 hi = static_cast<_Float16>(x);
     const _Float16 rest = Q32 ? static_cast<_Float16>(x - static_cast<float>(hi)) : hi;
     const _Float16 none = static_cast<_Float16>(0.f);
@@ -274,13 +295,14 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
   return static_cast<uint32_t>(uni(static_cast<int>(max(s[0], s[1]))));
 }
 
-// A page's radius parameters, one pair a lane, scaled by the power of two 2^k that brings the
-// largest into [2^4, 2^5) (as far as 2^15 goes); sets k.  Negative or non-finite words -- the encoder
-// writes neither -- scale like numbers just above the largest finite one.
-__device__ __forceinline__ uint32_t scale_page_params(uint32_t par, int& k) {
-  const uint32_t e = wave_max_u32(max(par & 0xffffu, par >> 16)) >> 10;   // biased exponent (and sign)
-  k = max(-12, min(15, kParamTop + 15 - static_cast<int>(e)));
-  return h2u(u2h(par) * u2h(static_cast<uint32_t>((k + 15) << 10) * 0x10001u));
+// A page's radius parameters, one pair a lane, times `down` (of the pair) and the power of two 2^k that
+// brings the largest into [2^4, 2^5); sets k.
+__device__ __forceinline__ uint32_t scale_page_params(uint32_t par, float down, int& k) {
+  const f16x2 p = u2h(par);
+  const float s = static_cast<float>(p.x) * down, z = static_cast<float>(p.y) * down;
+  const uint32_t e = wave_max_u32(max(f2u(s) & 0x7fffffffu, f2u(z) & 0x7fffffffu)) >> 23;
+  k = min(100, kParamTop + 127 - static_cast<int>(e));               // (a page of zeros: anything)
+  return h2u(to_half2(__builtin_ldexpf(s, k), __builtin_ldexpf(z, k)));
 }
 
 __device__ __forceinline__ float max3(float a, float b, float c) {
@@ -336,12 +358,13 @@ struct ScoreWalk {
   // that four accumulators serve a chain; without restarts simply step by step.
   static constexpr int kOps = kChain == 16 ? 1 : kChain;   // query operands kept
   uint32_t q_op[kOps][2];
-  uint32_t lane_lut, q_addr, par_put, par_get, voff_codes, low_mask;
+  uint32_t lane_lut, q_addr, par_put, par_get, voff_codes, low_mask, down_addr;
 
-  __device__ __forceinline__ void init(const uint8_t* lut, const QueryShared& q, const uint32_t* params, int lane) {
+  __device__ __forceinline__ void init(const uint8_t* lut, const QueryShared& q, const float* pair_down, const uint32_t* params, int lane) {
     const int row = lane >> 4, col = lane & 15;
     lane_lut = lds_addr(lut) + col * 16;
     q_addr = lds_addr(q.pairs) + row * kQueryBlock + col * 8;
+    down_addr = lds_addr(pair_down);
     par_put = lds_addr(params) + lane * 4;
     par_get = lds_addr(params) + row * 64;
     voff_codes = (row * kGroup + row_token<O>(col)) * UB;
@@ -449,7 +472,8 @@ struct ScoreWalk {
   __device__ __forceinline__ int run(__amdgpu_buffer_rsrc_t rc_nxt, __amdgpu_buffer_rsrc_t rp_nxt, int rot_nxt, int lane) {
     issue<0>(rc_nxt, rot_nxt);
     int k;
-    *(PQ_LDS uint32_t*)static_cast<uintptr_t>(par_put) = scale_page_params(par, k);
+    *(PQ_LDS uint32_t*)static_cast<uintptr_t>(par_put) =
+        scale_page_params(par, *(const PQ_LDS float*)static_cast<uintptr_t>(down_addr + lane * 4), k);
     load_params(rp_nxt, lane);
     wave_lds_sync();
     fetch_q(0);
@@ -501,7 +525,10 @@ struct ScoreWalk {
         for (int o = 0; o < 2; ++o) {
           const u32x2 v = *(const PQ_LDS u32x2*)static_cast<uintptr_t>(at + (2 * e + o) * 128);
           const uint32_t pick = (v.x & ~low_mask) | (Q32 ? v.y : 0u);
-          x[o] = (kd >> 1) ? pick >> 16 : pick & 0xffffu;
+          // without the pair's scale: no parameter carries the other half of it here
+          const float down = *(const PQ_LDS float*)static_cast<uintptr_t>(down_addr + (j0 + 2 * e + o) * 4);
+          const f16x2 picked = u2h(pick);
+          x[o] = h2u(to_half2(static_cast<float>((kd >> 1) ? picked.y : picked.x) * down, 0.f));
         }
         w[e] = x[0] | (x[1] << 16);
       }
@@ -639,6 +666,8 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     __attribute__((aligned(16))) uint32_t vpar[kQuantV ? kMatWaves : 1][kQuantV ? kGroup : 1];
     float red_ml[kMatWaves][NH][3];                                      // m, l, sum of p * zero-point
     int q_shift[kMaxHeads];
+    float pair_down[kPairs];
+    uint16_t exponents[NH][kHeadDim];
     int stage;
   };
   __shared__ Shared sh;
@@ -714,7 +743,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   int nv_cur, nv_nxt, rot_cur, rot_nxt;
   std::conditional_t<kGiven, GivenScores<kOrder, NH>, ScoreWalk<W, kOrder, NH, Q32, kQuantV ? 2 : 1, kChain>> w;
   if constexpr (kGiven) w.init(lane, a.n_heads, row_bytes);
-  else w.init(sh.lut, sh.q, sh.params[wave], lane);
+  else w.init(sh.lut, sh.q, sh.pair_down, sh.params[wave], lane);
   uint4 vr[kQuantV ? 1 : 4][8];                                        // fp16 values: four groups of 8 rows (32 tokens)
   uint4 vq[kQuantV ? kVLoads : 1];                                     // quantized values: the page's units
   u32x2 vpar = {0u, 0u};                                               // (scale, zero) of tokens 2 lane, 2 lane + 1
@@ -746,7 +775,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   }
   if constexpr (!kGiven) {
     fill_key_table<W, kMatThreads>(sh.lut, key_table<W>(a.table_index), tid);           // while the first page is under way
-    store_query_heads<NH, Q32>(sh.q, sh.q_shift, qf, sign, tid);
+    store_query_heads<NH, Q32>(sh.q, sh.q_shift, sh.pair_down, sh.exponents, qf, sign, tid);
     __syncthreads();
   }
 
@@ -768,7 +797,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     const int lane = lane_id(), col = lane & 15;
     int q_shift = 0;
     if constexpr (!kGiven) {
-      w.init(sh.lut, sh.q, sh.params[wave], lane);
+      w.init(sh.lut, sh.q, sh.pair_down, sh.params[wave], lane);
       q_shift = sh.q_shift[column_head<NH>(col)];
     }
     const int s_exp_before = s_exp;

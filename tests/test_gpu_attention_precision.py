@@ -132,3 +132,46 @@ def test_score_rows_a_gibibyte_apart(group):
     assert torch.equal(cache.attention(far), want)
     assert torch.equal(far[..., :length], near)
     assert bool(torch.isnan(far[..., length:]).all())
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("group", [1, 4, 8])
+@pytest.mark.parametrize("radius", [16.0, 400.0, 30000.0])
+@pytest.mark.parametrize("tail", [0, 50])
+@pytest.mark.parametrize("zero_heads", [0, 1, 2])
+def test_one_large_radius(zero_heads, tail, radius, group, dtype):
+    """Keys whose pair 5 is far larger than the others, with queries that are small there by as much, or
+    zero -- for no head, every second one or all: the other pairs decide the softmax.  With a tail of
+    un-quantized keys too."""
+    from packed import Packed, relative_error
+
+    heads, length = 2, 1280 + tail
+    keys = _random(21, length, heads, 128) * 0.25
+    keys[..., 5], keys[..., 69] = radius, 0.0
+    q = _random(22, 1, heads * group, 128)
+    q[..., 5] /= radius
+    q[..., 69] /= radius
+    if zero_heads:
+        q[:, ::3 - zero_heads, 5] = q[:, ::3 - zero_heads, 69] = 0.0
+    cache = Packed([keys.astype(dtype)], [_random(23, length, heads, 128)], q.astype(dtype), residual=tail > 0)
+    err = relative_error(cache.attention(), cache.exact()[1])
+    print(f"[precision] radius {radius} zero {zero_heads} group {group} {dtype.__name__} tail {tail}: {err:.2e}", flush=True)
+    assert err <= 1e-6
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("group", [1, 4, 8])
+@pytest.mark.parametrize("size", [1000.0, 30000.0])
+def test_one_large_query_element(size, group, dtype):
+    """The other way round: the query's largest element meets keys that are small there."""
+    from packed import Packed, relative_error
+
+    heads, length = 2, 1400
+    keys = _random(24, length, heads, 128)
+    keys[..., 7], keys[..., 71] = 1.0 / size, 0.5 / size
+    q = _random(25, 1, heads * group, 128)
+    q[..., 7] = size
+    cache = Packed([keys.astype(dtype)], [_random(26, length, heads, 128)], q.astype(dtype))
+    err = relative_error(cache.attention(), cache.exact()[1])
+    print(f"[precision] query element {size} group {group} {dtype.__name__}: {err:.2e}", flush=True)
+    assert err <= 1e-6
