@@ -240,19 +240,29 @@ __device__ __forceinline__ f16x2 u2h(uint32_t u) {
   __builtin_memcpy(&h, &u, 4);
   return h;
 }
-// A probability's fp16 parts, of x in [0, 2^kProbTop]: the nearest fp16 in the lanes of high-part
-// columns (part = {0, 1}), 2^kLowShift times what that leaves over -- at most 2^(kProbTop - 12) -- in
-// those of low-part ones (part = {-1, 2^kLowShift}).  An accumulator row of low parts is scaled back
-// when a chunk ends.  The two carry 22 bits of x until the high part is below fp16's normal range, a
-// bit less for every power of two below that: a token keeps 22 bits of its weight down to 2^-22 of
-// the largest, and vanishes at 2^-47.  (Where the output hangs on weights of 2^-25 beside an
-// attention sink its error is 4e-7 so, 5e-7 with fp32 weights, and was 3.3e-3 with both parts on one
-// scale and the largest at 2^4.)  kProbTop is no larger because it is added to the exponent before
-// the exponential, whose argument is rounded at that size (at 15: error 5.8e-7 where 8 shows 5.6e-7);
-// and one less than a power of two: where scores are so large that the sum is rounded to a multiple
-// of it, the weights still end at 2^8.
-constexpr int kProbTop = 7;
-constexpr int kLowShift = 15;
+// A probability's fp16 parts, of x in [0, 2^(15 - S)]: the nearest fp16 to 2^S x in the lanes of
+// high-part columns (part = {0, 2^S}), 2^kLowShift times what that leaves over -- 2^3 at most -- in
+// those of low-part ones (part = {-2^-S, 2^(S + kLowShift)}).  Accumulator rows are scaled back when a
+// chunk ends.  The two carry 22 bits until the high part is below fp16's normal range, a bit less for
+// every power of two below that: with S = 15 a token keeps 22 bits of its weight down to 2^-29 of the
+// largest, and vanishes at 2^-51.  (Where the output hangs on weights of 2^-25 beside an attention sink
+// its error is 4e-7 so, 5e-7 with fp32 weights, and was 3.3e-3 with both parts on one scale and the
+// largest at 2^4.)  2^S is not in the exponential's argument, which would be rounded at that size:
+// flat softmaxes 1.6e-7 with 2^7 there, 1.3e-7 so (fp32 throughout: 1.4e-7).
+constexpr int kLowShift = 12;
+template <int S>
+__device__ __forceinline__ f32x2 split_part(bool low) {
+  constexpr float kUp = static_cast<float>(1 << S);
+  return low ? f32x2{-1.f / kUp, kUp * (1 << kLowShift)} : f32x2{0.f, kUp};
+}
+template <int S>
+__device__ __forceinline__ uint32_t split_pair(float x0, float x1, f32x2 part) {
+  constexpr float kUp = static_cast<float>(1 << S);
+  const f16x2 h = {static_cast<_Float16>(fmaf(x0, kUp, 0.f)), static_cast<_Float16>(fmaf(x1, kUp, 0.f))};
+  const f16x2 r = {static_cast<_Float16>(fmaf(fmaf(static_cast<float>(h.x), part.x, x0), part.y, 0.f)),
+                   static_cast<_Float16>(fmaf(fmaf(static_cast<float>(h.y), part.x, x1), part.y, 0.f))};
+  return h2u(r);
+}
 // Sum of an accumulator's two parts, one in lanes 0 - 31, the other (already scaled back) in lanes
 // 32 - 63.  Where a value is infinite the high part is what the product is; a low part may be zero or
 // negative there.
@@ -467,7 +477,7 @@ struct ScoreWalk {
       steps<H + 1>(rc_nxt, rot_nxt);
     }
   }
-  // Scores of the page in cu / par, summed over the columns of a head (and left in all of them), scaled
+  // Scores of the page in cu / par, summed over the columns of a head and left as fold() says, scaled
   // by 2^(k + the head's query shift + kTableShift); returns k.  cu and par then hold the next page.
   __device__ __forceinline__ int run(__amdgpu_buffer_rsrc_t rc_nxt, __amdgpu_buffer_rsrc_t rp_nxt, int rot_nxt, int lane) {
     issue<0>(rc_nxt, rot_nxt);
@@ -491,18 +501,31 @@ struct ScoreWalk {
 #pragma unroll
       for (int j = 0; j < 4; ++j) s[4 + j] += done[j];
     }
-    fold();
+    fold(lane & 4);
     wave_lds_sync();
     return k;
   }
-  __device__ __forceinline__ void fold() {
+  // NH = 8: s[t] of all batches in both columns of a head.  NH = 4: the columns of half 0 keep batches
+  // 0 .. 3, those of half 1 batches 4 .. 7, in s[0] .. s[3].
+  __device__ __forceinline__ void fold(bool half) {
+    if constexpr (NH == 4) {
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
+      for (int t = 0; t < 8; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if constexpr (NH == 4) s[t][i] += dpp_of<0x124>(s[t][i]);          // row_ror:4: the other half's column
-        s[t][i] += dpp_of<0x128>(s[t][i]);                                 // row_ror:8: the other part's
-      }
+        for (int i = 0; i < 4; ++i) s[t][i] += dpp_of<0x124>(s[t][i]);     // row_ror:4: the neighbour in (part, half)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          s[j][i] = half ? s[4 + j][i] : s[j][i];
+          s[j][i] += dpp_of<0x128>(s[j][i]);                               // row_ror:8: the other two
+        }
+    } else {
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[t][i] += dpp_of<0x128>(s[t][i]);
+    }
   }
   // Scores of the residual group (un-quantized fp16 keys, rows past nv_res read as zero): a key row
   // is an operand as it lies in memory, 32 dims per instruction; same scaling with k = 0, table
@@ -549,7 +572,7 @@ struct ScoreWalk {
       s[t] = lo + hi;
       if (t & 1) __builtin_amdgcn_sched_barrier(0);
     }
-    fold();
+    fold(lane & 4);
   }
 };
 
@@ -560,25 +583,26 @@ template <TokenOrder O, int NH>
 struct GivenScores {
   f32x4 s[8];
   uint32_t voff;
+  uint32_t half_at;                                // bytes from batch j to the lane's j-th, by exclusive or
   __device__ __forceinline__ void init(int lane, int n_heads, uint32_t row_bytes) {
     voff = static_cast<uint32_t>(min(column_head<NH>(lane & 15), n_heads - 1)) * row_bytes +
            static_cast<uint32_t>(row_token<O>(4 * (lane >> 4))) * 4;
+    half_at = NH == 4 && (lane & 4) ? 256u : 0u;
   }
   // What lies past the sequence's end, and a masked page, reads as anything.  A whole page's four
   // consecutive scores are one load (an incomplete one's may leave the rows).
   __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, int rot, int nv) {
     static_assert(O != TokenOrder::kRows, "a lane's scores of a batch are consecutive");
-    if (nv == kGroup) {
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const uint4 v = buf_load16<kAuxCached>(rs, voff, static_cast<uint32_t>(batch_token<O>(t, rot)) * 4);
-        s[t] = f32x4{u2f(v.x), u2f(v.y), u2f(v.z), u2f(v.w)};
+    for (int j = 0; j < NH; ++j) {
+      const uint32_t at = voff + ((static_cast<uint32_t>(batch_token<O>(j, rot)) * 4) ^ half_at);
+      if (nv == kGroup) {
+        const uint4 v = buf_load16<kAuxCached>(rs, at, 0);
+        s[j] = f32x4{u2f(v.x), u2f(v.y), u2f(v.z), u2f(v.w)};
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[j][i] = u2f(buf_load4<kAuxCached>(rs, at, static_cast<uint32_t>(i) * 4));
       }
-    } else {
-#pragma unroll
-      for (int t = 0; t < 8; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) s[t][i] = u2f(buf_load4<kAuxCached>(rs, voff, static_cast<uint32_t>(batch_token<O>(t, rot) + i) * 4));
     }
   }
 };
@@ -648,11 +672,15 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   constexpr TokenOrder kOrder = kGiven && VB == 16 ? TokenOrder::kPlain : token_order(VB);
   constexpr int kChain = kQuantV ? 16 : 4;
   constexpr uint32_t kCodesBytes = kBlocks * kGroup * UB;
-  // Probabilities are exp2(score - m + kProbTop) with m the running maximum rounded up to a whole
-  // number (rescaling factors are then exact powers of two).  With quantized values they meet the
-  // token's scale before they are split; scales are taken times 2^s_exp, which brings the largest that
-  // the wavefront has seen into [2^3, 2^4), so that what is split stays below 2^12 and keeps its bits
+  // Probabilities are exp2(score - m) with m the running maximum rounded up to a whole number
+  // (rescaling factors are then exact powers of two).  With quantized values they meet the token's
+  // scale before they are split; scales are taken times 2^s_exp, which brings the largest that
+  // the wavefront has seen into [2^3, 2^4), so that what is split stays below 2^4 and keeps its bits
   // whatever the values' size (it is 2^-10: error 3e-6 so, 4e-3 with the scales as they are).
+  constexpr int kUp = kQuantV ? 15 - (kScaleTop + 1) : 15;               // the split's S
+  // The softmax of a token is the work of one lane in each part: with 4 heads the columns of the two
+  // halves take half of the batches each (kOwn) and hand their operand words to each other.
+  constexpr int kOwn = NH;
   constexpr int kVLoads = kQuantV ? kGroup * kHeadDim * VB / 8 / 1024 : 32;   // 1 KB wavefront loads per page of values
 
   struct Shared {
@@ -813,7 +841,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       wave_lds_sync();                                                 // (the walk has one between the token parameters' way in and out)
       if (sign < 0.f) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t) w.s[t] = -w.s[t];
+        for (int t = 0; t < kOwn; ++t) w.s[t] = -w.s[t];
       }
     } else {
       down = w.run(rc_nxt, rp_nxt, rot_nxt, lane) + kTableShift + q_shift;
@@ -827,27 +855,28 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     if constexpr (!kQuantV) load_rows(vr[2], rv_cur, 2, rot_cur);
     __builtin_amdgcn_sched_barrier(0);
 
-    // ---- online softmax (log2 domain) over the lane's 32 tokens ----
+    // ---- online softmax (log2 domain) over the lane's tokens: 4 row .. + 3 of kOwn batches ----
     // above zero, so that masked scores (-inf) stay masked whatever the scale is
     const float mult = fmaxf(__builtin_ldexpf(scale_abs, -down), 1.17549435e-38f);
     if (nv_cur < kGroup) {
-      const int row = lane_id() >> 4;
+      const int row = lane_id() >> 4, other = NH == 4 && (lane_id() & 4) ? 64 : 0;   // batch 4 + j: the token's bit 6 the other way
       int nv = uni(nv_cur);
       asm volatile("" : "+s"(nv));                                     // 32 conditions: not worth keeping in registers
 #pragma unroll
-      for (int t = 0; t < 8; ++t)
+      for (int t = 0; t < kOwn; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (batch_token<kOrder>(t, rot_cur) + row_token<kOrder>(4 * row + i) >= nv) w.s[t][i] = kNegInf;
+          if (((batch_token<kOrder>(t, rot_cur) + row_token<kOrder>(4 * row + i)) ^ other) >= nv) w.s[t][i] = kNegInf;
     }
     float pm = fmaxf(w.s[0][0], w.s[0][1]);
     pm = max3(pm, w.s[0][2], w.s[0][3]);
 #pragma unroll
-    for (int t = 1; t < 8; ++t) {
+    for (int t = 1; t < kOwn; ++t) {
       pm = max3(pm, w.s[t][0], w.s[t][1]);
       pm = max3(pm, w.s[t][2], w.s[t][3]);
     }
     {
+      if constexpr (NH == 4) pm = fmaxf(pm, dpp_of<0x124>(pm));
       auto r = __builtin_amdgcn_permlane16_swap(f2u(pm), f2u(pm), false, false);
       pm = fmaxf(u2f(r[0]), u2f(r[1]));
       auto q = __builtin_amdgcn_permlane32_swap(f2u(pm), f2u(pm), false, false);
@@ -871,19 +900,20 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       }
       m_run = m_new;
     }
-    const float off = dead ? 0.f : static_cast<float>(kProbTop) - m_run;
-    const f16x2 part = split_part(lane_id() & 8);
+    const float off = dead ? 0.f : -m_run;
+    const f32x2 part = split_part<kUp>(lane_id() & 8);
     uint32_t p_op[8][2];                                               // batch t: fp16 pairs of tokens 4 row + (0, 1), (2, 3)
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
+    for (int t = 0; t < kOwn; ++t) {
       float p[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(w.s[t][i], mult, off));
       if constexpr (kQuantV) {
         l_run += (p[0] + p[1]) + (p[2] + p[3]);
         // V~ = code * s + z (Section 2): fold s (times 2^s_exp) into the probability, collect p * z
+        const int lane = lane_id();
         const u32x4 vp = *(const PQ_LDS u32x4*)static_cast<uintptr_t>(
-            lds_addr(sh.vpar[wave]) + (batch_token<kOrder>(t, 0) + row_token<kOrder>(4 * row)) * 4);
+            lds_addr(sh.vpar[wave]) + (batch_token<kOrder>(t, 0) + row_token<kOrder>(4 * (lane >> 4)) + (NH == 4 && (lane & 4) ? 64 : 0)) * 4);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const f16x2 sz = u2h(vp[i]);
@@ -892,10 +922,20 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
         }
       }
       if constexpr (!kQuantV) {
-        if (t == 7) load_rows(vr[3], rv_cur, 3, rot_cur);
+        // (not all at once, nor behind the exponentials: 1 - 2 % with one head per KV head)
+        if (t == kOwn / 4) load_rows(vr[3], rv_cur, 3, rot_cur);
       }
-      p_op[t][0] = split_pair(p[0], p[1], part);
-      p_op[t][1] = split_pair(p[2], p[3], part);
+      p_op[t][0] = split_pair<kUp>(p[0], p[1], part);
+      p_op[t][1] = split_pair<kUp>(p[2], p[3], part);
+      if constexpr (NH == 4) {
+        // columns of half 1 take batch t from half 0 (row_ror:4), those of half 0 batch 4 + t from half 1 (row_ror:12)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int own = static_cast<int>(p_op[t][e]);
+          p_op[t][e] = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(own, own, 0x124, 0xf, 0xa, false));
+          p_op[4 + t][e] = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(own, own, 0x12c, 0xf, 0x5, false));
+        }
+      }
     }
 
     if constexpr (kGiven) w.load(rc_nxt, rot_nxt, nv_nxt);
@@ -968,10 +1008,14 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   {
     const int lane = lane_id(), row = lane >> 4, col = lane & 15;
     const int acc_head = NH == 8 ? 4 * (row & 1) : 0;                  // head of accumulator row i: acc_head + i
-    const float back = row >= 2 ? 1.f / (1 << kLowShift) : 1.f;                // rows of low parts
+    const float back = __builtin_ldexpf(1.f, row >= 2 ? -kUp - kLowShift : -kUp);   // rows 2, 3 are low parts
     // columns 0 .. NH - 1 are the heads' high parts; accumulator rows: high part + low part
-    const float l_tot = kQuantV ? sum_rows(l_run) : 0.f;
-    const float z_tot = kQuantV ? sum_rows(z_run) : 0.f;
+    float l_tot = kQuantV ? sum_rows(l_run) : 0.f;
+    float z_tot = kQuantV ? sum_rows(z_run) : 0.f;
+    if constexpr (kQuantV && NH == 4) {
+      l_tot += dpp_of<0x124>(l_tot);                                   // the other half's batches
+      z_tot += dpp_of<0x124>(z_tot);
+    }
     if (lane < NH) {
       sh.red_ml[wave][lane][0] = m_run;
       if constexpr (kQuantV) sh.red_ml[wave][lane][1] = l_tot;
