@@ -114,8 +114,6 @@ bool launch_scores_rt(int rt, int G, const DecodeArgs& a, dim3 grid, hipStream_t
 // on, "partials" below (and with quantized values at more than two query heads per KV head, and with
 // the grouped quantizer, which has a kernel of its own).
 enum class AttentionKernel { kPartials, kRoles };
-constexpr int kComputeUnits = 256;           // MI355X
-constexpr int kResidentGroups = 2 * kComputeUnits;   // work-groups of the attention and score kernels
 
 // Work-groups of four pages each that the shape could have, as far as 768 (the workspace's size is
 // stated in them).
@@ -193,34 +191,15 @@ Workspace carve_workspace(void* base, const pq_layout* l, int32_t n_seqs, int32_
   return w;
 }
 
-// Chunk plan of the uniform angle grid's attention kernel.  Two work-groups are resident on a compute
-// unit, and starting and ending one costs about as much as streaming 8 pages: chunks are as long as
-// they can be without leaving compute units idle at the end.  `share` is a resident work-group's part
-// of the launch if every sequence has max_seq_len tokens.  Measured (pages per chunk: microseconds;
-// "48 + 16": 48, the last quarter in chunks of 16):
-//   up to 16 pages a share   248 units x 2 .. 24 pages   8: 51, 16: 44, 24: 47;  8 x 1024  8: 64, 16: 61, 24: 68
-//   fp16 values              256 x 64      24: 110, 32: 110, 44: 107.5, 64: 110;  128 x 256  32: 210, 44: 212, 64: 208
-//                            512 x 8 .. 128  24: 240, 44: 238, 64: 239, 64 + 24: 233
-//   quantized values         256 x 4 .. 64   16: 54, 24: 43.4, 24 + 8: 44, 32: 55;  128 x 256  32: 131, 64: 126, 48 + 16: 125
-// (With fp16 values a work-group that is left alone streams faster; with quantized ones it does not.)
+// Chunk plan of the uniform angle grid's attention kernel for launches that are cut on the host, as if
+// every sequence had max_seq_len tokens (chunk_lengths() says why chunks are as long as they are).
 // The two-stage entry points, whose second one does not know the values' width, use the fp16 plan.
 ChunkPlan plan_uniform(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
   const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
   const int64_t units = static_cast<int64_t>(n_seqs) * l->n_kv_heads;
-  const int64_t share = (units * max_pages + kResidentGroups - 1) / kResidentGroups;
-  auto whole_rounds = [](int64_t pages) { return (pages + kMatWaves - 1) / kMatWaves * kMatWaves; };
-  int64_t big, small, n_big = 0;
-  if (max_pages < 2 * kMatWaves) {
-    big = small = max_pages;                             // less than two pages a wavefront: one chunk, nothing to merge
-  } else if (share <= 16) {
-    big = small = share <= 4 ? 4 : share <= 8 ? 8 : 16;
-  } else if (v_bits == 16 && share <= 64) {
-    big = small = std::min<int64_t>(64, whole_rounds(share * 4 / 3));
-  } else {
-    big = std::min<int64_t>(64, whole_rounds(share * 3 / 4));
-    small = std::max<int64_t>(8, std::min<int64_t>(24, whole_rounds(share / 4)));
-    n_big = std::max<int64_t>(1, max_pages * 4 / 5 / big);
-  }
+  const int64_t share = std::min<int64_t>(1 << 20, (units * max_pages + kResidentGroups - 1) / kResidentGroups);
+  const ChunkLengths len = chunk_lengths(static_cast<int>(share), static_cast<int>(max_pages), v_bits == 16);
+  int64_t big = len.big, small = len.small, n_big = big == small ? 0 : len.n_big;
   // as many partials as the workspace holds (its own plan has max_pages / 32 chunks or more)
   const int64_t most = static_cast<int64_t>(workspace_slots(l, n_seqs, n_q_heads, max_seq_len)) / (static_cast<int64_t>(n_seqs) * n_q_heads);
   auto chunks = [&] {
@@ -351,10 +330,32 @@ int launch_scores(const pq_layout* layout, DecodeArgs a, hipStream_t stream) {
   return e == hipSuccess ? PQ_OK : record_hip_error(e);
 }
 
+// Chunks per KV head, beyond one for each sequence, of a launch that is cut on the device by the
+// sequences' real lengths (BalancedPlan); 0: it is cut on the host.  As many as the workspace has
+// partials for, up to three a resident work-group.
+// The cut costs a launch 1 - 3 us (31 x 3000 tokens 45.1 -> 46.1, 8 x 8K with 32 KV heads 110.5 -> 112.6,
+// 32 x 8K with 2-bit values 43.1 -> 44.7), so that only those get it where a resident work-group may
+// have kCutShare pages or more, 90 us with fp16 values; below, a cut by max_seq_len loses as much at
+// most on uneven lengths.  With fewer than 16 units the host's cut has more chunks per unit than
+// are combined in the kernel; above 512 sequences reading all lengths in every work-group costs more
+// than uneven chunks do among so many.
+constexpr int64_t kCutShare = 48;
+int spare_chunks(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len) {
+  const int64_t units = static_cast<int64_t>(n_seqs) * l->n_kv_heads;
+  const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
+  if (!large_uniform_launch(l, n_seqs, max_seq_len) || units < kResidentGroups / kBalancedFan || n_seqs > kBalancedSeqs ||
+      l->n_kv_heads > kComputeUnits || units * max_pages < kCutShare * kResidentGroups || units * max_pages >= (int64_t{1} << 30))
+    return 0;
+  const int64_t partials = workspace_slots(l, n_seqs, l->n_kv_heads, max_seq_len) - units;     // (one query head per KV head)
+  return static_cast<int>(std::min<int64_t>(3 * kResidentGroups, partials) / l->n_kv_heads);
+}
+
 // Whether one kernel does all of pq_decode_attention (true), or the merge kernel follows: the
-// sequences are one chunk long, or a large launch has few enough chunks per unit.
+// sequences are one chunk long, the launch is cut on the device, or a large one has few enough chunks per
+// unit.
 bool merges_in_kernel(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
   if (l->angle_quantizer != PQ_ANGLE_UNIFORM) return false;
+  if (spare_chunks(l, n_seqs, max_seq_len) > 0) return true;
   const int n_chunks = plan_uniform(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
   return n_chunks == 1 || (n_chunks <= kMergeFan && large_uniform_launch(l, n_seqs, max_seq_len));
 }
@@ -430,7 +431,8 @@ int decode_launch(const pq_layout* layout, const void* q, pq_dtype q_dtype, int3
   // (the score-only kernel goes first: a third launch would cost more than a late combination)
   const bool merged = out != nullptr && (merges_in_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len) || (given && plan.n_chunks <= kMergeFan));
   a.merge_in_kernel = merged ? 1 : 0;
-  const dim3 grid(layout->n_kv_heads, n_seqs, plan.n_chunks);
+  a.spare_chunks = out != nullptr ? spare_chunks(layout, n_seqs, max_seq_len) : 0;
+  const dim3 grid = a.spare_chunks > 0 ? dim3(layout->n_kv_heads, n_seqs + a.spare_chunks) : dim3(layout->n_kv_heads, n_seqs, plan.n_chunks);
   a.table_index = key_table_index(layout);
   if (given) {
     const int ss = launch_scores(layout, a, stream);

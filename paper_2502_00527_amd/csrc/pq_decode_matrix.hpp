@@ -165,18 +165,23 @@ constexpr int kQueryBlock = 16 * 16 * 8 + 128;
 struct QueryShared {
   __attribute__((aligned(16))) uint8_t pairs[kBlocks * kQueryBlock];
 };
+// As loaded, so that nothing waits for it before store_query_heads(): thread = (head tid / 32, dims
+// 4 (tid % 32) ..+3); heads from n_heads on are zero.
 struct QueryFetch {
-  float v[4];
+  uint32_t w[4];
+  template <bool Q32>
+  __device__ __forceinline__ float value(int e) const {
+    return Q32 ? u2f(w[e]) : static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w[e / 2] >> (16 * (e % 2)))));
+  }
 };
-// thread = (head tid / 32, dims 4 (tid % 32) ..+3); heads from n_heads on are zero
-__device__ __forceinline__ QueryFetch fetch_query_heads(const DecodeArgs& a, bool q32, int64_t q_at, int tid) {
+template <bool Q32>
+__device__ __forceinline__ QueryFetch fetch_query_heads(const DecodeArgs& a, int64_t q_at, int tid) {
   QueryFetch f = {};
   const int h = tid >> 5;
   if (h < a.n_heads) {
     const int64_t at = q_at + h * kHeadDim + (tid & 31) * 4;
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      f.v[e] = q32 ? static_cast<const float*>(a.q)[at + e] : __half2float(static_cast<const __half*>(a.q)[at + e]);
+    if constexpr (Q32) __builtin_memcpy(f.w, static_cast<const float*>(a.q) + at, 16);
+    else __builtin_memcpy(f.w, static_cast<const __half*>(a.q) + at, 8);
   }
   return f;
 }
@@ -185,9 +190,12 @@ __device__ __forceinline__ QueryFetch fetch_query_heads(const DecodeArgs& a, boo
 template <int NH, bool Q32>
 __device__ __forceinline__ void store_query_heads(QueryShared& q, int* shifts, float* pair_down, uint16_t (*exponents)[kHeadDim],
                                                   const QueryFetch& f, float sign, int tid) {
+  float v[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = f.value<Q32>(e);
   uint32_t top = 0;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) top = max(top, f2u(f.v[e]) & 0x7fffffffu);
+  for (int e = 0; e < 4; ++e) top = max(top, f2u(v[e]) & 0x7fffffffu);
 #pragma unroll
   for (int d = 16; d >= 1; d >>= 1) top = max(top, static_cast<uint32_t>(__shfl_xor(static_cast<int>(top), d)));
   const int shift = min(kQueryTop + 127 - static_cast<int>(top >> 23), 126);
@@ -195,7 +203,7 @@ __device__ __forceinline__ void store_query_heads(QueryShared& q, int* shifts, f
   // exponents after the head's scale, the largest 64 + kQueryTop
 #pragma unroll
   for (int e = 0; e < 4; ++e)
-    if (h < NH) exponents[h][dim + e] = static_cast<uint16_t>(max(0, static_cast<int>((f2u(f.v[e]) & 0x7fffffffu) >> 23) + shift - 127 + 64));
+    if (h < NH) exponents[h][dim + e] = static_cast<uint16_t>(max(0, static_cast<int>((f2u(v[e]) & 0x7fffffffu) >> 23) + shift - 127 + 64));
   __syncthreads();
   if (h >= NH) return;
   int up[4];
@@ -212,7 +220,7 @@ __device__ __forceinline__ void store_query_heads(QueryShared& q, int* shifts, f
   for (int e = 0; e < 4; ++e) {
     const int j = (dim + e) & (kPairs - 1), comp = (dim + e) >> 6, kk = j & 15;
     _Float16* const at = reinterpret_cast<_Float16*>(q.pairs + (j >> 4) * kQueryBlock + kk * 128 + comp * 2);
-    const float x = sign * __builtin_ldexpf(f.v[e], shift + up[e]);
+    const float x = sign * __builtin_ldexpf(v[e], shift + up[e]);
     const _Float16 hi = static_cast<_Float16>(x);
     const _Float16 rest = Q32 ? static_cast<_Float16>(x - static_cast<float>(hi)) : hi;
     const _Float16 none = static_cast<_Float16>(0.f);
@@ -289,21 +297,6 @@ __device__ __forceinline__ f16x8 as_operand(uint32_t a, uint32_t b, uint32_t c, 
   return r;
 }
 __device__ __forceinline__ f16x8 as_operand(const uint4& v) { return as_operand(v.x, v.y, v.z, v.w); }
-
-// Maximum over the wavefront, as a scalar.
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
-  auto dpp = [](uint32_t v, auto ctrl) {
-    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), decltype(ctrl)::value, 0xf, 0xf, true));
-  };
-  x = max(x, dpp(x, std::integral_constant<int, 0xB1>{}));
-  x = max(x, dpp(x, std::integral_constant<int, 0x4E>{}));
-  x = max(x, dpp(x, std::integral_constant<int, 0x141>{}));
-  x = max(x, dpp(x, std::integral_constant<int, 0x140>{}));
-  auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-  x = max(r[0], r[1]);
-  auto s = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-  return static_cast<uint32_t>(uni(static_cast<int>(max(s[0], s[1]))));
-}
 
 // A page's radius parameters, one pair a lane, times `down` (of the pair) and the power of two 2^k that
 // brings the largest into [2^4, 2^5); sets k.
@@ -664,8 +657,9 @@ __device__ __forceinline__ constexpr float code_unscale(int k) {
 }
 
 // ---- attention ----------------------------------------------------------------------------------
-// kGiven: the scores are in a.scores (neither the codes nor the query are read then).
-template <int W, int VB, int NH, bool Q32, bool kGiven = false>
+// kCut: the chunks are cut on the device (a.spare_chunks > 0).  kGiven: the scores are in a.scores
+// (neither the codes nor the query are read then).
+template <int W, int VB, int NH, bool Q32, bool kCut, bool kGiven = false>
 __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   constexpr int UB = 2 * W;
   constexpr bool kQuantV = VB != 16;
@@ -689,6 +683,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       QueryShared q;
       __attribute__((aligned(16))) float red[2][NH][kHeadDim];           // end of the chunk; also lent to the merge
       float lent[kFinishLdsFloats];
+      int32_t pages[kCut ? kBalancedSeqs : 1];                           // of the sequences, while the chunks are cut
     };
     __attribute__((aligned(16))) uint32_t params[kMatWaves][kPairs];
     __attribute__((aligned(16))) uint32_t vpar[kQuantV ? kMatWaves : 1][kQuantV ? kGroup : 1];
@@ -701,32 +696,69 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   __shared__ Shared sh;
   static_assert(sizeof(Shared) <= 80 * 1024, "two work-groups per compute unit");
 
-  const int kvh = blockIdx.x, seq = blockIdx.y, chunk = blockIdx.z;
   const int tid = threadIdx.x;
   const int wave = uni(tid >> 6);
   const int lane = tid & 63;
-  const int big = min(chunk, a.n_big);
-  const int page0 = big * a.pages_per_chunk + (chunk - big) * a.pages_small;
-  // what does not depend on the sequence's length is fetched along with it
-  const int64_t first_head = static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0;
+  const int kvh = blockIdx.x;
+  int seq = blockIdx.y, chunk = blockIdx.z;
+  int L, n_pages, page0 = 0, n_chunks = 1, npg = 0;
+  int64_t row0 = 0;
+  // A launch cut on the device: what the sequences' lengths make of this work-group's slot.  False: nothing.
+  const int slot = seq;
+  BalancedPlan plan;
+  auto take_cut = [&] {
+    plan.store_others(a, sh.pages, tid);
+    const int chunks = plan.cut(a, VB == 16);
+    if (slot >= chunks) return false;
+    if (slot >= a.n_seqs) plan.locate(slot, seq, chunk);
+    int before;
+    plan.sequence(seq, n_pages, n_chunks, before);
+    const int big = min(chunk, plan.len.n_big);
+    page0 = big * plan.len.big + (chunk - big) * plan.len.small;
+    npg = min(chunk < plan.len.n_big ? plan.len.big : plan.len.small, n_pages - page0);
+    row0 = (static_cast<int64_t>(before) * a.n_kv_heads + kvh * n_chunks) * a.group_total + static_cast<int64_t>(a.head0) * n_chunks;
+    if (a.n_seqs > 64) __syncthreads();                                // the lengths make room for what shares their memory
+    return true;
+  };
+  // A first chunk, of sequence number `slot`: its pages are under way before the cut is made.
+  const bool cut_later = kCut && slot < a.n_seqs;
+  if constexpr (kCut) {
+    plan.load(a, lane);
+    if (!cut_later && !take_cut()) return;
+  } else {
+    const int big = min(chunk, a.n_big);
+    page0 = big * a.pages_per_chunk + (chunk - big) * a.pages_small;
+  }
+  // (the same in every lane; said once more where paths have joined, or these go to vector registers)
+  seq = uni(seq);
+  chunk = uni(chunk);
+  page0 = uni(page0);
+  // the query and the page numbers are asked for without waiting for the sequence's length
   QueryFetch qf;
-  if constexpr (!kGiven) qf = fetch_query_heads(a, Q32, first_head * kHeadDim, tid);
+  if constexpr (!kGiven)
+    qf = fetch_query_heads<Q32>(a, (static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0) * kHeadDim, tid);
   PageIds<kMatWaves> pids;
   pids.start(a, seq, page0 + wave);
-  const int L = uni(clamped_len(a, seq));
-  const int n_pages = pages_of_len(L);
+  L = uni(clamped_len(a, seq));
+  n_pages = pages_of_len(L);
+  if (cut_later) {
+    npg = min(kMatWaves, n_pages);                                     // at least
+  } else if (!kCut) {
+    n_chunks = chunks_of_pages(n_pages, a.pages_per_chunk, a.n_big, a.pages_small);
+    npg = min(chunk < a.n_big ? a.pages_per_chunk : a.pages_small, n_pages - page0);
+    row0 = (static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0) * a.n_chunks;
+  }
+  const int64_t first_head = static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0;
   if (page0 >= n_pages) {
     // nothing here; a sequence without pages gets its zero rows from its first work-group
-    if (a.merge_in_kernel && chunk == 0 && tid < a.n_heads * 32) {
-      const int64_t head_row = static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0;
-      reinterpret_cast<float4*>(a.out + head_row * kHeadDim)[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+    if (a.merge_in_kernel && chunk == 0 && tid < a.n_heads * 32)
+      reinterpret_cast<float4*>(a.out + first_head * kHeadDim)[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
     return;
   }
-  const int npg = min(chunk < a.n_big ? a.pages_per_chunk : a.pages_small, n_pages - page0);
   const float sign = a.scale_log2 < 0.f ? -1.f : 1.f, scale_abs = fabsf(a.scale_log2);
   const int row = lane >> 4, col = lane & 15;
-  const int n_w = npg > wave ? (npg - wave + kMatWaves - 1) / kMatWaves : 0;   // chunk pages wave, wave + 4, ...
+  npg = uni(npg);
+  int n_w = npg > wave ? (npg - wave + kMatWaves - 1) / kMatWaves : 0;   // chunk pages wave, wave + 4, ...
   const int res_page = (a.residual != nullptr && (L % kGroup) != 0) ? L / kGroup : -1;
   pids.n_p = n_w;
 
@@ -801,11 +833,21 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     load_rows(vr[0], rv_cur, 0, rot_cur);
     load_rows(vr[1], rv_cur, 1, rot_cur);
   }
+  if constexpr (kCut) {
+    if (cut_later) {
+      take_cut();                                                      // (a first chunk always exists)
+      npg = uni(npg);
+      n_w = npg > wave ? (npg - wave + kMatWaves - 1) / kMatWaves : 0;
+      pids.n_p = n_w;
+    }
+    n_chunks = uni(n_chunks);
+  }
+  const int stride = kCut ? n_chunks : a.n_chunks;
   if constexpr (!kGiven) {
     fill_key_table<W, kMatThreads>(sh.lut, key_table<W>(a.table_index), tid);           // while the first page is under way
     store_query_heads<NH, Q32>(sh.q, sh.q_shift, sh.pair_down, sh.exponents, qf, sign, tid);
-    __syncthreads();
   }
+  if constexpr (!kGiven) __syncthreads();
 
   // per lane: column (head, part), running maximum, sums over the lane's tokens
   // (fp16 values: the sums of p come from the matrix unit like one more dim, l_acc)
@@ -1064,7 +1106,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     __syncthreads();
   }
 
-  finish_chunk<NH>(a, seq, kvh, chunk, chunks_of_pages(n_pages, a.pages_per_chunk, a.n_big, a.pages_small), wave * 64 + lane_id(), [&](int h, int quad, float& M, float& l) {
+  finish_chunk<NH>(a, seq, kvh, chunk, n_chunks, row0, stride, wave * 64 + lane_id(), [&](int h, int quad, float& M, float& l) {
     M = fmaxf(fmaxf(sh.red_ml[0][h][0], sh.red_ml[1][h][0]), fmaxf(sh.red_ml[2][h][0], sh.red_ml[3][h][0]));
     f32x4 o = *reinterpret_cast<const f32x4*>(&sh.red[0][h][quad * 4]) + *reinterpret_cast<const f32x4*>(&sh.red[1][h][quad * 4]);
     l = 0.f;

@@ -1,17 +1,25 @@
 // How an attention launch is shared out among its work-groups, and how the pieces of one
 // (sequence, KV head) are put together again inside the kernel.
 //
-// One work-group per (KV head, sequence, chunk of pages), chunk-major: the KV heads of one page are
-// neighbours in memory and run together, every sequence's first chunks run first, and the
-// work-groups of chunks that only longer sequences have (empty ones for the others) come last.
-// More work-groups than are resident at once: the hardware hands them out as others finish, which
-// evens out the compute units' different speeds.  (A line of equal shares, one per resident
-// work-group, with the units end to end measured 236 against 206 us for 16 x 32K tokens at 4 query
-// heads per KV head: its work-groups stream from 512 places at once.)
+// A work-group takes a chunk of one (sequence, KV head)'s pages.  Work-groups are in chunk-major
+// order: the KV heads of one page are neighbours in memory and run together, every sequence's first
+// chunks run first, and chunks that only longer sequences have come last.  There are about as many as
+// are resident at once, or more: the hardware hands them out as others finish, which evens out the
+// compute units' different speeds.  (A line of equal shares, one per resident work-group, with the
+// units end to end measured 236 against 206 us for 16 x 32K tokens at 4 query heads per KV head: its
+// work-groups stream from 512 places at once.)
+//
+// Lengths are known on the device only.  Large launches cut the chunks there, by the pages that really
+// exist (struct BalancedPlan): the caller's max_seq_len may be far above, and one sequence may be far
+// longer than the others.  The grid has a place for every chunk that the cut can make and each
+// work-group finds its own; what is left over ends at once.  The other launches are cut on the host, as
+// if every sequence had max_seq_len tokens.  8 KV heads, 4 query heads each, microseconds (host cut ->
+// device cut): 1 x 128K + 63 x 1K tokens 168 -> 111, with 4-bit values 132 -> 80; 4 x 32K + 28 x 2K
+// 133 -> 95; 16 x 2K with a max_seq_len of 32K 27.7 -> 23.9; 64 of 1K .. 16K with one of 64K 270 -> 229.
 //
 // A unit -- one (sequence, KV head) -- that is one chunk long is finished there.  Otherwise every
 // chunk leaves its softmax partial (running maximum, denominator, un-normalised output) in the
-// workspace, and either pq_decode_merge_kernel follows, or the chunks register at the unit's arrival
+// workspace, and either pq_decode_merge_kernel follows (launches cut on the host), or the chunks register at the unit's arrival
 // word and whoever registers last combines them, in chunk order (so the result does not depend
 // on who that was), and writes the output row.  Nobody waits for anybody.
 //
@@ -27,6 +35,45 @@ namespace pq {
 // Most chunks of a unit that are combined in the kernel: arrivals at one word are taken one after
 // the other by the memory system, and whoever combines n partials waits for their loads.
 constexpr int kMergeFan = 16;
+constexpr int kBalancedFan = 32;              // (launches cut on the device have no other way)
+constexpr int kBalancedSeqs = 512;            // most sequences of theirs
+constexpr int kComputeUnits = 256;            // MI355X
+constexpr int kResidentGroups = 2 * kComputeUnits;   // work-groups of the attention kernel
+
+// Lengths of chunks, in pages: the first n_big chunks of a sequence are `big` long, the others `small`.
+// Starting and ending a chunk costs about as much as streaming 8 pages: chunks are as long as they
+// can be without leaving compute units idle at the end.  `share` is a resident work-group's part of
+// the launch's pages, `longest` the longest sequence.  Measured (pages per chunk: microseconds;
+// "48 + 16": 48, the last quarter in chunks of 16):
+//   up to 16 pages a share   248 units x 2 .. 24 pages   8: 51, 16: 44, 24: 47;  8 x 1024  8: 64, 16: 61, 24: 68
+//   fp16 values              256 x 64      24: 110, 32: 110, 44: 107.5, 64: 110;  128 x 256  32: 210, 44: 212, 64: 208
+//                            512 x 8 .. 128  24: 240, 44: 238, 64: 239, 64 + 24: 233
+//   quantized values         256 x 4 .. 64   16: 54, 24: 43.4, 24 + 8: 44, 32: 55;  128 x 256  32: 131, 64: 126, 48 + 16: 125
+// (With fp16 values a work-group that is left alone streams faster; with quantized ones it does not.)
+struct ChunkLengths {
+  int big, small, n_big;
+};
+constexpr int kWaveRound = 4;                 // pages: one for each wavefront of a work-group
+__host__ __device__ inline int whole_rounds(int pages) { return (pages + kWaveRound - 1) / kWaveRound * kWaveRound; }
+__host__ __device__ inline ChunkLengths chunk_lengths(int share, int longest, bool fp16_values) {
+  ChunkLengths c;
+  c.n_big = longest;                                       // more than there are
+  if (longest < 2 * kWaveRound) {
+    c.big = c.small = longest > 1 ? longest : 1;           // less than two pages a wavefront: one chunk, nothing to merge
+  } else if (share <= 16) {
+    c.big = c.small = share <= 4 ? 4 : (share <= 8 ? 8 : 16);
+  } else if (fp16_values && share <= 64) {
+    const int p = whole_rounds(share * 4 / 3);
+    c.big = c.small = p < 64 ? p : 64;
+  } else {
+    const int b = share < 96 ? whole_rounds(share * 3 / 4) : 64, s = share < 96 ? whole_rounds(share / 4) : 24;
+    c.big = b < 64 ? b : 64;
+    c.small = s < 8 ? 8 : (s > 24 ? 24 : s);
+    const int n = longest * 4 / 5 / c.big;
+    c.n_big = n > 1 ? n : 1;
+  }
+  return c;
+}
 
 namespace {
 
@@ -38,6 +85,156 @@ __device__ __forceinline__ int clamped_len(const DecodeArgs& a, int s) {
   return min(a.seq_lens[s], a.max_seq_len);
 }
 __device__ __forceinline__ int pages_of_len(int L) { return L > 0 ? (L + kGroup - 1) / kGroup : 0; }
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_of_u32(uint32_t x) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, 0xf, 0xf, true));
+}
+// Maximum / sum over the wavefront, as a scalar.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+  x = max(x, dpp_of_u32<0xB1>(x));
+  x = max(x, dpp_of_u32<0x4E>(x));
+  x = max(x, dpp_of_u32<0x141>(x));
+  x = max(x, dpp_of_u32<0x140>(x));
+  auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = max(r[0], r[1]);
+  auto s = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return static_cast<uint32_t>(uni(static_cast<int>(max(s[0], s[1]))));
+}
+__device__ __forceinline__ int wave_sum(int v) {
+  uint32_t x = static_cast<uint32_t>(v);
+  x += dpp_of_u32<0xB1>(x);
+  x += dpp_of_u32<0x4E>(x);
+  x += dpp_of_u32<0x141>(x);
+  x += dpp_of_u32<0x140>(x);
+  auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = r[0] + r[1];
+  auto s = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return uni(static_cast<int>(s[0] + s[1]));
+}
+
+// The cut of a launch into chunks, made alike by every wavefront of it.  Slot u of a KV head: chunk 0
+// of sequence u for the first n_seqs, then the second chunks of the sequences that have one, and so on.
+// Sequences 0 .. 63 sit in a register, the others in LDS.
+struct BalancedPlan {
+  int pages0, n0;                              // sequence `lane`: pages; chunks (0 past the last sequence, 1 if it is empty)
+  const int32_t* others;                       // LDS: pages of sequences 64 ..
+  int n_seqs, lane;
+  ChunkLengths len;
+  float per_big, per_small;
+
+  __device__ __forceinline__ void load(const DecodeArgs& a, int lane_) {
+    lane = lane_;
+    n_seqs = a.n_seqs;
+    pages0 = a.seq_lens[min(lane, n_seqs - 1)];                        // the length; waited for in cut()
+  }
+  // Sequences 64 .. into LDS (kBalancedSeqs words), by the whole work-group; holds a barrier if there are any.
+  __device__ __forceinline__ void store_others(const DecodeArgs& a, int32_t* lds, int tid) {
+    others = lds;
+    if (n_seqs > 64) {
+#pragma unroll 1
+      for (int s = tid; s < n_seqs; s += 256) lds[s] = pages_of_len(clamped_len(a, s));
+      __syncthreads();
+    }
+  }
+  // f(first sequence of the block, pages of this lane's, chunks of this lane's)
+  template <typename F>
+  __device__ __forceinline__ void for_blocks(F f) const {
+    f(0, pages0, n0);
+#pragma unroll 1
+    for (int s0 = 64; s0 < n_seqs; s0 += 64) {
+      const int p = s0 + lane < n_seqs ? others[s0 + lane] : 0;
+      f(s0, p, chunks_of(s0 + lane, p));
+    }
+  }
+  // ceil(x / d) for 0 <= x <= 2^24 (every page count), by the reciprocal of d; d >= 4, or x < 8
+  static __device__ __forceinline__ int div_up(int x, int d, float inverse) {
+    const int q = static_cast<int>(static_cast<float>(x) * inverse);   // off by one at most
+    const int rest = x - q * d;
+    return q + (rest > 0 ? 1 : 0) + (rest > d ? 1 : 0) - (rest <= -d ? 1 : 0);
+  }
+  // as chunks_of_pages()
+  __device__ __forceinline__ int chunks_of(int seq, int p) const {
+    const int rest = max(0, p - len.n_big * len.big);
+    const int n = min(div_up(p, len.big, per_big), len.n_big) + div_up(rest, len.small, per_small);
+    return seq < n_seqs ? max(1, n) : 0;
+  }
+  __device__ __forceinline__ int count() {
+    per_big = __builtin_amdgcn_rcpf(static_cast<float>(len.big));
+    per_small = __builtin_amdgcn_rcpf(static_cast<float>(len.small));
+    n0 = chunks_of(lane, pages0);
+    int sum = 0;
+    for_blocks([&](int, int, int n) { sum += n; });
+    return wave_sum(sum);
+  }
+  // after load() and store_others(); returns the chunks per KV head
+  __device__ __forceinline__ int cut(const DecodeArgs& a, bool fp16_values) {
+    pages0 = lane < n_seqs ? pages_of_len(min(pages0, a.max_seq_len)) : 0;
+    int sum = pages0, most = pages0;
+#pragma unroll 1
+    for (int s = 64 + lane; s < n_seqs; s += 64) {
+      sum += others[s];
+      most = max(most, others[s]);
+    }
+    const int total = wave_sum(sum), longest = static_cast<int>(wave_max_u32(static_cast<uint32_t>(most)));
+    // Lengths spread over a range (or all alike): as if all were the longest, which is what the rule was
+    // measured with.  A few far above the rest: by the pages there are.
+    const int even = n_seqs * longest;
+    const int pages_per_head = even <= total * 5 / 2 ? even : total;
+    len = chunk_lengths((pages_per_head * a.n_kv_heads + kResidentGroups - 1) / kResidentGroups, longest, fp16_values);
+    int chunks = count();
+    if (chunks > n_seqs + a.spare_chunks || uni(chunks_of(0, longest)) > kBalancedFan) {
+      // equal chunks, as short as there is room for: sum of ceil(p / c) <= n_seqs + total / c
+      len.big = len.small = whole_rounds(max((total + a.spare_chunks - 1) / a.spare_chunks, (longest + kBalancedFan - 1) / kBalancedFan));
+      len.n_big = longest;
+      chunks = count();
+    }
+    return chunks;
+  }
+  // sequence and chunk of slot u >= n_seqs, u < chunks
+  __device__ __forceinline__ void locate(int u, int& seq, int& chunk) const {
+    // most chunk numbers c below which at most u slots lie: sum of min(n, c) over the sequences
+    int lo = 1, before = n_seqs, hi = kBalancedFan;
+#pragma unroll 1
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) / 2;
+      int sum = 0;
+      for_blocks([&](int, int, int n) { sum += min(n, mid); });
+      sum = wave_sum(sum);
+      if (sum <= u) {
+        lo = mid;
+        before = sum;
+      } else {
+        hi = mid;
+      }
+    }
+    chunk = lo;
+    seq = 0;
+    int rank = u - before;
+    for_blocks([&](int s0, int, int n) {
+      const uint64_t have = __builtin_amdgcn_ballot_w64(n > lo);
+      const int of_block = __builtin_popcountll(have);
+      if (rank >= 0 && rank < of_block) {
+        const int below = static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(have >> 32),
+                                                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(have), 0)));
+        seq = s0 + __builtin_ctzll(__builtin_amdgcn_ballot_w64(n > lo && below == rank));
+      }
+      rank -= of_block;
+    });
+  }
+  // pages and chunks of a sequence, and the chunks of those before it
+  __device__ __forceinline__ void sequence(int seq, int& n_pages, int& n_chunks, int& chunks_before) const {
+    int sum = 0;
+    for_blocks([&](int s0, int p, int n) {
+      sum += s0 + lane < seq ? n : 0;
+      if (seq >= s0 && seq < s0 + 64) {
+        n_pages = __builtin_amdgcn_readlane(p, seq - s0);
+        n_chunks = __builtin_amdgcn_readlane(n, seq - s0);
+      }
+    });
+    chunks_before = wave_sum(sum);
+  }
+};
 
 // All memory operations this wavefront has issued are complete (for device-coherent stores:
 // performed at memory, where every other work-group's device-coherent loads will find them).
@@ -84,9 +281,10 @@ constexpr int kFinishLdsFloats = kFinishThreads * 5;
 // (cache policy sc1: performed past the L2s) and ordered by waiting for the stores before the
 // arrival is registered -- not by fences, which write back and invalidate whole caches (measured:
 // with fences in every work-group the launch takes twice as long).
+// The unit's partials: head h (from a.head0 on), chunk c in row row0 + h * stride + c.
 template <int NH, typename Partial>
-__device__ __forceinline__ void finish_chunk(const DecodeArgs& a, int seq, int kvh, int chunk, int n_chunks_seq, int tid,
-                                             Partial partial, float* lent, int* stage) {
+__device__ __forceinline__ void finish_chunk(const DecodeArgs& a, int seq, int kvh, int chunk, int n_chunks_seq, int64_t row0,
+                                             int stride, int tid, Partial partial, float* lent, int* stage) {
   const int h = tid >> 5, quad = tid & 31;             // 256 threads: 8 heads x 32 quads
   const bool mine = h < a.n_heads;
   const int64_t head_row = static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0;
@@ -101,13 +299,11 @@ __device__ __forceinline__ void finish_chunk(const DecodeArgs& a, int seq, int k
     }
     return;
   }
-  // partial of (head h, chunk c) of the unit: row h * n_chunks + c from the unit's first on
-  const int64_t row0 = head_row * a.n_chunks;
-  const uint32_t rows = static_cast<uint32_t>(a.n_heads * a.n_chunks);
+  const uint32_t rows = static_cast<uint32_t>(a.n_heads * stride);
   const __amdgpu_buffer_rsrc_t r_acc = make_rsrc(a.ws_acc + row0 * kHeadDim, rows * (kHeadDim * 4));
   const __amdgpu_buffer_rsrc_t r_ml = make_rsrc(a.ws_ml + row0 * 2, rows * 8);
   if (mine) {
-    const uint32_t row = static_cast<uint32_t>(h * a.n_chunks + chunk);
+    const uint32_t row = static_cast<uint32_t>(h * stride + chunk);
     __builtin_amdgcn_raw_buffer_store_b128(u32x4{f2u(o.x), f2u(o.y), f2u(o.z), f2u(o.w)}, r_acc, row * (kHeadDim * 4) + quad * 16, 0, kAuxDevice);
     if (quad == 0) __builtin_amdgcn_raw_buffer_store_b64(u32x2{f2u(M), f2u(l)}, r_ml, row * 8, 0, kAuxDevice);
   }
@@ -136,7 +332,7 @@ __device__ __forceinline__ void finish_chunk(const DecodeArgs& a, int seq, int k
     u32x4 v[kAtOnce];
 #pragma unroll
     for (int i = 0; i < kAtOnce; ++i) {
-      const uint32_t row = static_cast<uint32_t>(ch * a.n_chunks + min(k0 + i * kSlices, count - 1));
+      const uint32_t row = static_cast<uint32_t>(ch * stride + min(k0 + i * kSlices, count - 1));
       ml[i] = __builtin_amdgcn_raw_buffer_load_b64(r_ml, row * 8, 0, kAuxDevice);
       v[i] = __builtin_amdgcn_raw_buffer_load_b128(r_acc, row * (kHeadDim * 4) + quad * 16, 0, kAuxDevice);
     }

@@ -40,6 +40,10 @@ class Packed:
         at = 0
         for s, (k, v) in enumerate(zip(keys, values)):
             n, L = counts[s], k.shape[0]
+            if L == 0:
+                self.k64.append(torch.zeros((0, heads, D), dtype=torch.float64))
+                self.v64.append(torch.zeros((0, heads, D), dtype=torch.float64))
+                continue
             ids = np.arange(at, at + n, dtype=np.int32)
             self.table[s, :n] = ids
             at += n
@@ -76,10 +80,12 @@ class Packed:
         pq, (seqs, heads) = self.pq, self.q.shape[:2]
         out = torch.full((seqs, heads, D), float("nan"), device=DEV)
         size = pq.pq_decode_workspace_bytes(self.layout, seqs, heads, self.max_seq_len)
-        workspace = torch.full((size,), 0x5A, dtype=torch.uint8, device=DEV)
+        guarded = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device=DEV)
+        workspace = guarded[:size]
         pq.pq_decode_attention(self.layout, self.q, self.codes, self.params, self.v_pool, self.block_table, self.seq_lens,
                                self.max_seq_len, self.sm_scale, out, workspace, scores, self.residual, self.v_bits, self.v_params)
         torch.cuda.synchronize()
+        assert bool((guarded[size:] == 0x5A).all()), "written past the workspace"
         return out
 
     def scores(self):
