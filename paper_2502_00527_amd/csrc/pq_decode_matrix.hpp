@@ -361,11 +361,12 @@ struct ScoreWalk {
   // that four accumulators serve a chain; without restarts simply step by step.
   static constexpr int kOps = kChain == 16 ? 1 : kChain;   // query operands kept
   uint32_t q_op[kOps][2];
-  uint32_t lane_lut, q_addr, par_put, par_get, voff_codes, low_mask, down_addr;
+  uint32_t lane_lut, q_addr, par_put, par_get, voff_codes, low_mask, down_addr, table;
 
   __device__ __forceinline__ void init(const uint8_t* lut, const QueryShared& q, const float* pair_down, const uint32_t* params, int lane) {
     const int row = lane >> 4, col = lane & 15;
-    lane_lut = lds_addr(lut) + col * 16;
+    table = lds_addr(lut);
+    lane_lut = W == 8 ? col * 16 : table + col * 16;
     q_addr = lds_addr(q.pairs) + row * kQueryBlock + col * 8;
     down_addr = lds_addr(pair_down);
     par_put = lds_addr(params) + lane * 4;
@@ -382,8 +383,8 @@ struct ScoreWalk {
   __device__ __forceinline__ f32x4 lookup(const Unit<W / 2>& u) const {
     uint32_t addr;
     if constexpr (W == 8) {
-      // byte 0 from the lane's column, byte 1 from the symbol; the table starts at LDS address 0
-      addr = __builtin_amdgcn_perm(u.d[KK >> 2], lane_lut, 0x0c0c0000u | ((4u + (KK & 3)) << 8));
+      // byte 0 from the lane's column, byte 1 from the symbol; where the table starts is the read's offset
+      addr = __builtin_amdgcn_perm(u.d[KK >> 2], lane_lut, 0x0c0c0000u | ((4u + (KK & 3)) << 8)) + table;
     } else {
       constexpr int bit = KK * W, wi = bit >> 5, sh = bit & 31;
       uint32_t src = u.d[wi];
