@@ -24,7 +24,8 @@ bool layout_supported(const pq_layout* l) {
   return w == 6 || w == 8;
 }
 
-// One work-group per (sequence, KV head, chunk).  Chunks are whole pages, a
+// Chunks of the grouped quantizer's attention kernel, and the size of the workspace for all: one
+// work-group per (sequence, KV head, chunk).  Chunks are whole pages, a
 // multiple of the 4 wavefronts of a work-group; they shrink from 32 pages
 // until the launch has at least the 512 work-groups that are resident at
 // once (2 per compute unit).  Long chunks amortise the table build and keep
@@ -33,14 +34,8 @@ bool layout_supported(const pq_layout* l) {
 ChunkPlan plan_chunks(int32_t n_seqs, int32_t n_kv_heads, int32_t max_seq_len) {
   const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
   const int64_t units = static_cast<int64_t>(n_seqs) * n_kv_heads;
-#ifndef PQ_WANT_GROUPS
-#define PQ_WANT_GROUPS 512
-#endif
-  constexpr int64_t kWantGroups = PQ_WANT_GROUPS;
-#ifndef PQ_MAX_PPC
-#define PQ_MAX_PPC 32
-#endif
-  int32_t ppc = PQ_MAX_PPC;
+  constexpr int64_t kWantGroups = 512;
+  int32_t ppc = 32;
   while (ppc > 4 && units * ((max_pages + ppc - 1) / ppc) < kWantGroups) ppc >>= 1;
   ChunkPlan p;
   p.pages_per_chunk = ppc;

@@ -83,36 +83,37 @@ __global__ __launch_bounds__(kMergeThreads) void pq_decode_merge_kernel(
 
 // Score-only kernels: the kernel whose lanes are tokens on the uniform grid; the grouped quantizer has
 // one of its own (a table per page).
-template <int G, int RB, int TB, bool GA>
+template <int G, int RB, int TB, bool kGrouped>
 void launch_scores_one(const DecodeArgs& a, dim3 grid, hipStream_t st) {
-  if constexpr (GA) hipLaunchKernelGGL((pq_score_keys_kernel<G, RB, TB, true>), grid, dim3(kThreads), 0, st, a);
+  if constexpr (kGrouped) hipLaunchKernelGGL((pq_score_keys_kernel<G, RB, TB>), grid, dim3(kThreads), 0, st, a);
   else hipLaunchKernelGGL((pq_score_tokens_kernel<G, RB, TB>), grid, dim3(kThreads), 0, st, a);
 }
-template <int RB, int TB, bool GA>
+template <int RB, int TB, bool kGrouped>
 bool launch_scores_g(int G, const DecodeArgs& a, dim3 grid, hipStream_t st) {
   switch (G) {
-    case 1: launch_scores_one<1, RB, TB, GA>(a, grid, st); return true;
-    case 2: launch_scores_one<2, RB, TB, GA>(a, grid, st); return true;
-    case 4: launch_scores_one<4, RB, TB, GA>(a, grid, st); return true;
+    case 1: launch_scores_one<1, RB, TB, kGrouped>(a, grid, st); return true;
+    case 2: launch_scores_one<2, RB, TB, kGrouped>(a, grid, st); return true;
+    case 4: launch_scores_one<4, RB, TB, kGrouped>(a, grid, st); return true;
     default: return false;
   }
 }
-template <bool GA>
+template <bool kGrouped>
 bool launch_scores_rt(int rt, int G, const DecodeArgs& a, dim3 grid, hipStream_t st) {
   switch (rt) {
-    case 44: return launch_scores_g<4, 4, GA>(G, a, grid, st);
-    case 33: return launch_scores_g<3, 3, GA>(G, a, grid, st);
-    case 53: return launch_scores_g<5, 3, GA>(G, a, grid, st);
-    case 35: return launch_scores_g<3, 5, GA>(G, a, grid, st);
-    case 42: return launch_scores_g<4, 2, GA>(G, a, grid, st);
-    case 24: return launch_scores_g<2, 4, GA>(G, a, grid, st);
+    case 44: return launch_scores_g<4, 4, kGrouped>(G, a, grid, st);
+    case 33: return launch_scores_g<3, 3, kGrouped>(G, a, grid, st);
+    case 53: return launch_scores_g<5, 3, kGrouped>(G, a, grid, st);
+    case 35: return launch_scores_g<3, 5, kGrouped>(G, a, grid, st);
+    case 42: return launch_scores_g<4, 2, kGrouped>(G, a, grid, st);
+    case 24: return launch_scores_g<2, 4, kGrouped>(G, a, grid, st);
     default: return false;
   }
 }
 
-// The name an attention launch of the uniform angle grid runs under: "roles" from 256 work-groups
-// on, "partials" below (and with quantized values at more than two query heads per KV head, and with
-// the grouped quantizer, which has a kernel of its own).
+// The name an attention launch runs under, a label of its size in profiles: "roles" for the uniform angle
+// grid with pages for at least 256 work-groups, "partials" below (and with quantized values at more than
+// two query heads per KV head, and with the grouped quantizer, which has a kernel of its own).  On the
+// uniform grid both are the same kernel; pq_decode_kernel_name() has always told them apart.
 enum class AttentionKernel { kPartials, kRoles };
 
 // Work-groups of four pages each that the shape could have, as far as 768 (the workspace's size is
@@ -160,7 +161,8 @@ int key_table_index(const pq_layout* l) {
 
 // The caller's workspace: the chunks' partials and the units' arrival words.  Its size is that of
 // the chunk plan of plan_chunks() or of one partial for each of four_page_groups() + units, whichever
-// is larger; plan_uniform() keeps within it.
+// is larger; plan_uniform() and spare_chunks() keep within it.  (Of the words only `units` are used.
+// The size is what callers have been told, and the limit of the static scratch follows from it.)
 struct Workspace {
   float* acc;
   float* ml;
@@ -264,7 +266,7 @@ int check_decode_shape(const pq_layout* l, int32_t n_seqs, int32_t n_q_heads, in
   if (l->n_kv_heads <= 0 || n_q_heads % l->n_kv_heads != 0) return PQ_ERR_INVALID_ARG;
   if (!layout_supported(l)) return PQ_ERR_UNSUPPORTED;
   const int G = n_q_heads / l->n_kv_heads;
-  if (G > 16) return PQ_ERR_UNSUPPORTED;   // groups are processed 4, 2 or 1 query heads per pass
+  if (G > 16) return PQ_ERR_UNSUPPORTED;
   if (n_seqs > 65535 || n_q_heads > 65535) return PQ_ERR_UNSUPPORTED;   // grid.y, merge grid.x
   if (plan_chunks(n_seqs, l->n_kv_heads, max_seq_len).n_chunks > 65535) return PQ_ERR_UNSUPPORTED;   // grid.z
   return PQ_OK;

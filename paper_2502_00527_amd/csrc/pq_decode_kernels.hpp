@@ -29,9 +29,10 @@
 // In pq_decode_partials_kernel a last step folds the four wavefronts' (m, l, acc) into one
 // partial per (sequence, query head, chunk); pq_decode_merge_kernel combines the chunks.
 // (The score-only kernel of the uniform grid maps lanes to tokens instead: see PageWalk.)
-// No MFMA: the hot loop is a gather-accumulate.
+// No MFMA in these kernels: the hot loop is a gather-accumulate (the uniform grid's attention has one
+// on the matrix cores, pq_decode_matrix.hpp).
 //
-// Grouped angle quantizer (Section 3.2 as printed; template flag GA): the angle levels of a
+// Grouped angle quantizer (Section 3.2 as printed), which all but pq_score_tokens_kernel here serve: the angle levels of a
 // group are theta~_a = (a + 1/2) s_t + z_t with the group's own (s_t, z_t), so every wavefront
 // keeps a table of its own in LDS and rebuilds it from the page's angle parameters before it
 // scores the page (the appendix listing builds the same table from "tscale" and "tmn").
@@ -660,9 +661,8 @@ __device__ __forceinline__ BlockParams load_block_params(const uint32_t* page_pa
 // kernel's register budget the compiler otherwise issues one read, waits for it, and so on.  As
 // a block's last step goes by, its parameters are replaced by the next page's; as a unit's last
 // read is issued, the unit is replaced by the next page's.
-// The sum over the 64 pairs is associated exactly as in the attention kernels, where the four
-// 16-lane rows each sum one block and fold_rows adds (block 0 + block 2) + (block 1 + block 3):
-// a score from here equals, bit for bit, the one the attention kernels compute.
+// The sum over the 64 pairs is associated as in the lane layout of the other score kernel here, where the
+// four 16-lane rows each sum one block and fold_rows adds (block 0 + block 2) + (block 1 + block 3).
 template <int G, int RB, int TB, int kScorePipe = 4>
 struct PageWalk {
   static constexpr int W = RB + TB;
@@ -737,21 +737,20 @@ struct PageWalk {
   }
 };
 
-template <int G, int RB, int TB, int VB, bool GA>
+template <int G, int RB, int TB, int VB>
 __global__ PQ_KERNEL_ATTR void pq_decode_partials_kernel(const DecodeArgs a) {
   constexpr int W = RB + TB;
   constexpr int UB = 2 * W;              // bytes per unit
   constexpr int NA = 1 << TB;            // angle states
   constexpr int ROW = NA * 16;           // table bytes per pair
 
-  // one table per work-group, or (GA) one per wavefront; with GA the wavefront's table space is
-  // reused for its accumulators in the final fold, which keeps two work-groups per compute unit
+  // one table per wavefront, whose space is reused for its accumulators in the final fold: two
+  // work-groups fit on a compute unit that way
   constexpr int kLutBytes = kPairs * ROW;
-  __shared__ __attribute__((aligned(16))) uint8_t lut[(GA ? kWaves : 1) * kLutBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t lut[kWaves * kLutBytes];
   __shared__ __attribute__((aligned(16))) float prob[kWaves][kGroup * G];
   __shared__ __attribute__((aligned(16))) float alpha_s[kWaves][4];
-  __shared__ __attribute__((aligned(16))) float red_own[GA ? 4 : kWaves * G * kHeadDim];
-  static_assert(!GA || kLutBytes >= G * kHeadDim * 4, "table space too small for the accumulators");
+  static_assert(kLutBytes >= G * kHeadDim * 4, "table space too small for the accumulators");
   __shared__ float red_ml[kWaves][G][3];                              // m, l, sum of p * zero-point
   __shared__ __attribute__((aligned(16))) float q_lds[kHeadDim][4];   // q[dim][head]: table build, residual keys
   __shared__ float2 trig[kMaxAngleBins];                              // (cos, sin) of the uniform grid's bin centres
@@ -786,10 +785,10 @@ __global__ PQ_KERNEL_ATTR void pq_decode_partials_kernel(const DecodeArgs a) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[h][e] = 0.f;
 
-  const uint32_t lut_w = lds_addr(lut) + (GA ? wave * kLutBytes : 0);
+  const uint32_t lut_w = lds_addr(lut) + wave * kLutBytes;
   const uint32_t lut_row0 = lut_w + row * (kPairsPerUnit * ROW);
   auto red_acc = [&](int w) -> float* {   // [G][kHeadDim] accumulators of wavefront w in the final fold
-    return GA ? reinterpret_cast<float*>(lut + w * kLutBytes) : red_own + w * (G * kHeadDim);
+    return reinterpret_cast<float*>(lut + w * kLutBytes);
   };
   const uint32_t pw_addr = lds_addr(prob[wave]);
   const uint32_t voff_codes = (row * kGroup + col) * UB;          // unit of (block row, token col) of pass 0
@@ -810,7 +809,7 @@ __global__ PQ_KERNEL_ATTR void pq_decode_partials_kernel(const DecodeArgs a) {
   // Buffer descriptors of the wavefront's k-th page; a masked page gets empty descriptors
   // (every read returns zero) and zero valid tokens.
   constexpr bool kQuantV = VB != 16;
-  constexpr int kParamSets = GA ? 2 : 1;   // radius parameters (+ angle parameters) per pair
+  constexpr int kParamSets = 2;            // radius parameters, angle parameters per pair
   constexpr int kVLoads = kQuantV ? kGroup * kHeadDim * VB / 8 / 1024 : 32;   // 1 KB wave-loads per page
   constexpr int kTokPerLoad = kGroup / kVLoads;                              // 16 (4 bit), 32 (2 bit)
   // The 32 one-KB value loads of a page are issued in an order rotated by a page-dependent
@@ -854,7 +853,7 @@ __global__ PQ_KERNEL_ATTR void pq_decode_partials_kernel(const DecodeArgs a) {
   __amdgpu_buffer_rsrc_t rc_nxt = rs_empty, rp_nxt = rs_empty, rv_nxt = rs_empty, rvp_nxt = rs_empty;
   int nv_cur = 0, nv_nxt = 0, rot_cur = 0, rot_nxt = 0;
   uint4 praw[4];
-  uint32_t tpar = 0;                                               // GA: angle parameters of pair `lane`
+  uint32_t tpar = 0;                                               // angle parameters of pair `lane`
   Unit<W / 2> cu[8];
   constexpr int kRingSets = PQ_RING_SETS;                          // register quads of 4 value rows in flight
   uint4 ring[kRingSets][4];                                        // fp16 values
@@ -869,7 +868,7 @@ __global__ PQ_KERNEL_ATTR void pq_decode_partials_kernel(const DecodeArgs a) {
     page_setup(0, rc_cur, rp_cur, rv_cur, rvp_cur, nv_cur, rot_cur);
 #pragma unroll
     for (int i = 0; i < 4; ++i) praw[i] = buf_load16<kAuxCached>(rp_cur, voff_params, i * 16);
-    if constexpr (GA) tpar = buf_load4<kAuxCached>(rp_cur, lane * 4, kPairs * 4);
+    tpar = buf_load4<kAuxCached>(rp_cur, lane * 4, kPairs * 4);
 #pragma unroll
     for (int i = 0; i < 8; ++i) cu[i] = load_unit<W>(rc_cur, voff_codes, i * 16 * UB);
     if constexpr (kQuantV) {
@@ -890,10 +889,6 @@ __global__ PQ_KERNEL_ATTR void pq_decode_partials_kernel(const DecodeArgs a) {
   // (built while the first page's loads, issued above, are in flight)
   {
     load_query_lds<G>(q_lds, trig, a, (static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0) * kHeadDim, tid);
-    if constexpr (!GA) {
-      __syncthreads();
-      build_uniform_table<TB>(lut, q_lds, trig, tid, kThreads);
-    }
   }
   __syncthreads();
 
@@ -929,11 +924,9 @@ __global__ PQ_KERNEL_ATTR void pq_decode_partials_kernel(const DecodeArgs a) {
       rot_nxt = 0;
     }
 
-    if constexpr (GA) {
-      // this page's table (the previous page's was released by the barrier that ended its value phase)
-      build_group_table<TB>(lut_w, tpar, lds_addr(q_lds), lane);
-      wave_lds_sync();
-    }
+    // this page's table (the previous page's was released by the barrier that ended its value phase)
+    build_group_table<TB>(lut_w, tpar, lds_addr(q_lds), lane);
+    wave_lds_sync();
 
     // radius parameters of this lane's 16 pairs: rho~ = c * s + (z + s/2)
     float sf[16], zz[16];
@@ -1000,7 +993,7 @@ __global__ PQ_KERNEL_ATTR void pq_decode_partials_kernel(const DecodeArgs a) {
     // ---- next page's parameters and codes, into the registers the score phase released ----
 #pragma unroll
     for (int v4 = 0; v4 < 4; ++v4) praw[v4] = buf_load16<kAuxCached>(rp_nxt, voff_params, v4 * 16);
-    if constexpr (GA) tpar = buf_load4<kAuxCached>(rp_nxt, lane * 4, kPairs * 4);
+    tpar = buf_load4<kAuxCached>(rp_nxt, lane * 4, kPairs * 4);
 #pragma unroll
     for (int s = 0; s < 8; ++s) cu[s] = load_unit<W>(rc_nxt, voff_codes, s * 16 * UB);
     if constexpr (kQuantV) {
@@ -1098,17 +1091,16 @@ __global__ PQ_KERNEL_ATTR void pq_decode_partials_kernel(const DecodeArgs a) {
 // ---- query-key scores only, grouped angle quantizer --------------------------------------
 // Same tables, same page walk and same pair steps as the attention kernel, without softmax and
 // values: every wavefront scores its pages and stores the raw q . k~ of valid tokens.  (The
-// uniform grid is served by pq_score_tokens_kernel below; GA = false is not instantiated.)
-template <int G, int RB, int TB, bool GA>
+// uniform grid is served by pq_score_tokens_kernel below.)
+template <int G, int RB, int TB>
 __global__ __launch_bounds__(kThreads) void pq_score_keys_kernel(const DecodeArgs a) {
-  static_assert(GA, "the uniform grid is served by pq_score_tokens_kernel");
   constexpr int W = RB + TB;
   constexpr int UB = 2 * W;
   constexpr int NA = 1 << TB;
   constexpr int ROW = NA * 16;
   constexpr int kLutBytes = kPairs * ROW;
-  constexpr int kParamSets = GA ? 2 : 1;
-  __shared__ __attribute__((aligned(16))) uint8_t lut[(GA ? kWaves : 1) * kLutBytes];   // GA: one table per wavefront
+  constexpr int kParamSets = 2;
+  __shared__ __attribute__((aligned(16))) uint8_t lut[kWaves * kLutBytes];              // one table per wavefront
   __shared__ __attribute__((aligned(16))) float q_lds[kHeadDim][4];   // q[dim][head]: table builds, residual keys
   __shared__ float2 trig[kMaxAngleBins];                              // (cos, sin) of the uniform grid's bin centres
 
@@ -1125,7 +1117,7 @@ __global__ __launch_bounds__(kThreads) void pq_score_keys_kernel(const DecodeArg
   const int row = lane >> 4, col = lane & 15;
   const int my_head = (G == 4) ? row : (G == 2 ? (row >> 1) : 0);
   const bool owner = (G == 4) || (G == 2 && (row & 1) == 0) || (G == 1 && row == 0);
-  const uint32_t lut_w = lds_addr(lut) + (GA ? wave * kLutBytes : 0);
+  const uint32_t lut_w = lds_addr(lut) + wave * kLutBytes;
   const uint32_t lut_row0 = lut_w + row * (kPairsPerUnit * ROW);
   const uint32_t voff_codes = (row * kGroup + col) * UB;
   const uint32_t voff_params = row * (kPairsPerUnit * 4);
@@ -1157,16 +1149,12 @@ __global__ __launch_bounds__(kThreads) void pq_score_keys_kernel(const DecodeArg
     page_setup(0, rc_cur, rp_cur, nv_cur);
 #pragma unroll
     for (int i = 0; i < 4; ++i) praw[i] = buf_load16<kAuxCached>(rp_cur, voff_params, i * 16);
-    if constexpr (GA) tpar = buf_load4<kAuxCached>(rp_cur, lane * 4, kPairs * 4);
+    tpar = buf_load4<kAuxCached>(rp_cur, lane * 4, kPairs * 4);
 #pragma unroll
     for (int i = 0; i < 8; ++i) cu[i] = load_unit<W>(rc_cur, voff_codes, i * 16 * UB);
   }
   {
     load_query_lds<G>(q_lds, trig, a, (static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0) * kHeadDim, tid);
-    if constexpr (!GA) {
-      __syncthreads();
-      build_uniform_table<TB>(lut, q_lds, trig, tid, kThreads);
-    }
   }
   __syncthreads();
 
@@ -1191,16 +1179,14 @@ __global__ __launch_bounds__(kThreads) void pq_score_keys_kernel(const DecodeArg
       rc_nxt = rp_nxt = rs_empty;
       nv_nxt = 0;
     }
-    if constexpr (GA) {
-      wave_lds_sync();                                             // the previous page's table is no longer read
-      build_group_table<TB>(lut_w, tpar, lds_addr(q_lds), lane);
-      wave_lds_sync();
-    }
+    wave_lds_sync();                                             // the previous page's table is no longer read
+    build_group_table<TB>(lut_w, tpar, lds_addr(q_lds), lane);
+    wave_lds_sync();
     float sf[16], zz[16];
     unpack_radius_params(praw, sf, zz);
 #pragma unroll
     for (int v4 = 0; v4 < 4; ++v4) praw[v4] = buf_load16<kAuxCached>(rp_nxt, voff_params, v4 * 16);
-    if constexpr (GA) tpar = buf_load4<kAuxCached>(rp_nxt, lane * 4, kPairs * 4);
+    tpar = buf_load4<kAuxCached>(rp_nxt, lane * 4, kPairs * 4);
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       float part[G];

@@ -9,9 +9,9 @@ template <int RB, int TB, int VB>
 bool launch_g(int G, const DecodeArgs& a, dim3 grid, hipStream_t st) {
   const dim3 block(kThreads);
   switch (G) {
-    case 1: hipLaunchKernelGGL((pq_decode_partials_kernel<1, RB, TB, VB, true>), grid, block, 0, st, a); return true;
-    case 2: hipLaunchKernelGGL((pq_decode_partials_kernel<2, RB, TB, VB, true>), grid, block, 0, st, a); return true;
-    case 4: hipLaunchKernelGGL((pq_decode_partials_kernel<4, RB, TB, VB, true>), grid, block, 0, st, a); return true;
+    case 1: hipLaunchKernelGGL((pq_decode_partials_kernel<1, RB, TB, VB>), grid, block, 0, st, a); return true;
+    case 2: hipLaunchKernelGGL((pq_decode_partials_kernel<2, RB, TB, VB>), grid, block, 0, st, a); return true;
+    case 4: hipLaunchKernelGGL((pq_decode_partials_kernel<4, RB, TB, VB>), grid, block, 0, st, a); return true;
     default: return false;
   }
 }
