@@ -145,12 +145,6 @@ bool launch_attention(int w, int v_bits, bool roles, const DecodeArgs& a, dim3 g
   }
 }
 
-void launch_attention_given(int v_bits, const DecodeArgs& a, dim3 grid, hipStream_t st) {
-  if (v_bits == 16) launch_attention_given_v16(a, grid, st);
-  else if (v_bits == 4) launch_attention_given_v4(a, grid, st);
-  else launch_attention_given_v2(a, grid, st);
-}
-
 // Index of a bit allocation in the key-side tables of its symbol width (pq_decode_matrix.hpp).
 int key_table_index(const pq_layout* l) {
   const int w = l->r_bits + l->t_bits;
@@ -306,8 +300,9 @@ ChunkPlan plan_score_chunks(int32_t n_seqs, int32_t n_kv_heads, int32_t max_seq_
 
 // The raw scores of a launch, pass by pass over the query heads of a KV head; `a` is complete but for
 // what depends on the pass and the chunks.  Scores come from here whoever asks for them, so that
-// they are the same bit for bit: on the uniform grid pq_decode_attention stores them from here and
-// reads them back for the softmax.
+// they are the same bit for bit: on the uniform grid the attention kernel, whose own scores are rounded
+// otherwise, does not store them (and cannot read them back: its output would depend on whether they
+// were asked for).
 int launch_scores(const pq_layout* layout, DecodeArgs a, hipStream_t stream) {
   const bool grouped = layout->angle_quantizer == PQ_ANGLE_GROUPED;
   const int rt = layout->r_bits * 10 + layout->t_bits;
@@ -429,29 +424,23 @@ int decode_launch(const pq_layout* layout, const void* q, pq_dtype q_dtype, int3
   const int group_total = n_q_heads / layout->n_kv_heads;
   a.group_total = group_total;
   const bool roles = choose_attention_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len) == AttentionKernel::kRoles;
-  const bool given = scores && !grouped;
-  // (the score-only kernel goes first: a third launch would cost more than a late combination)
-  const bool merged = out != nullptr && (merges_in_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len) || (given && plan.n_chunks <= kMergeFan));
+  const bool merged = out != nullptr && merges_in_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len);
   a.merge_in_kernel = merged ? 1 : 0;
   a.spare_chunks = out != nullptr ? spare_chunks(layout, n_seqs, max_seq_len) : 0;
   const dim3 grid = a.spare_chunks > 0 ? dim3(layout->n_kv_heads, n_seqs + a.spare_chunks) : dim3(layout->n_kv_heads, n_seqs, plan.n_chunks);
   a.table_index = key_table_index(layout);
-  if (given) {
+  if (scores && !grouped) {
     const int ss = launch_scores(layout, a, stream);
     if (ss != PQ_OK) return ss;
   }
   hipError_t e = hipSuccess;
   // A pass over the cache serves up to 8 query heads of a KV head; with the grouped quantizer 4, 2 or 1.
-  // Given scores are addressed with 32-bit byte offsets from the pass's first row.
-  const int most = given && scores_stride >= (int64_t{1} << 27) ? 1 : kMaxHeads;
   for (int head0 = 0; head0 < group_total && e == hipSuccess;) {
     const int left = group_total - head0;
-    const int G = grouped ? (left >= 4 ? 4 : (left >= 2 ? 2 : 1)) : std::min(left, most);
+    const int G = grouped ? (left >= 4 ? 4 : (left >= 2 ? 2 : 1)) : std::min(left, kMaxHeads);
     a.head0 = head0;
     a.n_heads = G;
-    bool found = true;
-    if (given) launch_attention_given(v_bits, a, grid, stream);
-    else found = grouped ? launch_attention_partials_ga(rt, G, v_bits, a, grid, stream)
+    const bool found = grouped ? launch_attention_partials_ga(rt, G, v_bits, a, grid, stream)
                        : launch_attention(layout->r_bits + layout->t_bits, v_bits, roles, a, grid, stream);
     if (!found) return PQ_ERR_UNSUPPORTED;   // not reached: layout_supported() admits what is built
     e = hipGetLastError();

@@ -10,7 +10,6 @@
 #ifndef PQ_MATRIX_VB
 #define PQ_MATRIX_VB 16
 #define PQ_MATRIX_LAUNCH launch_attention_matrix_v16
-#define PQ_GIVEN_LAUNCH launch_attention_given_v16
 #endif
 
 namespace pq {
@@ -24,15 +23,6 @@ __global__ PQ_MATRIX_ATTR void pq_decode_roles_kernel(const DecodeArgs a) { atte
 template <int W, int VB, int NH, bool Q32, bool kCut>
 __global__ PQ_MATRIX_ATTR void pq_decode_partials_kernel(const DecodeArgs a) { attention_body<W, VB, NH, Q32, kCut>(a); }
 
-// The same over scores that have been computed already: a call that asks for its raw scores gets them
-// from the score-only kernel, and the softmax reads them back.  Bound by HBM: 272 bytes a token and KV
-// head instead of the codes' 64 + 256.  Both launches, 16 x 32K tokens, 4 query heads per KV head:
-// 260 us; with the whole attention kernel behind the score-only one 287; 8 x 8K, one head per KV head
-// 123 against 145; 16 x 16K, 4-bit values 86 against 116.  The values' rows go four consecutive ones
-// to a lane row, so that a lane's four scores are one load (four loads: 8 heads 7 us slower).
-template <int VB, int NH, bool kCut>
-__global__ PQ_MATRIX_ATTR void pq_decode_given_kernel(const DecodeArgs a) { attention_body<6, VB, NH, false, kCut, true>(a); }
-
 template <int W, int VB, int NH, bool Q32, bool kCut>
 void launch_named(bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st) {
   if (roles) hipLaunchKernelGGL((pq_decode_roles_kernel<W, VB, NH, Q32, kCut>), grid, dim3(kMatThreads), 0, st, a);
@@ -41,11 +31,6 @@ void launch_named(bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st) {
 template <int W, int VB, int NH, bool Q32>
 void launch_one(bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st) {
   a.spare_chunks > 0 ? launch_named<W, VB, NH, Q32, true>(roles, a, grid, st) : launch_named<W, VB, NH, Q32, false>(roles, a, grid, st);
-}
-template <int VB, int NH>
-void launch_given(const DecodeArgs& a, dim3 grid, hipStream_t st) {
-  if (a.spare_chunks > 0) hipLaunchKernelGGL((pq_decode_given_kernel<VB, NH, true>), grid, dim3(kMatThreads), 0, st, a);
-  else hipLaunchKernelGGL((pq_decode_given_kernel<VB, NH, false>), grid, dim3(kMatThreads), 0, st, a);
 }
 template <int W, int VB>
 void launch_q(bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st) {
@@ -66,9 +51,6 @@ bool launch_w(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st)
 
 bool PQ_MATRIX_LAUNCH(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st) {
   return matrix::launch_w<PQ_MATRIX_VB>(w, roles, a, grid, st);
-}
-void PQ_GIVEN_LAUNCH(const DecodeArgs& a, dim3 grid, hipStream_t st) {
-  a.n_heads <= 4 ? matrix::launch_given<PQ_MATRIX_VB, 4>(a, grid, st) : matrix::launch_given<PQ_MATRIX_VB, 8>(a, grid, st);
 }
 
 }  // namespace pq

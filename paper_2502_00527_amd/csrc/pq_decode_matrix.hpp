@@ -20,14 +20,13 @@
 // row sums of both parts are added at the end).  fp16 value rows are transposed pairwise with
 // v_perm_b32; quantized values need no conversion at all (a masked code is an fp16 denormal).
 //
-// What bounds it.  Per page (128 tokens of one KV head) a wavefront issues about 1030 vector
-// instructions with fp16 values, 1100 with 4-bit ones -- 128 table addresses, 100 for the query side,
-// 190 for the sums, 300 for the softmax, 130 - 220 for the values -- and 160 matrix instructions (640
-// cycles per page and compute unit); one multiply-add per (head, pair, token) and (head, dim, token)
-// on the vector unit took 2200.  With fp16 values a page is 41 KB, 3600 cycles of a compute unit's
-// share of HBM: memory-bound (16 x 32K tokens, 4 query heads per KV head: 209 us, 6.5 TB/s; 216 us
-// before).  With quantized values the page is 11 - 17 KB and vector issue is the longer side
-// (4-bit values at the same shape: 147 -> 126 us).
+// What bounds it.  Per page (128 tokens of one KV head) a wavefront issues about 1090 vector
+// instructions with fp16 values and up to 4 heads, and 196 matrix instructions, 36 of them for the
+// values; one multiply-add per (head, pair, token) and (head, dim, token) on the vector unit took 2200.
+// With fp16 values a page is 41 KB, 3600 cycles of a compute unit's share of HBM: memory-bound
+// (16 x 32K tokens, 4 query heads per KV head: 209 - 210 us, 6.5 TB/s; 217 on the vector unit).  With
+// quantized values the page is 11 - 17 KB and vector issue is the longer side (4-bit values at the
+// same shape: 153 -> 127 us).
 //
 // The table is kept 16 times in LDS, copy l in the 16-byte column l of a 256-byte row, and lane l
 // reads copy l % 16: reads of 16 lanes touch every bank once whatever the symbols are.  64 KB for
@@ -43,10 +42,6 @@ namespace pq {
 bool launch_attention_matrix_v16(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st);
 bool launch_attention_matrix_v4(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st);
 bool launch_attention_matrix_v2(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st);
-// Attention over the scores in a.scores (rows less than 512 MiB apart, unless a.n_heads is 1).
-void launch_attention_given_v16(const DecodeArgs& a, dim3 grid, hipStream_t st);
-void launch_attention_given_v4(const DecodeArgs& a, dim3 grid, hipStream_t st);
-void launch_attention_given_v2(const DecodeArgs& a, dim3 grid, hipStream_t st);
 
 namespace {
 
@@ -570,37 +565,6 @@ struct ScoreWalk {
   }
 };
 
-// The scores of a page where they have been computed already (raw fp32, in memory, as the score-only
-// kernel leaves them): each lane reads the 32 that the walk above would leave it.  Rows of a
-// descriptor are the page's part of the heads' score rows, `row_bytes` apart.
-template <TokenOrder O, int NH>
-struct GivenScores {
-  f32x4 s[8];
-  uint32_t voff;
-  uint32_t half_at;                                // bytes from batch j to the lane's j-th, by exclusive or
-  __device__ __forceinline__ void init(int lane, int n_heads, uint32_t row_bytes) {
-    voff = static_cast<uint32_t>(min(column_head<NH>(lane & 15), n_heads - 1)) * row_bytes +
-           static_cast<uint32_t>(row_token<O>(4 * (lane >> 4))) * 4;
-    half_at = NH == 4 && (lane & 4) ? 256u : 0u;
-  }
-  // What lies past the sequence's end, and a masked page, reads as anything.  A whole page's four
-  // consecutive scores are one load (an incomplete one's may leave the rows).
-  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, int rot, int nv) {
-    static_assert(O != TokenOrder::kRows, "a lane's scores of a batch are consecutive");
-#pragma unroll
-    for (int j = 0; j < NH; ++j) {
-      const uint32_t at = voff + ((static_cast<uint32_t>(batch_token<O>(j, rot)) * 4) ^ half_at);
-      if (nv == kGroup) {
-        const uint4 v = buf_load16<kAuxCached>(rs, at, 0);
-        s[j] = f32x4{u2f(v.x), u2f(v.y), u2f(v.z), u2f(v.w)};
-      } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) s[j][i] = u2f(buf_load4<kAuxCached>(rs, at, static_cast<uint32_t>(i) * 4));
-      }
-    }
-  }
-};
-
 // Pool pages of the pages a wavefront handles in a chunk (chunk pages wave, wave + NW, ...), read one by
 // one through the scalar cache, a page ahead of their use.  Entries of the table row are read
 // without knowing the sequence's length; `get` masks the pages past the wavefront's last one, and
@@ -658,13 +622,12 @@ __device__ __forceinline__ constexpr float code_unscale(int k) {
 }
 
 // ---- attention ----------------------------------------------------------------------------------
-// kCut: the chunks are cut on the device (a.spare_chunks > 0).  kGiven: the scores are in a.scores
-// (neither the codes nor the query are read then).
-template <int W, int VB, int NH, bool Q32, bool kCut, bool kGiven = false>
+// kCut: the chunks are cut on the device (a.spare_chunks > 0).
+template <int W, int VB, int NH, bool Q32, bool kCut>
 __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   constexpr int UB = 2 * W;
   constexpr bool kQuantV = VB != 16;
-  constexpr TokenOrder kOrder = kGiven && VB == 16 ? TokenOrder::kPlain : token_order(VB);
+  constexpr TokenOrder kOrder = token_order(VB);
   constexpr int kChain = kQuantV ? 16 : 4;
   constexpr uint32_t kCodesBytes = kBlocks * kGroup * UB;
   // Probabilities are exp2(score - m) with m the running maximum rounded up to a whole number
@@ -679,7 +642,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   constexpr int kVLoads = kQuantV ? kGroup * kHeadDim * VB / 8 / 1024 : 32;   // 1 KB wavefront loads per page of values
 
   struct Shared {
-    __attribute__((aligned(16))) uint8_t lut[kGiven ? 16 : (1 << W) * kTableRow];      // first: at LDS address 0
+    __attribute__((aligned(16))) uint8_t lut[(1 << W) * kTableRow];
     union {
       QueryShared q;
       __attribute__((aligned(16))) float red[2][NH][kHeadDim];           // end of the chunk; also lent to the merge
@@ -735,9 +698,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   chunk = uni(chunk);
   page0 = uni(page0);
   // the query and the page numbers are asked for without waiting for the sequence's length
-  QueryFetch qf;
-  if constexpr (!kGiven)
-    qf = fetch_query_heads<Q32>(a, (static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0) * kHeadDim, tid);
+  const QueryFetch qf = fetch_query_heads<Q32>(a, (static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0) * kHeadDim, tid);
   PageIds<kMatWaves> pids;
   pids.start(a, seq, page0 + wave);
   L = uni(clamped_len(a, seq));
@@ -757,19 +718,12 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     return;
   }
   const float sign = a.scale_log2 < 0.f ? -1.f : 1.f, scale_abs = fabsf(a.scale_log2);
-  const int row = lane >> 4, col = lane & 15;
   npg = uni(npg);
   int n_w = npg > wave ? (npg - wave + kMatWaves - 1) / kMatWaves : 0;   // chunk pages wave, wave + 4, ...
   const int res_page = (a.residual != nullptr && (L % kGroup) != 0) ? L / kGroup : -1;
   pids.n_p = n_w;
 
-  // 16 lanes a token row (fp16; four rows a load: 4 i + row in order kRows, 4 row + i in kPlain) or a block
-  // of units (quantized)
-  constexpr bool kRowOrder = kOrder == TokenOrder::kRows || kQuantV;
-  constexpr uint32_t kRowStep = kRowOrder ? 1024 : 256;
-  const uint32_t voff_values = kRowOrder ? lane * 16 : row * 1024 + col * 16;
-  const uint32_t row_bytes = static_cast<uint32_t>(a.scores_stride) * 4u;
-  // (with given scores rc is the page's part of the score rows)
+  const uint32_t voff_values = lane * 16;     // 16 lanes a token row (fp16) or a block of units (quantized)
   auto page_setup = [&](int k, __amdgpu_buffer_rsrc_t& rc, __amdgpu_buffer_rsrc_t& rp, __amdgpu_buffer_rsrc_t& rv,
                         __amdgpu_buffer_rsrc_t& rvp, int& nv, int& rot) {
     const int pid = pids.get(k);
@@ -781,14 +735,8 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     // same order keep hitting the same memory channels together, so the order is rotated
     rot = (ok && !kQuantV) ? (pid * 13 + kvh * 5) & 7 : 0;
     const bool packed = ok && page != res_page;                        // the residual group has no codes yet
-    if constexpr (kGiven) {
-      rc = make_rsrc(a.scores + first_head * a.scores_stride + static_cast<int64_t>(page) * kGroup,
-                     nv > 0 ? static_cast<uint32_t>(a.n_heads - 1) * row_bytes + static_cast<uint32_t>(nv) * 4u : 0u);
-      rp = rc;
-    } else {
-      rc = make_rsrc(a.codes + ph * kCodesBytes, packed ? kCodesBytes : 0u);
-      rp = make_rsrc(a.params + ph * kPairs, packed ? kPairs * 4u : 0u);
-    }
+    rc = make_rsrc(a.codes + ph * kCodesBytes, packed ? kCodesBytes : 0u);
+    rp = make_rsrc(a.params + ph * kPairs, packed ? kPairs * 4u : 0u);
     if constexpr (kQuantV) {
       // whole units are read; codes of slots past the sequence end are finite by construction
       // and meet a zero probability.  Their parameters could be anything: bounded by nv.
@@ -802,9 +750,8 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   };
   __amdgpu_buffer_rsrc_t rc_cur, rp_cur, rv_cur, rvp_cur, rc_nxt, rp_nxt, rv_nxt, rvp_nxt;
   int nv_cur, nv_nxt, rot_cur, rot_nxt;
-  std::conditional_t<kGiven, GivenScores<kOrder, NH>, ScoreWalk<W, kOrder, NH, Q32, kQuantV ? 2 : 1, kChain>> w;
-  if constexpr (kGiven) w.init(lane, a.n_heads, row_bytes);
-  else w.init(sh.lut, sh.q, sh.pair_down, sh.params[wave], lane);
+  ScoreWalk<W, kOrder, NH, Q32, kQuantV ? 2 : 1, kChain> w;
+  w.init(sh.lut, sh.q, sh.pair_down, sh.params[wave], lane);
   uint4 vr[kQuantV ? 1 : 4][8];                                        // fp16 values: four groups of 8 rows (32 tokens)
   uint4 vq[kQuantV ? kVLoads : 1];                                     // quantized values: the page's units
   u32x2 vpar = {0u, 0u};                                               // (scale, zero) of tokens 2 lane, 2 lane + 1
@@ -816,16 +763,12 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        dst[4 * b + i] = buf_load16<kAuxStream>(rv, voff_values, static_cast<uint32_t>((2 * g + b + rot) & 7) * 4096u + i * kRowStep);
+        dst[4 * b + i] = buf_load16<kAuxStream>(rv, voff_values, static_cast<uint32_t>((2 * g + b + rot) & 7) * 4096u + i * 1024u);
   };
   page_setup(0, rc_cur, rp_cur, rv_cur, rvp_cur, nv_cur, rot_cur);
-  if constexpr (kGiven) {
-    w.load(rc_cur, rot_cur, nv_cur);
-  } else {
-    w.load_params(rp_cur, lane);
+  w.load_params(rp_cur, lane);
 #pragma unroll
-    for (int t = 0; t < 8; ++t) w.load_unit_of(t, rc_cur, rot_cur);
-  }
+  for (int t = 0; t < 8; ++t) w.load_unit_of(t, rc_cur, rot_cur);
   if constexpr (kQuantV) {
     vpar = __builtin_amdgcn_raw_buffer_load_b64(rvp_cur, lane * 8, 0, kAuxCached);
 #pragma unroll
@@ -844,11 +787,9 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     n_chunks = uni(n_chunks);
   }
   const int stride = kCut ? n_chunks : a.n_chunks;
-  if constexpr (!kGiven) {
-    fill_key_table<W, kMatThreads>(sh.lut, key_table<W>(a.table_index), tid);           // while the first page is under way
-    store_query_heads<NH, Q32>(sh.q, sh.q_shift, sh.pair_down, sh.exponents, qf, sign, tid);
-  }
-  if constexpr (!kGiven) __syncthreads();
+  fill_key_table<W, kMatThreads>(sh.lut, key_table<W>(a.table_index), tid);           // while the first page is under way
+  store_query_heads<NH, Q32>(sh.q, sh.q_shift, sh.pair_down, sh.exponents, qf, sign, tid);
+  __syncthreads();
 
   // per lane: column (head, part), running maximum, sums over the lane's tokens
   // (fp16 values: the sums of p come from the matrix unit like one more dim, l_acc)
@@ -866,11 +807,8 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     page_setup(it + 1, rc_nxt, rp_nxt, rv_nxt, rvp_nxt, nv_nxt, rot_nxt);
     // lane constants of the score walk, derived anew for each page: the value phase needs their registers
     const int lane = lane_id(), col = lane & 15;
-    int q_shift = 0;
-    if constexpr (!kGiven) {
-      w.init(sh.lut, sh.q, sh.pair_down, sh.params[wave], lane);
-      q_shift = sh.q_shift[column_head<NH>(col)];
-    }
+    w.init(sh.lut, sh.q, sh.pair_down, sh.params[wave], lane);
+    const int q_shift = sh.q_shift[column_head<NH>(col)];
     const int s_exp_before = s_exp;
     if constexpr (kQuantV) {
       const int e = static_cast<int>(wave_max_u32(max(vpar.x & 0xffffu, vpar.y & 0xffffu)) >> 10);   // of the page's largest scale
@@ -879,20 +817,11 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       *(PQ_LDS u32x2*)static_cast<uintptr_t>(lds_addr(sh.vpar[wave]) + lane * 8) = u32x2{h2u(u2h(vpar.x) * factor), h2u(u2h(vpar.y) * factor)};
       vpar = __builtin_amdgcn_raw_buffer_load_b64(rvp_nxt, lane * 8, 0, kAuxCached);
     }
-    int down = 0;
-    if constexpr (kGiven) {
-      wave_lds_sync();                                                 // (the walk has one between the token parameters' way in and out)
-      if (sign < 0.f) {
-#pragma unroll
-        for (int t = 0; t < kOwn; ++t) w.s[t] = -w.s[t];
-      }
-    } else {
-      down = w.run(rc_nxt, rp_nxt, rot_nxt, lane) + kTableShift + q_shift;
-      if (pi == res_page) {
-        w.residual(a.residual + (static_cast<int64_t>(seq) * a.n_kv_heads + kvh) * (kGroup * kHeadDim), L - res_page * kGroup,
-                   rot_cur, lane_id());
-        down = q_shift;
-      }
+    int down = w.run(rc_nxt, rp_nxt, rot_nxt, lane) + kTableShift + q_shift;
+    if (pi == res_page) {
+      w.residual(a.residual + (static_cast<int64_t>(seq) * a.n_kv_heads + kvh) * (kGroup * kHeadDim), L - res_page * kGroup,
+                 rot_cur, lane_id());
+      down = q_shift;
     }
     // the groups the score walk had no registers for
     if constexpr (!kQuantV) load_rows(vr[2], rv_cur, 2, rot_cur);
@@ -980,8 +909,6 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
         }
       }
     }
-
-    if constexpr (kGiven) w.load(rc_nxt, rot_nxt, nv_nxt);
 
     // ---- values: acc += P^T V, 32 tokens (batches 2g, 2g + 1) per instruction ----
 #pragma unroll

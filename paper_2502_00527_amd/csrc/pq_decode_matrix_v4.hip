@@ -1,5 +1,4 @@
 // The attention kernels of pq_decode_matrix.hip for 4-bit quantized values.
 #define PQ_MATRIX_VB 4
 #define PQ_MATRIX_LAUNCH launch_attention_matrix_v4
-#define PQ_GIVEN_LAUNCH launch_attention_given_v4
 #include "pq_decode_matrix.hip"
