@@ -147,3 +147,13 @@ def test_bench_refuses_more_than_one_gpu():
     import sys
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode == 2 and "ONE GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_launches_cut_by_the_real_lengths(lib):
+    """Large launches merge in the kernel whatever max_seq_len is; few units keep the merge kernel."""
+    lay = pq.Layout(128, 4, 4, 128, 8)
+    assert pq.pq_decode_merges_in_kernel(lay, 64, 32, 131072) is True       # 23 chunks a sequence if all were that long
+    assert pq.pq_decode_merges_in_kernel(lay, 16, 32, 1 << 20) is True
+    assert pq.pq_decode_merges_in_kernel(lay, 1, 32, 1 << 20) is False      # 8 units
+    # the workspace is what it was: callers' buffers and the static scratch limit depend on it
+    assert pq.pq_decode_workspace_bytes(lay, 64, 32, 16384) == 64 * 32 * 4 * 130 * 4 + (512 + 768 + 512) * 8

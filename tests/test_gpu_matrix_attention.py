@@ -17,13 +17,16 @@ PLANS = [
     ("merge_kernel_two_chunks", 2, 32, 8, 1024, 1, 16, "f16"),  # 8 pages, few units: partials and merge kernel
     ("sixteen_page_chunks", 31, 32, 8, 3001, 129, 16, "f32"),   # merged in the kernel, odd number of sequences
     ("big_chunks", 8, 32, 8, 32768, 1, 16, "f16"),              # equal big chunks, fp16 values
-    ("big_then_small", 70, 8, 8, 8321, 1, 16, "f16"),           # more than 64 pages a share: two chunk lengths
+    ("big_then_small", 70, 8, 8, 8321, 1, 16, "f16"),           # more than 64 pages a share: two chunk lengths, cut on the device
     ("quantized_big_then_small", 20, 32, 8, 8192, 1, 4, "f16"),
     ("quantized_2bit_tail", 40, 14, 2, 8449, 100, 2, "f32"),    # 7 heads in one pass
     ("five_heads", 3, 40, 8, 1500, 7, 16, "f32"),
     ("sixteen_heads", 3, 32, 2, 2049, 2048, 16, "f16"),         # two passes of 8
 ]
 
+
+# one launch does everything, or the merge kernel follows
+SEPARATE_MERGE = {"merge_kernel_two_chunks", "five_heads", "sixteen_heads"}
 
 # every allocation on the small shapes; the others differ in the key-side table only
 CASES = [(p, b) for p in PLANS for b in [(4, 4), (3, 3), (3, 5), (2, 4), (5, 3), (4, 2)] if p[1] <= 8 or b in ((4, 4), (3, 3))]
@@ -32,6 +35,7 @@ CASES = [(p, b) for p in PLANS for b in [(4, 4), (3, 3), (3, 5), (2, 4), (5, 3),
 @pytest.mark.gpu
 @pytest.mark.parametrize("plan,bits", CASES, ids=lambda x: x[0] if isinstance(x[0], str) else f"r{x[0]}t{x[1]}")
 def test_attention_against_float64(plan, bits):
+    import paper_2502_00527_amd as pq
     from perf import cases
 
     name, seqs, q_heads, kv_heads, context, shortest, v_bits, dtype = plan
@@ -39,6 +43,8 @@ def test_attention_against_float64(plan, bits):
                        dtype=dtype, r_bits=bits[0], t_bits=bits[1], shuffled_pages=True)
     print(f"[matrix] {name} {bits}", flush=True)
     state = cases.prepare(case, 5)
+    merges = pq.pq_decode_merges_in_kernel(state["layout"], seqs, q_heads, state["max_seq_len"], v_bits)
+    assert merges == (name not in SEPARATE_MERGE), "the case no longer reaches the plan it is named after"
     state["workspace"].fill_(0x5A)                              # arrival words need no initialisation
     first = cases.run(state).clone()
     second = cases.run(state)
