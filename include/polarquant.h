@@ -198,10 +198,11 @@ int pq_encode_values(const pq_layout* layout, int32_t v_bits, const void* values
  *   workspace     device, >= pq_decode_workspace_bytes(layout, n_seqs, n_q_heads, max_seq_len),
  *                 256-byte aligned; contents are scratch
  *
- * Scores, softmax statistics and outputs are fp32.  The probabilities that weight the values are
- * fp32 too, except with quantized values and in 8-head passes, where they are rounded to fp16
- * (pairs of tokens for the two-term fp16 dot product with an fp32 accumulator; with quantized
- * values the token's fp16 scale is folded in before the rounding).
+ * Scores, softmax statistics and outputs are fp32.  On the uniform angle grid the factors of the two
+ * matrix products (query times radius parameter, reconstructed key, probability times value scale)
+ * are carried as two fp16 parts, 22 bits; with the grouped angle quantizer the probabilities that
+ * weight the values are fp32, or rounded to fp16 with quantized values (the token's fp16 scale
+ * folded in before the rounding).  `out` does not depend on whether `scores` is asked for.
  */
 int pq_decode_attention(const pq_layout* layout, const void* q, pq_dtype q_dtype, int32_t n_seqs,
                         int32_t n_q_heads, const void* codes_pool, const void* params_pool,
@@ -262,8 +263,8 @@ int pq_decode_merge(const pq_layout* layout, int32_t n_seqs, int32_t n_q_heads,
 
 /*
  * pq_decode_kernel_name -- name of the attention kernel pq_decode_partials / pq_decode_attention
- * launch for this shape ("" on invalid arguments).  The choice depends on the launch shape (see
- * pq_decode_partials); profiles and the benchmark use this to name the kernel that really ran.
+ * launch for this shape ("" on invalid arguments), as profiles show it.  The name tells large launches
+ * from small ones; on the uniform angle grid both are the same kernel.
  * The string is static storage.
  */
 const char* pq_decode_kernel_name(const pq_layout* layout, int32_t n_seqs, int32_t n_q_heads,
@@ -271,10 +272,9 @@ const char* pq_decode_kernel_name(const pq_layout* layout, int32_t n_seqs, int32
 
 /*
  * pq_decode_merges_in_kernel -- 1 if pq_decode_attention serves this shape with one kernel that
- * shares the launch out evenly and combines the partial results itself, 0 if it launches one
- * work-group per chunk followed by the merge kernel; a negative pq_status on invalid arguments.
- * Launches of few (sequence, KV head) units and the kernels without role specialisation take the
- * second form.  For profiles and the benchmark, like pq_decode_kernel_name.
+ * combines the partial results itself, 0 if the merge kernel follows; a negative pq_status on
+ * invalid arguments.  Launches of few (sequence, KV head) units whose sequences have several chunks, and
+ * the grouped angle quantizer's, take the second form.  For profiles and the benchmark, like pq_decode_kernel_name.
  */
 int pq_decode_merges_in_kernel(const pq_layout* layout, int32_t n_seqs, int32_t n_q_heads,
                                int32_t max_seq_len, int32_t v_bits);
