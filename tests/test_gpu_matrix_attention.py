@@ -14,7 +14,7 @@ torch = pytest.importorskip("torch")
 # name, sequences, query heads, KV heads, longest and shortest context, value bits, query type
 PLANS = [
     ("one_chunk", 1, 32, 8, 895, 895, 16, "f16"),               # 7 pages: a single chunk, written directly
-    ("merge_kernel_two_chunks", 2, 32, 8, 1024, 1, 16, "f16"),  # 8 pages, few units: partials and merge kernel
+    ("merge_kernel_two_chunks", 2, 32, 8, 1024, 1000, 16, "f16"),   # 8 pages, few units: partials and merge kernel
     ("sixteen_page_chunks", 31, 32, 8, 3001, 129, 16, "f32"),   # merged in the kernel, odd number of sequences
     ("big_chunks", 8, 32, 8, 32768, 1, 16, "f16"),              # equal big chunks, fp16 values
     ("big_then_small", 70, 8, 8, 8321, 1, 16, "f16"),           # more than 64 pages a share: two chunk lengths, cut on the device
