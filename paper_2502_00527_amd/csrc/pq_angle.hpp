@@ -16,6 +16,7 @@
 
 #include <math.h>
 #include <stdint.h>
+#include <string.h>
 
 #ifndef PQ_HD
 #define PQ_HD
@@ -113,6 +114,97 @@ PQ_HD inline uint32_t angle_bin_interior(float x, float y, const double* tan_edg
     const double mn = mnf, mx = mxf;
     uint32_t passed = 0;
     for (int k = 1; k < S; ++k) passed += mx * tan_edge[k] <= mn;
+    code ^= passed;
+  }
+  return code;
+}
+
+// ---- four fp16 pairs at a time ---------------------------------------------------------------
+// The same bins for four fp16 pairs with the octant found by byte look-ups.  A pair's octant number is
+// (x < 0) + 2 (y < 0) + 4 (past the diagonal), as in octant_of(): the three bits of four pairs are
+// gathered into the bytes of one word, which selects four bytes of the octant table.  Where the signs
+// are equal a pair ON the diagonal counts as past it, otherwise not: the octant that starts there.
+// Bin edges inside the octant are compared in fp32, sign(mx * tan - mn) by one fused multiply-add:
+// with 11-bit significands mn / mx is never nearer to an edge than the rounding of tan
+// (checked for every pair of significands in the tests).
+// The result does not hold where x = 0 or y = 0; `smallest` collects min(|x|, |y|) as fp16 bits
+// in its two halves, so that the caller can tell.
+namespace detail {
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 as_u16x2(uint32_t w) { return __builtin_bit_cast(u16x2, w); }
+__device__ __forceinline__ uint32_t as_word(u16x2 v) { return __builtin_bit_cast(uint32_t, v); }
+__device__ __forceinline__ uint32_t min_u16x2(uint32_t a, uint32_t b) { return as_word(__builtin_elementwise_min(as_u16x2(a), as_u16x2(b))); }
+__device__ __forceinline__ uint32_t max_u16x2(uint32_t a, uint32_t b) { return as_word(__builtin_elementwise_max(as_u16x2(a), as_u16x2(b))); }
+__device__ __forceinline__ uint32_t sub_u16x2(uint32_t a, uint32_t b) { return as_word(as_u16x2(a) - as_u16x2(b)); }
+__device__ __forceinline__ uint32_t top_bits_u16x2(uint32_t a) { return as_word(as_u16x2(a) >> static_cast<uint16_t>(15)); }
+__device__ __forceinline__ uint32_t pick_bytes(uint32_t hi, uint32_t lo, uint32_t sel) { return __builtin_amdgcn_perm(hi, lo, sel); }
+// bits of mx * tan - mn, of half HI of the words
+template <int HI>
+__device__ __forceinline__ uint32_t edge_bits(uint32_t mx, uint32_t mn, float tan_edge) {
+  uint32_t r;
+  if constexpr (HI == 0) asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel_hi:[1,0,1]" : "=v"(r) : "v"(mx), "s"(tan_edge), "v"(mn));
+  else asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(mx), "s"(tan_edge), "v"(mn));
+  return r;
+}
+#else
+inline uint32_t lanes(uint32_t a, uint32_t b, uint32_t (*f)(uint32_t, uint32_t)) {
+  return (f(a & 0xffffu, b & 0xffffu) & 0xffffu) | (f(a >> 16, b >> 16) << 16);
+}
+inline uint32_t min_u16x2(uint32_t a, uint32_t b) { return lanes(a, b, [](uint32_t p, uint32_t q) { return p < q ? p : q; }); }
+inline uint32_t max_u16x2(uint32_t a, uint32_t b) { return lanes(a, b, [](uint32_t p, uint32_t q) { return p < q ? q : p; }); }
+inline uint32_t sub_u16x2(uint32_t a, uint32_t b) { return lanes(a, b, [](uint32_t p, uint32_t q) { return p - q; }); }
+inline uint32_t top_bits_u16x2(uint32_t a) { return (a >> 15) & 0x00010001u; }
+inline uint32_t pick_bytes(uint32_t hi, uint32_t lo, uint32_t sel) {       // selectors 0 .. 7 only
+  uint32_t r = 0;
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t s = (sel >> (8 * i)) & 7u;
+    r |= (((s < 4 ? lo : hi) >> (8 * (s & 3))) & 0xffu) << (8 * i);
+  }
+  return r;
+}
+inline float half_to_float(uint32_t h) {                                    // finite, not negative
+  const int e = static_cast<int>(h >> 10);
+  return static_cast<float>(e == 0 ? ldexp(h & 1023u, -24) : ldexp(1024u + (h & 1023u), e - 25));
+}
+template <int HI>
+inline uint32_t edge_bits(uint32_t mx, uint32_t mn, float tan_edge) {
+  const float f = fmaf(half_to_float((mx >> (16 * HI)) & 0xffffu), tan_edge, -half_to_float((mn >> (16 * HI)) & 0xffffu));
+  uint32_t b;
+  memcpy(&b, &f, 4);
+  return b;
+}
+#endif
+// top bits of the four halves of (w0, w1), each in bit 7 of a byte (the other bits are anything)
+PQ_HD inline uint32_t top_bytes(uint32_t w1, uint32_t w0) { return pick_bytes(w1, w0, 0x07050301u); }
+}  // namespace detail
+
+// x, y: two words each, pairs 0, 1 and 2, 3; returns the bins in the four bytes.
+template <int TB>
+PQ_HD inline uint32_t angle_bins_of_four(const uint32_t (&x)[2], const uint32_t (&y)[2], const float* tan_edge, uint32_t& smallest) {
+  using namespace detail;
+  constexpr int NB = 1 << TB;
+  constexpr int S = NB >= 8 ? NB / 8 : 1;
+  constexpr uint32_t lo = octant_entries<TB>(0), hi = octant_entries<TB>(1);
+  uint32_t mn[2], mx[2], past[2];
+  for (int i = 0; i < 2; ++i) {
+    const uint32_t ax = x[i] & 0x7fff7fffu, ay = y[i] & 0x7fff7fffu;
+    mn[i] = min_u16x2(ax, ay);
+    mx[i] = max_u16x2(ax, ay);
+    // sign of |x| - |y| - (1 where the signs are equal)
+    past[i] = sub_u16x2(sub_u16x2(ax, ay), top_bits_u16x2(~(x[i] ^ y[i])));
+    smallest = min_u16x2(smallest, mn[i]);
+  }
+  const uint32_t idx = ((top_bytes(x[1], x[0]) >> 7) & 0x01010101u) | ((top_bytes(y[1], y[0]) >> 6) & 0x02020202u) |
+                       ((top_bytes(past[1], past[0]) >> 5) & 0x04040404u);
+  uint32_t code = pick_bytes(hi, lo, idx);
+  if (S > 1) {
+    uint32_t passed = 0;
+    for (int k = 1; k < S; ++k) {
+      const uint32_t e01 = pick_bytes(edge_bits<1>(mx[0], mn[0], tan_edge[k]), edge_bits<0>(mx[0], mn[0], tan_edge[k]), 0x07030703u);
+      const uint32_t e23 = pick_bytes(edge_bits<1>(mx[1], mn[1], tan_edge[k]), edge_bits<0>(mx[1], mn[1], tan_edge[k]), 0x07030703u);
+      passed += (pick_bytes(e23, e01, 0x05040100u) >> 7) & 0x01010101u;
+    }
     code ^= passed;
   }
   return code;

@@ -24,6 +24,10 @@ def host_lib(tmp_path_factory):
     lib.angle_bins_host.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_void_p]
     lib.angle_bins_interior_host.restype = ctypes.c_int
     lib.angle_bins_interior_host.argtypes = lib.angle_bins_host.argtypes
+    lib.angle_bins_of_four_host.restype = ctypes.c_int
+    lib.angle_bins_of_four_host.argtypes = lib.angle_bins_host.argtypes
+    lib.edge_mismatches_host.restype = ctypes.c_int64
+    lib.edge_mismatches_host.argtypes = [ctypes.c_int]
     lib.round_to_half_host.restype = None
     lib.round_to_half_host.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
     return lib
@@ -88,6 +92,32 @@ def test_interior_rule_agrees_with_the_full_rule(host_lib, t):
     assert bad.sum() <= 2
     bad = inside & (got != want)
     assert not np.any(bad & (edge > 1e-12)) and bad.sum() <= 2
+
+
+@pytest.mark.parametrize("t", [2, 3, 4, 5])
+def test_four_at_a_time_agrees_with_the_full_rule(host_lib, t):
+    """fp16 pairs, four at a time: the full rule's bin for every pair (diagonals included), and only groups
+    with a zero coordinate are declined."""
+    x, y = _inputs()
+    rng = np.random.default_rng(79)
+    bits = rng.integers(1, 0x7c00, (2, 400000)).astype(np.uint16) | (rng.integers(0, 2, (2, 400000)) << 15).astype(np.uint16)
+    near = rng.integers(0x3c00, 0x4400, 200000).astype(np.uint16)             # ratios around the edges and diagonals
+    x = np.concatenate([x.astype(np.float16), bits[0].view(np.float16), near.view(np.float16)])
+    y = np.concatenate([y.astype(np.float16), bits[1].view(np.float16), (near + rng.integers(-2, 3, near.size)).astype(np.uint16).view(np.float16)])
+    n = x.size // 4 * 4
+    x, y = np.ascontiguousarray(x[:n]), np.ascontiguousarray(y[:n])
+    got = np.empty(n, np.int32)
+    assert host_lib.angle_bins_of_four_host(x.ctypes.data, y.ctypes.data, n, t, got.ctypes.data) == 0
+    zero = ((x == 0) | (y == 0)).reshape(-1, 4).any(axis=1).repeat(4)
+    assert np.array_equal(got == -1, zero) and (~zero).sum() > 1000000
+    assert ((np.abs(x) == np.abs(y)) & ~zero).sum() > 10000
+    full = _host_bins(host_lib, x, y, t)
+    np.testing.assert_array_equal(got[~zero], full[~zero])
+
+
+@pytest.mark.parametrize("t", [4, 5])
+def test_edges_are_decided_in_fp32_for_every_pair_of_fp16_significands(host_lib, t):
+    assert host_lib.edge_mismatches_host(t) == 0
 
 
 def test_round_to_half_is_one_nearest_even_rounding(host_lib):

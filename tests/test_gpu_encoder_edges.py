@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import paper_2502_00527_amd as pq
-from oracle import cache_format, values as ovalues
+from oracle import cache_format, polar, values as ovalues
 
 pytestmark = pytest.mark.gpu
 GROUP = 128
@@ -47,3 +47,47 @@ def test_value_encoder_edges(kind, v_bits):
         np.testing.assert_array_equal(got[:n, :, 0].view(np.uint16), s.view(np.uint16))
         np.testing.assert_array_equal(got[:n, :, 1], z)             # (zeros may differ in their sign)
         assert not got[n:].any()
+
+
+def _keys(kind, n, heads, seed, dtype):
+    """[n, heads, 128]: keys on which the code's approximation is in doubt, or the quick angle rule does not hold."""
+    rng = np.random.default_rng(seed)
+    k = rng.standard_normal((n, heads, 128))
+    if kind == "lattice":                       # axes, diagonals and the origin; radii that meet bin edges
+        k = rng.integers(-15, 16, k.shape) * 0.5
+    elif kind == "diagonals":                   # no zeros, |x| = |y| in a quarter of the pairs
+        k = rng.choice([-1.0, 1.0], k.shape) * rng.integers(1, 5, k.shape) * 0.25
+    elif kind == "zeros":                       # zeros of both signs, a channel without any other number
+        k = np.where(rng.random(k.shape) < 0.3, np.copysign(0.0, k), k)
+        k[..., 5], k[..., 70] = 0.0, -0.0
+    elif kind == "flat":                        # constant radii: scale 0, or a few units of the radius
+        k = np.broadcast_to(k[:1], k.shape) * (1 + 2.0 ** -9 * rng.integers(-1, 2, (n, heads, 1)) * (rng.random((1, heads, 1)) < 0.5))
+    elif kind == "circle":                      # scales far below the radius
+        a = 2 * np.pi * rng.random((n, heads, 64))
+        k = 3 * np.concatenate([np.cos(a), np.sin(a)], axis=-1)
+    elif kind == "small":                       # fp16 denormals, denormal scales
+        k = k * 2.0 ** -20
+    elif kind == "wide":
+        k = np.clip(k * np.exp2(rng.integers(-24, 12, k.shape)), -20000, 20000)
+    return k.astype(dtype)
+
+
+@pytest.mark.parametrize("rt", [(4, 4), (3, 3), (5, 3), (3, 5), (4, 2), (2, 4)])
+@pytest.mark.parametrize("kind", ["normal", "lattice", "diagonals", "zeros", "flat", "circle", "small", "wide"])
+def test_key_encoder_edges(kind, rt):
+    for n, heads, dtype in ((1, 3, np.float16), (127, 1, np.float32), (300, 2, np.float16), (130, 2, np.float32)):
+        k = _keys(kind, n, heads, n, dtype)
+        enc = polar.encode_keys(k, *rt, GROUP)
+        n_pages = (n + GROUP - 1) // GROUP
+        layout = pq.Layout(128, *rt, GROUP, heads, 0)
+        codes = torch.full((n_pages, heads, 4, GROUP, 2 * sum(rt)), 0xA5, dtype=torch.uint8, device="cuda:0")
+        params = torch.full((n_pages, heads, 64, 2), 7.0, dtype=torch.float16, device="cuda:0")
+        order = np.arange(n_pages - 1, -1, -1, dtype=np.int32)                # pages out of order
+        pq.pq_encode_keys(layout, torch.from_numpy(k).to("cuda:0"), torch.from_numpy(order).to("cuda:0"), codes, params)
+        a, c, s, z = cache_format.unpack_pages(codes.cpu().numpy()[order], params.cpu().numpy()[order], n, *rt)
+        np.testing.assert_array_equal(s.view(np.uint16), enc["scale"].view(np.uint16))
+        np.testing.assert_array_equal(z.view(np.uint16), enc["zero"].view(np.uint16))
+        np.testing.assert_array_equal(c, enc["c"])
+        # two float64 evaluations of an irrational edge may differ in the last places
+        assert not np.any((a != enc["a"]) & (enc["edge_dist"] > 1e-12))
+        assert not codes.cpu().numpy()[order][-1, :, :, n - (n_pages - 1) * GROUP:].any()
