@@ -126,15 +126,19 @@ __device__ __forceinline__ const uint4* key_table(int index) {
   if constexpr (W == 8) return reinterpret_cast<const uint4*>(&key_tables8.word[index][0][0]);
   else return reinterpret_cast<const uint4*>(&key_tables6.word[index][0][0]);
 }
-// Fills the LDS table; a work-group barrier must follow before it is read.
+// Thread t loads the entry of symbol t % 2^W and stores it to as many of the symbol's copies as fall to it,
+// each lane starting at a copy of its own (16 lanes write to all banks).  A work-group barrier must
+// follow before the table is read.
+template <int W>
+__device__ __forceinline__ uint4 fetch_key_entry(const uint4* src, int tid) { return src[tid & ((1 << W) - 1)]; }
 template <int W, int NT>
-__device__ __forceinline__ void fill_key_table(uint8_t* lut, const uint4* src, int tid) {
-  constexpr int kSlots = (1 << W) * 16;              // 16-byte slot: symbol at / 16, copy at % 16
+__device__ __forceinline__ void store_key_entry(uint8_t* lut, const uint4& entry, int tid) {
+  constexpr int kCopies = 16 * (1 << W) / NT;        // of a thread
+  static_assert(kCopies * NT == 16 * (1 << W), "whole copies");
+  uint8_t* const row = lut + (tid & ((1 << W) - 1)) * kTableRow;
+  const int first = tid + (tid >> W) * kCopies;
 #pragma unroll
-  for (int i = 0; i < (kSlots + NT - 1) / NT; ++i) {
-    const int at = i * NT + tid;
-    if (kSlots % NT == 0 || at < kSlots) reinterpret_cast<uint4*>(lut)[at] = src[at >> 4];
-  }
+  for (int i = 0; i < kCopies; ++i) *reinterpret_cast<uint4*>(row + ((first + i) & 15) * 16) = entry;
 }
 
 // ---- query side -------------------------------------------------------------------------------
@@ -599,13 +603,26 @@ __device__ __forceinline__ int lane_id() {
   return l;
 }
 
-// Two work-groups share a compute unit, a wavefront of each a SIMD: they take the higher issue
+// Two work-groups share a compute unit, a wavefront of each a SIMD: with quantized values they take the higher issue
 // priority in turns, page by page, so that one's matrix instructions meet the other's vector work.
 __device__ __forceinline__ int priority_turn() {
   return static_cast<int>(((blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) / 256u) & 1u);
 }
 __device__ __forceinline__ void alternate_priority(int turn) {
   if (turn & 1) __builtin_amdgcn_s_setprio(1);
+  else __builtin_amdgcn_s_setprio(0);
+}
+
+// With fp16 values the priority falls with the part of the chunk that is left, so that the work-groups of a compute
+// unit get on alike.  Among equals the SIMD favours the older wavefront: of two work-groups that had started
+// together with four pages a wavefront each, one was done at 38 us, the other, by then alone with half of the loads
+// in flight, at 48.  One 128K sequence at 3+3 bits 63.0 -> 57.4 us, 64 ragged ones 241 -> 229, 31 x 3000 tokens
+// 40.4 -> 39.6; 16 x 32K 208.1 -> 208.9, one head per KV head 110.3 -> 110.8.  (The later work-group always first: 61 / 225 / 40.9 /
+// 210.4 / 112; by pages left, not by their part: 57 - 61 / 230 / 40.4 / 209.  With quantized values no difference from turns.)
+__device__ __forceinline__ void priority_of_rest(int left, int all) {
+  if (left == all) __builtin_amdgcn_s_setprio(3);
+  else if (4 * left >= 3 * all) __builtin_amdgcn_s_setprio(2);
+  else if (2 * left >= all) __builtin_amdgcn_s_setprio(1);
   else __builtin_amdgcn_s_setprio(0);
 }
 
@@ -642,11 +659,13 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   constexpr int kVLoads = kQuantV ? kGroup * kHeadDim * VB / 8 / 1024 : 32;   // 1 KB wavefront loads per page of values
 
   struct Shared {
-    __attribute__((aligned(16))) uint8_t lut[(1 << W) * kTableRow];
+    union {
+      __attribute__((aligned(16))) uint8_t lut[(1 << W) * kTableRow];
+      __attribute__((aligned(16))) float red[kMatWaves][NH][kHeadDim];   // end of the chunk
+    };
     union {
       QueryShared q;
-      __attribute__((aligned(16))) float red[2][NH][kHeadDim];           // end of the chunk; also lent to the merge
-      float lent[kFinishLdsFloats];
+      __attribute__((aligned(16))) float lent[kFinishLdsFloats];         // end of the chunk: to the merge
       int32_t pages[kCut ? kBalancedSeqs : 1];                           // of the sequences, while the chunks are cut
     };
     __attribute__((aligned(16))) uint32_t params[kMatWaves][kPairs];
@@ -684,6 +703,9 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     if (a.n_seqs > 64) __syncthreads();                                // the lengths make room for what shares their memory
     return true;
   };
+  // The key table's entry, and the query below, are asked for before the page's loads: whoever waits for them
+  // does not wait for the page as well (loads return in order).
+  const uint4 entry = fetch_key_entry<W>(key_table<W>(a.table_index), tid);
   // A first chunk, of sequence number `slot`: its pages are under way before the cut is made.
   const bool cut_later = kCut && slot < a.n_seqs;
   if constexpr (kCut) {
@@ -787,7 +809,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     n_chunks = uni(n_chunks);
   }
   const int stride = kCut ? n_chunks : a.n_chunks;
-  fill_key_table<W, kMatThreads>(sh.lut, key_table<W>(a.table_index), tid);           // while the first page is under way
+  store_key_entry<W, kMatThreads>(sh.lut, entry, tid);                                // while the first page is under way
   store_query_heads<NH, Q32>(sh.q, sh.q_shift, sh.pair_down, sh.exponents, qf, sign, tid);
   __syncthreads();
 
@@ -804,6 +826,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   for (int it = 0; it < n_w; ++it) {
     const int pi = page0 + wave + kMatWaves * it;
     if constexpr (kQuantV) alternate_priority(turn + it);             // (costs 1 % where memory is the bound)
+    else priority_of_rest(n_w - it, n_w);
     page_setup(it + 1, rc_nxt, rp_nxt, rv_nxt, rvp_nxt, nv_nxt, rot_nxt);
     // lane constants of the score walk, derived anew for each page: the value phase needs their registers
     const int lane = lane_id(), col = lane & 15;
@@ -974,7 +997,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     rc_cur = rc_nxt; rp_cur = rp_nxt; rv_cur = rv_nxt; rvp_cur = rvp_nxt; nv_cur = nv_nxt; rot_cur = rot_nxt;
   }
 
-  // ---- fold the four wavefronts: maxima and sums through LDS, accumulators in two rounds ----
+  // ---- fold the four wavefronts: maxima and sums through LDS, then the accumulators, where the key table was ----
   {
     const int lane = lane_id(), row = lane >> 4, col = lane & 15;
     const int acc_head = NH == 8 ? 4 * (row & 1) : 0;                  // head of accumulator row i: acc_head + i
@@ -1014,7 +1037,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
         acc[e][i] = sum_parts(acc[e][i] * back) * wgt[i];
         if constexpr (kQuantV) acc[e][i] *= code_unscale<VB>(e);
       }
-    if (wave < 2 && row < NH / 4) {
+    if (row < NH / 4) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         f32x4* const dst = reinterpret_cast<f32x4*>(&sh.red[wave][4 * row + i][col * 8]);
@@ -1023,20 +1046,12 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       }
     }
     __syncthreads();
-    if (wave >= 2 && row < NH / 4) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        f32x4* const dst = reinterpret_cast<f32x4*>(&sh.red[wave - 2][4 * row + i][col * 8]);
-        dst[0] += f32x4{acc[0][i], acc[1][i], acc[2][i], acc[3][i]};
-        dst[1] += f32x4{acc[4][i], acc[5][i], acc[6][i], acc[7][i]};
-      }
-    }
-    __syncthreads();
   }
 
   finish_chunk<NH>(a, seq, kvh, chunk, n_chunks, row0, stride, wave * 64 + lane_id(), [&](int h, int quad, float& M, float& l) {
     M = fmaxf(fmaxf(sh.red_ml[0][h][0], sh.red_ml[1][h][0]), fmaxf(sh.red_ml[2][h][0], sh.red_ml[3][h][0]));
-    f32x4 o = *reinterpret_cast<const f32x4*>(&sh.red[0][h][quad * 4]) + *reinterpret_cast<const f32x4*>(&sh.red[1][h][quad * 4]);
+    auto part = [&](int v) { return *reinterpret_cast<const f32x4*>(&sh.red[v][h][quad * 4]); };
+    f32x4 o = (part(0) + part(2)) + (part(1) + part(3));
     l = 0.f;
     if (M > kNegInf) {
       float zp = 0.f;                                                  // zero-point term: the same for every dim
