@@ -1,6 +1,7 @@
 // Host entry points of the decode path (pq_decode_*, pq_score_keys) and the chunk merge kernel.
 // The attention and score-only kernel templates live in pq_decode_kernels.hpp.
 #include <algorithm>
+#include <cstring>
 #include <mutex>
 
 #include "pq_decode_matrix.hpp"
@@ -222,14 +223,22 @@ ChunkPlan plan_attention(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int
 }
 
 // cos / sin of the centre of every angle bin of the uniform grid over [-pi, pi) (Section 3.2
-// mid-point reconstruction), evaluated in float64 on the host.
-void fill_angle_tables(DecodeArgs& a, int t_bits) {
-  const int nb = 1 << t_bits;
-  for (int s = 0; s < kMaxAngleBins; ++s) {
-    const double th = -M_PI + (s + 0.5) * (2.0 * M_PI / nb);
-    a.cos_tab[s] = s < nb ? static_cast<float>(cos(th)) : 0.f;
-    a.sin_tab[s] = s < nb ? static_cast<float>(sin(th)) : 0.f;
+// mid-point reconstruction), evaluated in float64 on the host; made once for each t_bits in 2 .. 5.
+struct AngleTable {
+  float cos_tab[kMaxAngleBins] = {}, sin_tab[kMaxAngleBins] = {};
+  explicit AngleTable(int t_bits) {
+    const int nb = 1 << t_bits;
+    for (int s = 0; s < nb; ++s) {
+      const double th = -M_PI + (s + 0.5) * (2.0 * M_PI / nb);
+      cos_tab[s] = static_cast<float>(cos(th));
+      sin_tab[s] = static_cast<float>(sin(th));
+    }
   }
+};
+void fill_angle_tables(DecodeArgs& a, int t_bits) {
+  static const AngleTable tables[4] = {AngleTable(2), AngleTable(3), AngleTable(4), AngleTable(5)};
+  memcpy(a.cos_tab, tables[t_bits - 2].cos_tab, sizeof(a.cos_tab));
+  memcpy(a.sin_tab, tables[t_bits - 2].sin_tab, sizeof(a.sin_tab));
 }
 
 // Device address of `scratch` on the current device (in host code the array's name is only a
@@ -357,6 +366,14 @@ bool merges_in_kernel(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_
   return n_chunks == 1 || (n_chunks <= kMergeFan && large_uniform_launch(l, n_seqs, max_seq_len));
 }
 
+// Work-groups of 8 wavefronts: sequences of one chunk with more pages than 4 wavefronts take at once, and no more
+// units than compute units (two work-groups of 4 share one otherwise).  One sequence of 777 tokens 13.3 -> 12.2 us,
+// 16 of them 15.0 -> 14.7; up to 4 pages the wider work-group costs 1 us (300 tokens: 9.7 -> 10.7).
+bool wide_groups(const pq_layout* l, const ChunkPlan& plan, int32_t n_seqs, int32_t max_seq_len) {
+  return l->angle_quantizer == PQ_ANGLE_UNIFORM && plan.n_chunks == 1 && max_seq_len > kWaveRound * kGroup &&
+         static_cast<int64_t>(n_seqs) * l->n_kv_heads <= kComputeUnits;
+}
+
 // Everything the decode entry points have in common: argument checks, kernel arguments, and the
 // launches.  `out` null = only the first stage of the two-stage (grid) path, the chunk partials.
 int decode_launch(const pq_layout* layout, const void* q, pq_dtype q_dtype, int32_t n_seqs, int32_t n_q_heads,
@@ -428,6 +445,7 @@ int decode_launch(const pq_layout* layout, const void* q, pq_dtype q_dtype, int3
   a.merge_in_kernel = merged ? 1 : 0;
   a.spare_chunks = out != nullptr ? spare_chunks(layout, n_seqs, max_seq_len) : 0;
   const dim3 grid = a.spare_chunks > 0 ? dim3(layout->n_kv_heads, n_seqs + a.spare_chunks) : dim3(layout->n_kv_heads, n_seqs, plan.n_chunks);
+  a.wide_groups = out != nullptr && wide_groups(layout, plan, n_seqs, max_seq_len) ? 1 : 0;
   a.table_index = key_table_index(layout);
   if (scores && !grouped) {
     const int ss = launch_scores(layout, a, stream);

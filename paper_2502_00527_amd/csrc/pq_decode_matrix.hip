@@ -16,21 +16,23 @@ namespace pq {
 namespace {
 namespace matrix {
 
-#define PQ_MATRIX_ATTR __launch_bounds__(kMatThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+#define PQ_MATRIX_ATTR(waves) __launch_bounds__(waves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
 template <int W, int VB, int NH, bool Q32, bool kCut>
-__global__ PQ_MATRIX_ATTR void pq_decode_roles_kernel(const DecodeArgs a) { attention_body<W, VB, NH, Q32, kCut>(a); }
-template <int W, int VB, int NH, bool Q32, bool kCut>
-__global__ PQ_MATRIX_ATTR void pq_decode_partials_kernel(const DecodeArgs a) { attention_body<W, VB, NH, Q32, kCut>(a); }
+__global__ PQ_MATRIX_ATTR(4) void pq_decode_roles_kernel(const DecodeArgs a) { attention_body<W, VB, NH, Q32, kCut, 4>(a); }
+template <int W, int VB, int NH, bool Q32, bool kCut, int kWaves>
+__global__ PQ_MATRIX_ATTR(kWaves) void pq_decode_partials_kernel(const DecodeArgs a) { attention_body<W, VB, NH, Q32, kCut, kWaves>(a); }
 
 template <int W, int VB, int NH, bool Q32, bool kCut>
 void launch_named(bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st) {
-  if (roles) hipLaunchKernelGGL((pq_decode_roles_kernel<W, VB, NH, Q32, kCut>), grid, dim3(kMatThreads), 0, st, a);
-  else hipLaunchKernelGGL((pq_decode_partials_kernel<W, VB, NH, Q32, kCut>), grid, dim3(kMatThreads), 0, st, a);
+  if (roles) hipLaunchKernelGGL((pq_decode_roles_kernel<W, VB, NH, Q32, kCut>), grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((pq_decode_partials_kernel<W, VB, NH, Q32, kCut, 4>), grid, dim3(256), 0, st, a);
 }
 template <int W, int VB, int NH, bool Q32>
 void launch_one(bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st) {
-  a.spare_chunks > 0 ? launch_named<W, VB, NH, Q32, true>(roles, a, grid, st) : launch_named<W, VB, NH, Q32, false>(roles, a, grid, st);
+  if (a.spare_chunks > 0) launch_named<W, VB, NH, Q32, true>(roles, a, grid, st);
+  else if (a.wide_groups && !roles) hipLaunchKernelGGL((pq_decode_partials_kernel<W, VB, NH, Q32, false, 8>), grid, dim3(512), 0, st, a);
+  else launch_named<W, VB, NH, Q32, false>(roles, a, grid, st);
 }
 template <int W, int VB>
 void launch_q(bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st) {

@@ -47,8 +47,6 @@ namespace {
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kMatWaves = 4;
-constexpr int kMatThreads = kMatWaves * 64;
 constexpr int kMaxHeads = 8;            // query heads of one pass: columns h (high part) and 8 + h (low part)
 
 // ---- key-side table ---------------------------------------------------------------------------
@@ -164,13 +162,13 @@ constexpr int kQueryBlock = 16 * 16 * 8 + 128;
 struct QueryShared {
   __attribute__((aligned(16))) uint8_t pairs[kBlocks * kQueryBlock];
 };
-// As loaded, so that nothing waits for it before store_query_heads(): thread = (head tid / 32, dims
-// 4 (tid % 32) ..+3); heads from n_heads on are zero.
+// As loaded, so that nothing waits for it before store_query_heads(): thread = (head tid / 32, pairs
+// 2 (tid % 32), + 1), x coordinates first; heads from n_heads on are zero.
 struct QueryFetch {
   uint32_t w[4];
   template <bool Q32>
-  __device__ __forceinline__ float value(int e) const {
-    return Q32 ? u2f(w[e]) : static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w[e / 2] >> (16 * (e % 2)))));
+  __device__ __forceinline__ float value(int comp, int e) const {
+    return Q32 ? u2f(w[2 * comp + e]) : static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w[comp] >> (16 * e))));
   }
 };
 template <bool Q32>
@@ -178,59 +176,65 @@ __device__ __forceinline__ QueryFetch fetch_query_heads(const DecodeArgs& a, int
   QueryFetch f = {};
   const int h = tid >> 5;
   if (h < a.n_heads) {
-    const int64_t at = q_at + h * kHeadDim + (tid & 31) * 4;
-    if constexpr (Q32) __builtin_memcpy(f.w, static_cast<const float*>(a.q) + at, 16);
-    else __builtin_memcpy(f.w, static_cast<const __half*>(a.q) + at, 8);
+    const int64_t at = q_at + h * kHeadDim + (tid & 31) * 2;
+#pragma unroll
+    for (int comp = 0; comp < 2; ++comp) {
+      if constexpr (Q32) __builtin_memcpy(f.w + 2 * comp, static_cast<const float*>(a.q) + at + comp * kPairs, 8);
+      else __builtin_memcpy(f.w + comp, static_cast<const __half*>(a.q) + at + comp * kPairs, 4);
+    }
   }
   return f;
 }
 // `shifts`: the power of two each head was multiplied with; `pair_down`: what the parameters of each
 // pair are to be multiplied with.  `exponents` is scratch.  Holds one work-group barrier.
+// (Both coordinates of a pair in one thread: 8 wide stores instead of 48 of 16 bits, and one 16-byte read of
+// the other heads' exponents.)
 template <int NH, bool Q32>
-__device__ __forceinline__ void store_query_heads(QueryShared& q, int* shifts, float* pair_down, uint16_t (*exponents)[kHeadDim],
+__device__ __forceinline__ void store_query_heads(QueryShared& q, int* shifts, float* pair_down, uint16_t (*exponents)[NH],
                                                   const QueryFetch& f, float sign, int tid) {
-  float v[4];
+  float v[2][2];                                             // [pair][coordinate]
+  uint32_t high[2];                                          // of the pair's two, as bits
 #pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = f.value<Q32>(e);
-  uint32_t top = 0;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) top = max(top, f2u(v[e]) & 0x7fffffffu);
-#pragma unroll
-  for (int d = 16; d >= 1; d >>= 1) top = max(top, static_cast<uint32_t>(__shfl_xor(static_cast<int>(top), d)));
+  for (int e = 0; e < 2; ++e) {
+    v[e][0] = f.value<Q32>(0, e);
+    v[e][1] = f.value<Q32>(1, e);
+    high[e] = max(f2u(v[e][0]) & 0x7fffffffu, f2u(v[e][1]) & 0x7fffffffu);
+  }
+  const uint32_t top = half_wave_max_u32(max(high[0], high[1]));
   const int shift = min(kQueryTop + 127 - static_cast<int>(top >> 23), 126);
-  const int h = tid >> 5, dim = (tid & 31) * 4;
+  const int h = tid >> 5, j0 = (tid & 31) * 2;
   // exponents after the head's scale, the largest 64 + kQueryTop
+  if (h < NH) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e)
-    if (h < NH) exponents[h][dim + e] = static_cast<uint16_t>(max(0, static_cast<int>((f2u(v[e]) & 0x7fffffffu) >> 23) + shift - 127 + 64));
+    for (int e = 0; e < 2; ++e) exponents[j0 + e][h] = static_cast<uint16_t>(max(0, static_cast<int>(high[e] >> 23) + shift - 127 + 64));
+  }
   __syncthreads();
   if (h >= NH) return;
-  int up[4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int j = (dim + e) & (kPairs - 1);
-    int most = 0;
+  for (int e = 0; e < 2; ++e) {
+    const int j = j0 + e, kk = j & 15;
+    uint32_t of_heads[NH / 2];
+    __builtin_memcpy(of_heads, exponents[j], NH * 2);
+    uint32_t most2 = of_heads[0];
 #pragma unroll
-    for (int o = 0; o < NH; ++o) most = max(most, max(static_cast<int>(exponents[o][j]), static_cast<int>(exponents[o][j + kPairs])));
-    up[e] = most == 0 ? 0 : 64 + kQueryTop - most;
-    if (h == 0 && dim + e < kPairs) pair_down[j] = most == 0 ? 0.f : __builtin_ldexpf(1.f, -up[e]);   // (not in any product: no say in the page's scale)
-  }
+    for (int o = 1; o < NH / 2; ++o) most2 = max_u16x2(most2, of_heads[o]);
+    const int most = static_cast<int>(max(most2 & 0xffffu, most2 >> 16));
+    const int up = most == 0 ? 0 : 64 + kQueryTop - most;
+    if (h == 0) pair_down[j] = most == 0 ? 0.f : __builtin_ldexpf(1.f, -up);   // (not in any product: no say in the page's scale)
+    f16x2 hi, rest;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int j = (dim + e) & (kPairs - 1), comp = (dim + e) >> 6, kk = j & 15;
-    _Float16* const at = reinterpret_cast<_Float16*>(q.pairs + (j >> 4) * kQueryBlock + kk * 128 + comp * 2);
-    const float x = sign * __builtin_ldexpf(v[e], shift + up[e]);
-    const _Float16 hi = static_cast<_Float16>(x);
-    const _Float16 rest = Q32 ? static_cast<_Float16>(x - static_cast<float>(hi)) : hi;
-    const _Float16 none = static_cast<_Float16>(0.f);
+    for (int comp = 0; comp < 2; ++comp) {
+      const float x = sign * __builtin_ldexpf(v[e][comp], shift + up);
+      hi[comp] = static_cast<_Float16>(x);
+      rest[comp] = Q32 ? static_cast<_Float16>(x - static_cast<float>(hi[comp])) : hi[comp];
+    }
+    uint8_t* const at = q.pairs + (j >> 4) * kQueryBlock + kk * 128 + h * 8;
 #pragma unroll
     for (int half = 0; half < 8 / NH; ++half) {
       const bool here = NH == 8 || ((kk >> 1) & 1) == half;
-      _Float16* const high = at + (half * NH + h) * 4;
-      _Float16* const low = high + 8 * 4;
-      high[0] = low[0] = here ? hi : none;
-      high[2] = none;
-      low[2] = here ? rest : none;
+      const uint32_t hw = here ? __builtin_bit_cast(uint32_t, hi) : 0u, rw = here ? __builtin_bit_cast(uint32_t, rest) : 0u;
+      *reinterpret_cast<u32x2*>(at + half * NH * 8) = u32x2{hw, 0u};
+      *reinterpret_cast<u32x2*>(at + half * NH * 8 + 64) = u32x2{hw, rw};
     }
   }
   if ((tid & 31) == 0) shifts[h] = shift;
@@ -639,10 +643,11 @@ __device__ __forceinline__ constexpr float code_unscale(int k) {
 }
 
 // ---- attention ----------------------------------------------------------------------------------
-// kCut: the chunks are cut on the device (a.spare_chunks > 0).
-template <int W, int VB, int NH, bool Q32, bool kCut>
+// kCut: the chunks are cut on the device (a.spare_chunks > 0).  kMatWaves: wavefronts of the work-group, 4 or 8.
+template <int W, int VB, int NH, bool Q32, bool kCut, int kMatWaves>
 __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   constexpr int UB = 2 * W;
+  constexpr int kMatThreads = kMatWaves * 64;
   constexpr bool kQuantV = VB != 16;
   constexpr TokenOrder kOrder = token_order(VB);
   constexpr int kChain = kQuantV ? 16 : 4;
@@ -673,11 +678,11 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     float red_ml[kMatWaves][NH][3];                                      // m, l, sum of p * zero-point
     int q_shift[kMaxHeads];
     float pair_down[kPairs];
-    uint16_t exponents[NH][kHeadDim];
+    __attribute__((aligned(16))) uint16_t exponents[kPairs][NH];
     int stage;
   };
   __shared__ Shared sh;
-  static_assert(sizeof(Shared) <= 80 * 1024, "two work-groups per compute unit");
+  static_assert(sizeof(Shared) <= (kMatWaves == 4 ? 80 : 160) * 1024, "eight wavefronts per compute unit");
 
   const int tid = threadIdx.x;
   const int wave = uni(tid >> 6);
@@ -997,7 +1002,13 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     rc_cur = rc_nxt; rp_cur = rp_nxt; rv_cur = rv_nxt; rvp_cur = rvp_nxt; nv_cur = nv_nxt; rot_cur = rot_nxt;
   }
 
-  // ---- fold the four wavefronts: maxima and sums through LDS, then the accumulators, where the key table was ----
+  auto top_of = [&](int h) {                                           // the wavefronts' largest maximum
+    float m = sh.red_ml[0][h][0];
+#pragma unroll
+    for (int v = 1; v < kMatWaves; ++v) m = fmaxf(m, sh.red_ml[v][h][0]);
+    return m;
+  };
+  // ---- fold the wavefronts: maxima and sums through LDS, then the accumulators, where the key table was ----
   {
     const int lane = lane_id(), row = lane >> 4, col = lane & 15;
     const int acc_head = NH == 8 ? 4 * (row & 1) : 0;                  // head of accumulator row i: acc_head + i
@@ -1026,7 +1037,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int h = acc_head + i;
-      const float M = fmaxf(fmaxf(sh.red_ml[0][h][0], sh.red_ml[1][h][0]), fmaxf(sh.red_ml[2][h][0], sh.red_ml[3][h][0]));
+      const float M = top_of(h);
       wgt[i] = M > kNegInf ? __builtin_amdgcn_exp2f(sh.red_ml[wave][h][0] - M) : 0.f;
       if constexpr (kQuantV) wgt[i] = __builtin_ldexpf(wgt[i], -s_exp);
     }
@@ -1049,9 +1060,10 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   }
 
   finish_chunk<NH>(a, seq, kvh, chunk, n_chunks, row0, stride, wave * 64 + lane_id(), [&](int h, int quad, float& M, float& l) {
-    M = fmaxf(fmaxf(sh.red_ml[0][h][0], sh.red_ml[1][h][0]), fmaxf(sh.red_ml[2][h][0], sh.red_ml[3][h][0]));
+    M = top_of(h);
     auto part = [&](int v) { return *reinterpret_cast<const f32x4*>(&sh.red[v][h][quad * 4]); };
     f32x4 o = (part(0) + part(2)) + (part(1) + part(3));
+    if constexpr (kMatWaves == 8) o += (part(4) + part(6)) + (part(5) + part(7));
     l = 0.f;
     if (M > kNegInf) {
       float zp = 0.f;                                                  // zero-point term: the same for every dim

@@ -90,14 +90,22 @@ template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_of_u32(uint32_t x) {
   return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, 0xf, 0xf, true));
 }
-// Maximum / sum over the wavefront, as a scalar.
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+// Maximum over each half of the wavefront, in all of its lanes.
+__device__ __forceinline__ uint32_t half_wave_max_u32(uint32_t x) {
   x = max(x, dpp_of_u32<0xB1>(x));
   x = max(x, dpp_of_u32<0x4E>(x));
   x = max(x, dpp_of_u32<0x141>(x));
   x = max(x, dpp_of_u32<0x140>(x));
   auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-  x = max(r[0], r[1]);
+  return max(r[0], r[1]);
+}
+__device__ __forceinline__ uint32_t max_u16x2(uint32_t a, uint32_t b) {
+  typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+// Maximum / sum over the wavefront, as a scalar.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+  x = half_wave_max_u32(x);
   auto s = __builtin_amdgcn_permlane32_swap(x, x, false, false);
   return static_cast<uint32_t>(uni(static_cast<int>(max(s[0], s[1]))));
 }
@@ -273,8 +281,8 @@ constexpr int kFinishLdsFloats = kFinishThreads * 5;
 
 // End of a chunk.  `partial(h, quad, M, l)` returns the chunk's un-normalised output for query head
 // h (of the a.n_heads <= NH this launch serves) and dimensions 4 quad .. 4 quad + 3, and sets the
-// head's running maximum M (log2 units) and denominator l.  All kFinishThreads threads of the
-// work-group call this; `lent` may be what `partial` reads, `stage` is a word of LDS.
+// head's running maximum M (log2 units) and denominator l.  All threads of the
+// work-group call this, the first kFinishThreads do the work; `lent` may be what `partial` reads, `stage` is a word of LDS.
 //
 // Partials that are combined in the kernel travel between work-groups that may sit on different
 // XCDs, each with an L2 of its own.  They are written and read with device-coherent accesses
@@ -361,8 +369,10 @@ __device__ __forceinline__ void finish_chunk(const DecodeArgs& a, int seq, int k
     float* const part_l = lent + kFinishThreads * 4;
     const float top = fmaxf(m, __shfl_xor(m, 32));
     const float wgt = top > kNegInf ? __builtin_amdgcn_exp2f(m - top) : 0.f;
-    part_o[tid] = r * wgt;
-    part_l[tid] = lt * wgt;
+    if (tid < kFinishThreads) {
+      part_o[tid] = r * wgt;
+      part_l[tid] = lt * wgt;
+    }
     __syncthreads();
     if (slice == 0) {
       r = part_o[tid] + part_o[tid + 32];
