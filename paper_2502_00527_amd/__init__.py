@@ -4,8 +4,10 @@ Every step of the path -- encoding keys into the polar-quantized cache (paper
 Section 3.2) and decode attention through the per-query lookup table (Section
 3.3, Appendix A) -- runs in the HIP kernels behind the C ABI.  This module
 turns torch tensors into device pointers and sizes, passes torch's current HIP
-stream, and raises on any non-zero status.  There is no fallback: if the
-shared library has not been built (`python -m paper_2502_00527_amd.build`),
+stream, and raises on any non-zero status.  The calls of a serving loop are marshalled
+natively (csrc/pq_binding.cpp, `_native`); what that declines -- a wrong argument, or an
+unusual one -- goes through the functions here, which raise or do the same by ctypes.  There is
+no fallback for the kernels: if the shared library has not been built (`python -m paper_2502_00527_amd.build`),
 the first call raises.
 
 The functions carry the names of the C entry points.
@@ -13,6 +15,7 @@ The functions carry the names of the C entry points.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 from ctypes import c_float, c_int, c_int32, c_int64, c_size_t, c_void_p
 from typing import Optional
@@ -31,6 +34,7 @@ PQ_F16, PQ_F32 = 0, 1
 PQ_STATIC_SCRATCH_BYTES = 8 << 20
 _LIB_NAME = "libpolarquant.so"
 _lib = None
+_calls = None
 
 
 class PolarQuantError(RuntimeError):
@@ -101,6 +105,29 @@ def load_library():
             fn.restype, fn.argtypes = res, args
         _lib = lib
     return _lib
+
+
+def _marshaller():
+    """The native marshalling module; raises if it is not built, like load_library()."""
+    global _calls
+    if _calls is None:
+        load_library()
+        try:
+            import torch  # noqa: F401  (the module is linked against its libraries)
+            module = importlib.import_module("._native", __package__)
+        except ImportError as e:
+            raise PolarQuantError(
+                f"the native binding cannot be loaded ({e}): build it with `python -m paper_2502_00527_amd.build`") from e
+        _calls = module
+    return _calls
+
+
+def _done(status, what: str) -> bool:
+    """What a native call returned: False if it declined, an error's exception raised."""
+    if status is None:
+        return False
+    _check(status, what)
+    return True
 
 
 def _check(status: int, what: str) -> None:
@@ -183,6 +210,8 @@ def _key_pool_pages(layout: Layout, codes_pool, params_pool) -> int:
 def pq_encode_keys(layout: Layout, keys, page_ids, codes_pool, params_pool) -> None:
     """keys [n_tokens, n_kv_heads, d] (last dim contiguous, fp16/fp32, device); page_ids int32
     [ceil(n_tokens/g)] device; pools uint8 device tensors holding whole pages."""
+    if _done((_calls or _marshaller()).encode_keys(layout, keys, page_ids, codes_pool, params_pool), "pq_encode_keys"):
+        return
     import torch
     if keys.dim() != 3 or keys.shape[1] != layout.n_kv_heads or keys.shape[2] != layout.head_dim:
         raise PolarQuantError("keys must be [n_tokens, n_kv_heads, head_dim]")
@@ -223,6 +252,10 @@ def pq_decode_attention(layout: Layout, q, codes_pool, params_pool, v_pool, bloc
     """One decode step per sequence; see include/polarquant.h.  `out` fp32 [n_seqs, n_q_heads, d];
     `scores` optional fp32 [n_seqs, n_q_heads, stride >= max_seq_len]; `workspace` a uint8 device
     tensor of at least pq_decode_workspace_bytes(...) bytes."""
+    if _done((_calls or _marshaller()).decode_attention(
+            layout, q, codes_pool, params_pool, v_pool, block_table, seq_lens, max_seq_len, sm_scale, out, workspace, scores,
+            residual, v_bits, v_params), "pq_decode_attention"):
+        return
     import torch
     c = _decode_common(layout, q, codes_pool, params_pool, v_pool, block_table, seq_lens, v_bits, v_params)
     st = load_library().pq_decode_attention(
@@ -289,6 +322,8 @@ def pq_vq_params_bytes_per_page(layout: Layout) -> int:
 def pq_encode_values(layout: Layout, v_bits: int, values, page_ids, vq_pool, vq_params) -> None:
     """values fp16 [n_tokens, n_kv_heads, d] (last dim contiguous, device); vq_pool uint8, vq_params fp16
     device tensors holding whole pages."""
+    if _done((_calls or _marshaller()).encode_values(layout, v_bits, values, page_ids, vq_pool, vq_params), "pq_encode_values"):
+        return
     import torch
     if values.dim() != 3 or values.shape[1] != layout.n_kv_heads or values.shape[2] != layout.head_dim:
         raise PolarQuantError("values must be [n_tokens, n_kv_heads, head_dim]")
@@ -305,6 +340,9 @@ def pq_encode_values(layout: Layout, v_bits: int, values, page_ids, vq_pool, vq_
 def pq_append_keys(layout: Layout, new_keys, residual, seq_lens, block_table, codes_pool, params_pool) -> None:
     """new_keys [n_seqs, n_kv_heads, d] fp16/fp32; residual fp16 [n_seqs, n_kv_heads, g, d]; seq_lens int32
     [n_seqs] = lengths before the append (the caller increments them afterwards)."""
+    if _done((_calls or _marshaller()).append_keys(
+            layout, new_keys, residual, seq_lens, block_table, codes_pool, params_pool), "pq_append_keys"):
+        return
     import torch
     if new_keys.dim() != 3 or new_keys.shape[1] != layout.n_kv_heads or new_keys.shape[2] != layout.head_dim:
         raise PolarQuantError("new_keys must be [n_seqs, n_kv_heads, head_dim]")
@@ -321,6 +359,9 @@ def pq_score_keys(layout: Layout, q, codes_pool, params_pool, block_table, seq_l
                   scores, residual=None) -> None:
     """Raw q . k~ of every cached token; `scores` fp32 [n_seqs, n_q_heads, stride >= max_seq_len];
     `residual` optional fp16 [n_seqs, n_kv_heads, g, d] (the un-quantized keys of the last group)."""
+    if _done((_calls or _marshaller()).score_keys(
+            layout, q, codes_pool, params_pool, block_table, seq_lens, max_seq_len, scores, residual), "pq_score_keys"):
+        return
     import torch
     if q.dim() != 3 or q.shape[2] != layout.head_dim:
         raise PolarQuantError("q must be [n_seqs, n_q_heads, head_dim]")

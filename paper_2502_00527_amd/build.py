@@ -1,4 +1,5 @@
-"""Builds libpolarquant.so (the HIP kernels and their C ABI) for gfx950, in-tree.
+"""Builds libpolarquant.so (the HIP kernels and their C ABI) for gfx950, and the Python binding's
+native part (_native.so), in-tree.
 
 `python -m paper_2502_00527_amd.build` compiles every source under csrc/ with
 hipcc; it cross-compiles without a GPU.  The flags matter for correctness:
@@ -12,6 +13,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
@@ -19,6 +21,10 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libpolarquant.so")
 SOURCES = ["pq_api.hip", "pq_encode.hip", "pq_values.hip", "pq_decode.hip", "pq_decode_matrix.hip", "pq_decode_matrix_v4.hip", "pq_decode_matrix_v2.hip",
            "pq_decode_partials_ga.hip"]
+
+# the Python binding's argument marshalling (host code only)
+BINDING = "pq_binding.cpp"
+BINDING_PATH = os.path.join(PKG_DIR, "_native.so")
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -40,6 +46,19 @@ def _filter(text: str) -> str:
                      if "packed-fp32-ops" not in l and "is not a recognized feature" not in l)
 
 
+def _binding_commands(inc, obj):
+    """Compile and link commands of the binding; it finds libpolarquant.so beside itself."""
+    import torch
+    from torch.utils import cpp_extension
+    torch_inc = [f for d in cpp_extension.include_paths() for f in ("-isystem", d)]
+    abi = f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"
+    compile_ = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", abi, *inc, *torch_inc, "-isystem", sysconfig.get_paths()["include"],
+                "-c", os.path.join(CSRC, BINDING), "-o", obj]
+    link = ["g++", "-shared", obj, "-o", BINDING_PATH, "-L", PKG_DIR, "-lpolarquant", "-Wl,-rpath,$ORIGIN",
+            *[f for d in cpp_extension.library_paths() for f in ("-L", d)], "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    return compile_, link
+
+
 def build(verbose: bool = True, extra_flags=()) -> str:
     """Compiles every translation unit (in parallel) and links libpolarquant.so."""
     obj_dir = os.path.join(PKG_DIR, "_build")
@@ -52,6 +71,11 @@ def build(verbose: bool = True, extra_flags=()) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, obj, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    binding_obj = os.path.join(obj_dir, BINDING.replace(".cpp", ".o"))
+    compile_, link_binding = _binding_commands(inc, binding_obj)
+    if verbose:
+        print(" ".join(compile_), flush=True)
+    binding = subprocess.Popen(compile_, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     objs = []
     for src, obj, proc in procs:
         out, _ = proc.communicate()
@@ -66,6 +90,12 @@ def build(verbose: bool = True, extra_flags=()) -> str:
     res = subprocess.run(link, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("link failed:\n" + _filter(res.stdout + res.stderr))
+    out, _ = binding.communicate()
+    if binding.returncode != 0:
+        raise RuntimeError(f"g++ failed on {BINDING}:\n{out}")
+    res = subprocess.run(link_binding, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("link of the binding failed:\n" + res.stdout + res.stderr)
     return LIB_PATH
 
 

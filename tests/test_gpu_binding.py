@@ -1,0 +1,60 @@
+"""The two ways the arguments of a call are marshalled."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("op,v_bits", [("decode", 16), ("decode", 2), ("score", 16), ("prefill", 4), ("serve", 16)])
+def test_both_ways_of_marshalling_make_the_same_call(op, v_bits, monkeypatch):
+    """With the native module declining everything the calls go through ctypes."""
+    from perf import cases
+
+    pq = cases.pq
+    case = cases._case("both", op, 3, 8, 2, 700, min_context=700 if op == "prefill" else 300, v_bits=v_bits, shuffled_pages=True)
+    native = cases.run(cases.prepare(case, 9))
+
+    class Declines:
+        def __getattr__(self, name):
+            return lambda *a: None
+
+    pq._marshaller()
+    monkeypatch.setattr(pq, "_calls", Declines())
+    by_ctypes = cases.run(cases.prepare(case, 9))
+    as_tuple = lambda x: x if isinstance(x, tuple) else (x,)
+    for a, b in zip(as_tuple(native), as_tuple(by_ctypes)):
+        assert torch.equal(a, b)
+
+
+def test_what_the_native_module_declines_still_works_or_raises():
+    from perf import cases
+
+    pq = cases.pq
+    state = cases.prepare(cases._case("odd", "decode", 2, 8, 2, 700, min_context=300), 11)
+    want = cases.run(state).clone()
+    calls = pq._marshaller()
+    args = [state[k] for k in ("layout", "q", "codes", "params", "v_pool", "block_table", "seq_lens", "max_seq_len", "sm_scale", "out", "workspace")]
+    assert calls.decode_attention(*args, None, None, 16, None) == 0
+    for at, odd in ((7, np.int64(state["max_seq_len"])), (8, np.float32(state["sm_scale"])), (1, torch.nn.Parameter(state["q"], requires_grad=False))):
+        unusual = list(args)
+        unusual[at] = odd
+        state["out"].zero_()
+        pq.pq_decode_attention(*unusual)
+        assert torch.equal(state["out"], want)
+    for at, wrong in ((1, state["q"].double()), (1, state["q"].transpose(0, 1)), (2, state["codes"].cpu()), (5, state["block_table"].long()),
+                      (6, state["seq_lens"].float()), (4, state["v_pool"][:1]), (9, state["out"].half()), (3, state["params"][:1])):
+        bad = list(args)
+        bad[at] = wrong
+        assert calls.decode_attention(*bad, None, None, 16, None) is None
+        with pytest.raises(pq.PolarQuantError):
+            pq.pq_decode_attention(*bad)
+    with pytest.raises(pq.PolarQuantError, match="workspace"):
+        pq.pq_decode_attention(*args[:10], state["workspace"][:256])
+    with torch.cuda.stream(torch.cuda.Stream()):                          # torch's current stream, not the default one
+        torch.cuda.current_stream().wait_stream(torch.cuda.default_stream())
+        state["out"].zero_()
+        cases.run(state)
+        got = state["out"].clone()
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
