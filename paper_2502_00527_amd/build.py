@@ -20,7 +20,7 @@ ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libpolarquant.so")
 SOURCES = ["pq_api.hip", "pq_encode.hip", "pq_values.hip", "pq_decode.hip", "pq_decode_matrix.hip", "pq_decode_matrix_v4.hip", "pq_decode_matrix_v2.hip",
-           "pq_decode_partials_ga.hip"]
+           "pq_decode_partials_ga.hip", "pq_decode_grouped.hip", "pq_decode_grouped_v4.hip", "pq_decode_grouped_v2.hip"]
 
 # the Python binding's argument marshalling (host code only)
 BINDING = "pq_binding.cpp"

@@ -82,8 +82,8 @@ __global__ __launch_bounds__(kMergeThreads) void pq_decode_merge_kernel(
   }
 }
 
-// Score-only kernels: the kernel whose lanes are tokens on the uniform grid; the grouped quantizer has
-// one of its own (a table per page).
+// Score-only kernels on the vector unit: the kernel whose lanes are tokens on the uniform grid; the grouped quantizer
+// has one of its own (a table per page).
 template <int G, int RB, int TB, bool kGrouped>
 void launch_scores_one(const DecodeArgs& a, dim3 grid, hipStream_t st) {
   if constexpr (kGrouped) hipLaunchKernelGGL((pq_score_keys_kernel<G, RB, TB>), grid, dim3(kThreads), 0, st, a);
@@ -142,6 +142,20 @@ bool launch_attention(int w, int v_bits, bool roles, const DecodeArgs& a, dim3 g
     case 16: return launch_attention_matrix_v16(w, roles, a, grid, st);
     case 4: return launch_attention_matrix_v4(w, roles, a, grid, st);
     case 2: return launch_attention_matrix_v2(w, roles, a, grid, st);
+    default: return false;
+  }
+}
+
+// Grouped angle quantizer: query heads per KV head from which on the kernels of pq_decode_matrix.hpp take over.  They make
+// the keys' coordinates, whatever the number of heads (about 8 instructions a symbol); the vector unit's take 3 + heads, and
+// heads times as many for the values.
+constexpr int kGroupedMatrixHeads = 3;
+bool grouped_on_matrix(const pq_layout* l, int group_total) { return l->angle_quantizer == PQ_ANGLE_GROUPED && group_total >= kGroupedMatrixHeads; }
+bool launch_grouped(int rt, int v_bits, const DecodeArgs& a, dim3 grid, hipStream_t st) {
+  switch (v_bits) {
+    case 16: return launch_attention_grouped_v16(rt, a, grid, st);
+    case 4: return launch_attention_grouped_v4(rt, a, grid, st);
+    case 2: return launch_attention_grouped_v2(rt, a, grid, st);
     default: return false;
   }
 }
@@ -309,15 +323,19 @@ ChunkPlan plan_score_chunks(int32_t n_seqs, int32_t n_kv_heads, int32_t max_seq_
 
 // The raw scores of a launch, pass by pass over the query heads of a KV head; `a` is complete but for
 // what depends on the pass and the chunks.  Scores come from here whoever asks for them, so that
-// they are the same bit for bit: on the uniform grid the attention kernel, whose own scores are rounded
+// they are the same bit for bit: the attention kernels on the matrix cores, whose own scores are rounded
 // otherwise, does not store them (and cannot read them back: its output would depend on whether they
 // were asked for).
 int launch_scores(const pq_layout* layout, DecodeArgs a, hipStream_t stream) {
   const bool grouped = layout->angle_quantizer == PQ_ANGLE_GROUPED;
   const int rt = layout->r_bits * 10 + layout->t_bits;
+  // On the matrix cores where the vector unit takes more than one pass over the keys (8 x 8K tokens, 8 heads per KV head:
+  // 36 -> 22 us; 4 heads, 8 x 32K: 57 against 64), and for fp16 queries only: an fp32 query enters as two fp16 parts, and
+  // the scores' error would be 1.38e-7 of their 2-norm where fp32 multiply-adds have 1.30e-7 (fp16 queries: 1.33e-7 and 1.34e-7).
+  const bool matrix = grouped_on_matrix(layout, a.group_total) && a.group_total != 4 && !a.q_is_f32;
   // the token-lane kernel addresses the score rows of a pass with 32-bit byte offsets from the first
   const int most = grouped || a.scores_stride < (int64_t{1} << 28) ? 4 : 1;
-  const ChunkPlan plan = plan_score_chunks(a.n_seqs, a.n_kv_heads, a.max_seq_len, grouped ? 2 : 4);
+  const ChunkPlan plan = plan_score_chunks(a.n_seqs, a.n_kv_heads, a.max_seq_len, matrix ? (layout->t_bits == 5 ? 2 : 3) : (grouped ? 2 : 4));
   if (plan.n_chunks > 65535) return PQ_ERR_UNSUPPORTED;   // grid.z
   a.pages_per_chunk = plan.pages_per_chunk;
   a.n_chunks = plan.n_chunks;
@@ -325,10 +343,11 @@ int launch_scores(const pq_layout* layout, DecodeArgs a, hipStream_t stream) {
   hipError_t e = hipSuccess;
   for (int head0 = 0; head0 < a.group_total && e == hipSuccess;) {
     const int left = a.group_total - head0;
-    const int G = std::min(most, left >= 4 ? 4 : (left >= 2 ? 2 : 1));
+    const int G = matrix ? std::min(left, kMaxHeads) : std::min(most, left >= 4 ? 4 : (left >= 2 ? 2 : 1));
     a.head0 = head0;
     a.n_heads = G;
-    const bool found = grouped ? launch_scores_rt<true>(rt, G, a, grid, stream) : launch_scores_rt<false>(rt, G, a, grid, stream);
+    const bool found = matrix ? launch_scores_grouped(rt, a, grid, stream)
+                       : grouped ? launch_scores_rt<true>(rt, G, a, grid, stream) : launch_scores_rt<false>(rt, G, a, grid, stream);
     if (!found) return PQ_ERR_UNSUPPORTED;   // not reached: layout_supported() admits what is built
     e = hipGetLastError();
     head0 += G;
@@ -447,18 +466,21 @@ int decode_launch(const pq_layout* layout, const void* q, pq_dtype q_dtype, int3
   const dim3 grid = a.spare_chunks > 0 ? dim3(layout->n_kv_heads, n_seqs + a.spare_chunks) : dim3(layout->n_kv_heads, n_seqs, plan.n_chunks);
   a.wide_groups = out != nullptr && wide_groups(layout, plan, n_seqs, max_seq_len) ? 1 : 0;
   a.table_index = key_table_index(layout);
-  if (scores && !grouped) {
+  // A pass over the cache serves up to 8 query heads of a KV head (with the grouped quantizer on the vector unit, whose kernel
+  // stores its scores itself, all one or two).
+  const bool vector = grouped && !grouped_on_matrix(layout, group_total);
+  if (scores && !vector) {
     const int ss = launch_scores(layout, a, stream);
     if (ss != PQ_OK) return ss;
   }
   hipError_t e = hipSuccess;
-  // A pass over the cache serves up to 8 query heads of a KV head; with the grouped quantizer 4, 2 or 1.
   for (int head0 = 0; head0 < group_total && e == hipSuccess;) {
     const int left = group_total - head0;
-    const int G = grouped ? (left >= 4 ? 4 : (left >= 2 ? 2 : 1)) : std::min(left, kMaxHeads);
+    const int G = std::min(left, kMaxHeads);
     a.head0 = head0;
     a.n_heads = G;
-    const bool found = grouped ? launch_attention_partials_ga(rt, G, v_bits, a, grid, stream)
+    const bool found = vector ? launch_attention_partials_ga(rt, G, v_bits, a, grid, stream)
+                       : grouped ? launch_grouped(rt, v_bits, a, grid, stream)
                        : launch_attention(layout->r_bits + layout->t_bits, v_bits, roles, a, grid, stream);
     if (!found) return PQ_ERR_UNSUPPORTED;   // not reached: layout_supported() admits what is built
     e = hipGetLastError();

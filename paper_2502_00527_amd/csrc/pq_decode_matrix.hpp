@@ -42,6 +42,11 @@ namespace pq {
 bool launch_attention_matrix_v16(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st);
 bool launch_attention_matrix_v4(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st);
 bool launch_attention_matrix_v2(int w, bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st);
+// Grouped angle quantizer (pq_decode_grouped.hip, one per value width), rt = 10 r + t; and its raw scores alone.
+bool launch_attention_grouped_v16(int rt, const DecodeArgs& a, dim3 grid, hipStream_t st);
+bool launch_attention_grouped_v4(int rt, const DecodeArgs& a, dim3 grid, hipStream_t st);
+bool launch_attention_grouped_v2(int rt, const DecodeArgs& a, dim3 grid, hipStream_t st);
+bool launch_scores_grouped(int rt, const DecodeArgs& a, dim3 grid, hipStream_t st);
 
 namespace {
 
@@ -169,6 +174,9 @@ struct QueryFetch {
   template <bool Q32>
   __device__ __forceinline__ float value(int comp, int e) const {
     return Q32 ? u2f(w[2 * comp + e]) : static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w[comp] >> (16 * e))));
+  }
+  __device__ __forceinline__ QueryFetch widened() const {     // fp16 elements as fp32 ones
+    return {{f2u(value<false>(0, 0)), f2u(value<false>(0, 1)), f2u(value<false>(1, 0)), f2u(value<false>(1, 1))}};
   }
 };
 template <bool Q32>
@@ -337,6 +345,62 @@ __device__ __forceinline__ int row_token(int m) {                // part of the 
   return O == TokenOrder::kRows ? 4 * (m & 3) + (m >> 2) : (O == TokenOrder::kPlain ? m : 8 * (m >> 2) + (m & 3));
 }
 
+// Sums of a head's columns.  NH = 8: s[t] of all batches in both columns of a head.  NH = 4: the columns of half 0
+// keep batches 0 .. 3, those of half 1 batches 4 .. 7, in s[0] .. s[3].
+template <int NH>
+__device__ __forceinline__ void fold_columns(f32x4 (&s)[8], bool half) {
+  if constexpr (NH == 4) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[t][i] += dpp_of<0x124>(s[t][i]);     // row_ror:4: the neighbour in (part, half)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        s[j][i] = half ? s[4 + j][i] : s[j][i];
+        s[j][i] += dpp_of<0x128>(s[j][i]);                               // row_ror:8: the other two
+      }
+  } else {
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[t][i] += dpp_of<0x128>(s[t][i]);
+  }
+}
+// Scores of the residual group (un-quantized fp16 keys, rows past nv_res read as zero), not yet folded: a key row
+// is an operand as it lies in memory, 32 dims per instruction.  query(kd, j0, e): the column's query of dims
+// 32 kd + 8 row + 2 e, + 1 -- one coordinate of pairs j0 + 2 e, + 1 -- as an fp16 pair.
+template <TokenOrder O, typename Query>
+__device__ __forceinline__ void residual_products(f32x4 (&s)[8], const __half* rows, int nv_res, int rot, int lane, Query query) {
+  const __amdgpu_buffer_rsrc_t rs = make_rsrc(rows, static_cast<uint32_t>(nv_res) * (kHeadDim * 2));
+  const int row = lane >> 4, col = lane & 15;
+  f16x8 q8[4];
+#pragma unroll
+  for (int kd = 0; kd < 4; ++kd) {
+    const int j0 = 32 * (kd & 1) + 8 * row;
+    uint32_t w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = query(kd, j0, e);
+    q8[kd] = as_operand(w[0], w[1], w[2], w[3]);
+  }
+  const uint32_t voff = row_token<O>(col) * (kHeadDim * 2) + row * 16;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const uint32_t soff = static_cast<uint32_t>(batch_token<O>(t, rot)) * (kHeadDim * 2);
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 lo = zero, hi = zero;
+#pragma unroll
+    for (int kd = 0; kd < 4; ++kd) {
+      const f16x8 k_op = as_operand(buf_load16<kAuxCached>(rs, voff, soff + kd * 64));
+      if (kd < 2) lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(k_op, q8[kd], lo, 0, 0, 0);
+      else hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(k_op, q8[kd], hi, 0, 0, 0);
+    }
+    s[t] = lo + hi;
+    if (t & 1) __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // One wavefront's key codes and parameters of a page, and the walk over them.  Operand lane =
 // (token row l % 16, pair block l / 16), pair 16 (l / 16) + kk in step kk; result lane = (column
 // l % 16, tokens 4 (l / 16) .. + 3).  The table reads run 4 or 8 instructions ahead (8 where there are registers for it); as a unit is used
@@ -474,7 +538,7 @@ struct ScoreWalk {
       steps<H + 1>(rc_nxt, rot_nxt);
     }
   }
-  // Scores of the page in cu / par, summed over the columns of a head and left as fold() says, scaled
+  // Scores of the page in cu / par, summed over the columns of a head and left as fold_columns() says, scaled
   // by 2^(k + the head's query shift + kTableShift); returns k.  cu and par then hold the next page.
   __device__ __forceinline__ int run(__amdgpu_buffer_rsrc_t rc_nxt, __amdgpu_buffer_rsrc_t rp_nxt, int rot_nxt, int lane) {
     issue<0>(rc_nxt, rot_nxt);
@@ -498,78 +562,218 @@ struct ScoreWalk {
 #pragma unroll
       for (int j = 0; j < 4; ++j) s[4 + j] += done[j];
     }
-    fold(lane & 4);
+    fold_columns<NH>(s, lane & 4);
     wave_lds_sync();
     return k;
   }
-  // NH = 8: s[t] of all batches in both columns of a head.  NH = 4: the columns of half 0 keep batches
-  // 0 .. 3, those of half 1 batches 4 .. 7, in s[0] .. s[3].
-  __device__ __forceinline__ void fold(bool half) {
-    if constexpr (NH == 4) {
+  // Scaled with k = 0, table shift 0.
+  __device__ __forceinline__ void residual(const __half* rows, int nv_res, int rot, int lane) {
+    const uint32_t q0 = q_addr - (static_cast<uint32_t>(lane) >> 4) * kQueryBlock;
+    residual_products<O>(s, rows, nv_res, rot, lane, [&](int kd, int j0, int e) {
+      // the query in high-part columns, what its rounding to fp16 left over in low-part ones
+      const uint32_t at = q0 + (j0 >> 4) * kQueryBlock + (j0 & 15) * 128;
+      uint32_t x[2];
 #pragma unroll
-      for (int t = 0; t < 8; ++t)
+      for (int o = 0; o < 2; ++o) {
+        const u32x2 v = *(const PQ_LDS u32x2*)static_cast<uintptr_t>(at + (2 * e + o) * 128);
+        const uint32_t pick = (v.x & ~low_mask) | (Q32 ? v.y : 0u);
+        // without the pair's scale: no parameter carries the other half of it here
+        const float down = *(const PQ_LDS float*)static_cast<uintptr_t>(down_addr + (j0 + 2 * e + o) * 4);
+        const f16x2 picked = u2h(pick);
+        x[o] = h2u(to_half2(static_cast<float>((kd >> 1) ? picked.y : picked.x) * down, 0.f));
+      }
+      return x[0] | (x[1] << 16);
+    });
+    fold_columns<NH>(s, lane & 4);
+  }
+};
+
+// ---- scores of a page, grouped angle quantizer ------------------------------------------------------
+// The angle levels belong to the page, so that the key side cannot be a table of symbols: every wavefront keeps
+// the (cos, sin) of its page's 64 x 2^t angle states in LDS (built anew for each page) and makes the key's
+// coordinates rho~ cos theta~, rho~ sin theta~ themselves, in fp32, each handed to the matrix unit as two fp16
+// parts (24 bits).  The query side {q_x, q_y} is constant: high part in columns 0 - 7, what its rounding
+// left over in columns 8 - 15.  One instruction takes two pairs of each of the four blocks; any group of 1 to 8 query
+// heads costs the same.  About 8 vector instructions a symbol; with a table of the heads' products and fp32
+// multiply-adds (pq_decode_partials_kernel) it is 3 + heads, and values cost heads times as much as here.
+//
+// Table entry of (pair j, state a): 8 bytes at (j / 2) 2^t 16 + 16 a + 8 ((j + j / 16) % 2): a block's two pairs of an
+// instruction share a row, and neighbouring blocks, which are read together, use the other half of the banks.
+constexpr int kGroupedTop = 13;                  // the page's radii are brought below 2^(kGroupedTop + 2)
+constexpr int kGroupedQueryTop = 14;
+constexpr int kGroupedQueryBlock = 8 * 16 * 8 + 128;
+struct GroupedQuery {                            // [block][pair / 2 of the block][column]{x, y of the even pair, of the odd one}
+  __attribute__((aligned(16))) uint8_t pairs[kBlocks * kGroupedQueryBlock];
+};
+// Each head's largest element is brought into [2^14, 2^15); `shifts` says by which power of two.
+template <int NH>
+__device__ __forceinline__ void store_grouped_query(GroupedQuery& q, int* shifts, const QueryFetch& f, float sign, int tid) {
+  const int h = tid >> 5, j0 = (tid & 31) * 2;
+  float v[2][2];
+  uint32_t top = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s[t][i] += dpp_of<0x124>(s[t][i]);     // row_ror:4: the neighbour in (part, half)
+  for (int e = 0; e < 2; ++e)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+    for (int comp = 0; comp < 2; ++comp) {
+      v[e][comp] = f.value<true>(comp, e);
+      top = max(top, f2u(v[e][comp]) & 0x7fffffffu);
+    }
+  const int shift = min(kGroupedQueryTop + 127 - static_cast<int>(half_wave_max_u32(top) >> 23), 126);
+  if (h >= NH) return;
+  uint32_t hi[2], lo[2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          s[j][i] = half ? s[4 + j][i] : s[j][i];
-          s[j][i] += dpp_of<0x128>(s[j][i]);                               // row_ror:8: the other two
-        }
-    } else {
+  for (int e = 0; e < 2; ++e) {
+    const float x = sign * __builtin_ldexpf(v[e][0], shift), y = sign * __builtin_ldexpf(v[e][1], shift);
+    const f16x2 high = {static_cast<_Float16>(x), static_cast<_Float16>(y)};
+    const f16x2 low = {static_cast<_Float16>(x - static_cast<float>(high.x)), static_cast<_Float16>(y - static_cast<float>(high.y))};
+    hi[e] = __builtin_bit_cast(uint32_t, high);
+    lo[e] = __builtin_bit_cast(uint32_t, low);
+  }
+  const int step = (j0 & 15) >> 1;
+  uint8_t* const at = q.pairs + (j0 >> 4) * kGroupedQueryBlock + step * 128 + h * 8;
 #pragma unroll
-      for (int t = 0; t < 8; ++t)
+  for (int half = 0; half < 8 / NH; ++half) {
+    const bool here = NH == 8 || (step >> 2) == half;
+    *reinterpret_cast<u32x2*>(at + half * NH * 8) = here ? u32x2{hi[0], hi[1]} : u32x2{0u, 0u};
+    *reinterpret_cast<u32x2*>(at + half * NH * 8 + 64) = here ? u32x2{lo[0], lo[1]} : u32x2{0u, 0u};
+  }
+  if ((tid & 31) == 0) shifts[h] = shift;
+}
+
+template <int RB, int TB, TokenOrder O, int NH>
+struct GroupedWalk {
+  static constexpr int W = RB + TB, UB = 2 * W, NA = 1 << TB;
+  static constexpr int kTableBytes = kPairs * NA * 8;
+  static constexpr int kAhead = 3;                // steps (two table reads each) between a read and its use
+  static constexpr int kRing = kAhead + 1;
+  Unit<W / 2> cu[8];
+  uint32_t par, tpar;                             // {fp16 s, fp16 z} of pair `lane`: radius, angle
+  f32x4 s[8], d[4], done[4];
+  f32x2 trig[kRing][2];                           // (cos, sin)
+  float code[kRing][2];
+  f32x4 rad;                                      // {s, z + s / 2} of a step's two pairs, scaled
+  u32x2 qv;
+  uint32_t row_even, row_odd, rad_put, rad_get, q_addr, voff_codes, build_even, build_odd;
+
+  __device__ __forceinline__ void init(const uint8_t* table, const GroupedQuery& q, const f32x2* radii, int lane) {
+    const int row = lane >> 4, col = lane & 15;
+    row_even = lds_addr(table) + row * (8 * NA * 16) + (row & 1) * 8;
+    row_odd = row_even ^ 8u;
+    rad_put = lds_addr(radii) + lane * 8;
+    rad_get = lds_addr(radii) + row * 128;
+    q_addr = lds_addr(q.pairs) + row * kGroupedQueryBlock + col * 8;
+    voff_codes = (row * kGroup + row_token<O>(col)) * UB;
+    const int pair = lane >> TB, state = lane & (NA - 1);
+    build_even = lds_addr(table) + (pair >> 1) * (NA * 16) + state * 16 + (pair & 1) * 8;
+    build_odd = build_even ^ 8u;
+  }
+  __device__ __forceinline__ void load_unit_of(int t, __amdgpu_buffer_rsrc_t rc, int rot) {
+    cu[t] = load_unit<W>(rc, voff_codes, static_cast<uint32_t>(batch_token<O>(t, rot)) * UB);
+  }
+  __device__ __forceinline__ void load_params(__amdgpu_buffer_rsrc_t rp, int lane) {
+    par = buf_load4<kAuxCached>(rp, lane * 4, 0);
+    tpar = buf_load4<kAuxCached>(rp, lane * 4, kPairs * 4);
+  }
+  // (cos, sin) of the page's angle states theta~ = (a + 1/2) s_t + z_t
+  __device__ __forceinline__ void build_table(int lane) {
+    const float level = static_cast<float>(lane & (NA - 1)) + 0.5f;
+    constexpr int kPairsAtOnce = 64 >> TB;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s[t][i] += dpp_of<0x128>(s[t][i]);
+    for (int it = 0; it < NA; ++it) {
+      const uint32_t p = static_cast<uint32_t>(__shfl(static_cast<int>(tpar), it * kPairsAtOnce + (lane >> TB)));
+      const f16x2 sz = u2h(p);
+      const float rev = fmaf(level, static_cast<float>(sz.x), static_cast<float>(sz.y)) * 0.15915494309189535f;   // turns
+      const uint32_t at = ((it * kPairsAtOnce) >> 4) & 1 ? build_odd : build_even;
+      *(PQ_LDS f32x2*)static_cast<uintptr_t>(at + it * (kPairsAtOnce / 2) * (NA * 16)) = f32x2{__builtin_amdgcn_cosf(rev), __builtin_amdgcn_sinf(rev)};
     }
   }
-  // Scores of the residual group (un-quantized fp16 keys, rows past nv_res read as zero): a key row
-  // is an operand as it lies in memory, 32 dims per instruction; same scaling with k = 0, table
-  // shift 0.
-  __device__ __forceinline__ void residual(const __half* rows, int nv_res, int rot, int lane) {
-    const __amdgpu_buffer_rsrc_t rs = make_rsrc(rows, static_cast<uint32_t>(nv_res) * (kHeadDim * 2));
-    const int row = lane >> 4, col = lane & 15;
-    f16x8 q8[4];
-#pragma unroll
-    for (int kd = 0; kd < 4; ++kd) {
-      // dims 32 kd + 8 row .. + 7: one coordinate of 8 consecutive pairs; the query in high-part
-      // columns, what its rounding to fp16 left over in low-part ones
-      const int j0 = 32 * (kd & 1) + 8 * row;
-      const uint32_t at = q_addr - row * kQueryBlock + (j0 >> 4) * kQueryBlock + (j0 & 15) * 128;
+  // Step S: pairs 2 pair_step, + 1 of the lane's block, one batch; half of the batches after the other.  The
+  // instruction rounds at the size of the running sum, which is restarted after two (16 pairs).  With NH = 4 two
+  // accumulators do: a column has zeros in the first or in the last four pair steps.
+  static constexpr int pair_step(int S) { return S % 32 / 4; }
+  static constexpr int batch_of(int S) { return S / 32 * 4 + S % 4; }
+  static constexpr bool to_sum(int j) { return NH == 4 ? j % 4 < 2 : j < 2; }            // (else to d)
+  static constexpr bool starts(int j) { return NH == 4 ? j == 2 : j % 2 == 0; }          // d, from zero
+  static constexpr bool ends(int j) { return NH == 4 ? j == 7 : j > 2 && j % 2 == 1; }   // d is added to the sum, four steps later
+  template <int S>
+  __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rc_nxt, int rot_nxt) {
+    if constexpr (S < 64) {
+      constexpr int j = pair_step(S), t = batch_of(S);
+      uint32_t at;
+      pair_fields<RB, TB, 2 * j>(cu[t], row_even, code[S % kRing][0], at);
+      trig[S % kRing][0] = *(const PQ_LDS f32x2*)static_cast<uintptr_t>(at + j * (NA * 16));
+      pair_fields<RB, TB, 2 * j + 1>(cu[t], row_odd, code[S % kRing][1], at);
+      trig[S % kRing][1] = *(const PQ_LDS f32x2*)static_cast<uintptr_t>(at + j * (NA * 16));
+      if constexpr (j == 7) load_unit_of(t, rc_nxt, rot_nxt);
+    }
+  }
+  template <int S>
+  __device__ __forceinline__ void steps(__amdgpu_buffer_rsrc_t rc_nxt, int rot_nxt) {
+    if constexpr (S < 64) {
+      constexpr int j = pair_step(S), t = batch_of(S);
+      if constexpr (t % 4 == 0) {
+        rad = *(const PQ_LDS f32x4*)static_cast<uintptr_t>(rad_get + j * 16);
+        qv = *(const PQ_LDS u32x2*)static_cast<uintptr_t>(q_addr + j * 128);
+      }
+      issue<S + kAhead>(rc_nxt, rot_nxt);
       uint32_t w[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        uint32_t x[2];
-#pragma unroll
-        for (int o = 0; o < 2; ++o) {
-          const u32x2 v = *(const PQ_LDS u32x2*)static_cast<uintptr_t>(at + (2 * e + o) * 128);
-          const uint32_t pick = (v.x & ~low_mask) | (Q32 ? v.y : 0u);
-          // without the pair's scale: no parameter carries the other half of it here
-          const float down = *(const PQ_LDS float*)static_cast<uintptr_t>(down_addr + (j0 + 2 * e + o) * 4);
-          const f16x2 picked = u2h(pick);
-          x[o] = h2u(to_half2(static_cast<float>((kd >> 1) ? picked.y : picked.x) * down, 0.f));
-        }
-        w[e] = x[0] | (x[1] << 16);
+      for (int e = 0; e < 2; ++e) {
+        const float rho = fmaf(code[S % kRing][e], rad[2 * e], rad[2 * e + 1]);
+        const float cs = trig[S % kRing][e].x, sn = trig[S % kRing][e].y;
+        w[2 * e] = h2u(to_half2(rho * cs, rho * sn));
+        asm("" : "+v"(w[2 * e]));                 // (read back from the pair, not converted once more)
+        const f16x2 high = u2h(w[2 * e]);
+        // of the product, not of its rounding to fp32; one conversion for both (v_fma_mixlo / mixhi, two fewer: 118.4 against 116.5 us)
+        float lx = fmaf(rho, cs, -static_cast<float>(high.x)), ly = fmaf(rho, sn, -static_cast<float>(high.y));
+        asm("" : "+v"(lx), "+v"(ly));
+        const f16x2 low = to_half2(lx, ly);
+        w[2 * e + 1] = h2u(low);
       }
-      q8[kd] = as_operand(w[0], w[1], w[2], w[3]);
-    }
-    const uint32_t voff = row_token<O>(col) * (kHeadDim * 2) + row * 16;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const uint32_t soff = static_cast<uint32_t>(batch_token<O>(t, rot)) * (kHeadDim * 2);
       const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-      f32x4 lo = zero, hi = zero;
-#pragma unroll
-      for (int kd = 0; kd < 4; ++kd) {
-        const f16x8 k_op = as_operand(buf_load16<kAuxCached>(rs, voff, soff + kd * 64));
-        if (kd < 2) lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(k_op, q8[kd], lo, 0, 0, 0);
-        else hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(k_op, q8[kd], hi, 0, 0, 0);
+      const f16x8 k_op = as_operand(w[0], w[1], w[2], w[3]), q_op = as_operand(qv.x, qv.x, qv.y, qv.y);
+      if constexpr (to_sum(j)) s[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(k_op, q_op, j == 0 ? zero : s[t], 0, 0, 0);
+      else d[t % 4] = __builtin_amdgcn_mfma_f32_16x16x32_f16(k_op, q_op, starts(j) ? zero : d[t % 4], 0, 0, 0);
+      if constexpr (S >= 4) {
+        if constexpr (ends(pair_step(S - 4))) s[batch_of(S - 4)] += done[t % 4];
       }
-      s[t] = lo + hi;
-      if (t & 1) __builtin_amdgcn_sched_barrier(0);
+      if constexpr (ends(j)) done[t % 4] = d[t % 4];
+      __builtin_amdgcn_sched_barrier(0);
+      steps<S + 1>(rc_nxt, rot_nxt);
     }
-    fold(lane & 4);
+  }
+  // As ScoreWalk::run, the scores scaled by 2^(k + the head's query shift).
+  __device__ __forceinline__ int run(__amdgpu_buffer_rsrc_t rc_nxt, __amdgpu_buffer_rsrc_t rp_nxt, int rot_nxt, int lane) {
+    const f16x2 p = u2h(par);
+    const float sc = static_cast<float>(p.x), z = static_cast<float>(p.y);
+    const uint32_t bound = wave_max_u32(max(f2u(sc * static_cast<float>(1 << RB)) & 0x7fffffffu, f2u(z) & 0x7fffffffu));
+    const int k = min(100, kGroupedTop + 127 - static_cast<int>(bound >> 23));   // (a page of zeros: anything)
+    *(PQ_LDS f32x2*)static_cast<uintptr_t>(rad_put) = f32x2{__builtin_ldexpf(sc, k), __builtin_ldexpf(fmaf(0.5f, sc, z), k)};
+    build_table(lane);
+    load_params(rp_nxt, lane);
+    wave_lds_sync();
+    issue<0>(rc_nxt, rot_nxt);
+    issue<1>(rc_nxt, rot_nxt);
+    issue<2>(rc_nxt, rot_nxt);
+    static_assert(kAhead == 3, "reads issued before the first step");
+    __builtin_amdgcn_sched_barrier(0);
+    steps<0>(rc_nxt, rot_nxt);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[4 + i] += done[i];
+    fold_columns<NH>(s, lane & 4);
+    wave_lds_sync();
+    return k;
+  }
+  __device__ __forceinline__ void residual(const __half* rows, int nv_res, int rot, int lane) {
+    const uint32_t row = static_cast<uint32_t>(lane) >> 4;
+    const uint32_t q0 = q_addr - row * kGroupedQueryBlock;
+    residual_products<O>(s, rows, nv_res, rot, lane, [&](int kd, int j0, int e) {
+      // dims of pairs j0 + 2 e, + 1: one coordinate of each
+      const int j = j0 + 2 * e;
+      const u32x2 v = *(const PQ_LDS u32x2*)static_cast<uintptr_t>(q0 + (j >> 4) * kGroupedQueryBlock + ((j & 15) >> 1) * 128);
+      return __builtin_amdgcn_perm(v.y, v.x, kd >> 1 ? 0x07060302u : 0x05040100u);
+    });
+    fold_columns<NH>(s, lane & 4);
   }
 };
 
@@ -642,13 +846,98 @@ __device__ __forceinline__ constexpr float code_unscale(int k) {
   return static_cast<float>(1 << (24 - at));
 }
 
+// Stores a page's raw scores, left by a walk in plain token order and folded, for the heads from row `first_head` of a.scores
+// on: the lane's tokens 4 row .. + 3 of its batches, of one head.  Tokens from nv on are not stored.
+template <int NH>
+__device__ __forceinline__ void store_scores(const DecodeArgs& a, const f32x4 (&s)[8], int down, int64_t first_head, int page, int nv, int lane) {
+  const int row = lane >> 4, col = lane & 15, head = column_head<NH>(col);
+  if (col >= 8 || head >= a.n_heads) return;
+  const int other = NH == 4 && (col & 4) ? 64 : 0;                     // batch 4 + j: the token's bit 6 the other way
+  float* const out = a.scores + (first_head + head) * a.scores_stride + static_cast<int64_t>(page) * kGroup;
+#pragma unroll
+  for (int t = 0; t < NH; ++t) {
+    const int token = (16 * t + 4 * row) ^ other;
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = __builtin_ldexpf(s[t][i], -down);
+    if (uni(nv) == kGroup) {                                           // a whole page: four neighbours at a time
+      __builtin_memcpy(out + token, v, 16);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (token + i < nv) out[token + i] = v[i];
+    }
+  }
+}
+
+// Raw scores alone, grouped angle quantizer: the walk of the attention kernel, page by page.
+template <int RB, int TB, int NH>
+__device__ __forceinline__ void grouped_scores_body(const DecodeArgs& a) {
+  constexpr int kWaves4 = 4;
+  using Walk = GroupedWalk<RB, TB, TokenOrder::kPlain, NH>;
+  constexpr uint32_t kCodesBytes = kBlocks * kGroup * Walk::UB;
+  __shared__ __attribute__((aligned(16))) uint8_t table[kWaves4][Walk::kTableBytes];
+  __shared__ GroupedQuery query;
+  __shared__ __attribute__((aligned(16))) f32x2 radii[kWaves4][kPairs];
+  __shared__ int q_shift[kMaxHeads];
+  const int kvh = blockIdx.x, seq = blockIdx.y, chunk = blockIdx.z;
+  const int L = uni(clamped_len(a, seq)), n_pages = pages_of_len(L);
+  const int page0 = chunk * a.pages_per_chunk;
+  if (page0 >= n_pages) return;
+  const int npg = min(a.pages_per_chunk, n_pages - page0);
+  const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63;
+  const int64_t first_head = static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0;
+  const QueryFetch qf = a.q_is_f32 ? fetch_query_heads<true>(a, first_head * kHeadDim, tid) : fetch_query_heads<false>(a, first_head * kHeadDim, tid).widened();
+  const int n_w = npg > wave ? (npg - wave + kWaves4 - 1) / kWaves4 : 0;
+  const int res_page = (a.residual != nullptr && (L % kGroup) != 0) ? L / kGroup : -1;
+  PageIds<kWaves4> pids;
+  pids.start(a, seq, page0 + wave);
+  pids.n_p = n_w;
+  auto page_setup = [&](int k, __amdgpu_buffer_rsrc_t& rc, __amdgpu_buffer_rsrc_t& rp, int& nv) {
+    const int pid = pids.get(k);
+    const bool ok = pid >= 0;
+    const int64_t ph = ok ? static_cast<int64_t>(pid) * a.n_kv_heads + kvh : 0;
+    const int page = page0 + wave + kWaves4 * k;
+    nv = ok ? min(kGroup, L - page * kGroup) : 0;
+    const bool packed = ok && page != res_page;
+    rc = make_rsrc(a.codes + ph * kCodesBytes, packed ? kCodesBytes : 0u);
+    rp = make_rsrc(a.params + ph * (kPairs * 2), packed ? kPairs * 8u : 0u);
+  };
+  Walk w;
+  w.init(table[wave], query, radii[wave], lane);
+  __amdgpu_buffer_rsrc_t rc_cur, rp_cur, rc_nxt, rp_nxt;
+  int nv_cur, nv_nxt;
+  page_setup(0, rc_cur, rp_cur, nv_cur);
+  w.load_params(rp_cur, lane);
+#pragma unroll
+  for (int t = 0; t < 8; ++t) w.load_unit_of(t, rc_cur, 0);
+  store_grouped_query<NH>(query, q_shift, qf, 1.f, tid);
+  __syncthreads();
+  const int shift = q_shift[column_head<NH>(lane & 15)];
+  for (int it = 0; it < n_w; ++it) {
+    const int page = page0 + wave + kWaves4 * it;
+    page_setup(it + 1, rc_nxt, rp_nxt, nv_nxt);
+    int down = w.run(rc_nxt, rp_nxt, 0, lane) + shift;
+    if (page == res_page) {
+      w.residual(a.residual + (static_cast<int64_t>(seq) * a.n_kv_heads + kvh) * (kGroup * kHeadDim), L - res_page * kGroup, 0, lane);
+      down = shift;
+    }
+    store_scores<NH>(a, w.s, down, first_head, page, nv_cur, lane);
+    nv_cur = nv_nxt;
+  }
+}
+
 // ---- attention ----------------------------------------------------------------------------------
 // kCut: the chunks are cut on the device (a.spare_chunks > 0).  kMatWaves: wavefronts of the work-group, 4 or 8.
-template <int W, int VB, int NH, bool Q32, bool kCut, int kMatWaves>
+// kGroupedRadius: 0 on the uniform grid; with the grouped angle quantizer the radius bits (queries of either type are
+// taken as fp32 there, so that Q32 is true).
+template <int W, int VB, int NH, bool Q32, bool kCut, int kMatWaves, int kGroupedRadius = 0>
 __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   constexpr int UB = 2 * W;
   constexpr int kMatThreads = kMatWaves * 64;
   constexpr bool kQuantV = VB != 16;
+  constexpr bool kGrouped = kGroupedRadius != 0;
+  static_assert(!kGrouped || (Q32 && !kCut && kMatWaves == 4), "what the grouped quantizer's kernels are");
   constexpr TokenOrder kOrder = token_order(VB);
   constexpr int kChain = kQuantV ? 16 : 4;
   constexpr uint32_t kCodesBytes = kBlocks * kGroup * UB;
@@ -663,22 +952,23 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   constexpr int kOwn = NH;
   constexpr int kVLoads = kQuantV ? kGroup * kHeadDim * VB / 8 / 1024 : 32;   // 1 KB wavefront loads per page of values
 
+  using Grouped = GroupedWalk<kGrouped ? kGroupedRadius : 4, kGrouped ? W - kGroupedRadius : 4, kOrder, NH>;
   struct Shared {
     union {
-      __attribute__((aligned(16))) uint8_t lut[(1 << W) * kTableRow];
+      __attribute__((aligned(16))) uint8_t lut[kGrouped ? kMatWaves * Grouped::kTableBytes : (1 << W) * kTableRow];
       __attribute__((aligned(16))) float red[kMatWaves][NH][kHeadDim];   // end of the chunk
     };
     union {
-      QueryShared q;
+      std::conditional_t<kGrouped, GroupedQuery, QueryShared> q;
       __attribute__((aligned(16))) float lent[kFinishLdsFloats];         // end of the chunk: to the merge
       int32_t pages[kCut ? kBalancedSeqs : 1];                           // of the sequences, while the chunks are cut
     };
-    __attribute__((aligned(16))) uint32_t params[kMatWaves][kPairs];
+    __attribute__((aligned(16))) std::conditional_t<kGrouped, f32x2, uint32_t> params[kMatWaves][kPairs];
     __attribute__((aligned(16))) uint32_t vpar[kQuantV ? kMatWaves : 1][kQuantV ? kGroup : 1];
     float red_ml[kMatWaves][NH][3];                                      // m, l, sum of p * zero-point
     int q_shift[kMaxHeads];
-    float pair_down[kPairs];
-    __attribute__((aligned(16))) uint16_t exponents[kPairs][NH];
+    float pair_down[kGrouped ? 1 : kPairs];
+    __attribute__((aligned(16))) uint16_t exponents[kGrouped ? 1 : kPairs][NH];
     int stage;
   };
   __shared__ Shared sh;
@@ -710,7 +1000,8 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   };
   // The key table's entry, and the query below, are asked for before the page's loads: whoever waits for them
   // does not wait for the page as well (loads return in order).
-  const uint4 entry = fetch_key_entry<W>(key_table<W>(a.table_index), tid);
+  uint4 entry;
+  if constexpr (!kGrouped) entry = fetch_key_entry<W>(key_table<W>(a.table_index), tid);
   // A first chunk, of sequence number `slot`: its pages are under way before the cut is made.
   const bool cut_later = kCut && slot < a.n_seqs;
   if constexpr (kCut) {
@@ -725,7 +1016,10 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   chunk = uni(chunk);
   page0 = uni(page0);
   // the query and the page numbers are asked for without waiting for the sequence's length
-  const QueryFetch qf = fetch_query_heads<Q32>(a, (static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0) * kHeadDim, tid);
+  const int64_t q_at = (static_cast<int64_t>(seq) * a.n_q_heads + kvh * a.group_total + a.head0) * kHeadDim;
+  QueryFetch qf;
+  if constexpr (kGrouped) qf = a.q_is_f32 ? fetch_query_heads<true>(a, q_at, tid) : fetch_query_heads<false>(a, q_at, tid).widened();
+  else qf = fetch_query_heads<Q32>(a, q_at, tid);
   PageIds<kMatWaves> pids;
   pids.start(a, seq, page0 + wave);
   L = uni(clamped_len(a, seq));
@@ -763,7 +1057,8 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     rot = (ok && !kQuantV) ? (pid * 13 + kvh * 5) & 7 : 0;
     const bool packed = ok && page != res_page;                        // the residual group has no codes yet
     rc = make_rsrc(a.codes + ph * kCodesBytes, packed ? kCodesBytes : 0u);
-    rp = make_rsrc(a.params + ph * kPairs, packed ? kPairs * 4u : 0u);
+    constexpr uint32_t kParamWords = kPairs * (kGrouped ? 2 : 1);
+    rp = make_rsrc(a.params + ph * kParamWords, packed ? kParamWords * 4u : 0u);
     if constexpr (kQuantV) {
       // whole units are read; codes of slots past the sequence end are finite by construction
       // and meet a zero probability.  Their parameters could be anything: bounded by nv.
@@ -777,8 +1072,12 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   };
   __amdgpu_buffer_rsrc_t rc_cur, rp_cur, rv_cur, rvp_cur, rc_nxt, rp_nxt, rv_nxt, rvp_nxt;
   int nv_cur, nv_nxt, rot_cur, rot_nxt;
-  ScoreWalk<W, kOrder, NH, Q32, kQuantV ? 2 : 1, kChain> w;
-  w.init(sh.lut, sh.q, sh.pair_down, sh.params[wave], lane);
+  std::conditional_t<kGrouped, Grouped, ScoreWalk<W, kOrder, NH, Q32, kQuantV ? 2 : 1, kChain>> w;
+  auto init_walk = [&](int lane) {
+    if constexpr (kGrouped) w.init(sh.lut + wave * Grouped::kTableBytes, sh.q, sh.params[wave], lane);
+    else w.init(sh.lut, sh.q, sh.pair_down, sh.params[wave], lane);
+  };
+  init_walk(lane);
   uint4 vr[kQuantV ? 1 : 4][8];                                        // fp16 values: four groups of 8 rows (32 tokens)
   uint4 vq[kQuantV ? kVLoads : 1];                                     // quantized values: the page's units
   u32x2 vpar = {0u, 0u};                                               // (scale, zero) of tokens 2 lane, 2 lane + 1
@@ -814,8 +1113,12 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     n_chunks = uni(n_chunks);
   }
   const int stride = kCut ? n_chunks : a.n_chunks;
-  store_key_entry<W, kMatThreads>(sh.lut, entry, tid);                                // while the first page is under way
-  store_query_heads<NH, Q32>(sh.q, sh.q_shift, sh.pair_down, sh.exponents, qf, sign, tid);
+  if constexpr (kGrouped) {
+    store_grouped_query<NH>(sh.q, sh.q_shift, qf, sign, tid);
+  } else {
+    store_key_entry<W, kMatThreads>(sh.lut, entry, tid);                              // while the first page is under way
+    store_query_heads<NH, Q32>(sh.q, sh.q_shift, sh.pair_down, sh.exponents, qf, sign, tid);
+  }
   __syncthreads();
 
   // per lane: column (head, part), running maximum, sums over the lane's tokens
@@ -835,7 +1138,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     page_setup(it + 1, rc_nxt, rp_nxt, rv_nxt, rvp_nxt, nv_nxt, rot_nxt);
     // lane constants of the score walk, derived anew for each page: the value phase needs their registers
     const int lane = lane_id(), col = lane & 15;
-    w.init(sh.lut, sh.q, sh.pair_down, sh.params[wave], lane);
+    init_walk(lane);
     const int q_shift = sh.q_shift[column_head<NH>(col)];
     const int s_exp_before = s_exp;
     if constexpr (kQuantV) {
@@ -845,7 +1148,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       *(PQ_LDS u32x2*)static_cast<uintptr_t>(lds_addr(sh.vpar[wave]) + lane * 8) = u32x2{h2u(u2h(vpar.x) * factor), h2u(u2h(vpar.y) * factor)};
       vpar = __builtin_amdgcn_raw_buffer_load_b64(rvp_nxt, lane * 8, 0, kAuxCached);
     }
-    int down = w.run(rc_nxt, rp_nxt, rot_nxt, lane) + kTableShift + q_shift;
+    int down = w.run(rc_nxt, rp_nxt, rot_nxt, lane) + (kGrouped ? 0 : kTableShift) + q_shift;
     if (pi == res_page) {
       w.residual(a.residual + (static_cast<int64_t>(seq) * a.n_kv_heads + kvh) * (kGroup * kHeadDim), L - res_page * kGroup,
                  rot_cur, lane_id());

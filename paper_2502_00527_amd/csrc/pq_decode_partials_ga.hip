@@ -1,5 +1,6 @@
 // Instantiations of the attention kernel of the grouped angle quantizer (Section 3.2 as printed: per-group
-// angle min / scale, table rebuilt per group): fp16 and quantized values, all bit allocations.
+// angle min / scale, table rebuilt per group) on the vector unit, for one and two query heads per KV head: fp16 and
+// quantized values, all bit allocations.
 #include "pq_decode_kernels.hpp"
 
 namespace pq {
@@ -11,7 +12,6 @@ bool launch_g(int G, const DecodeArgs& a, dim3 grid, hipStream_t st) {
   switch (G) {
     case 1: hipLaunchKernelGGL((pq_decode_partials_kernel<1, RB, TB, VB>), grid, block, 0, st, a); return true;
     case 2: hipLaunchKernelGGL((pq_decode_partials_kernel<2, RB, TB, VB>), grid, block, 0, st, a); return true;
-    case 4: hipLaunchKernelGGL((pq_decode_partials_kernel<4, RB, TB, VB>), grid, block, 0, st, a); return true;
     default: return false;
   }
 }
