@@ -169,8 +169,8 @@ int pq_encode_values(const pq_layout* layout, int32_t v_bits, const void* values
  *
  *   q             device [n_seqs][n_q_heads][d], post-RoPE, q_dtype PQ_F16 or PQ_F32.
  *                 Query head h reads KV head h / (n_q_heads / n_kv_heads); the ratio may be
- *                 1 .. 16.  A pass over the cache serves up to 8 query heads (with the grouped
- *                 angle quantizer 4, 2 or 1), so a ratio of 1 .. 8 reads the cache once,
+ *                 1 .. 16.  A pass over the cache serves up to 8 query heads, so a ratio of 1 .. 8
+ *                 reads the cache once,
  *                 12 = 8 + 4 twice, ...
  *   block_table   device int32 [n_seqs][max_pages_per_seq]: page of tokens
  *                 [i*g, (i+1)*g) of each sequence; entries past a sequence's last page
@@ -200,9 +200,10 @@ int pq_encode_values(const pq_layout* layout, int32_t v_bits, const void* values
  *
  * Scores, softmax statistics and outputs are fp32.  On the uniform angle grid the factors of the two
  * matrix products (query times radius parameter, reconstructed key, probability times value scale)
- * are carried as two fp16 parts, 22 bits; with the grouped angle quantizer the probabilities that
- * weight the values are fp32, or rounded to fp16 with quantized values (the token's fp16 scale
- * folded in before the rounding).  `out` does not depend on whether `scores` is asked for.
+ * are carried as two fp16 parts, 22 bits; with the grouped angle quantizer and three or more query
+ * heads per KV head likewise, with one or two the probabilities that weight the values are fp32, or
+ * rounded to fp16 with quantized values (the token's fp16 scale folded in before the rounding).
+ * `out` does not depend on whether `scores` is asked for.
  */
 int pq_decode_attention(const pq_layout* layout, const void* q, pq_dtype q_dtype, int32_t n_seqs,
                         int32_t n_q_heads, const void* codes_pool, const void* params_pool,
@@ -274,7 +275,7 @@ const char* pq_decode_kernel_name(const pq_layout* layout, int32_t n_seqs, int32
  * pq_decode_merges_in_kernel -- 1 if pq_decode_attention serves this shape with one kernel that
  * combines the partial results itself, 0 if the merge kernel follows; a negative pq_status on
  * invalid arguments.  Launches of few (sequence, KV head) units whose sequences have several chunks, and
- * the grouped angle quantizer's, take the second form.  For profiles and the benchmark, like pq_decode_kernel_name.
+ * the grouped angle quantizer's with one or two query heads per KV head, take the second form.  For profiles and the benchmark, like pq_decode_kernel_name.
  */
 int pq_decode_merges_in_kernel(const pq_layout* layout, int32_t n_seqs, int32_t n_q_heads,
                                int32_t max_seq_len, int32_t v_bits);

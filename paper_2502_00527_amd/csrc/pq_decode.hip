@@ -126,9 +126,12 @@ int64_t four_page_groups(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len
   return std::min<int64_t>(kCountedGroups, (bound + 3) / 4);
 }
 
-// Uniform angle grid, and pages enough for at least 256 work-groups.
+// Pages enough for at least 256 work-groups (and on the uniform angle grid).
+bool large_launch(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len) {
+  return n_seqs <= 4096 && four_page_groups(l, n_seqs, max_seq_len) >= kComputeUnits;
+}
 bool large_uniform_launch(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len) {
-  return l->angle_quantizer == PQ_ANGLE_UNIFORM && n_seqs <= 4096 && four_page_groups(l, n_seqs, max_seq_len) >= kComputeUnits;
+  return l->angle_quantizer == PQ_ANGLE_UNIFORM && large_launch(l, n_seqs, max_seq_len);
 }
 
 AttentionKernel choose_attention_kernel(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads,
@@ -377,12 +380,13 @@ int spare_chunks(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len) {
 
 // Whether one kernel does all of pq_decode_attention (true), or the merge kernel follows: the
 // sequences are one chunk long, the launch is cut on the device, or a large one has few enough chunks per
-// unit.
+// unit.  (Grouped quantizer, 16 x 16K tokens: 115.6 -> 114.7 us without the launch, 4 x 8K 23.7 -> 22.7.  Its vector-unit kernel
+// leaves partials only.)
 bool merges_in_kernel(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
-  if (l->angle_quantizer != PQ_ANGLE_UNIFORM) return false;
+  if (l->angle_quantizer != PQ_ANGLE_UNIFORM && !grouped_on_matrix(l, n_q_heads / l->n_kv_heads)) return false;
   if (spare_chunks(l, n_seqs, max_seq_len) > 0) return true;
-  const int n_chunks = plan_uniform(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
-  return n_chunks == 1 || (n_chunks <= kMergeFan && large_uniform_launch(l, n_seqs, max_seq_len));
+  const int n_chunks = plan_attention(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
+  return n_chunks == 1 || (n_chunks <= kMergeFan && large_launch(l, n_seqs, max_seq_len));
 }
 
 // Work-groups of 8 wavefronts: sequences of one chunk with more pages than 4 wavefronts take at once, and no more

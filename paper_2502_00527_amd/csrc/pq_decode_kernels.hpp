@@ -11,8 +11,8 @@
 // This header holds what the vector-unit kernels share (streaming loads, table builds, pair steps,
 // value steps, residual keys) and the kernels themselves: pq_decode_partials_kernel, whose
 // wavefronts alternate between a score and a value phase and which serves the grouped angle
-// quantizer, and the score-only kernels of both quantizers.  Attention over the uniform angle grid is on
-// the matrix cores (pq_decode_matrix.hpp).
+// quantizer with one or two query heads per KV head, and the score-only kernels of both quantizers.  All other
+// attention is on the matrix cores (pq_decode_matrix.hpp).
 //
 // Mapping to the machine in the attention kernels.  A work-group is 4 wavefronts; the table of
 // all query heads that share the KV head lives in LDS with the heads interleaved (one 16-byte
@@ -91,7 +91,7 @@ struct DecodeArgs {
   float sin_tab[kMaxAngleBins];
 };
 
-// Launcher of the grouped quantizer's attention kernels (rt = 10 r + t; pq_decode_partials_ga.hip).
+// Launcher of the grouped quantizer's vector-unit attention kernels (rt = 10 r + t; pq_decode_partials_ga.hip).
 // Returns false, and launches nothing, if there is no kernel for the combination; launch errors are
 // left to hipGetLastError().
 bool launch_attention_partials_ga(int rt, int G, int v_bits, const DecodeArgs& a, dim3 grid, hipStream_t st);
@@ -169,7 +169,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 // Tuning constants of the attention kernel (measured on MI355X): 4 quads of 4 value rows in
 // flight per wavefront (8 rows in flight measure the same, 4 rows 4 % slower; the number of
 // quads must divide the 8 quads of a page), and a register budget of 2 wavefronts per SIMD --
-// with 4 query heads a third wavefront only fits with spills and runs 10-30 % slower.
+// a third wavefront does not pay.
 #ifndef PQ_RING_SETS
 #define PQ_RING_SETS 4
 #endif
@@ -774,10 +774,11 @@ __global__ PQ_KERNEL_ATTR void pq_decode_partials_kernel(const DecodeArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
 
+  static_assert(G <= 2, "more heads go to the matrix cores");
   const int row = lane >> 4;             // score phase: pair block; value phase: token slot
   const int col = lane & 15;             // score phase: token in the pass; value phase: dim slice
-  const int my_head = (G == 4) ? row : (G == 2 ? (row >> 1) : 0);
-  const bool owner = (G == 4) || (G == 2 && (row & 1) == 0) || (G == 1 && row == 0);
+  const int my_head = G == 2 ? (row >> 1) : 0;
+  const bool owner = (G == 2 && (row & 1) == 0) || (G == 1 && row == 0);
 
   float m_run = kNegInf, l_run = 0.f, z_run = 0.f;
   float acc[G][8];

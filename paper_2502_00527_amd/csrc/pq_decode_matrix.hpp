@@ -1,6 +1,7 @@
-// Attention kernel of the uniform angle grid, on the matrix cores.
+// Attention kernel on the matrix cores: the uniform angle grid, and the grouped angle quantizer from three query heads per
+// KV head on (whose score walk, GroupedWalk, has its own description).
 //
-// Scores.  A key pair is reconstructed as rho~ (cos theta~, sin theta~), rho~ = s (c + 1/2) + z
+// Scores, uniform grid.  A key pair is reconstructed as rho~ (cos theta~, sin theta~), rho~ = s (c + 1/2) + z
 // (Section 3.2), and the score is sum over pairs of q . k~.  Written with the four products
 //     q_x s, q_y s, q_x z, q_y z          (per pair and page: the query side)
 //     c' cos, c' sin, cos, sin, c' = c + 1/2   (a function of the packed symbol alone: the key side)
