@@ -176,9 +176,9 @@ __device__ __forceinline__ double shuffle_fold(double v, bool smallest) {
 // step done again with the exact operations.
 // Angle codes: four pairs at a time for fp16 keys (pq_angle.hpp), pair by pair for fp32.
 //
-// Bound: vector issue (26 instructions a pair, the root four times as long as the others), with the load of
-// the one round of work-groups before it; 72 registers, seven of a compute unit's possible eight work-groups are
-// resident.  32768 tokens x 8 heads, 84 MB, fp16 keys at 4+4 bits: 33.2 -> 20.1 us, fp32 keys 42.7 -> 32.7,
+// Bound: neither the vector unit (26 instructions a pair, 43 % of the issue slots) nor HBM (51 %) alone, but one behind the
+// other: the launch is a single round of work-groups that all load, compute and store at the same time; 72 registers,
+// seven of a compute unit's possible eight work-groups are resident (64 registers for the eighth: spills, 25.4 us).  32768 tokens x 8 heads, 84 MB, fp16 keys at 4+4 bits: 33.2 -> 20.1 us, fp32 keys 42.7 -> 32.7,
 // grouped angles (whose float64 arc tangents remain) 80.5 -> 62.  Before: 69 instructions a pair -- rounded roots and IEEE
 // divisions for all pairs, 20 for the angle -- and one token's loads at a time.  Two tokens a thread in work-groups of 512,
 // which all fit: 21.0 us; one in 1024: 22.6.

@@ -98,3 +98,35 @@ def test_sizes_far_apart(what, q_heads, monkeypatch):
     err = float((cases.run(state).double() - cases.exact(case, 8)).norm() / cases.exact(case, 8).norm())
     print("[sizes]", what, q_heads, err, flush=True)
     assert err <= 6e-6
+
+
+@pytest.mark.parametrize("shape", [(4, 32, 8, 3000, True), (40, 12, 4, 1000, True), (3, 8, 8, 2000, True), (2, 24, 8, 777, False)], ids=str)
+def test_two_stages_and_graph_replay(shape):
+    """Partials and merge as two calls, and the call captured in a graph, give the call's result (the two ways of merging
+    add the same partials in another order)."""
+    from perf import cases
+
+    pq = cases.pq
+    seqs, q_heads, kv_heads, context, grouped = shape
+    case = cases._case("stages", "decode", seqs, q_heads, kv_heads, context, min_context=context // 2, grouped_angles=grouped)
+    state = cases.prepare(case, 4)
+    want = cases.run(state).clone()
+    pq.pq_decode_partials(state["layout"], state["q"], state["codes"], state["params"], state["v_pool"], state["block_table"],
+                          state["seq_lens"], state["max_seq_len"], state["sm_scale"], state["workspace"])
+    out = torch.full_like(want, float("nan"))
+    pq.pq_decode_merge(state["layout"], seqs, q_heads, state["seq_lens"], state["max_seq_len"], out, state["workspace"])
+    assert float((out - want).norm() / want.norm()) <= 1e-6
+
+    stream = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        cases.run(state)
+    for turn in range(4):
+        state["out"].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(state["out"], want)
+        state["q"].copy_(state["q"].flip(0) if seqs > 1 else -state["q"])      # new inputs are picked up
+        want = cases.run(state).clone()
+        torch.cuda.synchronize()
