@@ -919,11 +919,13 @@ __device__ __forceinline__ void grouped_scores_body(const DecodeArgs& a) {
     const int page = page0 + wave + kWaves4 * it;
     page_setup(it + 1, rc_nxt, rp_nxt, nv_nxt);
     int down = w.run(rc_nxt, rp_nxt, 0, lane) + shift;
-    if (page == res_page) {
-      w.residual(a.residual + (static_cast<int64_t>(seq) * a.n_kv_heads + kvh) * (kGroup * kHeadDim), L - res_page * kGroup, 0, lane);
+    int nv = nv_cur;
+    if (page == res_page) {                                            // its keys are here, whatever the block table says
+      nv = L - res_page * kGroup;
+      w.residual(a.residual + (static_cast<int64_t>(seq) * a.n_kv_heads + kvh) * (kGroup * kHeadDim), nv, 0, lane);
       down = shift;
     }
-    store_scores<NH>(a, w.s, down, first_head, page, nv_cur, lane);
+    store_scores<NH>(a, w.s, down, first_head, page, nv, lane);
     nv_cur = nv_nxt;
   }
 }

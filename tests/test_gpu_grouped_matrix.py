@@ -130,3 +130,35 @@ def test_two_stages_and_graph_replay(shape):
         state["q"].copy_(state["q"].flip(0) if seqs > 1 else -state["q"])      # new inputs are picked up
         want = cases.run(state).clone()
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("q_heads", [1, 3, 4, 8, 16])
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_scores_of_a_tail_without_a_page(q_heads, dtype):
+    """The un-quantized keys of the last, incomplete group are scored whatever the block table holds for it: a caller that
+    wants scores alone has no packed page there.  Dot products of 128 terms: the bound of the scores, 5e-7."""
+    from perf import cases
+
+    pq = cases.pq
+    case = cases._case("tail", "serve", 4, q_heads, 1, 600, min_context=130, dtype=dtype, grouped_angles=True, shuffled_pages=True)
+    state = cases.prepare(case, 3)
+    cases.run(state)                                                      # the new keys are appended
+    lens = state["seq_lens"].tolist()
+    scores = []
+    for entry in (None, -1, state["codes"].shape[0] + 5):
+        table = state["block_table"].clone()
+        for s, n in enumerate(lens):
+            if entry is not None and n % 128:
+                table[s, n // 128] = entry
+        out = torch.full((4, q_heads, state["max_seq_len"]), float("nan"), device="cuda:0")
+        pq.pq_score_keys(state["layout"], state["q"], state["codes"], state["params"], table, state["seq_lens"], state["max_seq_len"],
+                         out, state["residual"])
+        scores.append(out)
+    for out in scores[1:]:
+        assert torch.equal(out.nan_to_num(nan=-7.0), scores[0].nan_to_num(nan=-7.0))
+    for s, n in enumerate(lens):
+        assert not torch.isnan(scores[1][s, :, :n]).any() and torch.isnan(scores[1][s, :, n:]).all()
+        tail = n % 128
+        if tail:
+            want = torch.matmul(state["q"][s].double(), state["residual"][s, 0, :tail].double().t().contiguous())
+            assert float((scores[1][s, :, n - tail:n].double() - want).norm() / want.norm()) <= 5e-7
