@@ -76,9 +76,9 @@ __device__ __forceinline__ float half_minus(uint32_t w, float z) {
   else asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(w), "v"(z));
   return d;
 }
-__device__ __forceinline__ float max3_abs(float a, float b, float c) {          // max(a, |b|, |c|)
+__device__ __forceinline__ float max3_abs(float a, float b, float c) {          // max(a, |b|, |c|), NaN if one of them is
   float r;
-  asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  asm("v_maximum3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
 
@@ -111,7 +111,7 @@ __device__ __forceinline__ uint32_t quantize8(const uint32_t (&w)[4], float s, f
     t[e + 1] = __builtin_fmaf(half_minus<1>(w[e / 2], z), inv, kRounder);
     off = max3_abs(off, rest(e), rest(e + 1));
   }
-  if (__builtin_amdgcn_ballot_w64(off > half * (1.f - 0x1p-16f)) != 0) {
+  if (__builtin_amdgcn_ballot_w64(!(off <= half * (1.f - 0x1p-16f))) != 0) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       asm volatile("" : "+v"(t[e]));             // remainders are made again: eight registers less, which is a wavefront more
@@ -119,6 +119,10 @@ __device__ __forceinline__ uint32_t quantize8(const uint32_t (&w)[4], float s, f
       // past half of s by the bit pattern: from half on if the code is odd, above half if it is even
       const uint32_t limit = __float_as_uint(half) - (__float_as_uint(t[e]) & 1u);
       t[e] += (__float_as_uint(r) & 0x7fffffffu) > limit ? __builtin_copysignf(1.f, r) : 0.f;
+    }
+    if (__builtin_amdgcn_ballot_w64(off != off) != 0) {     // NaN: code 0, and nothing of its bit pattern beside it
+#pragma unroll
+      for (int e = 0; e < 8; ++e) t[e] = __builtin_fmaxf(t[e], kRounder);
     }
   }
   if (__builtin_amdgcn_ballot_w64(clamp) != 0) {

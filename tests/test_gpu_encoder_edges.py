@@ -49,6 +49,35 @@ def test_value_encoder_edges(kind, v_bits):
         assert not got[n:].any()
 
 
+@pytest.mark.parametrize("v_bits", [4, 2])
+def test_a_nan_stays_where_it_is(v_bits):
+    """A NaN among the values has code 0; the other codes, of its own token and of the tokens beside it, and all
+    parameters are those of the values without it."""
+    n, heads = 300, 2
+    for kind in ("normal", "lattice", "denormal", "flat"):
+        v = _rows(kind, n, heads, 5)
+        rng = np.random.default_rng(6)
+        hit = (rng.random(v.shape) < 0.04) & (rng.random((n, heads, 1)) < 0.5)
+        hit[7, 0], hit[7, 0, 3] = True, False                       # a token with a single number left
+        hit[8] = False
+        without = np.where(hit, np.min(np.where(hit, np.float16(np.inf), v), axis=-1, keepdims=True), v)
+        with_nan = v.copy()
+        with_nan.view(np.uint16)[hit] = rng.choice(np.array([0x7e00, 0xfe00, 0x7fff, 0xffff], np.uint16), int(hit.sum()))
+        n_pages = (n + GROUP - 1) // GROUP
+        layout = pq.Layout(128, 4, 4, GROUP, heads, 0)
+        ids = torch.arange(n_pages, dtype=torch.int32, device="cuda:0")
+        got = []
+        for values in (with_nan, without):
+            pool = torch.full((n_pages, pq.pq_vq_bytes_per_page(layout, v_bits)), 0xA5, dtype=torch.uint8, device="cuda:0")
+            params = torch.full((n_pages, heads, GROUP, 2), 7.0, dtype=torch.float16, device="cuda:0")
+            pq.pq_encode_values(layout, v_bits, torch.from_numpy(values).to("cuda:0"), ids, pool, params)
+            got.append((pool.cpu().numpy(), params.cpu().numpy()))
+        np.testing.assert_array_equal(got[0][0], got[1][0], err_msg=kind)
+        np.testing.assert_array_equal(got[0][1], got[1][1], err_msg=kind)
+        want = cache_format.pack_value_page_stream(ovalues.quantize_values(without, v_bits)[0], v_bits, GROUP)
+        np.testing.assert_array_equal(got[0][0].reshape(want.shape), want)
+
+
 def _keys(kind, n, heads, seed, dtype):
     """[n, heads, 128]: keys on which the code's approximation is in doubt, or the quick angle rule does not hold."""
     rng = np.random.default_rng(seed)
