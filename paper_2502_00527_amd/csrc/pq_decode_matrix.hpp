@@ -194,48 +194,64 @@ __device__ __forceinline__ QueryFetch fetch_query_heads(const DecodeArgs& a, int
   }
   return f;
 }
-// `shifts`: the power of two each head was multiplied with; `pair_down`: what the parameters of each
-// pair are to be multiplied with.  `exponents` is scratch.  Holds one work-group barrier.
+// A query's elements as a thread has them, and the powers of two they are multiplied with: brings the head's
+// largest element, then the pair's largest of any head, into [2^T, 2^(T + 1)).
+template <int NH, bool Q32, int T>
+struct QueryScale {
+  float v[2][2];                                             // [pair][coordinate]
+  int shift, up[2];                                          // of the head, of the pair
+  // `pair_down`: what the parameters of each pair are to be multiplied with.  `exponents` is scratch.  Holds
+  // one work-group barrier; up is set in threads of heads below NH only.
+  __device__ __forceinline__ QueryScale(const QueryFetch& f, float* pair_down, uint16_t (*exponents)[NH], int tid) {
+    uint32_t high[2];                                        // of the pair's two, as bits
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      v[e][0] = f.value<Q32>(0, e);
+      v[e][1] = f.value<Q32>(1, e);
+      high[e] = max(f2u(v[e][0]) & 0x7fffffffu, f2u(v[e][1]) & 0x7fffffffu);
+    }
+    const uint32_t top = half_wave_max_u32(max(high[0], high[1]));
+    shift = min(T + 127 - static_cast<int>(top >> 23), 126);
+    const int h = tid >> 5, j0 = (tid & 31) * 2;
+    // exponents after the head's scale, the largest 64 + T
+    if (h < NH) {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) exponents[j0 + e][h] = static_cast<uint16_t>(max(0, static_cast<int>(high[e] >> 23) + shift - 127 + 64));
+    }
+    __syncthreads();
+    if (h >= NH) return;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      uint32_t of_heads[NH / 2];
+      __builtin_memcpy(of_heads, exponents[j0 + e], NH * 2);
+      uint32_t most2 = of_heads[0];
+#pragma unroll
+      for (int o = 1; o < NH / 2; ++o) most2 = max_u16x2(most2, of_heads[o]);
+      const int most = static_cast<int>(max(most2 & 0xffffu, most2 >> 16));
+      up[e] = most == 0 ? 0 : 64 + T - most;
+      if (h == 0) pair_down[j0 + e] = most == 0 ? 0.f : __builtin_ldexpf(1.f, -up[e]);   // (not in any product: no say in the page's scale)
+    }
+  }
+  __device__ __forceinline__ float scaled(int e, int comp, float sign) const { return sign * __builtin_ldexpf(v[e][comp], shift + up[e]); }
+};
+// `shifts`: the power of two each head was multiplied with.  Holds the barrier of QueryScale.
 // (Both coordinates of a pair in one thread: 8 wide stores instead of 48 of 16 bits, and one 16-byte read of
 // the other heads' exponents.)
 template <int NH, bool Q32>
 __device__ __forceinline__ void store_query_heads(QueryShared& q, int* shifts, float* pair_down, uint16_t (*exponents)[NH],
                                                   const QueryFetch& f, float sign, int tid) {
-  float v[2][2];                                             // [pair][coordinate]
-  uint32_t high[2];                                          // of the pair's two, as bits
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    v[e][0] = f.value<Q32>(0, e);
-    v[e][1] = f.value<Q32>(1, e);
-    high[e] = max(f2u(v[e][0]) & 0x7fffffffu, f2u(v[e][1]) & 0x7fffffffu);
-  }
-  const uint32_t top = half_wave_max_u32(max(high[0], high[1]));
-  const int shift = min(kQueryTop + 127 - static_cast<int>(top >> 23), 126);
+  const QueryScale<NH, Q32, kQueryTop> x(f, pair_down, exponents, tid);
   const int h = tid >> 5, j0 = (tid & 31) * 2;
-  // exponents after the head's scale, the largest 64 + kQueryTop
-  if (h < NH) {
-#pragma unroll
-    for (int e = 0; e < 2; ++e) exponents[j0 + e][h] = static_cast<uint16_t>(max(0, static_cast<int>(high[e] >> 23) + shift - 127 + 64));
-  }
-  __syncthreads();
   if (h >= NH) return;
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
     const int j = j0 + e, kk = j & 15;
-    uint32_t of_heads[NH / 2];
-    __builtin_memcpy(of_heads, exponents[j], NH * 2);
-    uint32_t most2 = of_heads[0];
-#pragma unroll
-    for (int o = 1; o < NH / 2; ++o) most2 = max_u16x2(most2, of_heads[o]);
-    const int most = static_cast<int>(max(most2 & 0xffffu, most2 >> 16));
-    const int up = most == 0 ? 0 : 64 + kQueryTop - most;
-    if (h == 0) pair_down[j] = most == 0 ? 0.f : __builtin_ldexpf(1.f, -up);   // (not in any product: no say in the page's scale)
     f16x2 hi, rest;
 #pragma unroll
     for (int comp = 0; comp < 2; ++comp) {
-      const float x = sign * __builtin_ldexpf(v[e][comp], shift + up);
-      hi[comp] = static_cast<_Float16>(x);
-      rest[comp] = Q32 ? static_cast<_Float16>(x - static_cast<float>(hi[comp])) : hi[comp];
+      const float v = x.scaled(e, comp, sign);
+      hi[comp] = static_cast<_Float16>(v);
+      rest[comp] = Q32 ? static_cast<_Float16>(v - static_cast<float>(hi[comp])) : hi[comp];
     }
     uint8_t* const at = q.pairs + (j >> 4) * kQueryBlock + kk * 128 + h * 8;
 #pragma unroll
@@ -246,7 +262,7 @@ __device__ __forceinline__ void store_query_heads(QueryShared& q, int* shifts, f
       *reinterpret_cast<u32x2*>(at + half * NH * 8 + 64) = u32x2{hw, rw};
     }
   }
-  if ((tid & 31) == 0) shifts[h] = shift;
+  if ((tid & 31) == 0) shifts[h] = x.shift;
 }
 
 __device__ __forceinline__ f16x2 to_half2(float x, float y) { return __builtin_convertvector((f32x2{x, y}), f16x2); }
@@ -598,33 +614,30 @@ struct ScoreWalk {
 // heads costs the same.  About 8 vector instructions a symbol; with a table of the heads' products and fp32
 // multiply-adds (pq_decode_partials_kernel) it is 3 + heads, and values cost heads times as much as here.
 //
+// Scales: as on the uniform grid (QueryShared), each head's and then each pair's largest query element goes to the top and
+// the pair's radius parameters are multiplied the other way, so that a key coordinate keeps its 24 bits until its products
+// are 2^-15 of the page's largest of any head, whatever the radius is.  (With one scale a page a radius of 15000 beside ones
+// of 2^-9, where the query is small in that pair, left the scores an error of 1.2e-5; 1.4e-7 so, as with fp32 multiply-adds.)
+//
 // Table entry of (pair j, state a): 8 bytes at (j / 2) 2^t 16 + 16 a + 8 ((j + j / 16) % 2): a block's two pairs of an
 // instruction share a row, and neighbouring blocks, which are read together, use the other half of the banks.
-constexpr int kGroupedTop = 13;                  // the page's radii are brought below 2^(kGroupedTop + 2)
+constexpr int kGroupedTop = 13;                  // the page's radii, times their pairs' scales, are brought below 2^(kGroupedTop + 2)
 constexpr int kGroupedQueryTop = 14;
 constexpr int kGroupedQueryBlock = 8 * 16 * 8 + 128;
 struct GroupedQuery {                            // [block][pair / 2 of the block][column]{x, y of the even pair, of the odd one}
   __attribute__((aligned(16))) uint8_t pairs[kBlocks * kGroupedQueryBlock];
 };
-// Each head's largest element is brought into [2^14, 2^15); `shifts` says by which power of two.
+// Scaled like the uniform grid's query (QueryScale); `shifts` says by which power of two a head was.
 template <int NH>
-__device__ __forceinline__ void store_grouped_query(GroupedQuery& q, int* shifts, const QueryFetch& f, float sign, int tid) {
+__device__ __forceinline__ void store_grouped_query(GroupedQuery& q, int* shifts, float* pair_down, uint16_t (*exponents)[NH],
+                                                    const QueryFetch& f, float sign, int tid) {
+  const QueryScale<NH, true, kGroupedQueryTop> scale(f, pair_down, exponents, tid);
   const int h = tid >> 5, j0 = (tid & 31) * 2;
-  float v[2][2];
-  uint32_t top = 0;
-#pragma unroll
-  for (int e = 0; e < 2; ++e)
-#pragma unroll
-    for (int comp = 0; comp < 2; ++comp) {
-      v[e][comp] = f.value<true>(comp, e);
-      top = max(top, f2u(v[e][comp]) & 0x7fffffffu);
-    }
-  const int shift = min(kGroupedQueryTop + 127 - static_cast<int>(half_wave_max_u32(top) >> 23), 126);
   if (h >= NH) return;
   uint32_t hi[2], lo[2];
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
-    const float x = sign * __builtin_ldexpf(v[e][0], shift), y = sign * __builtin_ldexpf(v[e][1], shift);
+    const float x = scale.scaled(e, 0, sign), y = scale.scaled(e, 1, sign);
     const f16x2 high = {static_cast<_Float16>(x), static_cast<_Float16>(y)};
     const f16x2 low = {static_cast<_Float16>(x - static_cast<float>(high.x)), static_cast<_Float16>(y - static_cast<float>(high.y))};
     hi[e] = __builtin_bit_cast(uint32_t, high);
@@ -638,7 +651,7 @@ __device__ __forceinline__ void store_grouped_query(GroupedQuery& q, int* shifts
     *reinterpret_cast<u32x2*>(at + half * NH * 8) = here ? u32x2{hi[0], hi[1]} : u32x2{0u, 0u};
     *reinterpret_cast<u32x2*>(at + half * NH * 8 + 64) = here ? u32x2{lo[0], lo[1]} : u32x2{0u, 0u};
   }
-  if ((tid & 31) == 0) shifts[h] = shift;
+  if ((tid & 31) == 0) shifts[h] = scale.shift;
 }
 
 template <int RB, int TB, TokenOrder O, int NH>
@@ -654,9 +667,10 @@ struct GroupedWalk {
   float code[kRing][2];
   f32x4 rad;                                      // {s, z + s / 2} of a step's two pairs, scaled
   u32x2 qv;
-  uint32_t row_even, row_odd, rad_put, rad_get, q_addr, voff_codes, build_even, build_odd;
+  uint32_t row_even, row_odd, rad_put, rad_get, q_addr, voff_codes, build_even, build_odd, down_addr;
 
-  __device__ __forceinline__ void init(const uint8_t* table, const GroupedQuery& q, const f32x2* radii, int lane) {
+  __device__ __forceinline__ void init(const uint8_t* table, const GroupedQuery& q, const float* pair_down, const f32x2* radii, int lane) {
+    down_addr = lds_addr(pair_down);
     const int row = lane >> 4, col = lane & 15;
     row_even = lds_addr(table) + row * (8 * NA * 16) + (row & 1) * 8;
     row_odd = row_even ^ 8u;
@@ -746,7 +760,8 @@ struct GroupedWalk {
   // As ScoreWalk::run, the scores scaled by 2^(k + the head's query shift).
   __device__ __forceinline__ int run(__amdgpu_buffer_rsrc_t rc_nxt, __amdgpu_buffer_rsrc_t rp_nxt, int rot_nxt, int lane) {
     const f16x2 p = u2h(par);
-    const float sc = static_cast<float>(p.x), z = static_cast<float>(p.y);
+    const float pair = *(const PQ_LDS float*)static_cast<uintptr_t>(down_addr + lane * 4);
+    const float sc = static_cast<float>(p.x) * pair, z = static_cast<float>(p.y) * pair;
     const uint32_t bound = wave_max_u32(max(f2u(sc * static_cast<float>(1 << RB)) & 0x7fffffffu, f2u(z) & 0x7fffffffu));
     const int k = min(100, kGroupedTop + 127 - static_cast<int>(bound >> 23));   // (a page of zeros: anything)
     *(PQ_LDS f32x2*)static_cast<uintptr_t>(rad_put) = f32x2{__builtin_ldexpf(sc, k), __builtin_ldexpf(fmaf(0.5f, sc, z), k)};
@@ -772,7 +787,10 @@ struct GroupedWalk {
       // dims of pairs j0 + 2 e, + 1: one coordinate of each
       const int j = j0 + 2 * e;
       const u32x2 v = *(const PQ_LDS u32x2*)static_cast<uintptr_t>(q0 + (j >> 4) * kGroupedQueryBlock + ((j & 15) >> 1) * 128);
-      return __builtin_amdgcn_perm(v.y, v.x, kd >> 1 ? 0x07060302u : 0x05040100u);
+      const f16x2 two = u2h(__builtin_amdgcn_perm(v.y, v.x, kd >> 1 ? 0x07060302u : 0x05040100u));
+      // without the pairs' scales: no parameter carries the other half of them here
+      const f32x2 pairs = *(const PQ_LDS f32x2*)static_cast<uintptr_t>(down_addr + j * 4);
+      return h2u(to_half2(static_cast<float>(two.x) * pairs.x, static_cast<float>(two.y) * pairs.y));
     });
     fold_columns<NH>(s, lane & 4);
   }
@@ -881,6 +899,8 @@ __device__ __forceinline__ void grouped_scores_body(const DecodeArgs& a) {
   __shared__ GroupedQuery query;
   __shared__ __attribute__((aligned(16))) f32x2 radii[kWaves4][kPairs];
   __shared__ int q_shift[kMaxHeads];
+  __shared__ __attribute__((aligned(16))) float pair_down[kPairs];
+  __shared__ __attribute__((aligned(16))) uint16_t exponents[kPairs][NH];
   const int kvh = blockIdx.x, seq = blockIdx.y, chunk = blockIdx.z;
   const int L = uni(clamped_len(a, seq)), n_pages = pages_of_len(L);
   const int page0 = chunk * a.pages_per_chunk;
@@ -905,14 +925,14 @@ __device__ __forceinline__ void grouped_scores_body(const DecodeArgs& a) {
     rp = make_rsrc(a.params + ph * (kPairs * 2), packed ? kPairs * 8u : 0u);
   };
   Walk w;
-  w.init(table[wave], query, radii[wave], lane);
+  w.init(table[wave], query, pair_down, radii[wave], lane);
   __amdgpu_buffer_rsrc_t rc_cur, rp_cur, rc_nxt, rp_nxt;
   int nv_cur, nv_nxt;
   page_setup(0, rc_cur, rp_cur, nv_cur);
   w.load_params(rp_cur, lane);
 #pragma unroll
   for (int t = 0; t < 8; ++t) w.load_unit_of(t, rc_cur, 0);
-  store_grouped_query<NH>(query, q_shift, qf, 1.f, tid);
+  store_grouped_query<NH>(query, q_shift, pair_down, exponents, qf, 1.f, tid);
   __syncthreads();
   const int shift = q_shift[column_head<NH>(lane & 15)];
   for (int it = 0; it < n_w; ++it) {
@@ -970,8 +990,8 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     __attribute__((aligned(16))) uint32_t vpar[kQuantV ? kMatWaves : 1][kQuantV ? kGroup : 1];
     float red_ml[kMatWaves][NH][3];                                      // m, l, sum of p * zero-point
     int q_shift[kMaxHeads];
-    float pair_down[kGrouped ? 1 : kPairs];
-    __attribute__((aligned(16))) uint16_t exponents[kGrouped ? 1 : kPairs][NH];
+    __attribute__((aligned(16))) float pair_down[kPairs];
+    __attribute__((aligned(16))) uint16_t exponents[kPairs][NH];
     int stage;
   };
   __shared__ Shared sh;
@@ -1077,7 +1097,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   int nv_cur, nv_nxt, rot_cur, rot_nxt;
   std::conditional_t<kGrouped, Grouped, ScoreWalk<W, kOrder, NH, Q32, kQuantV ? 2 : 1, kChain>> w;
   auto init_walk = [&](int lane) {
-    if constexpr (kGrouped) w.init(sh.lut + wave * Grouped::kTableBytes, sh.q, sh.params[wave], lane);
+    if constexpr (kGrouped) w.init(sh.lut + wave * Grouped::kTableBytes, sh.q, sh.pair_down, sh.params[wave], lane);
     else w.init(sh.lut, sh.q, sh.pair_down, sh.params[wave], lane);
   };
   init_walk(lane);
@@ -1117,7 +1137,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   }
   const int stride = kCut ? n_chunks : a.n_chunks;
   if constexpr (kGrouped) {
-    store_grouped_query<NH>(sh.q, sh.q_shift, qf, sign, tid);
+    store_grouped_query<NH>(sh.q, sh.q_shift, sh.pair_down, sh.exponents, qf, sign, tid);
   } else {
     store_key_entry<W, kMatThreads>(sh.lut, entry, tid);                              // while the first page is under way
     store_query_heads<NH, Q32>(sh.q, sh.q_shift, sh.pair_down, sh.exponents, qf, sign, tid);

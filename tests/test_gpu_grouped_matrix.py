@@ -162,3 +162,44 @@ def test_scores_of_a_tail_without_a_page(q_heads, dtype):
         if tail:
             want = torch.matmul(state["q"][s].double(), state["residual"][s, 0, :tail].double().t().contiguous())
             assert float((scores[1][s, :, n - tail:n].double() - want).norm() / want.norm()) <= 5e-7
+
+
+@pytest.mark.parametrize("op,q_heads,dtype", [("score", 3, "f16"), ("score", 8, "f16"), ("decode", 4, "f16"), ("decode", 4, "f32"), ("decode", 8, "f32")])
+@pytest.mark.parametrize("tail", [False, True])
+def test_one_large_radius_costs_the_others_no_bits(op, q_heads, dtype, tail, monkeypatch):
+    """A pair with radii of 15000 beside others of 2^-9, in a pair where the queries are 2^-20 of their largest: products of
+    one size.  Bounds as for inputs of one size, 5e-7 for scores and 3e-6 for the output (fp32 arithmetic: 1.3e-7 and 4e-7)."""
+    from perf import cases
+
+    pq = cases.pq
+    case = cases._case("radius", "serve" if tail else op, 2, q_heads, 1, 500, grouped_angles=True, dtype=dtype)
+    keys, queries = cases._keys, cases._queries
+
+    def scaled_keys(case, seed, seq, length):
+        k = keys(case, seed, seq, length).float()
+        big = 15000.0 * torch.tanh(k[..., [7, 71]])
+        k *= 2.0 ** -9
+        k[..., [7, 71]] = big
+        return k.to(cases._float_dtype(case))
+
+    def scaled_queries(case, seed):
+        q = queries(case, seed).float() * 2.0 ** 9
+        q[..., [7, 71]] *= 2.0 ** -20
+        return q.to(cases._float_dtype(case))
+
+    monkeypatch.setattr(cases, "_keys", scaled_keys)
+    monkeypatch.setattr(cases, "_queries", scaled_queries)
+    state, want = cases.prepare(case, 12), cases.exact(case, 12)
+    got = cases.run(state)
+    if tail:                                                              # the new keys are in the residual rows
+        got, want = got[0], want[0]
+    if tail and op == "score":                                            # the tail's scores, of the sequence that has one
+        n = int(state["seq_lens"][1])
+        scores = torch.zeros((2, q_heads, state["max_seq_len"]), device="cuda:0")
+        pq.pq_score_keys(state["layout"], state["q"], state["codes"], state["params"], state["block_table"], state["seq_lens"],
+                         state["max_seq_len"], scores, state["residual"])
+        got = scores[1, :, n // 128 * 128:n]
+        want = torch.matmul(state["q"][1].double(), state["residual"][1, 0, :n % 128].double().t().contiguous())
+    err = float((got.double() - want).norm() / want.norm())
+    print("[radius]", op, q_heads, dtype, tail, err, flush=True)
+    assert err <= (5e-7 if op == "score" else 3e-6), err
