@@ -127,8 +127,8 @@ PQ_HD inline uint32_t angle_bin_interior(float x, float y, const double* tan_edg
 // Bin edges inside the octant are compared in fp32, sign(mx * tan - mn) by one fused multiply-add:
 // with 11-bit significands mn / mx is never nearer to an edge than the rounding of tan
 // (checked for every pair of significands in the tests).
-// The result does not hold where x = 0 or y = 0; `smallest` collects min(|x|, |y|) as fp16 bits
-// in its two halves, so that the caller can tell.
+// The result does not hold where x = 0 or y = 0, unless settle_zeros() has been over the pairs; `smallest` collects
+// min(|x|, |y|) as fp16 bits in its two halves, so that the caller can tell.
 namespace detail {
 #if defined(__HIP_DEVICE_COMPILE__)
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
@@ -208,6 +208,21 @@ PQ_HD inline uint32_t angle_bins_of_four(const uint32_t (&x)[2], const uint32_t 
     code ^= passed;
   }
   return code;
+}
+
+// Two fp16 pairs a word: gives zero coordinates the sign of the octant that the pair's axis belongs to (the one that
+// starts there; theta = +pi stays in the last), and the origin the direction theta = 0, so that
+// angle_bins_of_four holds for them.  Other pairs stay as they are.
+PQ_HD inline void settle_zeros(uint32_t& x, uint32_t& y) {
+  using namespace detail;
+  constexpr uint32_t kOne = 0x00010001u;
+  const uint32_t ax = x & 0x7fff7fffu, ay = y & 0x7fff7fffu;
+  const uint32_t zx = top_bits_u16x2(sub_u16x2(ax, kOne)), zy = top_bits_u16x2(sub_u16x2(ay, kOne));   // 1 if zero
+  const uint32_t xn = top_bits_u16x2(x) & ~zx, yn = top_bits_u16x2(y);
+  const uint32_t yneg = yn & (~zy | xn);                     // y = -0 counts as negative beside x < 0 only (theta = -pi)
+  const uint32_t xneg = xn | (zx & ~(zy | yn));              // x = 0: left of the upper half axis, right of the lower one
+  x = ax | (xneg << 15) | (zx & zy);
+  y = ay | (yneg << 15);
 }
 
 // v rounded to the nearest fp16 value, ties to even, returned as a double (|v| < 65504).  One

@@ -243,16 +243,16 @@ __device__ __forceinline__ void encode_group(const KT* keys, int64_t token_strid
       }
       // a coordinate is zero in some lane
       if (__builtin_expect(__builtin_amdgcn_ballot_w64((smallest & 0xffffu) == 0 || (smallest >> 16) == 0) != 0, 0)) {
-        uint32_t bins[2] = {0u, 0u};
 #pragma unroll
         for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(raw[it].x[0][i]), "+v"(raw[it].y[0][i]));   // (nothing of it is prepared outside)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          bins[e >> 2] |= angle_bin<TB>(raw[it].x_of(e), raw[it].y_of(e), tan_edge) << (8 * (e & 3));
+        for (int g = 0; g < 2; ++g) {
+          uint32_t xw[2] = {raw[it].x[0][2 * g], raw[it].x[0][2 * g + 1]}, yw[2] = {raw[it].y[0][2 * g], raw[it].y[0][2 * g + 1]};
+          settle_zeros(xw[0], yw[0]);
+          settle_zeros(xw[1], yw[1]);
+          ang[it][g] = angle_bins_of_four<TB>(xw, yw, tan_edge_f, smallest);
           __builtin_amdgcn_sched_barrier(0);
         }
-        ang[it][0] = bins[0];
-        ang[it][1] = bins[1];
       }
     }
     __builtin_amdgcn_sched_barrier(0);           // one token after the other: registers

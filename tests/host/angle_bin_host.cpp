@@ -67,6 +67,30 @@ extern "C" int angle_bins_of_four_host(const uint16_t* x, const uint16_t* y, int
   return 0;
 }
 
+// The same after settle_zeros(): holds for every pair.
+extern "C" int angle_bins_of_four_settled_host(const uint16_t* x, const uint16_t* y, int64_t n, int t_bits, int32_t* codes) {
+  float tan_edge[4] = {0, 0, 0, 0};
+  const int nb = 1 << t_bits;
+  for (int k = 1; k < nb / 8 && k < 4; ++k) tan_edge[k] = (float)tan(k * (2.0 * M_PI / nb));
+  for (int64_t i = 0; i < n; i += 4) {
+    uint32_t xw[2], yw[2], smallest = 0xffffffffu, c;
+    for (int j = 0; j < 2; ++j) {
+      xw[j] = x[i + 2 * j] | ((uint32_t)x[i + 2 * j + 1] << 16);
+      yw[j] = y[i + 2 * j] | ((uint32_t)y[i + 2 * j + 1] << 16);
+      pq::settle_zeros(xw[j], yw[j]);
+    }
+    switch (t_bits) {
+      case 2: c = pq::angle_bins_of_four<2>(xw, yw, tan_edge, smallest); break;
+      case 3: c = pq::angle_bins_of_four<3>(xw, yw, tan_edge, smallest); break;
+      case 4: c = pq::angle_bins_of_four<4>(xw, yw, tan_edge, smallest); break;
+      case 5: c = pq::angle_bins_of_four<5>(xw, yw, tan_edge, smallest); break;
+      default: return -1;
+    }
+    for (int j = 0; j < 4; ++j) codes[i + j] = (int32_t)((c >> (8 * j)) & 0xffu);
+  }
+  return 0;
+}
+
 // Number of pairs (mn, mx) of fp16 significands and exponent differences for which sign(mx * tan - mn) in
 // fp32, with tan rounded to fp32, is not that of float64.  Every ratio of two fp16 numbers in (2^-3, 1] is one of them.
 extern "C" int64_t edge_mismatches_host(int t_bits) {

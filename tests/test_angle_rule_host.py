@@ -26,6 +26,8 @@ def host_lib(tmp_path_factory):
     lib.angle_bins_interior_host.argtypes = lib.angle_bins_host.argtypes
     lib.angle_bins_of_four_host.restype = ctypes.c_int
     lib.angle_bins_of_four_host.argtypes = lib.angle_bins_host.argtypes
+    lib.angle_bins_of_four_settled_host.restype = ctypes.c_int
+    lib.angle_bins_of_four_settled_host.argtypes = lib.angle_bins_host.argtypes
     lib.edge_mismatches_host.restype = ctypes.c_int64
     lib.edge_mismatches_host.argtypes = [ctypes.c_int]
     lib.round_to_half_host.restype = None
@@ -113,6 +115,24 @@ def test_four_at_a_time_agrees_with_the_full_rule(host_lib, t):
     assert ((np.abs(x) == np.abs(y)) & ~zero).sum() > 10000
     full = _host_bins(host_lib, x, y, t)
     np.testing.assert_array_equal(got[~zero], full[~zero])
+
+
+@pytest.mark.parametrize("t", [2, 3, 4, 5])
+def test_four_at_a_time_with_zeros_settled_is_the_full_rule(host_lib, t):
+    """Every fp16 number, finite or infinite, beside a zero of either sign in either coordinate, and pairs without zeros among them."""
+    every = np.arange(65536, dtype=np.uint16)
+    every = every[(every & 0x7fff) <= 0x7c00].view(np.float16)
+    plus, minus = np.zeros_like(every), -np.zeros_like(every)
+    rng = np.random.default_rng(80)
+    a, b = rng.integers(-3, 4, (2, 400000)).astype(np.float16) * np.float16(0.5)     # zeros, axes and diagonals side by side
+    a, b = np.copysign(a, rng.standard_normal(a.size)).astype(np.float16), np.copysign(b, rng.standard_normal(b.size)).astype(np.float16)
+    x = np.concatenate([every, every, plus, minus, a, plus[:8], minus[:8], plus[:8], minus[:8]])
+    y = np.concatenate([plus, minus, every, every, b, plus[:8], minus[:8], minus[:8], plus[:8]])
+    n = x.size // 4 * 4
+    x, y = np.ascontiguousarray(x[:n]), np.ascontiguousarray(y[:n])
+    got = np.empty(n, np.int32)
+    assert host_lib.angle_bins_of_four_settled_host(x.ctypes.data, y.ctypes.data, n, t, got.ctypes.data) == 0
+    np.testing.assert_array_equal(got, _host_bins(host_lib, x, y, t))
 
 
 @pytest.mark.parametrize("t", [4, 5])
