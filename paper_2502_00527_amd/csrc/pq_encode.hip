@@ -221,8 +221,13 @@ __device__ __forceinline__ void encode_group(const KT* keys, int64_t token_strid
 #pragma unroll
     for (int e = 0; e < 8; ++e) n[it][e] = raw[it].squared(e);
     if constexpr (GA) {
+      if (it > 0 && __builtin_amdgcn_readfirstlane(wave) * 8 + 32 * it >= nv) {   // all tokens of the step past the end: any token of the group will do
 #pragma unroll
-      for (int e = 0; e < 8; ++e) th[it][e] = atan2(static_cast<double>(raw[it].y_of(e)), static_cast<double>(raw[it].x_of(e)));
+        for (int e = 0; e < 8; ++e) th[it][e] = th[it > 0 ? it - 1 : 0][e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) th[it][e] = atan2(static_cast<double>(raw[it].y_of(e)), static_cast<double>(raw[it].x_of(e)));
+      }
     } else if constexpr (sizeof(KT) == 4) {
       ang[it][0] = ang[it][1] = 0u;
 #pragma unroll

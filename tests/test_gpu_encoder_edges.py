@@ -120,3 +120,21 @@ def test_key_encoder_edges(kind, rt):
         # two float64 evaluations of an irrational edge may differ in the last places
         assert not np.any((a != enc["a"]) & (enc["edge_dist"] > 1e-12))
         assert not codes.cpu().numpy()[order][-1, :, :, n - (n_pages - 1) * GROUP:].any()
+
+
+@pytest.mark.parametrize("n", [1, 8, 9, 33, 64, 97, 127, 129])
+def test_grouped_angles_of_partial_pages(n):
+    """Whole steps of a wavefront lie past the end: they have no say in the group's angles."""
+    for dtype, rt in ((np.float16, (4, 4)), (np.float32, (3, 5))):
+        k = _keys("normal", n, 2, n, dtype)
+        enc = polar.encode_keys(k, *rt, GROUP, grouped_angles=True)
+        n_pages = (n + GROUP - 1) // GROUP
+        layout = pq.Layout(128, *rt, GROUP, 2, 1)
+        codes = torch.full((n_pages, 2, 4, GROUP, 2 * sum(rt)), 0xA5, dtype=torch.uint8, device="cuda:0")
+        params = torch.full((n_pages, 2, 2, 64, 2), 7.0, dtype=torch.float16, device="cuda:0")
+        pq.pq_encode_keys(layout, torch.from_numpy(k).to("cuda:0"), torch.arange(n_pages, dtype=torch.int32, device="cuda:0"), codes, params)
+        a, c, s, z, ts, tz = cache_format.unpack_pages(codes.cpu().numpy(), params.cpu().numpy(), n, *rt)
+        for got, want in ((s, "scale"), (z, "zero"), (ts, "t_scale"), (tz, "t_zero")):
+            np.testing.assert_array_equal(got.view(np.uint16), enc[want].view(np.uint16))
+        np.testing.assert_array_equal(c, enc["c"])
+        assert not np.any((a != enc["a"]) & (enc["edge_dist"] > 1e-12))
