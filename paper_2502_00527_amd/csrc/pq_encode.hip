@@ -521,7 +521,7 @@ extern "C" int pq_encode_keys(const pq_layout* layout, const void* keys, pq_dtyp
   if ((reinterpret_cast<uintptr_t>(codes_pool) & 15u) || (reinterpret_cast<uintptr_t>(params_pool) & 15u))
     return PQ_ERR_INVALID_ARG;
   const int64_t n_groups = (n_tokens + kGroup - 1) / kGroup;
-  if (n_groups > 0x7fffffff || layout->n_kv_heads > 65535) return PQ_ERR_UNSUPPORTED;
+  if (n_groups >= (int64_t{1} << 24) || layout->n_kv_heads > 65535) return PQ_ERR_UNSUPPORTED;
 
   EncodeArgs a;
   a.keys = keys;
@@ -535,26 +535,29 @@ extern "C" int pq_encode_keys(const pq_layout* layout, const void* keys, pq_dtyp
   a.n_kv_heads = layout->n_kv_heads;
   fill_edges(a, layout->t_bits);
 
-  const int64_t blocks = n_groups * layout->n_kv_heads;
-  if (blocks > 0x7fffffff) return PQ_ERR_UNSUPPORTED;
-  const dim3 grid(static_cast<uint32_t>(blocks));
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  hipError_t e = hipSuccess;
-  switch (layout->r_bits * 10 + layout->t_bits + (layout->angle_quantizer == PQ_ANGLE_GROUPED ? 100 : 0)) {
-    case 144: e = launch_encode<4, 4, true>(a, key_dtype, grid, st); break;
-    case 133: e = launch_encode<3, 3, true>(a, key_dtype, grid, st); break;
-    case 153: e = launch_encode<5, 3, true>(a, key_dtype, grid, st); break;
-    case 135: e = launch_encode<3, 5, true>(a, key_dtype, grid, st); break;
-    case 142: e = launch_encode<4, 2, true>(a, key_dtype, grid, st); break;
-    case 124: e = launch_encode<2, 4, true>(a, key_dtype, grid, st); break;
-    case 44: e = launch_encode<4, 4>(a, key_dtype, grid, st); break;
-    case 33: e = launch_encode<3, 3>(a, key_dtype, grid, st); break;
-    case 53: e = launch_encode<5, 3>(a, key_dtype, grid, st); break;
-    case 35: e = launch_encode<3, 5>(a, key_dtype, grid, st); break;
-    case 42: e = launch_encode<4, 2>(a, key_dtype, grid, st); break;
-    case 24: e = launch_encode<2, 4>(a, key_dtype, grid, st); break;
-    default: return PQ_ERR_UNSUPPORTED;
-  }
+  const int kind = layout->r_bits * 10 + layout->t_bits + (layout->angle_quantizer == PQ_ANGLE_GROUPED ? 100 : 0);
+  const hipError_t e = for_group_ranges(n_groups, layout->n_kv_heads, [&](int64_t first, int64_t groups) {
+    EncodeArgs part = a;
+    part.keys = static_cast<const char*>(keys) + first * kGroup * token_stride * (key_dtype == PQ_F16 ? 2 : 4);
+    part.page_ids += first;
+    part.n_tokens -= first * kGroup;
+    const dim3 grid(static_cast<uint32_t>(groups * layout->n_kv_heads));
+    switch (kind) {
+      case 144: return launch_encode<4, 4, true>(part, key_dtype, grid, st);
+      case 133: return launch_encode<3, 3, true>(part, key_dtype, grid, st);
+      case 153: return launch_encode<5, 3, true>(part, key_dtype, grid, st);
+      case 135: return launch_encode<3, 5, true>(part, key_dtype, grid, st);
+      case 142: return launch_encode<4, 2, true>(part, key_dtype, grid, st);
+      case 124: return launch_encode<2, 4, true>(part, key_dtype, grid, st);
+      case 44: return launch_encode<4, 4>(part, key_dtype, grid, st);
+      case 33: return launch_encode<3, 3>(part, key_dtype, grid, st);
+      case 53: return launch_encode<5, 3>(part, key_dtype, grid, st);
+      case 35: return launch_encode<3, 5>(part, key_dtype, grid, st);
+      case 42: return launch_encode<4, 2>(part, key_dtype, grid, st);
+      default: return launch_encode<2, 4>(part, key_dtype, grid, st);     // layout_supported() admits no other
+    }
+  });
   if (e != hipSuccess) return record_hip_error(e);
   return PQ_OK;
 }

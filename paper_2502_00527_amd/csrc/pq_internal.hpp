@@ -35,4 +35,15 @@ struct ChunkPlan {
 };
 ChunkPlan plan_chunks(int32_t n_seqs, int32_t n_kv_heads, int32_t max_seq_len);
 
+// An encoder's work-groups (256 threads) are one a (token group, KV head) in a one-dimensional grid, which HIP limits to
+// 2^32 - 1 threads: launch(first group, groups) is called for as many ranges of token groups as that takes.
+template <typename F>
+hipError_t for_group_ranges(int64_t n_groups, int32_t n_kv_heads, F launch) {
+  const int64_t most = ((int64_t{1} << 24) - 1) / n_kv_heads;            // 256 and more: n_kv_heads < 2^16
+  hipError_t e = hipSuccess;
+  for (int64_t first = 0; first < n_groups && e == hipSuccess; first += most)
+    e = launch(first, n_groups - first < most ? n_groups - first : most);
+  return e;
+}
+
 }  // namespace pq

@@ -240,7 +240,7 @@ extern "C" int pq_encode_values(const pq_layout* layout, int32_t v_bits, const v
       head_stride < 0 || (reinterpret_cast<uintptr_t>(vq_pool) & 15u) || (reinterpret_cast<uintptr_t>(vq_params_pool) & 3u))
     return PQ_ERR_INVALID_ARG;
   const int64_t n_groups = (n_tokens + kGroup - 1) / kGroup;
-  if (n_groups > 0x7fffffff || layout->n_kv_heads > 65535) return PQ_ERR_UNSUPPORTED;
+  if (n_groups >= (int64_t{1} << 24) || layout->n_kv_heads > 65535) return PQ_ERR_UNSUPPORTED;
   ValueArgs a;
   a.values = static_cast<const __half*>(values);
   a.page_ids = page_ids;
@@ -251,13 +251,17 @@ extern "C" int pq_encode_values(const pq_layout* layout, int32_t v_bits, const v
   a.n_tokens = n_tokens;
   a.n_pool_pages = n_pool_pages;
   a.n_kv_heads = layout->n_kv_heads;
-  const int64_t blocks = n_groups * layout->n_kv_heads;
-  if (blocks > 0x7fffffff) return PQ_ERR_UNSUPPORTED;
-  const dim3 grid(static_cast<uint32_t>(blocks));
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  if (v_bits == 4) hipLaunchKernelGGL(pq_encode_values_kernel<4>, grid, dim3(kValueThreads), 0, st, a);
-  else hipLaunchKernelGGL(pq_encode_values_kernel<2>, grid, dim3(kValueThreads), 0, st, a);
-  const hipError_t e = hipGetLastError();
+  const hipError_t e = for_group_ranges(n_groups, layout->n_kv_heads, [&](int64_t first, int64_t groups) {
+    ValueArgs part = a;
+    part.values += first * kGroup * token_stride;
+    part.page_ids += first;
+    part.n_tokens -= first * kGroup;
+    const dim3 grid(static_cast<uint32_t>(groups * layout->n_kv_heads));
+    if (v_bits == 4) hipLaunchKernelGGL(pq_encode_values_kernel<4>, grid, dim3(kValueThreads), 0, st, part);
+    else hipLaunchKernelGGL(pq_encode_values_kernel<2>, grid, dim3(kValueThreads), 0, st, part);
+    return hipGetLastError();
+  });
   if (e != hipSuccess) return record_hip_error(e);
   return PQ_OK;
 }

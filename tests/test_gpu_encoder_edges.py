@@ -138,3 +138,36 @@ def test_grouped_angles_of_partial_pages(n):
             np.testing.assert_array_equal(got.view(np.uint16), enc[want].view(np.uint16))
         np.testing.assert_array_equal(c, enc["c"])
         assert not np.any((a != enc["a"]) & (enc["edge_dist"] > 1e-12))
+
+
+def test_more_work_groups_than_one_launch_takes():
+    """2^24 work-groups of 256 threads are more than a grid may have: the encoders launch in parts.  The heads are views of
+    one row, and only pages before, across and behind the parts' border have a place in the pools."""
+    heads, groups = 4096, 4200
+    part = (2 ** 24 - 1) // heads
+    n = groups * GROUP - 5
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(1)
+    rows = torch.randn((n, 1, 128), generator=g, device="cuda:0", dtype=torch.float16)
+    kept = [3, part - 1, part, groups - 1]
+    ids = torch.full((groups,), -1, dtype=torch.int32)
+    ids[kept] = torch.arange(4, dtype=torch.int32)
+    ids = ids.to("cuda:0")
+    pools = []
+    for h in (heads, 1):
+        layout = pq.Layout(128, 3, 3, GROUP, h, 0)
+        codes = torch.zeros((4, h, 4 * GROUP * 12), dtype=torch.uint8, device="cuda:0")
+        params = torch.zeros((4, h, 64, 2), dtype=torch.float16, device="cuda:0")
+        vq = torch.zeros((4, h, GROUP * 128 // 4), dtype=torch.uint8, device="cuda:0")
+        vq_params = torch.zeros((4, h, GROUP, 2), dtype=torch.float16, device="cuda:0")
+        if h > 1:
+            pq.pq_encode_keys(layout, rows.expand(n, h, 128), ids, codes, params)
+            pq.pq_encode_values(layout, 2, rows.expand(n, h, 128), ids, vq, vq_params)
+        else:
+            for page, group in enumerate(kept):
+                at = torch.tensor([page], dtype=torch.int32, device="cuda:0")
+                pq.pq_encode_keys(layout, rows[group * GROUP:(group + 1) * GROUP], at, codes, params)
+                pq.pq_encode_values(layout, 2, rows[group * GROUP:(group + 1) * GROUP], at, vq, vq_params)
+        pools.append((codes, params, vq, vq_params))
+    for many, one in zip(*pools):
+        assert torch.equal(many, one.expand_as(many)) and bool(one.any())
