@@ -6,7 +6,8 @@ Section 3.2) and decode attention through the per-query lookup table (Section
 turns torch tensors into device pointers and sizes, passes torch's current HIP
 stream, and raises on any non-zero status.  The calls of a serving loop are marshalled
 natively (csrc/pq_binding.cpp, `_native`); what that declines -- a wrong argument, or an
-unusual one -- goes through the functions here, which raise or do the same by ctypes.  There is
+unusual one -- goes through the functions here, which raise or do the same by ctypes, and so does
+everything where it is not built for this interpreter and torch.  There is
 no fallback for the kernels: if the shared library has not been built (`python -m paper_2502_00527_amd.build`),
 the first call raises.
 
@@ -17,6 +18,7 @@ from __future__ import annotations
 import ctypes
 import importlib
 import os
+import warnings
 from ctypes import c_float, c_int, c_int32, c_int64, c_size_t, c_void_p
 from typing import Optional
 
@@ -107,18 +109,28 @@ def load_library():
     return _lib
 
 
+class _ByCtypes:
+    """In the place of the native marshalling module: declines every call."""
+
+    @staticmethod
+    def _decline(*args):
+        return None
+
+    decode_attention = score_keys = encode_keys = encode_values = append_keys = _decline
+
+
 def _marshaller():
-    """The native marshalling module; raises if it is not built, like load_library()."""
+    """The native marshalling module, or what stands in for it if it cannot be loaded."""
     global _calls
     if _calls is None:
         load_library()
         try:
             import torch  # noqa: F401  (the module is linked against its libraries)
-            module = importlib.import_module("._native", __package__)
+            _calls = importlib.import_module("._native", __package__)
         except ImportError as e:
-            raise PolarQuantError(
-                f"the native binding cannot be loaded ({e}): build it with `python -m paper_2502_00527_amd.build`") from e
-        _calls = module
+            warnings.warn(f"calls are marshalled by ctypes, which takes the host about 10 us longer: {e} "
+                          "(`python -m paper_2502_00527_amd.build` builds the native part)", RuntimeWarning, stacklevel=3)
+            _calls = _ByCtypes()
     return _calls
 
 

@@ -1,5 +1,6 @@
 """Builds libpolarquant.so (the HIP kernels and their C ABI) for gfx950, and the Python binding's
-native part (_native.so), in-tree.
+native part (_native.<ABI tag>.so), in-tree.  The latter is host code that only makes calls cheaper: where a compiler
+or the headers for it are missing the build says so and goes on.
 
 `python -m paper_2502_00527_amd.build` compiles every source under csrc/ with
 hipcc; it cross-compiles without a GPU.  The flags matter for correctness:
@@ -22,9 +23,9 @@ LIB_PATH = os.path.join(PKG_DIR, "libpolarquant.so")
 SOURCES = ["pq_api.hip", "pq_encode.hip", "pq_values.hip", "pq_decode.hip", "pq_decode_matrix.hip", "pq_decode_matrix_v4.hip", "pq_decode_matrix_v2.hip",
            "pq_decode_partials_ga.hip", "pq_decode_grouped.hip", "pq_decode_grouped_v4.hip", "pq_decode_grouped_v2.hip"]
 
-# the Python binding's argument marshalling (host code only)
+# the Python binding's argument marshalling (host code only), named for the interpreter it is built for
 BINDING = "pq_binding.cpp"
-BINDING_PATH = os.path.join(PKG_DIR, "_native.so")
+BINDING_PATH = os.path.join(PKG_DIR, "_native" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -46,13 +47,30 @@ def _filter(text: str) -> str:
                      if "packed-fp32-ops" not in l and "is not a recognized feature" not in l)
 
 
+def binding_lacks():
+    """What the binding cannot be built without and is not there; None if it can be."""
+    if shutil.which("g++") is None:
+        return "g++"
+    python_h = os.path.join(sysconfig.get_paths()["include"], "Python.h")
+    if not os.path.exists(python_h):
+        return python_h
+    try:
+        from torch.utils import cpp_extension
+    except ImportError as e:
+        return str(e)
+    header = os.path.join("torch", "csrc", "autograd", "python_variable.h")
+    if not any(os.path.exists(os.path.join(d, header)) for d in cpp_extension.include_paths()):
+        return header
+    return None
+
+
 def _binding_commands(inc, obj):
     """Compile and link commands of the binding; it finds libpolarquant.so beside itself."""
     import torch
     from torch.utils import cpp_extension
     torch_inc = [f for d in cpp_extension.include_paths() for f in ("-isystem", d)]
-    abi = f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"
-    compile_ = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", abi, *inc, *torch_inc, "-isystem", sysconfig.get_paths()["include"],
+    abi = [f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DPQ_TORCH_VERSION="{torch.__version__}"']
+    compile_ = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", *abi, *inc, *torch_inc, "-isystem", sysconfig.get_paths()["include"],
                 "-c", os.path.join(CSRC, BINDING), "-o", obj]
     link = ["g++", "-shared", obj, "-o", BINDING_PATH, "-L", PKG_DIR, "-lpolarquant", "-Wl,-rpath,$ORIGIN",
             *[f for d in cpp_extension.library_paths() for f in ("-L", d)], "-ltorch_python", "-ltorch_cpu", "-lc10"]
@@ -60,7 +78,7 @@ def _binding_commands(inc, obj):
 
 
 def build(verbose: bool = True, extra_flags=()) -> str:
-    """Compiles every translation unit (in parallel) and links libpolarquant.so."""
+    """Compiles every translation unit (in parallel) and links libpolarquant.so and the binding."""
     obj_dir = os.path.join(PKG_DIR, "_build")
     os.makedirs(obj_dir, exist_ok=True)
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
@@ -71,11 +89,17 @@ def build(verbose: bool = True, extra_flags=()) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, obj, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-    binding_obj = os.path.join(obj_dir, BINDING.replace(".cpp", ".o"))
-    compile_, link_binding = _binding_commands(inc, binding_obj)
-    if verbose:
-        print(" ".join(compile_), flush=True)
-    binding = subprocess.Popen(compile_, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    for name in os.listdir(PKG_DIR):                       # of an earlier build, or of one for another interpreter
+        if name.startswith("_native.") and name.endswith(".so"):
+            os.unlink(os.path.join(PKG_DIR, name))
+    binding, lacks = None, binding_lacks()
+    if lacks is None:
+        compile_, link_binding = _binding_commands(inc, os.path.join(obj_dir, BINDING.replace(".cpp", ".o")))
+        if verbose:
+            print(" ".join(compile_), flush=True)
+        binding = subprocess.Popen(compile_, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    else:
+        print(f"{BINDING} is not built ({lacks} is missing): calls are marshalled by ctypes", file=sys.stderr, flush=True)
     objs = []
     for src, obj, proc in procs:
         out, _ = proc.communicate()
@@ -90,6 +114,8 @@ def build(verbose: bool = True, extra_flags=()) -> str:
     res = subprocess.run(link, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("link failed:\n" + _filter(res.stdout + res.stderr))
+    if binding is None:
+        return LIB_PATH
     out, _ = binding.communicate()
     if binding.returncode != 0:
         raise RuntimeError(f"g++ failed on {BINDING}:\n{out}")

@@ -264,6 +264,19 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", "Argument marshalling fo
 }  // namespace
 
 PyMODINIT_FUNC PyInit__native(void) {
+  // tensors are read through the headers of one torch
+  PyObject* const torch = PyImport_ImportModule("torch");
+  if (!torch) return nullptr;
+  PyObject* const version = PyObject_GetAttrString(torch, "__version__");
+  Py_DECREF(torch);
+  if (!version) return nullptr;
+  PyObject* const text = PyObject_Str(version);
+  Py_DECREF(version);
+  if (!text) return nullptr;
+  const bool same = PyUnicode_CompareWithASCIIString(text, PQ_TORCH_VERSION) == 0;
+  if (!same) PyErr_Format(PyExc_ImportError, "_native was built for torch %s, this is %U", PQ_TORCH_VERSION, text);
+  Py_DECREF(text);
+  if (!same) return nullptr;
   PyObject* const torch_c = PyImport_ImportModule("torch._C");
   if (!torch_c) return nullptr;
   get_device = PyObject_GetAttrString(torch_c, "_cuda_getDevice");
