@@ -126,7 +126,9 @@ def _marshaller():
         load_library()
         try:
             import torch  # noqa: F401  (the module is linked against its libraries)
-            _calls = importlib.import_module("._native", __package__)
+            module = importlib.import_module("._native", __package__)
+            module.set_layout_type(Layout)
+            _calls = module
         except ImportError as e:
             warnings.warn(f"calls are marshalled by ctypes, which takes the host about 10 us longer: {e} "
                           "(`python -m paper_2502_00527_amd.build` builds the native part)", RuntimeWarning, stacklevel=3)

@@ -10,6 +10,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <climits>
+#include <cstring>
 
 #include "polarquant.h"
 
@@ -18,26 +19,18 @@ namespace {
 // The value of an argument that is not usable here; unwinds to the function's end, which returns None.
 struct Decline {};
 
-struct LayoutView {
-  Py_buffer buffer = {};
-  explicit LayoutView(PyObject* o) {
-    if (PyObject_GetBuffer(o, &buffer, PyBUF_SIMPLE) != 0) {
-      PyErr_Clear();
-      buffer.obj = nullptr;
-      throw Decline{};
-    }
-    if (buffer.len != static_cast<Py_ssize_t>(sizeof(pq_layout))) {
-      PyBuffer_Release(&buffer);
-      throw Decline{};
-    }
-  }
-  LayoutView(const LayoutView&) = delete;
-  LayoutView& operator=(const LayoutView&) = delete;
-  ~LayoutView() {
-    if (buffer.obj) PyBuffer_Release(&buffer);
-  }
-  const pq_layout* get() const { return static_cast<const pq_layout*>(buffer.buf); }
-};
+// The layout class of __init__.py; no other object is taken for a layout, whatever bytes it holds.
+PyObject* layout_type = nullptr;
+pq_layout layout_of(PyObject* o) {
+  Py_buffer buffer;
+  if (!layout_type || reinterpret_cast<PyObject*>(Py_TYPE(o)) != layout_type || PyObject_GetBuffer(o, &buffer, PyBUF_SIMPLE) != 0) throw Decline{};
+  pq_layout layout;
+  const bool whole = buffer.len == static_cast<Py_ssize_t>(sizeof(layout));
+  if (whole) memcpy(&layout, buffer.buf, sizeof(layout));
+  PyBuffer_Release(&buffer);
+  if (!whole) throw Decline{};
+  return layout;
+}
 
 const at::Tensor& device_tensor(PyObject* o) {
   if (!THPVariable_CheckExact(o)) throw Decline{};
@@ -114,21 +107,21 @@ PyObject* guarded(Py_ssize_t n_args, Py_ssize_t want, F call) {
     Py_RETURN_NONE;
   }
 }
+struct Unlocked {
+  PyThreadState* const state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
 template <typename F>
 int without_lock(F f) {
-  int status;
-  Py_BEGIN_ALLOW_THREADS
-  status = f();
-  Py_END_ALLOW_THREADS
-  return status;
+  const Unlocked unlocked;
+  return f();
 }
 
 // (layout, q, codes, params, v_pool, block_table, seq_lens, max_seq_len, sm_scale, out, workspace, scores, residual,
 //  v_bits, v_params)
 PyObject* decode_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded(n, 15, [&] {
-    const LayoutView layout(a[0]);
-    const pq_layout* l = layout.get();
+    const pq_layout layout = layout_of(a[0]), *const l = &layout;
     const at::Tensor& q = contiguous_tensor(a[1]);
     check_rows(q, l, false);
     const at::Tensor &codes = contiguous_tensor(a[2]), &params = contiguous_tensor(a[3]);
@@ -176,8 +169,7 @@ PyObject* decode_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // (layout, q, codes, params, block_table, seq_lens, max_seq_len, scores, residual)
 PyObject* score_keys(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded(n, 9, [&] {
-    const LayoutView layout(a[0]);
-    const pq_layout* l = layout.get();
+    const pq_layout layout = layout_of(a[0]), *const l = &layout;
     const at::Tensor& q = contiguous_tensor(a[1]);
     check_rows(q, l, false);
     const at::Tensor &codes = contiguous_tensor(a[2]), &params = contiguous_tensor(a[3]);
@@ -203,8 +195,7 @@ PyObject* score_keys(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // (layout, keys, page_ids, codes, params)
 PyObject* encode_keys(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded(n, 5, [&] {
-    const LayoutView layout(a[0]);
-    const pq_layout* l = layout.get();
+    const pq_layout layout = layout_of(a[0]), *const l = &layout;
     const at::Tensor& keys = device_tensor(a[1]);
     check_rows(keys, l, true);
     if (keys.stride(2) != 1) throw Decline{};
@@ -221,8 +212,7 @@ PyObject* encode_keys(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // (layout, v_bits, values, page_ids, vq_pool, vq_params)
 PyObject* encode_values(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded(n, 6, [&] {
-    const LayoutView layout(a[0]);
-    const pq_layout* l = layout.get();
+    const pq_layout layout = layout_of(a[0]), *const l = &layout;
     const int32_t v_bits = integer32(integer(a[1]));
     const at::Tensor& values = device_tensor(a[2]);
     check_rows(values, l, true);
@@ -239,8 +229,7 @@ PyObject* encode_values(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // (layout, new_keys, residual, seq_lens, block_table, codes, params)
 PyObject* append_keys(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded(n, 7, [&] {
-    const LayoutView layout(a[0]);
-    const pq_layout* l = layout.get();
+    const pq_layout layout = layout_of(a[0]), *const l = &layout;
     const at::Tensor& keys = contiguous_tensor(a[1]);
     check_rows(keys, l, true);
     const at::Tensor &codes = contiguous_tensor(a[5]), &params = contiguous_tensor(a[6]);
@@ -256,9 +245,15 @@ PyObject* append_keys(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
+PyObject* set_layout_type(PyObject*, PyObject* type) {
+  Py_INCREF(type);
+  Py_XSETREF(layout_type, type);
+  Py_RETURN_NONE;
+}
+
 #define PQ_METHOD(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {PQ_METHOD(decode_attention), PQ_METHOD(score_keys), PQ_METHOD(encode_keys), PQ_METHOD(encode_values),
-                         PQ_METHOD(append_keys), {nullptr, nullptr, 0, nullptr}};
+                         PQ_METHOD(append_keys), {"set_layout_type", set_layout_type, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", "Argument marshalling for libpolarquant.", -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

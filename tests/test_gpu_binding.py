@@ -58,3 +58,26 @@ def test_what_the_native_module_declines_still_works_or_raises():
         got = state["out"].clone()
     torch.cuda.synchronize()
     assert torch.equal(got, want)
+
+
+def test_only_a_layout_is_taken_for_one():
+    """Other objects that hold the same bytes raise, as the Python functions do."""
+    from perf import cases
+
+    pq = cases.pq
+    state = cases.prepare(cases._case("layout", "score", 2, 8, 2, 300), 11)
+    args = [state[k] for k in ("q", "codes", "params", "block_table", "seq_lens", "max_seq_len", "scores")]
+    calls = pq._marshaller()
+    assert calls.score_keys(state["layout"], *args, None) == 0
+    for other in (bytes(state["layout"]), bytearray(state["layout"]), memoryview(state["layout"]), None, 7):
+        assert calls.score_keys(other, *args, None) is None
+        with pytest.raises((AttributeError, TypeError)):
+            pq.pq_score_keys(other, *args)
+
+    class Named(pq.Layout):
+        pass
+
+    want = state["scores"].clone()
+    state["scores"].zero_()
+    pq.pq_score_keys(Named(128, 4, 4, 128, 2, 0), *args)
+    assert torch.equal(state["scores"], want)
