@@ -6,25 +6,66 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("op,v_bits", [("decode", 16), ("decode", 2), ("score", 16), ("prefill", 4), ("serve", 16)])
-def test_both_ways_of_marshalling_make_the_same_call(op, v_bits, monkeypatch):
-    """With the native module declining everything the calls go through ctypes."""
+class Recorder:
+    """The native module, and what each of its calls returned."""
+
+    def __init__(self, module):
+        self.module, self.made = module, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            status = getattr(self.module, name)(*args)
+            self.made.append((name, status))
+            return status
+        return call
+
+
+class Declines:
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+@pytest.mark.parametrize("op,v_bits,calls", [("decode", 16, ["decode_attention"]), ("decode", 2, ["decode_attention"]), ("score", 16, ["score_keys"]),
+                                             ("prefill", 4, ["encode_keys", "encode_values"]), ("prefill", 16, ["encode_keys"]),
+                                             ("serve", 16, ["append_keys", "decode_attention"]), ("serve", 4, ["append_keys", "decode_attention"])])
+def test_both_ways_of_marshalling_make_the_same_call(op, v_bits, calls, monkeypatch):
+    """With the native module declining everything the calls go through ctypes; otherwise it makes them all."""
     from perf import cases
 
     pq = cases.pq
     case = cases._case("both", op, 3, 8, 2, 700, min_context=700 if op == "prefill" else 300, v_bits=v_bits, shuffled_pages=True)
-    native = cases.run(cases.prepare(case, 9))
-
-    class Declines:
-        def __getattr__(self, name):
-            return lambda *a: None
-
-    pq._marshaller()
-    monkeypatch.setattr(pq, "_calls", Declines())
-    by_ctypes = cases.run(cases.prepare(case, 9))
-    as_tuple = lambda x: x if isinstance(x, tuple) else (x,)
-    for a, b in zip(as_tuple(native), as_tuple(by_ctypes)):
+    native = Recorder(pq._marshaller())
+    results = []
+    for way in (native, Declines()):
+        monkeypatch.setattr(pq, "_calls", way)
+        result = cases.run(cases.prepare(case, 9))
+        results.append(result if isinstance(result, tuple) else (result,))
+    assert native.made == [(name, 0) for name in calls]
+    for a, b in zip(*results):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("v_bits", [16, 4])
+def test_scores_and_residual_are_marshalled(v_bits, monkeypatch):
+    from perf import cases
+
+    pq = cases.pq
+    case = cases._case("all", "serve", 3, 8, 2, 700, min_context=300, v_bits=v_bits, shuffled_pages=True)
+    native = Recorder(pq._marshaller())
+    results = []
+    for way in (native, Declines()):
+        monkeypatch.setattr(pq, "_calls", way)
+        st = cases.prepare(case, 9)
+        cases.run(st)
+        scores, alone = torch.full((2, 3, 8, st["max_seq_len"] + 3), -7.0, device="cuda:0")
+        pq.pq_decode_attention(st["layout"], st["q"], st["codes"], st["params"], st["v_pool"], st["block_table"], st["seq_lens"], st["max_seq_len"],
+                               st["sm_scale"], st["out"], st["workspace"], scores, st["residual"], v_bits, st["v_params"])
+        pq.pq_score_keys(st["layout"], st["q"], st["codes"], st["params"], st["block_table"], st["seq_lens"], st["max_seq_len"], alone, st["residual"])
+        results.append((st["out"], scores, alone))
+    assert native.made == [("append_keys", 0), ("decode_attention", 0), ("decode_attention", 0), ("score_keys", 0)]
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+    assert torch.equal(results[0][1], results[0][2]) and bool((results[0][1] == -7.0).any())
 
 
 def test_what_the_native_module_declines_still_works_or_raises():
