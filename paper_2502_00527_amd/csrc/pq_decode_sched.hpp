@@ -374,7 +374,7 @@ __device__ __forceinline__ void finish_chunk(const DecodeArgs& a, int seq, int k
       part_l[tid] = lt * wgt;
     }
     __syncthreads();
-    if (slice == 0) {
+    if (slice == 0 && tid < kFinishThreads) {
       r = part_o[tid] + part_o[tid + 32];
       lt = part_l[tid] + part_l[tid + 32];
     }
