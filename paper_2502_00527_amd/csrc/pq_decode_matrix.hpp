@@ -308,16 +308,6 @@ __device__ __forceinline__ float sum_parts(float x) {
   return __builtin_isinf(high) ? high : high + low;
 }
 constexpr int kScaleTop = 3;
-__device__ __forceinline__ f16x2 split_part(bool low) {
-  return low ? f16x2{static_cast<_Float16>(-1.f), static_cast<_Float16>(1 << kLowShift)} : f16x2{static_cast<_Float16>(0.f), static_cast<_Float16>(1.f)};
-}
-__device__ __forceinline__ uint32_t split_pair(float x0, float x1, f16x2 part) {
-  const f16x2 h = to_half2(x0, x1);
-  const float minus_low = static_cast<float>(part.x), unit = static_cast<float>(part.y);
-  const f16x2 r = {static_cast<_Float16>(fmaf(fmaf(static_cast<float>(h.x), minus_low, x0), unit, 0.f)),
-                   static_cast<_Float16>(fmaf(fmaf(static_cast<float>(h.y), minus_low, x1), unit, 0.f))};
-  return h2u(r);
-}
 __device__ __forceinline__ f16x8 as_operand(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
   const u32x4 v = {a, b, c, d};
   f16x8 r;
