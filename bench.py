@@ -325,8 +325,9 @@ def main() -> int:
         enc_bytes = keys.numel() * keys.element_size() + e_codes.numel() + e_params.numel()
         enc = {"entry_point": "pq_encode_keys", "tokens": n_tok, "kv_heads": pre.n_kv_heads, "ms_per_call": ms_enc,
                "pairs_per_s": n_tok * pre.n_kv_heads * (pre.head_dim // 2) / (ms_enc * 1e-3),
-               "GBps": enc_bytes / (ms_enc * 1e-3) / 1e9, "bound": "alu",
-               "note": "exactly rounded fp32 radius chain and exact angle classification; not HBM-bound"}
+               "GBps": enc_bytes / (ms_enc * 1e-3) / 1e9, "bound": "alu" if pre.grouped_angles else "hbm and alu in turn",
+               "note": "float64 arc tangents" if pre.grouped_angles else
+                       "work-groups load, compute and store in step: neither HBM nor the vector unit is busy all the time"}
         del keys, e_codes, e_params
 
     traffic, traffic_source = read_traffic_note(wl.name, kernel) if args.v_bits == 16 and not wl.grouped_angles else (None, None)

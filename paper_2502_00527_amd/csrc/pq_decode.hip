@@ -113,7 +113,7 @@ bool launch_scores_rt(int rt, int G, const DecodeArgs& a, dim3 grid, hipStream_t
 
 // The name an attention launch runs under, a label of its size in profiles: "roles" for the uniform angle
 // grid with pages for at least 256 work-groups, "partials" below (and with quantized values at more than
-// two query heads per KV head, and with the grouped quantizer, which has a kernel of its own).  On the
+// two query heads per KV head, and for all kernels of the grouped quantizer).  On the
 // uniform grid both are the same kernel; pq_decode_kernel_name() has always told them apart.
 enum class AttentionKernel { kPartials, kRoles };
 
@@ -126,7 +126,7 @@ int64_t four_page_groups(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len
   return std::min<int64_t>(kCountedGroups, (bound + 3) / 4);
 }
 
-// Pages enough for at least 256 work-groups (and on the uniform angle grid).
+// Pages enough for at least 256 work-groups; the second: and on the uniform angle grid.
 bool large_launch(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len) {
   return n_seqs <= 4096 && four_page_groups(l, n_seqs, max_seq_len) >= kComputeUnits;
 }
@@ -150,8 +150,10 @@ bool launch_attention(int w, int v_bits, bool roles, const DecodeArgs& a, dim3 g
 }
 
 // Grouped angle quantizer: query heads per KV head from which on the kernels of pq_decode_matrix.hpp take over.  They make
-// the keys' coordinates, whatever the number of heads (about 8 instructions a symbol); the vector unit's take 3 + heads, and
-// heads times as many for the values.
+// the keys' coordinates, whatever the number of heads (about 11 instructions a symbol); the vector unit's take 3 + heads, and
+// heads times as many for the values.  Vector unit against matrix cores, microseconds: 3 heads, which are two passes of the
+// former, 16 x 16K tokens 231 / 116.  2 heads 16 x 16K 117 / 114, with 4-bit values 78.5 / 82, one sequence of 1000 14.7 / 14.5; 1 head 114 /
+// 114, 76 / 81, 13.5 / 14.2.
 constexpr int kGroupedMatrixHeads = 3;
 bool grouped_on_matrix(const pq_layout* l, int group_total) { return l->angle_quantizer == PQ_ANGLE_GROUPED && group_total >= kGroupedMatrixHeads; }
 bool launch_grouped(int rt, int v_bits, const DecodeArgs& a, dim3 grid, hipStream_t st) {
@@ -391,7 +393,9 @@ bool merges_in_kernel(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_
 
 // Work-groups of 8 wavefronts: sequences of one chunk with more pages than 4 wavefronts take at once, and no more
 // units than compute units (two work-groups of 4 share one otherwise).  One sequence of 777 tokens 13.3 -> 12.2 us,
-// 16 of them 15.0 -> 14.7; up to 4 pages the wider work-group costs 1 us (300 tokens: 9.7 -> 10.7).
+// 16 of them 15.0 -> 14.7; up to 4 pages the wider work-group costs 1 us (300 tokens: 9.7 -> 10.7).  From 8 pages on
+// chunk_lengths() makes two chunks: 8 units 13.0, 64 units 13.8 us; one chunk of 8 wavefronts 13.1 and 14.8 (4-bit values 12.7 and 12.7;
+// 13.0 and 13.1), but with 256 units, a work-group on every compute unit, 20.0 and 18.5 (4-bit values 15.9, 14.7).
 bool wide_groups(const pq_layout* l, const ChunkPlan& plan, int32_t n_seqs, int32_t max_seq_len) {
   return l->angle_quantizer == PQ_ANGLE_UNIFORM && plan.n_chunks == 1 && max_seq_len > kWaveRound * kGroup &&
          static_cast<int64_t>(n_seqs) * l->n_kv_heads <= kComputeUnits;

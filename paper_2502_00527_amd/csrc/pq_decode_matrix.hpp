@@ -601,8 +601,8 @@ struct ScoreWalk {
 // coordinates rho~ cos theta~, rho~ sin theta~ themselves, in fp32, each handed to the matrix unit as two fp16
 // parts (24 bits).  The query side {q_x, q_y} is constant: high part in columns 0 - 7, what its rounding
 // left over in columns 8 - 15.  One instruction takes two pairs of each of the four blocks; any group of 1 to 8 query
-// heads costs the same.  About 8 vector instructions a symbol; with a table of the heads' products and fp32
-// multiply-adds (pq_decode_partials_kernel) it is 3 + heads, and values cost heads times as much as here.
+// heads costs the same.  About 11 vector instructions a symbol (1440 a page, table and fold included); with a table of the heads'
+// products and fp32 multiply-adds (pq_decode_partials_kernel) it is 3 + heads, and values cost heads times as much as here.
 //
 // Scales: as on the uniform grid (QueryShared), each head's and then each pair's largest query element goes to the top and
 // the pair's radius parameters are multiplied the other way, so that a key coordinate keeps its 24 bits until its products

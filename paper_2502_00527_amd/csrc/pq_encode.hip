@@ -174,14 +174,17 @@ __device__ __forceinline__ double shuffle_fold(double v, bool smallest) {
 // (root 2^-23, reciprocal and the three roundings 2^-24 each, z <= rho <= maximum); only where
 // such a quotient is that near to a whole number (2 10^-5 of the pairs at 4 bits) is the wavefront's
 // step done again with the exact operations.
-// Angle codes: four pairs at a time for fp16 keys (pq_angle.hpp), pair by pair for fp32.
+// Angle codes: four pairs at a time for fp16 keys (pq_angle.hpp), a second time where a lane has a zero coordinate; pair by pair
+// for fp32.
 //
 // Bound: neither the vector unit (26 instructions a pair, 43 % of the issue slots) nor HBM (51 %) alone, but one behind the
-// other: the launch is a single round of work-groups that all load, compute and store at the same time; 72 registers,
-// seven of a compute unit's possible eight work-groups are resident (64 registers for the eighth: spills, 25.4 us).  32768 tokens x 8 heads, 84 MB, fp16 keys at 4+4 bits: 33.2 -> 20.1 us, fp32 keys 42.7 -> 32.7,
+// other: work-groups that start together load, compute and store at the same time.  With 72 registers seven of a compute
+// unit's possible eight are resident (64 registers for the eighth: spills, 25.4 us), 1792 of the 2048 of 32768 tokens x 8 heads;
+// the others follow.  That is 84 MB, fp16 keys at 4+4 bits: 33.2 -> 20.1 us, fp32 keys 42.7 -> 32.7,
 // grouped angles (whose float64 arc tangents remain) 80.5 -> 62.  Before: 69 instructions a pair -- rounded roots and IEEE
 // divisions for all pairs, 20 for the angle -- and one token's loads at a time.  Two tokens a thread in work-groups of 512,
-// which all fit: 21.0 us; one in 1024: 22.6.
+// which all fit: 21.0 us; one in 1024: 22.6.  Zero coordinates in every step (a dead channel; the same input again and again): 16.8 us
+// without, 20.4 with them at 4+4 bits, 18.4 and 23.3 at 3+5; with the integer rule for those steps 28.3 and 35.6.
 template <bool GA>
 struct EncodeShared {                                        // LDS of encode_group
   uint32_t mn[kEncThreads / 64][kPairs];                     // per-wavefront minima / maxima of n (bits: n >= 0)

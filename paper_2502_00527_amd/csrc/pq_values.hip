@@ -1,8 +1,8 @@
 // Token-wise value quantization (paper Section 2, the formula for Q(V_n[j]); used by the paper in
 // Section 6.3 "+ value quantization" and the dagger rows of its throughput table):
 //   code = Clamp(round((v - z) / s), 0, 2^b - 1),  z = min of the token's d values, s = (max - min) / (2^b - 1),
-// round-half-to-even, s and z stored as fp16 and used as stored, fp32 arithmetic with IEEE
-// division; a constant row (s == 0) gets code 0.  Dequantized value: code * s + z.
+// round-half-to-even, s and z stored as fp16 and used as stored, codes as fp32 arithmetic with IEEE
+// division gives them; a constant row (s == 0) and a NaN get code 0.  Dequantized value: code * s + z.
 //
 // One work-group quantizes one page (128 tokens) of one KV head: thread = (dim slices sl and sl + 8 of
 // 8 dims each, sl = tid % 8; 4 consecutive tokens), all eight 16-byte loads of it under way together; a
