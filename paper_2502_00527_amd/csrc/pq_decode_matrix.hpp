@@ -833,7 +833,7 @@ __device__ __forceinline__ void alternate_priority(int turn) {
 // With fp16 values the priority falls with the part of the chunk that is left, so that the work-groups of a compute
 // unit get on alike.  Among equals the SIMD favours the older wavefront: of two work-groups that had started
 // together with four pages a wavefront each, one was done at 38 us, the other, by then alone with half of the loads
-// in flight, at 48.  One 128K sequence at 3+3 bits 63.0 -> 57.4 us, 64 ragged ones 241 -> 229, 31 x 3000 tokens
+// in flight, at 48.  One 128K sequence at 3+3 bits 63.0 -> 57.4 us (on a device where it takes 56.5 without, 55.6), 64 ragged ones 241 -> 229, 31 x 3000 tokens
 // 40.4 -> 39.6; 16 x 32K 208.1 -> 208.9, one head per KV head 110.3 -> 110.8.  (The later work-group always first: 61 / 225 / 40.9 /
 // 210.4 / 112; by pages left, not by their part: 57 - 61 / 230 / 40.4 / 209.  With quantized values no difference from turns.)
 __device__ __forceinline__ void priority_of_rest(int left, int all) {

@@ -177,7 +177,7 @@ __device__ __forceinline__ double shuffle_fold(double v, bool smallest) {
 // Angle codes: four pairs at a time for fp16 keys (pq_angle.hpp), a second time where a lane has a zero coordinate; pair by pair
 // for fp32.
 //
-// Bound: neither the vector unit (26 instructions a pair, 43 % of the issue slots) nor HBM (51 %) alone, but one behind the
+// Bound: neither the vector unit (25 instructions a pair, 44 % of the issue slots) nor HBM (52 %) alone, but one behind the
 // other: work-groups that start together load, compute and store at the same time.  With 72 registers seven of a compute
 // unit's possible eight are resident (64 registers for the eighth: spills, 25.4 us), 1792 of the 2048 of 32768 tokens x 8 heads;
 // the others follow.  That is 84 MB, fp16 keys at 4+4 bits: 33.2 -> 20.1 us, fp32 keys 42.7 -> 32.7,
