@@ -130,9 +130,9 @@ def _marshaller():
             module.set_layout_type(Layout)
             _calls = module
         except ImportError as e:
+            _calls = _ByCtypes()
             warnings.warn(f"calls are marshalled by ctypes, which takes the host about 10 us longer: {e} "
                           "(`python -m paper_2502_00527_amd.build` builds the native part)", RuntimeWarning, stacklevel=3)
-            _calls = _ByCtypes()
     return _calls
 
 

@@ -78,6 +78,29 @@ def test_a_nan_stays_where_it_is(v_bits):
         np.testing.assert_array_equal(got[0][0].reshape(want.shape), want)
 
 
+@pytest.mark.parametrize("v_bits", [4, 2])
+def test_an_infinity_stays_in_its_row(v_bits):
+    """A row with an infinite value has an infinite scale and codes 0; the rows beside it are what they are without it."""
+    n, heads = 300, 2
+    v = _rows("normal", n, heads, 5)
+    hit = np.random.default_rng(6).random((n, heads)) < 0.2
+    inf = v.copy()
+    inf[hit, 9] = np.inf
+    inf[hit & (np.arange(n) % 2 == 0)[:, None], 100] = -np.inf
+    n_pages = (n + GROUP - 1) // GROUP
+    layout = pq.Layout(128, 4, 4, GROUP, heads, 0)
+    pool = torch.full((n_pages, pq.pq_vq_bytes_per_page(layout, v_bits)), 0xA5, dtype=torch.uint8, device="cuda:0")
+    params = torch.full((n_pages, heads, GROUP, 2), 7.0, dtype=torch.float16, device="cuda:0")
+    ids = torch.arange(n_pages, dtype=torch.int32, device="cuda:0")
+    pq.pq_encode_values(layout, v_bits, torch.from_numpy(inf).to("cuda:0"), ids, pool, params)
+    codes, s, z = ovalues.quantize_values(v, v_bits)
+    want = cache_format.pack_value_page_stream(np.where(hit[..., None], 0, codes), v_bits, GROUP)
+    np.testing.assert_array_equal(pool.cpu().numpy().reshape(want.shape), want)
+    got = params.permute(0, 2, 1, 3).reshape(n_pages * GROUP, heads, 2).cpu().numpy()[:n]
+    assert np.isinf(got[hit][:, 0]).all()
+    np.testing.assert_array_equal(got[~hit], np.stack([s, z], axis=-1)[~hit])
+
+
 def _keys(kind, n, heads, seed, dtype):
     """[n, heads, 128]: keys on which the code's approximation is in doubt, or the quick angle rule does not hold."""
     rng = np.random.default_rng(seed)
