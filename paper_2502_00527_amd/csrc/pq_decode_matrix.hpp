@@ -26,8 +26,13 @@
 // values; one multiply-add per (head, pair, token) and (head, dim, token) on the vector unit took 2200.
 // With fp16 values a page is 41 KB, 3600 cycles of a compute unit's share of HBM: memory-bound
 // (16 x 32K tokens, 4 query heads per KV head: 209 - 210 us, 6.5 TB/s; 217 on the vector unit).  With
-// quantized values the page is 11 - 17 KB and vector issue is the longer side (4-bit values at the
-// same shape: 153 -> 127 us).
+// quantized values the page is 11 - 17 KB and issue slots are the longer side, with the clock: a wavefront takes 10700 cycles a
+// page beside another one (8400 alone), the same when every page comes from the caches, but at 1.5 - 1.6 GHz from memory and at 2.0 GHz
+// from the caches -- power.  What helps is less to issue: one wait for four operands instead of four, two steps' queries in
+// one LDS read, lane constants kept where the registers allow it, denominators and zero-point sums by one multiply-add a token,
+// the next page's scales found among the values: 796 -> 690 vector instructions, 10700 -> 9600 cycles, and for 16 x 32K tokens
+// with 4-bit values 124 -> 120 us, 32 ragged ones with 2-bit values 42.7 -> 41.6.  (The values of one page beside the scores of
+// the next one, in one instruction stream: the same issue slots, 11200 cycles, +2 %.)
 //
 // The table is kept 16 times in LDS, copy l in the 16-byte column l of a 256-byte row, and lane l
 // reads copy l % 16: reads of 16 lanes touch every bank once whatever the symbols are.  64 KB for
@@ -314,6 +319,14 @@ __device__ __forceinline__ f16x8 as_operand(uint32_t a, uint32_t b, uint32_t c, 
   __builtin_memcpy(&r, &v, 16);
   return r;
 }
+// {a, b, a, b}, the second half as one 64-bit move
+__device__ __forceinline__ f16x8 twice(uint32_t a, uint32_t b) {
+  typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+  const uint64_t ab = __builtin_bit_cast(uint64_t, (u32x2{a, b}));
+  uint64_t again = ab;
+  asm("" : "+v"(again));                          // (or the halves are copied one by one)
+  return __builtin_bit_cast(f16x8, (u64x2{ab, again}));
+}
 __device__ __forceinline__ f16x8 as_operand(const uint4& v) { return as_operand(v.x, v.y, v.z, v.w); }
 
 // A page's radius parameters, one pair a lane, times `down` (of the pair) and the power of two 2^k that
@@ -326,6 +339,11 @@ __device__ __forceinline__ uint32_t scale_page_params(uint32_t par, float down, 
   return h2u(to_half2(__builtin_ldexpf(s, k), __builtin_ldexpf(z, k)));
 }
 
+__device__ __forceinline__ float max2(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
 __device__ __forceinline__ float max3(float a, float b, float c) {
   float r;
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
@@ -367,12 +385,16 @@ __device__ __forceinline__ void fold_columns(f32x4 (&s)[8], bool half) {
       for (int i = 0; i < 4; ++i) {
         s[j][i] = half ? s[4 + j][i] : s[j][i];
         s[j][i] += dpp_of<0x128>(s[j][i]);                               // row_ror:8: the other two
+        asm volatile("" : "+v"(s[j][i]));                                // (here, as one instruction, not behind the next branch)
       }
   } else {
 #pragma unroll
     for (int t = 0; t < 8; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) s[t][i] += dpp_of<0x128>(s[t][i]);
+      for (int i = 0; i < 4; ++i) {
+        s[t][i] += dpp_of<0x128>(s[t][i]);
+        asm volatile("" : "+v"(s[t][i]));
+      }
   }
 }
 // Scores of the residual group (un-quantized fp16 keys, rows past nv_res read as zero), not yet folded: a key row
@@ -429,12 +451,17 @@ struct ScoreWalk {
   uint32_t par;                                 // {fp16 s, fp16 z} of pair `lane`
   f32x4 s[8], d[4], done[4];                    // sums, the chain under way, the chain before it
   f32x4 entry[kAhead + 1][4];
-  u32x2 qv[2];                                  // query and scaled parameters of two steps: fetched early enough that
-  uint32_t sz[2];                               // waiting for them does not wait for the table reads under way
+  // query and scaled parameters of the next steps: fetched early enough that waiting for them does not wait for the
+  // table reads under way; step by step, or (kPairFetch) two steps at a time, half as many LDS operations
+  static constexpr bool kPairFetch = kChain == 16;
+  static constexpr int kFetched = kPairFetch ? 4 : 2;
+  u32x2 qv[kFetched];
+  uint32_t sz[kFetched];
   // Order of the half-steps: a chain's steps first for one half of the batches, then for the other, so
   // that four accumulators serve a chain; without restarts simply step by step.
   static constexpr int kOps = kChain == 16 ? 1 : kChain;   // query operands kept
   uint32_t q_op[kOps][2];
+  f16x8 q_twice;                                // kOps = 1: the operand as a whole, made a half-step ahead
   uint32_t lane_lut, q_addr, par_put, par_get, voff_codes, low_mask, down_addr, table;
 
   __device__ __forceinline__ void init(const uint8_t* lut, const QueryShared& q, const float* pair_down, const uint32_t* params, int lane) {
@@ -473,16 +500,28 @@ struct ScoreWalk {
     }
     return *(const PQ_LDS f32x4*)static_cast<uintptr_t>(addr);
   }
+  // after the operand of step `made` has been made: what is fetched into the place its query had
+  static constexpr bool fetches_after(int made) { return kPairFetch ? (made & 1) && made + 3 < 16 : made + 2 < 16; }
   __device__ __forceinline__ void fetch_q(int kk) {
-    qv[kk & 1] = *(const PQ_LDS u32x2*)static_cast<uintptr_t>(q_addr + kk * 128);
-    sz[kk & 1] = *(const PQ_LDS uint32_t*)static_cast<uintptr_t>(par_get + kk * 4);
+    constexpr int kMask = kFetched - 1;
+    if constexpr (kPairFetch) {
+      const u32x2 two = *(const PQ_LDS u32x2*)static_cast<uintptr_t>(par_get + kk * 4);
+      qv[kk & kMask] = *(const PQ_LDS u32x2*)static_cast<uintptr_t>(q_addr + kk * 128);
+      qv[(kk + 1) & kMask] = *(const PQ_LDS u32x2*)static_cast<uintptr_t>(q_addr + (kk + 1) * 128);
+      sz[kk & kMask] = two.x;
+      sz[(kk + 1) & kMask] = two.y;
+    } else {
+      qv[kk & kMask] = *(const PQ_LDS u32x2*)static_cast<uintptr_t>(q_addr + kk * 128);
+      sz[kk & kMask] = *(const PQ_LDS uint32_t*)static_cast<uintptr_t>(par_get + kk * 4);
+    }
   }
+  __device__ __forceinline__ void fetch_after(int made) { fetch_q(kPairFetch ? made + 3 : made + 2); }
   // The step's query operand: q s and q z rounded to fp16 in high-part columns, what the rounding
   // left over -- exact for fp16 queries -- in low-part ones.
   __device__ __forceinline__ void make_query_operand(int kk) {
-    const f16x2 p = u2h(sz[kk & 1]);
+    const f16x2 p = u2h(sz[kk & (kFetched - 1)]);
     const f16x2 s_ = {p.x, p.x}, z_ = {p.y, p.y};
-    const u32x2 v = qv[kk & 1];
+    const u32x2 v = qv[kk & (kFetched - 1)];
     const f16x2 q = u2h(v.x), ql = Q32 ? u2h(v.x & low_mask) : u2h(v.y);
     f16x2 ys = __builtin_elementwise_fma(q, s_, -(ql * s_));
     f16x2 yz = __builtin_elementwise_fma(q, z_, -(ql * z_));
@@ -492,6 +531,7 @@ struct ScoreWalk {
     }
     q_op[kk % kOps][0] = h2u(ys);
     q_op[kk % kOps][1] = h2u(yz);
+    if constexpr (kOps == 1) q_twice = twice(q_op[0][0], q_op[0][1]);
   }
   // Half-step H: batches 4 half ..+3 of pair step kk.
   static constexpr int step_of(int H) { return H / (2 * kOps) * kOps + H % kOps; }
@@ -508,13 +548,23 @@ struct ScoreWalk {
       }
     }
   }
+  // LDS operations issued after the table reads of half-step H when that half-step begins: its matrix instructions wait
+  // once, for their four operands together (a wait each took issue slots: a walk alone on its SIMD 4309 -> 3880 cycles,
+  // two together 6364 -> 6115).
+  static constexpr int younger(int H) {
+    int n = 4 * (kAhead - 1);
+    for (int h = H - kAhead; h < H; ++h)
+      if (makes_operand(h) && fetches_after(step_of(h) + kOps)) n += 2;
+    return n;
+  }
+  static constexpr bool makes_operand(int H) { return half_of(H) == 1 && step_of(H) + kOps < 16; }
   template <int H>
   __device__ __forceinline__ void steps(__amdgpu_buffer_rsrc_t rc_nxt, int rot_nxt) {
     if constexpr (H < 32) {
       constexpr int kk = step_of(H), half = half_of(H);
+      if constexpr (kAhead > 1 && H >= kAhead) __builtin_amdgcn_s_waitcnt(0xc07f | younger(H) << 8);   // lgkmcnt alone
       issue<H + kAhead>(rc_nxt, rot_nxt);
-      const uint32_t b0 = q_op[kk % kOps][0], b1 = q_op[kk % kOps][1];
-      const f16x8 q8 = as_operand(b0, b1, b0, b1);
+      const f16x8 q8 = kOps == 1 ? q_twice : twice(q_op[kk % kOps][0], q_op[kk % kOps][1]);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int t = half * 4 + j;
@@ -537,29 +587,33 @@ struct ScoreWalk {
         for (int j = 0; j < 4; ++j) done[j] = d[j];
       }
       // the step's operand has been used for the last time: make that of the same step of the next chain
-      if constexpr (half == 1 && kk + kOps < 16) {
+      if constexpr (makes_operand(H)) {
         make_query_operand(kk + kOps);
-        if constexpr (kk + kOps + 2 < 16) fetch_q(kk + kOps + 2);
+        if constexpr (fetches_after(kk + kOps)) fetch_after(kk + kOps);
       }
       __builtin_amdgcn_sched_barrier(0);
       steps<H + 1>(rc_nxt, rot_nxt);
     }
   }
-  // Scores of the page in cu / par, summed over the columns of a head and left as fold_columns() says, scaled
-  // by 2^(k + the head's query shift + kTableShift); returns k.  cu and par then hold the next page.
-  __device__ __forceinline__ int run(__amdgpu_buffer_rsrc_t rc_nxt, __amdgpu_buffer_rsrc_t rp_nxt, int rot_nxt, int lane) {
-    issue<0>(rc_nxt, rot_nxt);
+  // Puts the parameters in par, scaled by 2^k, where the walk reads them (and must have ended); returns k.
+  __device__ __forceinline__ int prepare(int lane) {
     int k;
     *(PQ_LDS uint32_t*)static_cast<uintptr_t>(par_put) =
         scale_page_params(par, *(const PQ_LDS float*)static_cast<uintptr_t>(down_addr + lane * 4), k);
+    return k;
+  }
+  // Scores of the page in cu whose parameters have been prepared, summed over the columns of a head and left as
+  // fold_columns() says, scaled by 2^(k + the head's query shift + kTableShift + what is returned).  cu and par then hold the next page.
+  __device__ __forceinline__ int run(__amdgpu_buffer_rsrc_t rc_nxt, __amdgpu_buffer_rsrc_t rp_nxt, int rot_nxt, int lane) {
     load_params(rp_nxt, lane);
     wave_lds_sync();
+    issue<0>(rc_nxt, rot_nxt);
     fetch_q(0);
-    fetch_q(1);
+    fetch_q(kFetched / 2);
 #pragma unroll
     for (int kk = 0; kk < kOps; ++kk) {
       make_query_operand(kk);
-      fetch_q(kk + 2);
+      if (fetches_after(kk)) fetch_after(kk);
     }
     if constexpr (kAhead == 2) issue<1>(rc_nxt, rot_nxt);
     static_assert(kAhead == 1 || kAhead == 2, "reads issued before the first half-step");
@@ -571,7 +625,7 @@ struct ScoreWalk {
     }
     fold_columns<NH>(s, lane & 4);
     wave_lds_sync();
-    return k;
+    return 0;
   }
   // Scaled with k = 0, table shift 0.
   __device__ __forceinline__ void residual(const __half* rows, int nv_res, int rot, int lane) {
@@ -747,7 +801,8 @@ struct GroupedWalk {
       steps<S + 1>(rc_nxt, rot_nxt);
     }
   }
-  // As ScoreWalk::run, the scores scaled by 2^(k + the head's query shift).
+  __device__ __forceinline__ int prepare(int) const { return 0; }     // (run() does it all)
+  // As ScoreWalk::run, the scores scaled by 2^(what is returned + the head's query shift).
   __device__ __forceinline__ int run(__amdgpu_buffer_rsrc_t rc_nxt, __amdgpu_buffer_rsrc_t rp_nxt, int rot_nxt, int lane) {
     const f16x2 p = u2h(par);
     const float pair = *(const PQ_LDS float*)static_cast<uintptr_t>(down_addr + lane * 4);
@@ -977,7 +1032,8 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       int32_t pages[kCut ? kBalancedSeqs : 1];                           // of the sequences, while the chunks are cut
     };
     __attribute__((aligned(16))) std::conditional_t<kGrouped, f32x2, uint32_t> params[kMatWaves][kPairs];
-    __attribute__((aligned(16))) uint32_t vpar[kQuantV ? kMatWaves : 1][kQuantV ? kGroup : 1];
+    // {scale, zero} of the page's values; the same with 1 in the zero's place
+    __attribute__((aligned(16))) uint32_t vpar[kQuantV ? kMatWaves : 1][2][kQuantV ? kGroup : 1];
     float red_ml[kMatWaves][NH][3];                                      // m, l, sum of p * zero-point
     int q_shift[kMaxHeads];
     __attribute__((aligned(16))) float pair_down[kPairs];
@@ -1136,35 +1192,54 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
 
   // per lane: column (head, part), running maximum, sums over the lane's tokens
   // (fp16 values: the sums of p come from the matrix unit like one more dim, l_acc)
-  float m_run = kNegInf, l_run = 0.f, z_run = 0.f;
+  // (quantized values: sums of p in high-part columns, of p * zero-point in low-part ones, lz_run)
+  float m_run = kNegInf, lz_run = 0.f;
   int s_exp = 15;                                                      // (as far as fp16 goes)
   f32x4 l_acc = {0.f, 0.f, 0.f, 0.f};
   f32x4 acc[8];                                                        // dim 8 col + e; columns 4 row .. + 3
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+  const int lane0 = lane;
+  int q_shift = kQuantV ? sh.q_shift[column_head<NH>(lane & 15)] : 0;
+  const uint32_t vpar_put = lds_addr(sh.vpar[kQuantV ? wave : 0]) + lane * 8;
+  const uint32_t vpar_get = lds_addr(sh.vpar[kQuantV ? wave : 0]) +
+                            (row_token<kOrder>(4 * (lane >> 4)) + (NH == 4 && (lane & 4) ? 64 : 0) + (lane & 8 ? 0 : kGroup)) * 4;
+  // A page's parameters brought to their scales and put in LDS: of the first page here, of the others among the values of the
+  // page before, where nobody waits for the reductions one behind the other.
+  int page_shift = 0, s_exp_page = s_exp;
+  auto prepare_page = [&](int lane) {
+    if constexpr (kQuantV) {
+      const int e = static_cast<int>(wave_max_u32(max(vpar.x & 0xffffu, vpar.y & 0xffffu)) >> 10);   // of the page's largest scale
+      s_exp_page = max(-12, min(s_exp, kScaleTop + 15 - e));
+      const f16x2 factor = u2h(static_cast<uint32_t>((s_exp_page + 15) << 10) | 0x3c000000u);         // {2^s_exp, 1}
+      const u32x2 sz = {h2u(u2h(vpar.x) * factor), h2u(u2h(vpar.y) * factor)};
+      *(PQ_LDS u32x2*)static_cast<uintptr_t>(vpar_put) = sz;
+      *(PQ_LDS u32x2*)static_cast<uintptr_t>(vpar_put + kGroup * 4) = u32x2{(sz.x & 0xffffu) | 0x3c000000u, (sz.y & 0xffffu) | 0x3c000000u};
+    }
+    page_shift = w.prepare(lane);
+  };
+  prepare_page(lane);
   const int turn = priority_turn();
   for (int it = 0; it < n_w; ++it) {
     const int pi = page0 + wave + kMatWaves * it;
     if constexpr (kQuantV) alternate_priority(turn + it);             // (costs 1 % where memory is the bound)
     else priority_of_rest(n_w - it, n_w);
     page_setup(it + 1, rc_nxt, rp_nxt, rv_nxt, rvp_nxt, nv_nxt, rot_nxt);
-    // lane constants of the score walk, derived anew for each page: the value phase needs their registers
-    const int lane = lane_id(), col = lane & 15;
-    init_walk(lane);
-    const int q_shift = sh.q_shift[column_head<NH>(col)];
-    const int s_exp_before = s_exp;
-    if constexpr (kQuantV) {
-      const int e = static_cast<int>(wave_max_u32(max(vpar.x & 0xffffu, vpar.y & 0xffffu)) >> 10);   // of the page's largest scale
-      s_exp = max(-12, min(s_exp, kScaleTop + 15 - e));
-      const f16x2 factor = u2h(static_cast<uint32_t>((s_exp + 15) << 10) | 0x3c000000u);              // {2^s_exp, 1}
-      *(PQ_LDS u32x2*)static_cast<uintptr_t>(lds_addr(sh.vpar[wave]) + lane * 8) = u32x2{h2u(u2h(vpar.x) * factor), h2u(u2h(vpar.y) * factor)};
-      vpar = __builtin_amdgcn_raw_buffer_load_b64(rvp_nxt, lane * 8, 0, kAuxCached);
+    // lane constants of the score walk, with fp16 values derived anew for each page: the value phase needs their registers
+    auto lane_now = [&] { return kQuantV ? lane0 : lane_id(); };
+    const int lane = lane_now();
+    if constexpr (!kQuantV) {
+      init_walk(lane);
+      q_shift = sh.q_shift[column_head<NH>(lane & 15)];
     }
-    int down = w.run(rc_nxt, rp_nxt, rot_nxt, lane) + (kGrouped ? 0 : kTableShift) + q_shift;
+    const int s_exp_before = s_exp;
+    s_exp = s_exp_page;
+    if constexpr (kQuantV) vpar = __builtin_amdgcn_raw_buffer_load_b64(rvp_nxt, lane * 8, 0, kAuxCached);
+    int down = w.run(rc_nxt, rp_nxt, rot_nxt, lane) + page_shift + (kGrouped ? 0 : kTableShift) + q_shift;
     if (pi == res_page) {
       w.residual(a.residual + (static_cast<int64_t>(seq) * a.n_kv_heads + kvh) * (kGroup * kHeadDim), L - res_page * kGroup,
-                 rot_cur, lane_id());
+                 rot_cur, lane_now());
       down = q_shift;
     }
     // the groups the score walk had no registers for
@@ -1175,7 +1250,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     // above zero, so that masked scores (-inf) stay masked whatever the scale is
     const float mult = fmaxf(__builtin_ldexpf(scale_abs, -down), 1.17549435e-38f);
     if (nv_cur < kGroup) {
-      const int row = lane_id() >> 4, other = NH == 4 && (lane_id() & 4) ? 64 : 0;   // batch 4 + j: the token's bit 6 the other way
+      const int row = lane_now() >> 4, other = NH == 4 && (lane_now() & 4) ? 64 : 0;   // batch 4 + j: the token's bit 6 the other way
       int nv = uni(nv_cur);
       asm volatile("" : "+s"(nv));                                     // 32 conditions: not worth keeping in registers
 #pragma unroll
@@ -1184,7 +1259,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
         for (int i = 0; i < 4; ++i)
           if (((batch_token<kOrder>(t, rot_cur) + row_token<kOrder>(4 * row + i)) ^ other) >= nv) w.s[t][i] = kNegInf;
     }
-    float pm = fmaxf(w.s[0][0], w.s[0][1]);
+    float pm = max2(w.s[0][0], w.s[0][1]);
     pm = max3(pm, w.s[0][2], w.s[0][3]);
 #pragma unroll
     for (int t = 1; t < kOwn; ++t) {
@@ -1192,23 +1267,20 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       pm = max3(pm, w.s[t][2], w.s[t][3]);
     }
     {
-      if constexpr (NH == 4) pm = fmaxf(pm, dpp_of<0x124>(pm));
+      if constexpr (NH == 4) pm = max2(pm, dpp_of<0x124>(pm));
       auto r = __builtin_amdgcn_permlane16_swap(f2u(pm), f2u(pm), false, false);
-      pm = fmaxf(u2f(r[0]), u2f(r[1]));
+      pm = max2(u2f(r[0]), u2f(r[1]));
       auto q = __builtin_amdgcn_permlane32_swap(f2u(pm), f2u(pm), false, false);
-      pm = fmaxf(u2f(q[0]), u2f(q[1]));
+      pm = max2(u2f(q[0]), u2f(q[1]));
     }
-    const float m_new = fmaxf(m_run, __builtin_ceilf(pm * mult));
+    const float m_new = max2(m_run, __builtin_ceilf(pm * mult));
     const bool dead = !(m_new > kNegInf);                              // nothing valid seen so far
     if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0 || s_exp != s_exp_before) {
       const float alpha = dead ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first page
-      if constexpr (kQuantV) {
-        l_run *= alpha;
-        z_run *= alpha;
-      }
+      if constexpr (kQuantV) lz_run *= alpha;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        float al = __shfl(alpha, (NH == 8 ? 4 * ((lane_id() >> 4) & 1) : 0) + i);   // head of accumulator row i
+        float al = __shfl(alpha, (NH == 8 ? 4 * ((lane_now() >> 4) & 1) : 0) + i);   // head of accumulator row i
         if constexpr (!kQuantV) l_acc[i] *= al;
         else al = __builtin_ldexpf(al, s_exp - s_exp_before);
 #pragma unroll
@@ -1217,7 +1289,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       m_run = m_new;
     }
     const float off = dead ? 0.f : -m_run;
-    const f32x2 part = split_part<kUp>(lane_id() & 8);
+    const f32x2 part = split_part<kUp>(lane_now() & 8);
     uint32_t p_op[8][2];                                               // batch t: fp16 pairs of tokens 4 row + (0, 1), (2, 3)
 #pragma unroll
     for (int t = 0; t < kOwn; ++t) {
@@ -1225,15 +1297,12 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(w.s[t][i], mult, off));
       if constexpr (kQuantV) {
-        l_run += (p[0] + p[1]) + (p[2] + p[3]);
-        // V~ = code * s + z (Section 2): fold s (times 2^s_exp) into the probability, collect p * z
-        const int lane = lane_id();
-        const u32x4 vp = *(const PQ_LDS u32x4*)static_cast<uintptr_t>(
-            lds_addr(sh.vpar[wave]) + (batch_token<kOrder>(t, 0) + row_token<kOrder>(4 * (lane >> 4)) + (NH == 4 && (lane & 4) ? 64 : 0)) * 4);
+        // V~ = code * s + z (Section 2): fold s (times 2^s_exp) into the probability, collect p * z (low-part columns; p in the others)
+        const u32x4 vp = *(const PQ_LDS u32x4*)static_cast<uintptr_t>(vpar_get + batch_token<kOrder>(t, 0) * 4);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const f16x2 sz = u2h(vp[i]);
-          z_run = fmaf(p[i], static_cast<float>(sz.y), z_run);
+          lz_run = fmaf(p[i], static_cast<float>(sz.y), lz_run);
           p[i] = fmaf(p[i], static_cast<float>(sz.x), 0.f);
         }
       }
@@ -1257,6 +1326,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     // ---- values: acc += P^T V, 32 tokens (batches 2g, 2g + 1) per instruction ----
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
+      if (g == 1) prepare_page(lane_now());
       const f16x8 pa = as_operand(p_op[2 * g][0], p_op[2 * g][1], p_op[2 * g + 1][0], p_op[2 * g + 1][1]);
       if constexpr (VB == 16) {
         constexpr uint32_t kOnes = 0x3c003c00u;
@@ -1330,12 +1400,9 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     const int acc_head = NH == 8 ? 4 * (row & 1) : 0;                  // head of accumulator row i: acc_head + i
     const float back = __builtin_ldexpf(1.f, row >= 2 ? -kUp - kLowShift : -kUp);   // rows 2, 3 are low parts
     // columns 0 .. NH - 1 are the heads' high parts; accumulator rows: high part + low part
-    float l_tot = kQuantV ? sum_rows(l_run) : 0.f;
-    float z_tot = kQuantV ? sum_rows(z_run) : 0.f;
-    if constexpr (kQuantV && NH == 4) {
-      l_tot += dpp_of<0x124>(l_tot);                                   // the other half's batches
-      z_tot += dpp_of<0x124>(z_tot);
-    }
+    float l_tot = kQuantV ? sum_rows(lz_run) : 0.f;
+    if constexpr (kQuantV && NH == 4) l_tot += dpp_of<0x12c>(l_tot);   // the other half's batches (row_ror:12, of the same part)
+    const float z_tot = kQuantV ? dpp_of<0x128>(l_tot) : 0.f;          // of the head's low-part column
     if (lane < NH) {
       sh.red_ml[wave][lane][0] = m_run;
       if constexpr (kQuantV) sh.red_ml[wave][lane][1] = l_tot;
