@@ -360,24 +360,36 @@ int launch_scores(const pq_layout* layout, DecodeArgs a, hipStream_t stream) {
   return e == hipSuccess ? PQ_OK : record_hip_error(e);
 }
 
-// Chunks per KV head, beyond one for each sequence, of a launch that is cut on the device by the
-// sequences' real lengths (BalancedPlan); 0: it is cut on the host.  As many as the workspace has
-// partials for, up to three a resident work-group.
-// The cut costs a launch 1 - 3 us (31 x 3000 tokens 45.1 -> 46.1, 8 x 8K with 32 KV heads 110.5 -> 112.6,
-// 32 x 8K with 2-bit values 43.1 -> 44.7), so that only those get it where a resident work-group may
-// have kCutShare pages or more, 90 us with fp16 values; below, a cut by max_seq_len loses as much at
-// most on uneven lengths.  With fewer than 16 units the host's cut has more chunks per unit than
-// are combined in the kernel; above 512 sequences reading all lengths in every work-group costs more
+// How a launch is cut into chunks on the device by the sequences' real lengths (BalancedPlan); spare_chunks 0: it is cut on the
+// host.  The grid has n_seqs + spare_chunks places per KV head.  fit_chunks: how many chunks per KV head are resident at once, if
+// that cut (BalancedPlan::cut_resident) is tried.
+// Three kinds of launches: sequences of at least two chunks that leave places on the compute units (fit_chunks > 0), from four pages a
+// resident work-group on (below, chunks are one round long); launches where a resident work-group may have kCutShare pages or more, up to three
+// work-groups a resident one or as many as the workspace has partials for; and the others, cut as if every sequence had max_seq_len
+// tokens.  With fewer than 16 units the host's cut has more chunks per unit than are combined in the kernel (but for launches
+// of kCutShare pages, whose chunks may be 32 of a unit); above 512 sequences reading all lengths in every work-group costs more
 // than uneven chunks do among so many.
 constexpr int64_t kCutShare = 48;
-int spare_chunks(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len) {
+struct DeviceCut {
+  int32_t spare_chunks, fit_chunks;
+};
+DeviceCut device_cut(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
   const int64_t units = static_cast<int64_t>(n_seqs) * l->n_kv_heads;
   const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
   if (!large_uniform_launch(l, n_seqs, max_seq_len) || units < kResidentGroups / kBalancedFan || n_seqs > kBalancedSeqs ||
-      l->n_kv_heads > kComputeUnits || units * max_pages < kCutShare * kResidentGroups || units * max_pages >= (int64_t{1} << 30))
-    return 0;
+      l->n_kv_heads > kComputeUnits || units * max_pages >= (int64_t{1} << 30))
+    return {0, 0};
+  const bool large = units * max_pages >= kCutShare * kResidentGroups;
+  const int resident = 2 * (kComputeUnits / l->n_kv_heads);
+  const int n_chunks = plan_uniform(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
+  const bool fit = n_seqs <= 64 && n_seqs < resident && n_chunks >= 2 && n_chunks <= (large ? kBalancedFan : kMergeFan) &&
+                   units * max_pages > kWaveRound * kResidentGroups;
+  // (the workspace has room for the host's chunks, and at this size for one partial of each resident work-group; more places than
+  // that cost time: 16 sequences of 2K tokens with a max_seq_len of 32K 21.7 us with three work-groups a resident one)
+  if (fit) return {std::max(n_seqs * n_chunks, resident) - n_seqs, resident};
+  if (!large) return {0, 0};
   const int64_t partials = workspace_slots(l, n_seqs, l->n_kv_heads, max_seq_len) - units;     // (one query head per KV head)
-  return static_cast<int>(std::min<int64_t>(3 * kResidentGroups, partials) / l->n_kv_heads);
+  return {static_cast<int32_t>(std::min<int64_t>(3 * kResidentGroups, partials) / l->n_kv_heads), 0};
 }
 
 // Whether one kernel does all of pq_decode_attention (true), or the merge kernel follows: the
@@ -386,7 +398,7 @@ int spare_chunks(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len) {
 // leaves partials only.)
 bool merges_in_kernel(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
   if (l->angle_quantizer != PQ_ANGLE_UNIFORM && !grouped_on_matrix(l, n_q_heads / l->n_kv_heads)) return false;
-  if (spare_chunks(l, n_seqs, max_seq_len) > 0) return true;
+  if (device_cut(l, v_bits, n_seqs, n_q_heads, max_seq_len).spare_chunks > 0) return true;
   const int n_chunks = plan_attention(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
   return n_chunks == 1 || (n_chunks <= kMergeFan && large_launch(l, n_seqs, max_seq_len));
 }
@@ -470,7 +482,9 @@ int decode_launch(const pq_layout* layout, const void* q, pq_dtype q_dtype, int3
   const bool roles = choose_attention_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len) == AttentionKernel::kRoles;
   const bool merged = out != nullptr && merges_in_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len);
   a.merge_in_kernel = merged ? 1 : 0;
-  a.spare_chunks = out != nullptr ? spare_chunks(layout, n_seqs, max_seq_len) : 0;
+  const DeviceCut cut = out != nullptr ? device_cut(layout, v_bits, n_seqs, n_q_heads, max_seq_len) : DeviceCut{0, 0};
+  a.spare_chunks = cut.spare_chunks;
+  a.fit_chunks = cut.fit_chunks;
   const dim3 grid = a.spare_chunks > 0 ? dim3(layout->n_kv_heads, n_seqs + a.spare_chunks) : dim3(layout->n_kv_heads, n_seqs, plan.n_chunks);
   a.wide_groups = out != nullptr && wide_groups(layout, plan, n_seqs, max_seq_len) ? 1 : 0;
   a.table_index = key_table_index(layout);

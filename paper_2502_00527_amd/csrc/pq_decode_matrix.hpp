@@ -595,19 +595,27 @@ struct ScoreWalk {
       steps<H + 1>(rc_nxt, rot_nxt);
     }
   }
-  // Puts the parameters in par, scaled by 2^k, where the walk reads them (and must have ended); returns k.
+  // Puts the parameters in par, scaled by 2^k, where the walk reads them (and must have ended); returns k.  Without chains that
+  // restart (quantized values) the caller does so before run(), otherwise run() does (fp16 values: one sequence of
+  // 1000 tokens 13.3 us so, 13.45 with it before).
+  static constexpr bool kPrepared = kChain == 16;
   __device__ __forceinline__ int prepare(int lane) {
     int k;
     *(PQ_LDS uint32_t*)static_cast<uintptr_t>(par_put) =
         scale_page_params(par, *(const PQ_LDS float*)static_cast<uintptr_t>(down_addr + lane * 4), k);
     return k;
   }
-  // Scores of the page in cu whose parameters have been prepared, summed over the columns of a head and left as
-  // fold_columns() says, scaled by 2^(k + the head's query shift + kTableShift + what is returned).  cu and par then hold the next page.
+  // Scores of the page in cu, summed over the columns of a head and left as fold_columns() says, scaled by 2^(k of prepare(),
+  // if run() calls it what is returned, + the head's query shift + kTableShift).  cu and par then hold the next page.
   __device__ __forceinline__ int run(__amdgpu_buffer_rsrc_t rc_nxt, __amdgpu_buffer_rsrc_t rp_nxt, int rot_nxt, int lane) {
+    int k = 0;
+    if constexpr (!kPrepared) {
+      issue<0>(rc_nxt, rot_nxt);
+      k = prepare(lane);
+    }
     load_params(rp_nxt, lane);
     wave_lds_sync();
-    issue<0>(rc_nxt, rot_nxt);
+    if constexpr (kPrepared) issue<0>(rc_nxt, rot_nxt);
     fetch_q(0);
     fetch_q(kFetched / 2);
 #pragma unroll
@@ -625,7 +633,7 @@ struct ScoreWalk {
     }
     fold_columns<NH>(s, lane & 4);
     wave_lds_sync();
-    return 0;
+    return k;
   }
   // Scaled with k = 0, table shift 0.
   __device__ __forceinline__ void residual(const __half* rows, int nv_res, int rot, int lane) {
@@ -801,7 +809,7 @@ struct GroupedWalk {
       steps<S + 1>(rc_nxt, rot_nxt);
     }
   }
-  __device__ __forceinline__ int prepare(int) const { return 0; }     // (run() does it all)
+  static constexpr bool kPrepared = false;
   // As ScoreWalk::run, the scores scaled by 2^(what is returned + the head's query shift).
   __device__ __forceinline__ int run(__amdgpu_buffer_rsrc_t rc_nxt, __amdgpu_buffer_rsrc_t rp_nxt, int rot_nxt, int lane) {
     const f16x2 p = u2h(par);
@@ -1057,12 +1065,12 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     plan.store_others(a, sh.pages, tid);
     const int chunks = plan.cut(a, VB == 16);
     if (slot >= chunks) return false;
-    if (slot >= a.n_seqs) plan.locate(slot, seq, chunk);
+    if (slot >= a.n_seqs && !plan.locate(slot, seq, chunk)) return false;
     int before;
     plan.sequence(seq, n_pages, n_chunks, before);
-    const int big = min(chunk, plan.len.n_big);
-    page0 = big * plan.len.big + (chunk - big) * plan.len.small;
-    npg = min(chunk < plan.len.n_big ? plan.len.big : plan.len.small, n_pages - page0);
+    int most;
+    plan.pages_of_chunk(seq, chunk, page0, most);
+    npg = min(most, n_pages - page0);
     row0 = (static_cast<int64_t>(before) * a.n_kv_heads + kvh * n_chunks) * a.group_total + static_cast<int64_t>(a.head0) * n_chunks;
     if (a.n_seqs > 64) __syncthreads();                                // the lengths make room for what shares their memory
     return true;
@@ -1205,8 +1213,9 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   const uint32_t vpar_put = lds_addr(sh.vpar[kQuantV ? wave : 0]) + lane * 8;
   const uint32_t vpar_get = lds_addr(sh.vpar[kQuantV ? wave : 0]) +
                             (row_token<kOrder>(4 * (lane >> 4)) + (NH == 4 && (lane & 4) ? 64 : 0) + (lane & 8 ? 0 : kGroup)) * 4;
-  // A page's parameters brought to their scales and put in LDS: of the first page here, of the others among the values of the
-  // page before, where nobody waits for the reductions one behind the other.
+  // Quantized values: a page's parameters brought to their scales and put in LDS -- of the first page here, of the others among the
+  // values of the page before, where nobody waits for the reductions one behind the other.
+  static_assert(std::remove_reference_t<decltype(w)>::kPrepared == (kQuantV && !kGrouped), "who prepares the parameters");
   int page_shift = 0, s_exp_page = s_exp;
   auto prepare_page = [&](int lane) {
     if constexpr (kQuantV) {
@@ -1217,7 +1226,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       *(PQ_LDS u32x2*)static_cast<uintptr_t>(vpar_put) = sz;
       *(PQ_LDS u32x2*)static_cast<uintptr_t>(vpar_put + kGroup * 4) = u32x2{(sz.x & 0xffffu) | 0x3c000000u, (sz.y & 0xffffu) | 0x3c000000u};
     }
-    page_shift = w.prepare(lane);
+    if constexpr (kQuantV && !kGrouped) page_shift = w.prepare(lane);
   };
   prepare_page(lane);
   const int turn = priority_turn();

@@ -9,13 +9,13 @@
 // units end to end measured 236 against 206 us for 16 x 32K tokens at 4 query heads per KV head: its
 // work-groups stream from 512 places at once.)
 //
-// Lengths are known on the device only.  Large launches cut the chunks there, by the pages that really
-// exist (struct BalancedPlan): the caller's max_seq_len may be far above, and one sequence may be far
-// longer than the others.  The grid has a place for every chunk that the cut can make and each
-// work-group finds its own; what is left over ends at once.  The other launches are cut on the host, as
+// Lengths are known on the device only.  Launches of sequences that leave places on the compute units, and large ones, cut the
+// chunks there, by the pages that really exist (struct BalancedPlan; device_cut() says which launches): the caller's
+// max_seq_len may be far above, and one sequence may be far longer than the others.  The grid has a place for every chunk
+// that the cut can make and each work-group finds its own; what is left over ends at once.  The other launches are cut on the host, as
 // if every sequence had max_seq_len tokens.  8 KV heads, 4 query heads each, microseconds (host cut ->
-// device cut): 1 x 128K + 63 x 1K tokens 168 -> 111, with 4-bit values 132 -> 80; 4 x 32K + 28 x 2K
-// 133 -> 95; 16 x 2K with a max_seq_len of 32K 27.7 -> 23.9; 64 of 1K .. 16K with one of 64K 270 -> 229.
+// device cut): 1 x 128K + 63 x 1K tokens 168 -> 104, with 4-bit values 132 -> 67; 4 x 32K + 28 x 2K
+// 133 -> 78; 8 x 4K with a max_seq_len of 32K 39.8 -> 20.8; 64 of 1K .. 16K with one of 64K 270 -> 229.
 //
 // A unit -- one (sequence, KV head) -- that is one chunk long is finished there.  Otherwise every
 // chunk leaves its softmax partial (running maximum, denominator, un-normalised output) in the
@@ -109,6 +109,17 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
   auto s = __builtin_amdgcn_permlane32_swap(x, x, false, false);
   return static_cast<uint32_t>(uni(static_cast<int>(max(s[0], s[1]))));
 }
+// Sum over the lanes up to and including this one.
+__device__ __forceinline__ int wave_prefix(int v) {
+  // shifts within the rows of 16, then the rows' last lanes to the rows behind them
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);      // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);     // row_bcast:15 to rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);     // row_bcast:31 to rows 2 and 3
+  return v;
+}
 __device__ __forceinline__ int wave_sum(int v) {
   uint32_t x = static_cast<uint32_t>(v);
   x += dpp_of_u32<0xB1>(x);
@@ -130,6 +141,9 @@ struct BalancedPlan {
   int n_seqs, lane;
   ChunkLengths len;
   float per_big, per_small;
+  enum Kind { kGeneral, kAlike, kFitted } kind;   // which cut it is (cut_resident)
+  int others0, size0;                          // kFitted: chunks behind the first ones, of the sequences up to this lane's; pages a chunk
+  int units;                                   // kFitted: compute units for each KV head
 
   __device__ __forceinline__ void load(const DecodeArgs& a, int lane_) {
     lane = lane_;
@@ -167,10 +181,13 @@ struct BalancedPlan {
     const int n = min(div_up(p, len.big, per_big), len.n_big) + div_up(rest, len.small, per_small);
     return seq < n_seqs ? max(1, n) : 0;
   }
-  __device__ __forceinline__ int count() {
+  __device__ __forceinline__ void find_chunks() {
     per_big = __builtin_amdgcn_rcpf(static_cast<float>(len.big));
     per_small = __builtin_amdgcn_rcpf(static_cast<float>(len.small));
     n0 = chunks_of(lane, pages0);
+  }
+  __device__ __forceinline__ int count() {
+    find_chunks();
     int sum = 0;
     for_blocks([&](int, int, int n) { sum += n; });
     return wave_sum(sum);
@@ -178,6 +195,11 @@ struct BalancedPlan {
   // after load() and store_others(); returns the chunks per KV head
   __device__ __forceinline__ int cut(const DecodeArgs& a, bool fp16_values) {
     pages0 = lane < n_seqs ? pages_of_len(min(pages0, a.max_seq_len)) : 0;
+    kind = kGeneral;
+    if (a.fit_chunks > 0) {
+      const int slots = cut_resident(a);
+      if (slots > 0) return slots;
+    }
     int sum = pages0, most = pages0;
 #pragma unroll 1
     for (int s = 64 + lane; s < n_seqs; s += 64) {
@@ -199,8 +221,94 @@ struct BalancedPlan {
     }
     return chunks;
   }
-  // sequence and chunk of slot u >= n_seqs, u < chunks
-  __device__ __forceinline__ void locate(int u, int& seq, int& chunk) const {
+  // The cut of a launch of at most 64 sequences that leaves places on the compute units when every sequence has one work-group.
+  // If all sequences are equally long nothing has to be counted (kAlike), and if they are as long as the host was told its chunk
+  // lengths are the measured ones.  If they are not, what matters is that all chunks start at once and that the two work-groups of a compute unit
+  // are not both long ones (kFitted): the shortest whole rounds with no more chunks than are resident together, a sequence's
+  // chunks alike, and locate_fitted() says who takes which.  Returns the slots that may have a chunk, 0 if neither will do.
+  // Measured (8 KV heads, 4 query heads each, microseconds: chunks cut on the host, or here by chunk_lengths() from 48 pages a
+  // share on, and dealt out chunk by chunk -> this):
+  //   32 x 512 .. 8K tokens 70.9 -> 61.4, 3+3-bit keys and 2-bit values 42.4 -> 38.7;  8 x 2K .. 30K, 4-bit values 54.1 -> 41.8
+  //   6 x 500 .. 12K 36.4 -> 27.1;  30 x 300 .. 2500 29.3 -> 25.2;  16 x 4K .. 32K 142.8 -> 114.3;  8 x 4K .. 8K, 32 KV heads 82.1 -> 77.0
+  //   alike: 16 x 2K with a max_seq_len of 32K 20.7 -> 20.8, 16 x 8K 60.0 -> 59.4, 31 x 3000 43.5 -> 43.5;  8 x 8K, 32 KV heads 109.4 -> 109.0
+  __device__ __forceinline__ int cut_resident(const DecodeArgs& a) {
+    const int max_pages = pages_of_len(a.max_seq_len);
+    const int first_pages = uni(pages0);
+    if (__builtin_amdgcn_ballot_w64(lane < n_seqs && pages0 != first_pages) == 0) {
+      kind = kAlike;
+      len.big = a.pages_per_chunk;
+      len.small = a.pages_small;
+      len.n_big = a.n_big;
+      if (first_pages != max_pages) {                                  // shorter ones: as many chunks as there are places
+        const int n = a.fit_chunks / n_seqs;
+        len.big = len.small = max(kWaveRound, whole_rounds((first_pages + n - 1) / n));
+        len.n_big = max_pages;
+      }
+      find_chunks();
+      return n_seqs * uni(n0);
+    }
+    const int total = wave_sum(pages0);
+#pragma unroll 1
+    for (int c = whole_rounds(max((total + a.fit_chunks - 1) / a.fit_chunks, (max_pages + kBalancedFan - 1) / kBalancedFan)); c <= a.pages_per_chunk; c += 2 * kWaveRound) {
+      // two lengths at a time, their counts in the halves of a word
+      const int n = lane < n_seqs ? max(1, div_up(pages0, c, __builtin_amdgcn_rcpf(static_cast<float>(c)))) : 0;
+      const int m = lane < n_seqs ? max(1, div_up(pages0, c + kWaveRound, __builtin_amdgcn_rcpf(static_cast<float>(c + kWaveRound)))) : 0;
+      const int both = wave_sum(n | (m << 16));
+      const bool first = (both & 0xffff) <= a.fit_chunks;
+      if (first || (both >> 16) <= a.fit_chunks) {
+        kind = kFitted;
+        n0 = first ? n : m;
+        size0 = div_up(pages0, n0, __builtin_amdgcn_rcpf(static_cast<float>(n0)));
+        units = kComputeUnits / a.n_kv_heads;
+        others0 = wave_prefix(max(n0 - 1, 0));
+        return 2 * units;
+      }
+    }
+    return 0;
+  }
+  // Slot u takes its place on compute unit u % units of its KV head, if work-groups are handed out in order (which they are:
+  // of 512 work-groups i and i + 256 shared a unit, 256 times of 256; nothing but time hangs on it).  The first slots have the sequences' first chunks; of the others, the longest chunk goes to the unit
+  // with the least to do, the next one to the next.  False: there are no more.
+  __device__ __forceinline__ bool locate_fitted(int u, int& seq, int& chunk) const {
+    const int alone = max(0, units - n_seqs);                          // units without a first chunk
+    int rank = u - n_seqs;
+    if (u >= units) {
+      const int partner = u - units;
+      const bool open = lane < min(n_seqs, units) && lane >= n_seqs - units;           // the units of these sequences' first chunks have a place left
+      rank = alone + __builtin_popcountll(__builtin_amdgcn_ballot_w64(open)) + partner - n_seqs;
+      if (partner < n_seqs) {
+        const int mine = __builtin_amdgcn_readlane(size0, partner);
+        rank = alone + __builtin_popcountll(__builtin_amdgcn_ballot_w64(open && (size0 < mine || (size0 == mine && lane < partner))));
+      }
+    }
+    if (rank >= __builtin_amdgcn_readlane(others0, 63)) return false;
+    // by the rounds a chunk takes, then second chunks, third ones ...
+    const int rounds = (size0 + kWaveRound - 1) / kWaveRound;
+    uint64_t have = 0;
+    for (int r = uni(static_cast<int>(wave_max_u32(static_cast<uint32_t>(n0 > 1 ? rounds : 0))));; --r) {
+      for (chunk = 1;; ++chunk) {
+        have = __builtin_amdgcn_ballot_w64(rounds == r && n0 > chunk);
+        const int n = __builtin_popcountll(have);
+        if (n == 0) break;
+        if (rank < n) {
+          const int below = static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(have >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(have), 0)));
+          seq = __builtin_ctzll(__builtin_amdgcn_ballot_w64(rounds == r && n0 > chunk && below == rank));
+          return true;
+        }
+        rank -= n;
+      }
+      if (r <= 0) return false;                                        // (not reached: rank is below the number of chunks)
+    }
+  }
+  // sequence and chunk of slot u >= n_seqs, u < what the cut returned; false: it has none
+  __device__ __forceinline__ bool locate(int u, int& seq, int& chunk) const {
+    if (kind == kFitted) return locate_fitted(u, seq, chunk);
+    if (kind == kAlike) {
+      chunk = uni(static_cast<int>(static_cast<float>(u) * __builtin_amdgcn_rcpf(static_cast<float>(n_seqs))));   // off by one at most
+      chunk += u - chunk * n_seqs >= n_seqs ? 1 : (u - chunk * n_seqs < 0 ? -1 : 0);
+      seq = u - chunk * n_seqs;
+      return true;
+    }
     // most chunk numbers c below which at most u slots lie: sum of min(n, c) over the sequences
     int lo = 1, before = n_seqs, hi = kBalancedFan;
 #pragma unroll 1
@@ -229,9 +337,27 @@ struct BalancedPlan {
       }
       rank -= of_block;
     });
+    return true;
+  }
+  // first page and most pages of a chunk
+  __device__ __forceinline__ void pages_of_chunk(int seq, int chunk, int& first, int& most) const {
+    if (kind == kFitted) {
+      most = __builtin_amdgcn_readlane(size0, seq);
+      first = chunk * most;
+      return;
+    }
+    const int big = min(chunk, len.n_big);
+    first = big * len.big + (chunk - big) * len.small;
+    most = chunk < len.n_big ? len.big : len.small;
   }
   // pages and chunks of a sequence, and the chunks of those before it
   __device__ __forceinline__ void sequence(int seq, int& n_pages, int& n_chunks, int& chunks_before) const {
+    if (kind != kGeneral) {
+      n_pages = __builtin_amdgcn_readlane(pages0, seq);
+      n_chunks = __builtin_amdgcn_readlane(n0, seq);
+      chunks_before = kind == kAlike ? seq * n_chunks : seq + __builtin_amdgcn_readlane(others0, seq) - (n_chunks - 1);
+      return;
+    }
     int sum = 0;
     for_blocks([&](int s0, int p, int n) {
       sum += s0 + lane < seq ? n : 0;
