@@ -368,7 +368,7 @@ int launch_scores(const pq_layout* layout, DecodeArgs a, hipStream_t stream) {
 // work-groups a resident one or as many as the workspace has partials for; and the others, cut as if every sequence had max_seq_len
 // tokens.  With fewer than 16 units the host's cut has more chunks per unit than are combined in the kernel (but for launches
 // of kCutShare pages, whose chunks may be 32 of a unit); above 512 sequences reading all lengths in every work-group costs more
-// than uneven chunks do among so many.
+// than uneven chunks do among so many.  The grouped quantizer's matrix kernels have the first kind and the last one.
 constexpr int64_t kCutShare = 48;
 struct DeviceCut {
   int32_t spare_chunks, fit_chunks;
@@ -376,18 +376,19 @@ struct DeviceCut {
 DeviceCut device_cut(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
   const int64_t units = static_cast<int64_t>(n_seqs) * l->n_kv_heads;
   const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
-  if (!large_uniform_launch(l, n_seqs, max_seq_len) || units < kResidentGroups / kBalancedFan || n_seqs > kBalancedSeqs ||
+  const bool uniform = l->angle_quantizer == PQ_ANGLE_UNIFORM;
+  if (!(uniform || grouped_on_matrix(l, n_q_heads / l->n_kv_heads)) || !large_launch(l, n_seqs, max_seq_len) || units < kResidentGroups / kBalancedFan || n_seqs > kBalancedSeqs ||
       l->n_kv_heads > kComputeUnits || units * max_pages >= (int64_t{1} << 30))
     return {0, 0};
   const bool large = units * max_pages >= kCutShare * kResidentGroups;
   const int resident = 2 * (kComputeUnits / l->n_kv_heads);
-  const int n_chunks = plan_uniform(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
-  const bool fit = n_seqs <= 64 && n_seqs < resident && n_chunks >= 2 && n_chunks <= (large ? kBalancedFan : kMergeFan) &&
+  const int n_chunks = plan_attention(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
+  const bool fit = n_seqs <= 64 && n_seqs < resident && n_chunks >= 2 && n_chunks <= (large && uniform ? kBalancedFan : kMergeFan) &&
                    units * max_pages > kWaveRound * kResidentGroups;
   // (the workspace has room for the host's chunks, and at this size for one partial of each resident work-group; more places than
   // that cost time: 16 sequences of 2K tokens with a max_seq_len of 32K 21.7 us with three work-groups a resident one)
   if (fit) return {std::max(n_seqs * n_chunks, resident) - n_seqs, resident};
-  if (!large) return {0, 0};
+  if (!large || !uniform) return {0, 0};
   const int64_t partials = workspace_slots(l, n_seqs, l->n_kv_heads, max_seq_len) - units;     // (one query head per KV head)
   return {static_cast<int32_t>(std::min<int64_t>(3 * kResidentGroups, partials) / l->n_kv_heads), 0};
 }

@@ -15,15 +15,20 @@ namespace grouped {
 
 #define PQ_GROUPED_ATTR __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
-template <int RB, int TB, int VB, int NH>
-__global__ PQ_GROUPED_ATTR void pq_decode_partials_kernel(const DecodeArgs a) { attention_body<RB + TB, VB, NH, true, false, 4, RB>(a); }
+template <int RB, int TB, int VB, int NH, bool kCut>
+__global__ PQ_GROUPED_ATTR void pq_decode_partials_kernel(const DecodeArgs a) { attention_body<RB + TB, VB, NH, true, kCut, 4, RB>(a); }
 template <int RB, int TB, int NH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TB == 5 ? 2 : 3, TB == 5 ? 2 : 3))) void pq_score_grouped_kernel(const DecodeArgs a) { grouped_scores_body<RB, TB, NH>(a); }
 
+template <int RB, int TB, int NH>
+void launch_heads(const DecodeArgs& a, dim3 grid, hipStream_t st) {
+  if (a.spare_chunks > 0) hipLaunchKernelGGL((pq_decode_partials_kernel<RB, TB, PQ_GROUPED_VB, NH, true>), grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((pq_decode_partials_kernel<RB, TB, PQ_GROUPED_VB, NH, false>), grid, dim3(256), 0, st, a);
+}
 template <int RB, int TB>
 bool launch(const DecodeArgs& a, dim3 grid, hipStream_t st) {
-  if (a.n_heads <= 4) hipLaunchKernelGGL((pq_decode_partials_kernel<RB, TB, PQ_GROUPED_VB, 4>), grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((pq_decode_partials_kernel<RB, TB, PQ_GROUPED_VB, 8>), grid, dim3(256), 0, st, a);
+  if (a.n_heads <= 4) launch_heads<RB, TB, 4>(a, grid, st);
+  else launch_heads<RB, TB, 8>(a, grid, st);
   return true;
 }
 template <int RB, int TB>

@@ -1013,7 +1013,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   constexpr int kMatThreads = kMatWaves * 64;
   constexpr bool kQuantV = VB != 16;
   constexpr bool kGrouped = kGroupedRadius != 0;
-  static_assert(!kGrouped || (Q32 && !kCut && kMatWaves == 4), "what the grouped quantizer's kernels are");
+  static_assert(!kGrouped || (Q32 && kMatWaves == 4), "what the grouped quantizer's kernels are");
   constexpr TokenOrder kOrder = token_order(VB);
   constexpr int kChain = kQuantV ? 16 : 4;
   constexpr uint32_t kCodesBytes = kBlocks * kGroup * UB;

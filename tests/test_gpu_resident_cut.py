@@ -72,3 +72,30 @@ def test_every_chunk_is_taken(kind, group, v_bits, rt):
     print(f"[resident cut] {kind} group {group} v{v_bits}: {err:.2e}", flush=True)
     assert err <= (2e-6 if v_bits == 16 else 2.4e-5)
     assert torch.equal(out, cache.attention())
+
+
+# sequences, KV heads, longest and shortest context
+GROUPED = [(20, 8, 2000, 1), (9, 16, 2050, 300), (40, 4, 1800, 1), (17, 8, 2048, 2048)]
+
+
+@pytest.mark.parametrize("bits", [(4, 4), (3, 3), (5, 3), (3, 5), (4, 2), (2, 4)])
+@pytest.mark.parametrize("v_bits,group,dtype", [(16, 3, "f16"), (16, 7, "f32"), (4, 4, "f32"), (4, 12, "f16"), (2, 4, "f16"), (2, 8, "f16")])
+def test_grouped_quantizer(bits, v_bits, group, dtype):
+    """The same cut with the grouped angle quantizer (three query heads per KV head and more); bounds as in test_gpu_grouped_matrix.py."""
+    from perf import cases
+
+    import paper_2502_00527_amd as pq
+
+    seqs, heads, longest, shortest = GROUPED[(sum(bits) + bits[0] + v_bits + group) % len(GROUPED)]
+    case = cases._case("cut", "decode", seqs, heads * group, heads, longest, min_context=shortest, r_bits=bits[0], t_bits=bits[1], v_bits=v_bits,
+                       dtype=dtype, shuffled_pages=True, grouped_angles=True)
+    print("[resident cut]", case, flush=True)
+    state = cases.prepare(case, 3)
+    assert pq.pq_decode_merges_in_kernel(state["layout"], seqs, heads * group, state["max_seq_len"], v_bits)
+    got, want = cases.run(state).clone(), cases.exact(case, 3)
+    for s in range(seqs):
+        err = float((got[s].double() - want[s]).norm() / want[s].norm())
+        assert err <= (1.2e-5 if v_bits == 16 else 1e-4), (s, err)
+    err = float((got.double() - want).norm() / want.norm())
+    assert err <= (6e-6 if v_bits == 16 else 4e-5), err
+    assert torch.equal(got, cases.run(state))
