@@ -304,11 +304,11 @@ __device__ __forceinline__ uint32_t split_pair(float x0, float x1, f32x2 part) {
                    static_cast<_Float16>(fmaf(fmaf(static_cast<float>(h.y), part.x, x1), part.y, 0.f))};
   return h2u(r);
 }
-// Sum of an accumulator's two parts, one in lanes 0 - 31, the other (already scaled back) in lanes
-// 32 - 63.  Where a value is infinite the high part is what the product is; a low part may be zero or
-// negative there.
-__device__ __forceinline__ float sum_parts(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(f2u(x), f2u(x), false, false);
+// Sums of two accumulators' parts, the high ones in lanes 0 - 31, the low ones (already scaled back) in lanes
+// 32 - 63: of x in lanes 0 - 31, of y in the others.  Where a value is infinite the high part is what the product is; a low
+// part may be zero or negative there.
+__device__ __forceinline__ float sum_parts(float x, float y) {
+  auto r = __builtin_amdgcn_permlane32_swap(f2u(x), f2u(y), false, false);
   const float high = u2f(r[0]), low = u2f(r[1]);
   return __builtin_isinf(high) ? high : high + low;
 }
@@ -1042,7 +1042,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     __attribute__((aligned(16))) std::conditional_t<kGrouped, f32x2, uint32_t> params[kMatWaves][kPairs];
     // {scale, zero} of the page's values; the same with 1 in the zero's place
     __attribute__((aligned(16))) uint32_t vpar[kQuantV ? kMatWaves : 1][2][kQuantV ? kGroup : 1];
-    float red_ml[kMatWaves][NH][3];                                      // m, l, sum of p * zero-point
+    __attribute__((aligned(16))) float red_ml[3][NH][kMatWaves];          // m, l, sum of p * zero-point; a head's read together
     int q_shift[kMaxHeads];
     __attribute__((aligned(16))) float pair_down[kPairs];
     __attribute__((aligned(16))) uint16_t exponents[kPairs][NH];
@@ -1400,10 +1400,12 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   auto top_of = [&](int h) {                                           // the wavefronts' largest maximum
     float m = sh.red_ml[0][h][0];
 #pragma unroll
-    for (int v = 1; v < kMatWaves; ++v) m = fmaxf(m, sh.red_ml[v][h][0]);
+    for (int v = 1; v < kMatWaves; ++v) m = fmaxf(m, sh.red_ml[0][h][v]);
     return m;
   };
   // ---- fold the wavefronts: maxima and sums through LDS, then the accumulators, where the key table was ----
+  // (Two accumulators' parts at a time, each in half of the lanes: with a value a time, in lanes that half of the time held
+  // nothing, the fold was 224 instructions instead of 112 and one sequence of 777 tokens 12.3 us instead of 11.6.)
   {
     const int lane = lane_id(), row = lane >> 4, col = lane & 15;
     const int acc_head = NH == 8 ? 4 * (row & 1) : 0;                  // head of accumulator row i: acc_head + i
@@ -1413,15 +1415,15 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     if constexpr (kQuantV && NH == 4) l_tot += dpp_of<0x12c>(l_tot);   // the other half's batches (row_ror:12, of the same part)
     const float z_tot = kQuantV ? dpp_of<0x128>(l_tot) : 0.f;          // of the head's low-part column
     if (lane < NH) {
-      sh.red_ml[wave][lane][0] = m_run;
-      if constexpr (kQuantV) sh.red_ml[wave][lane][1] = l_tot;
-      sh.red_ml[wave][lane][2] = z_tot;
+      sh.red_ml[0][lane][wave] = m_run;
+      if constexpr (kQuantV) sh.red_ml[1][lane][wave] = l_tot;
+      sh.red_ml[2][lane][wave] = z_tot;
     }
     if constexpr (!kQuantV) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float l = tsum32(l_acc[i] * back, l_acc[i] * back);
-        if (col == 0 && row < NH / 4) sh.red_ml[wave][4 * row + i][1] = l;
+        if (col == 0 && row < NH / 4) sh.red_ml[1][4 * row + i][wave] = l;
       }
     }
     __syncthreads();
@@ -1430,23 +1432,21 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
     for (int i = 0; i < 4; ++i) {
       const int h = acc_head + i;
       const float M = top_of(h);
-      wgt[i] = M > kNegInf ? __builtin_amdgcn_exp2f(sh.red_ml[wave][h][0] - M) : 0.f;
+      wgt[i] = M > kNegInf ? __builtin_amdgcn_exp2f(sh.red_ml[0][h][wave] - M) : 0.f;
       if constexpr (kQuantV) wgt[i] = __builtin_ldexpf(wgt[i], -s_exp);
     }
+    // dims 8 col .. + 3 in lanes 0 - 31, 8 col + 4 .. + 7 in lanes 32 - 63
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        acc[e][i] = sum_parts(acc[e][i] * back) * wgt[i];
-        if constexpr (kQuantV) acc[e][i] *= code_unscale<VB>(e);
-      }
-    if (row < NH / 4) {
+    for (int e = 0; e < 4; ++e)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        f32x4* const dst = reinterpret_cast<f32x4*>(&sh.red[wave][4 * row + i][col * 8]);
-        dst[0] = f32x4{acc[0][i], acc[1][i], acc[2][i], acc[3][i]};
-        dst[1] = f32x4{acc[4][i], acc[5][i], acc[6][i], acc[7][i]};
+        acc[e][i] = sum_parts(acc[e][i] * back, acc[4 + e][i] * back) * wgt[i];
+        if constexpr (kQuantV) acc[e][i] *= row < 2 ? code_unscale<VB>(e) : code_unscale<VB>(4 + e);
       }
+    if ((row & 1) < NH / 4) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<f32x4*>(&sh.red[wave][4 * (row & 1) + i][col * 8 + 4 * (row >> 1)]) = f32x4{acc[0][i], acc[1][i], acc[2][i], acc[3][i]};
     }
     __syncthreads();
   }
@@ -1461,9 +1461,9 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
       float zp = 0.f;                                                  // zero-point term: the same for every dim
 #pragma unroll
       for (int v = 0; v < kMatWaves; ++v) {
-        const float wg = __builtin_amdgcn_exp2f(sh.red_ml[v][h][0] - M);
-        l = fmaf(wg, sh.red_ml[v][h][1], l);
-        zp = fmaf(wg, sh.red_ml[v][h][2], zp);
+        const float wg = __builtin_amdgcn_exp2f(sh.red_ml[0][h][v] - M);
+        l = fmaf(wg, sh.red_ml[1][h][v], l);
+        zp = fmaf(wg, sh.red_ml[2][h][v], zp);
       }
       if constexpr (kQuantV) o += zp;
     }
