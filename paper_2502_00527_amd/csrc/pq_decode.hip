@@ -405,8 +405,8 @@ bool merges_in_kernel(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_
 }
 
 // Work-groups of 8 wavefronts: sequences of one chunk with more pages than 4 wavefronts take at once, and no more
-// units than compute units (two work-groups of 4 share one otherwise).  One sequence of 777 tokens 13.3 -> 12.2 us,
-// 16 of them 15.0 -> 14.7; up to 4 pages the wider work-group costs 1 us (300 tokens: 9.7 -> 10.7).  From 8 pages on
+// units than compute units (two work-groups of 4 share one otherwise).  One sequence of 777 tokens 13.3 -> 12.2 us
+// (11.5 now, with a shorter end of the chunk), 16 of them 15.0 -> 14.7; up to 4 pages the wider work-group costs 1 us (300 tokens: 9.7 -> 10.7).  From 8 pages on
 // chunk_lengths() makes two chunks: 8 units 13.0, 64 units 13.8 us; one chunk of 8 wavefronts 13.1 and 14.8 (4-bit values 12.7 and 12.7;
 // 13.0 and 13.1), but with 256 units, a work-group on every compute unit, 20.0 and 18.5 (4-bit values 15.9, 14.7).
 bool wide_groups(const pq_layout* l, const ChunkPlan& plan, int32_t n_seqs, int32_t max_seq_len) {
