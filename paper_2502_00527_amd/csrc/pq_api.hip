@@ -24,27 +24,6 @@ bool layout_supported(const pq_layout* l) {
   return w == 6 || w == 8;
 }
 
-// Chunks of the grouped quantizer's attention kernel, and the size of the workspace for all: one
-// work-group per (sequence, KV head, chunk).  Chunks are whole pages, a
-// multiple of the 4 wavefronts of a work-group; they shrink from 32 pages
-// until the launch has at least the 512 work-groups that are resident at
-// once (2 per compute unit).  Long chunks amortise the table build and keep
-// each wavefront's page pipeline running; measured on MI355X, a target of 512
-// beat 2048 by 4 % at 16 x 32K and by 16 % for one 128K sequence.
-ChunkPlan plan_chunks(int32_t n_seqs, int32_t n_kv_heads, int32_t max_seq_len) {
-  const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
-  const int64_t units = static_cast<int64_t>(n_seqs) * n_kv_heads;
-  constexpr int64_t kWantGroups = 512;
-  int32_t ppc = 32;
-  while (ppc > 4 && units * ((max_pages + ppc - 1) / ppc) < kWantGroups) ppc >>= 1;
-  ChunkPlan p;
-  p.pages_per_chunk = ppc;
-  p.n_chunks = static_cast<int32_t>((max_pages + ppc - 1) / ppc);
-  p.n_big = p.n_chunks;
-  p.pages_small = ppc;
-  return p;
-}
-
 namespace {
 
 // What the device streams when nothing else is done: each wavefront reads 40 KB blocks (the size

@@ -117,23 +117,6 @@ bool launch_scores_rt(int rt, int G, const DecodeArgs& a, dim3 grid, hipStream_t
 // uniform grid both are the same kernel; pq_decode_kernel_name() has always told them apart.
 enum class AttentionKernel { kPartials, kRoles };
 
-// Work-groups of four pages each that the shape could have, as far as 768 (the workspace's size is
-// stated in them).
-constexpr int64_t kCountedGroups = 768;
-int64_t four_page_groups(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len) {
-  const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
-  const int64_t bound = static_cast<int64_t>(n_seqs) * l->n_kv_heads * max_pages;   // pages x KV heads, at most
-  return std::min<int64_t>(kCountedGroups, (bound + 3) / 4);
-}
-
-// Pages enough for at least 256 work-groups; the second: and on the uniform angle grid.
-bool large_launch(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len) {
-  return n_seqs <= 4096 && four_page_groups(l, n_seqs, max_seq_len) >= kComputeUnits;
-}
-bool large_uniform_launch(const pq_layout* l, int32_t n_seqs, int32_t max_seq_len) {
-  return l->angle_quantizer == PQ_ANGLE_UNIFORM && large_launch(l, n_seqs, max_seq_len);
-}
-
 AttentionKernel choose_attention_kernel(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads,
                                         int32_t max_seq_len) {
   const bool name_fits = v_bits == 16 || n_q_heads / l->n_kv_heads <= 2;
@@ -149,13 +132,6 @@ bool launch_attention(int w, int v_bits, bool roles, const DecodeArgs& a, dim3 g
   }
 }
 
-// Grouped angle quantizer: query heads per KV head from which on the kernels of pq_decode_matrix.hpp take over.  They make
-// the keys' coordinates, whatever the number of heads (about 11 instructions a symbol); the vector unit's take 3 + heads, and
-// heads times as many for the values.  Vector unit against matrix cores, microseconds: 3 heads, which are two passes of the
-// former, 16 x 16K tokens 231 / 116.  2 heads 16 x 16K 117 / 114, with 4-bit values 78.5 / 82, one sequence of 1000 14.7 / 14.5; 1 head 114 /
-// 114, 76 / 81, 13.5 / 14.2.
-constexpr int kGroupedMatrixHeads = 3;
-bool grouped_on_matrix(const pq_layout* l, int group_total) { return l->angle_quantizer == PQ_ANGLE_GROUPED && group_total >= kGroupedMatrixHeads; }
 bool launch_grouped(int rt, int v_bits, const DecodeArgs& a, dim3 grid, hipStream_t st) {
   switch (v_bits) {
     case 16: return launch_attention_grouped_v16(rt, a, grid, st);
@@ -186,13 +162,6 @@ struct Workspace {
 
 size_t round256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
 
-size_t workspace_slots(const pq_layout* l, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
-  const ChunkPlan plan = plan_chunks(n_seqs, l->n_kv_heads, max_seq_len);
-  const size_t units = static_cast<size_t>(n_seqs) * l->n_kv_heads;
-  const size_t chunk_slots = static_cast<size_t>(n_seqs) * n_q_heads * plan.n_chunks;
-  return std::max(chunk_slots, (static_cast<size_t>(four_page_groups(l, n_seqs, max_seq_len)) + units) * (n_q_heads / l->n_kv_heads));
-}
-
 Workspace carve_workspace(void* base, const pq_layout* l, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
   const size_t slots = workspace_slots(l, n_seqs, n_q_heads, max_seq_len);
   const size_t acc_bytes = round256(slots * kHeadDim * sizeof(float));
@@ -205,40 +174,6 @@ Workspace carve_workspace(void* base, const pq_layout* l, int32_t n_seqs, int32_
   const size_t words = units + static_cast<size_t>(four_page_groups(l, n_seqs, max_seq_len)) + units;
   w.bytes = acc_bytes + ml_bytes + round256(words * sizeof(uint64_t));
   return w;
-}
-
-// Chunk plan of the uniform angle grid's attention kernel for launches that are cut on the host, as if
-// every sequence had max_seq_len tokens (chunk_lengths() says why chunks are as long as they are).
-// The two-stage entry points, whose second one does not know the values' width, use the fp16 plan.
-ChunkPlan plan_uniform(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
-  const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
-  const int64_t units = static_cast<int64_t>(n_seqs) * l->n_kv_heads;
-  const int64_t share = std::min<int64_t>(1 << 20, (units * max_pages + kResidentGroups - 1) / kResidentGroups);
-  const ChunkLengths len = chunk_lengths(static_cast<int>(share), static_cast<int>(max_pages), v_bits == 16);
-  int64_t big = len.big, small = len.small, n_big = big == small ? 0 : len.n_big;
-  // as many partials as the workspace holds (its own plan has max_pages / 32 chunks or more)
-  const int64_t most = static_cast<int64_t>(workspace_slots(l, n_seqs, n_q_heads, max_seq_len)) / (static_cast<int64_t>(n_seqs) * n_q_heads);
-  auto chunks = [&] {
-    const int64_t first = std::min(n_big, (max_pages + big - 1) / big), rest = max_pages - n_big * big;
-    return first + (rest > 0 ? (rest + small - 1) / small : 0);
-  };
-  while (chunks() > most && small < max_pages) {
-    small += 4;
-    if (small > big) {
-      big = small;
-      n_big = 0;
-    }
-  }
-  ChunkPlan p;
-  p.pages_per_chunk = static_cast<int32_t>(big);
-  p.pages_small = static_cast<int32_t>(small);
-  p.n_chunks = static_cast<int32_t>(chunks());
-  p.n_big = static_cast<int32_t>(n_big == 0 && big == small ? p.n_chunks : n_big);
-  return p;
-}
-ChunkPlan plan_attention(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
-  return l->angle_quantizer == PQ_ANGLE_UNIFORM ? plan_uniform(l, v_bits, n_seqs, n_q_heads, max_seq_len)
-                                                : plan_chunks(n_seqs, l->n_kv_heads, max_seq_len);
 }
 
 // cos / sin of the centre of every angle bin of the uniform grid over [-pi, pi) (Section 3.2
@@ -358,60 +293,6 @@ int launch_scores(const pq_layout* layout, DecodeArgs a, hipStream_t stream) {
     head0 += G;
   }
   return e == hipSuccess ? PQ_OK : record_hip_error(e);
-}
-
-// How a launch is cut into chunks on the device by the sequences' real lengths (BalancedPlan); spare_chunks 0: it is cut on the
-// host.  The grid has n_seqs + spare_chunks places per KV head.  fit_chunks: how many chunks per KV head are resident at once, if
-// that cut (BalancedPlan::cut_resident) is tried.
-// Three kinds of launches: sequences of at least two chunks that leave places on the compute units (fit_chunks > 0), from four pages a
-// resident work-group on (below, chunks are one round long); launches where a resident work-group may have kCutShare pages or more, up to three
-// work-groups a resident one or as many as the workspace has partials for; and the others, cut as if every sequence had max_seq_len
-// tokens.  With fewer than 16 units the host's cut has more chunks per unit than are combined in the kernel (but for launches
-// of kCutShare pages, whose chunks may be 32 of a unit); above 512 sequences reading all lengths in every work-group costs more
-// than uneven chunks do among so many.  The grouped quantizer's matrix kernels have the first kind and the last one.
-constexpr int64_t kCutShare = 48;
-struct DeviceCut {
-  int32_t spare_chunks, fit_chunks;
-};
-DeviceCut device_cut(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
-  const int64_t units = static_cast<int64_t>(n_seqs) * l->n_kv_heads;
-  const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
-  const bool uniform = l->angle_quantizer == PQ_ANGLE_UNIFORM;
-  if (!(uniform || grouped_on_matrix(l, n_q_heads / l->n_kv_heads)) || !large_launch(l, n_seqs, max_seq_len) || units < kResidentGroups / kBalancedFan || n_seqs > kBalancedSeqs ||
-      l->n_kv_heads > kComputeUnits || units * max_pages >= (int64_t{1} << 30))
-    return {0, 0};
-  const bool large = units * max_pages >= kCutShare * kResidentGroups;
-  const int resident = 2 * (kComputeUnits / l->n_kv_heads);
-  const int n_chunks = plan_attention(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
-  const bool fit = n_seqs <= 64 && n_seqs < resident && n_chunks >= 2 && n_chunks <= (large && uniform ? kBalancedFan : kMergeFan) &&
-                   units * max_pages > kWaveRound * kResidentGroups;
-  // (the workspace has room for the host's chunks, and at this size for one partial of each resident work-group; more places than
-  // that cost time: 16 sequences of 2K tokens with a max_seq_len of 32K 21.7 us with three work-groups a resident one)
-  if (fit) return {std::max(n_seqs * n_chunks, resident) - n_seqs, resident};
-  if (!large || !uniform) return {0, 0};
-  const int64_t partials = workspace_slots(l, n_seqs, l->n_kv_heads, max_seq_len) - units;     // (one query head per KV head)
-  return {static_cast<int32_t>(std::min<int64_t>(3 * kResidentGroups, partials) / l->n_kv_heads), 0};
-}
-
-// Whether one kernel does all of pq_decode_attention (true), or the merge kernel follows: the
-// sequences are one chunk long, the launch is cut on the device, or a large one has few enough chunks per
-// unit.  (Grouped quantizer, 16 x 16K tokens: 115.6 -> 114.7 us without the launch, 4 x 8K 23.7 -> 22.7.  Its vector-unit kernel
-// leaves partials only.)
-bool merges_in_kernel(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
-  if (l->angle_quantizer != PQ_ANGLE_UNIFORM && !grouped_on_matrix(l, n_q_heads / l->n_kv_heads)) return false;
-  if (device_cut(l, v_bits, n_seqs, n_q_heads, max_seq_len).spare_chunks > 0) return true;
-  const int n_chunks = plan_attention(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
-  return n_chunks == 1 || (n_chunks <= kMergeFan && large_launch(l, n_seqs, max_seq_len));
-}
-
-// Work-groups of 8 wavefronts: sequences of one chunk with more pages than 4 wavefronts take at once, and no more
-// units than compute units (two work-groups of 4 share one otherwise).  One sequence of 777 tokens 13.3 -> 12.2 us
-// (11.5 now, with a shorter end of the chunk), 16 of them 15.0 -> 14.7; up to 4 pages the wider work-group costs 1 us (300 tokens: 9.7 -> 10.7).  From 8 pages on
-// chunk_lengths() makes two chunks: 8 units 13.0, 64 units 13.8 us; one chunk of 8 wavefronts 13.1 and 14.8 (4-bit values 12.7 and 12.7;
-// 13.0 and 13.1), but with 256 units, a work-group on every compute unit, 20.0 and 18.5 (4-bit values 15.9, 14.7).
-bool wide_groups(const pq_layout* l, const ChunkPlan& plan, int32_t n_seqs, int32_t max_seq_len) {
-  return l->angle_quantizer == PQ_ANGLE_UNIFORM && plan.n_chunks == 1 && max_seq_len > kWaveRound * kGroup &&
-         static_cast<int64_t>(n_seqs) * l->n_kv_heads <= kComputeUnits;
 }
 
 // Everything the decode entry points have in common: argument checks, kernel arguments, and the
