@@ -145,3 +145,13 @@ def test_each_launch_gets_its_cut(lib, lens, kv_heads, bound, uniform, of_groupe
     assert cut.kind == (of_grouped if grouped else uniform)
     if cut.kind != ON_HOST:
         cut.check()
+
+
+@pytest.mark.parametrize("lens,v_bits", [(spread(8, 1000, 8000), 16), (spread(8, 1000, 8000), 4), (spread(16, 300, 4000), 16), (spread(16, 300, 4000), 2),
+                                         (spread(32, 512, 8000), 16), (spread(32, 512, 8000), 4), (spread(4, 2000, 16000), 16)])
+def test_a_loose_bound_changes_nothing(lib, lens, v_bits):
+    """A serving program passes the model's context, or what a graph was captured with, for max_seq_len."""
+    tight = Cut(lib, lens, 8, max(lens), v_bits=v_bits).check()
+    for bound in (16384, 32768, 65536, 131072):
+        cut = Cut(lib, lens, 8, bound, v_bits=v_bits).check()
+        assert cut.kind == FITTED and cut.sizes() == tight.sizes() and cut.rounds() == tight.rounds(), (bound, cut.sizes(), tight.sizes())
