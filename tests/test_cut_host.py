@@ -155,3 +155,13 @@ def test_a_loose_bound_changes_nothing(lib, lens, v_bits):
     for bound in (16384, 32768, 65536, 131072):
         cut = Cut(lib, lens, 8, bound, v_bits=v_bits).check()
         assert cut.kind == FITTED and cut.sizes() == tight.sizes() and cut.rounds() == tight.rounds(), (bound, cut.sizes(), tight.sizes())
+
+
+@pytest.mark.parametrize("lens,kv_heads", [(spread(31, 750, 1500), 8), (spread(28, 96, 1530), 8), (spread(25, 1125, 1500), 8), (spread(7, 577, 1200), 32)])
+def test_no_round_is_lost_to_even_chunks(lib, lens, kv_heads):
+    """Two chunks of up to three rounds of four pages: 8 + 4 pages, three rounds, and not 6 + 6, four."""
+    cut = Cut(lib, lens, kv_heads, 1536).check()
+    assert cut.kind == FITTED
+    for pages, chunks in zip(cut.pages, cut.chunks):
+        assert sum((size + 3) // 4 for _, size, _ in chunks.values()) == (pages + 3) // 4, (pages, chunks)
+    assert cut.rounds()[0] <= 3
