@@ -177,7 +177,8 @@ struct BalancedPlan {
     // (at most kBalancedFan chunks of the longest sequence there is: by max_seq_len, 8 x 1K .. 8K tokens with one of 128K had chunks of
     // 32 pages where 8 do, 42.5 us instead of 25.5)
     const int total = wave_sum(pages0), longest = static_cast<int>(wave_max_u32(static_cast<uint32_t>(pages0)));
-    // as long as the longest of the host's (with longer ones, work-groups that come as others go are the better balance)
+    // As long as the longest of the host's; with longer ones, work-groups that come as others go are the better balance: 48 x 3K .. 12K
+    // tokens in chunks of 68 pages 155 us, by the general rule 143.
     constexpr int kLongest = 64;
 #pragma unroll 1
     for (int c = whole_rounds(max((total + a.fit_chunks - 1) / a.fit_chunks, (longest + kBalancedFan - 1) / kBalancedFan)); c <= kLongest; c += 2 * kWaveRound) {
@@ -186,7 +187,7 @@ struct BalancedPlan {
       const int m = lane < n_seqs ? max(1, div_up(pages0, c + kWaveRound, __builtin_amdgcn_rcpf(static_cast<float>(c + kWaveRound)))) : 0;
       const int both = wave_sum(n | (m << 16));
       const bool first = (both & 0xffff) <= a.fit_chunks;
-      if (first || (both >> 16) <= a.fit_chunks) {
+      if (first || (c < kLongest && (both >> 16) <= a.fit_chunks)) {
         kind = kFitted;
         n0 = first ? n : m;
         units = kComputeUnits / a.n_kv_heads;

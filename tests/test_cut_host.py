@@ -165,3 +165,9 @@ def test_no_round_is_lost_to_even_chunks(lib, lens, kv_heads):
     for pages, chunks in zip(cut.pages, cut.chunks):
         assert sum((size + 3) // 4 for _, size, _ in chunks.values()) == (pages + 3) // 4, (pages, chunks)
     assert cut.rounds()[0] <= 3
+
+
+@pytest.mark.parametrize("lens", [spread(48, 3000, 12000), spread(52, 3000, 12000), spread(45, 2000, 16000)])
+def test_chunks_that_start_together_are_64_pages_at_most(lib, lens):
+    cut = Cut(lib, lens, 8).check()
+    assert max(cut.sizes()) <= 64, (cut.kind, cut.sizes())
