@@ -364,10 +364,11 @@ int decode_launch(const pq_layout* layout, const void* q, pq_dtype q_dtype, int3
   const bool roles = choose_attention_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len) == AttentionKernel::kRoles;
   const bool merged = out != nullptr && merges_in_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len);
   a.merge_in_kernel = merged ? 1 : 0;
-  const DeviceCut cut = out != nullptr ? device_cut(layout, v_bits, n_seqs, n_q_heads, max_seq_len) : DeviceCut{0, 0};
+  const DeviceCut cut = out != nullptr ? device_cut(layout, v_bits, n_seqs, n_q_heads, max_seq_len) : DeviceCut{0, 0, 0};
+  a.cut_places = cut.places;
   a.spare_chunks = cut.spare_chunks;
   a.fit_chunks = cut.fit_chunks;
-  const dim3 grid = a.spare_chunks > 0 ? dim3(layout->n_kv_heads, n_seqs + a.spare_chunks) : dim3(layout->n_kv_heads, n_seqs, plan.n_chunks);
+  const dim3 grid = a.cut_places > 0 ? dim3(layout->n_kv_heads, a.cut_places) : dim3(layout->n_kv_heads, n_seqs, plan.n_chunks);
   a.wide_groups = out != nullptr && wide_groups(layout, plan, n_seqs, max_seq_len) ? 1 : 0;
   a.table_index = key_table_index(layout);
   // A pass over the cache serves up to 8 query heads of a KV head (with the grouped quantizer on the vector unit, whose kernel

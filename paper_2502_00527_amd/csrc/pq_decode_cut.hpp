@@ -67,8 +67,9 @@ struct BalancedPlan {
   int n_seqs, lane;
   ChunkLengths len;
   float per_big, per_small;
-  enum Kind { kGeneral, kAlike, kFitted } kind;   // which cut it is (cut_resident)
-  int others0, size0;                          // kFitted: chunks behind the first ones, of the sequences up to this lane's; pages a chunk
+  enum Kind { kGeneral, kGrid, kFitted } kind;    // which cut it is; kGrid: slot u is chunk u / n_seqs of sequence u % n_seqs
+  int others0;                                 // kGrid, kFitted: chunks behind the first ones, of the sequences up to this lane's
+  int size0;                                   // kFitted: pages a chunk
   int units;                                   // kFitted: compute units for each KV head
 
   __device__ __forceinline__ void load(const DecodeArgs& a, int lane_) {
@@ -125,6 +126,7 @@ struct BalancedPlan {
     if (a.fit_chunks > 0) {
       const int slots = cut_resident(a);
       if (slots > 0) return slots;
+      if (a.spare_chunks == 0) return cut_as_host(a);
     }
     int sum = pages0, most = pages0;
 #pragma unroll 1
@@ -147,9 +149,23 @@ struct BalancedPlan {
     }
     return chunks;
   }
+  // The host's chunks, as if the grid were (sequence, chunk).
+  __device__ __forceinline__ int cut_as_host(const DecodeArgs& a) {
+    kind = kGrid;
+    len.big = a.pages_per_chunk;
+    len.small = a.pages_small;
+    len.n_big = a.n_big;
+    find_chunks();
+    others0 = wave_prefix(max(n0 - 1, 0));
+    return n_seqs * a.n_chunks;
+  }
+  // Chunks that are resident together are as long as the longest of the host's; with longer ones, work-groups that come as others go are
+  // the better balance (48 x 3K .. 12K tokens in chunks of 68 pages 155 us, by the general rule 143).  Up to kShort pages, a chunk's start
+  // and end are worth an empty place.
+  static constexpr int kLongest = 64, kShort = 12;
   // The cut of a launch of at most 64 sequences that leaves places on the compute units when every sequence has one work-group.
-  // If all sequences are equally long nothing has to be counted (kAlike), and if they are as long as the host was told its chunk
-  // lengths are the measured ones.  If they are not, what matters is that all chunks start at once and that the two work-groups of a compute unit
+  // If all sequences are equally long nothing has to be counted, and if they are as long as the host was told its chunk
+  // lengths are the measured ones.  If lengths differ, what matters is that all chunks start at once and that the two work-groups of a compute unit
   // are not both long ones (kFitted): the shortest whole rounds with no more chunks than are resident together, a sequence's
   // chunks alike, and locate_fitted() says who takes which.  Returns the slots that may have a chunk, 0 if neither will do.
   // Measured (8 KV heads, 4 query heads each, microseconds: chunks cut on the host, or here by chunk_lengths() from 48 pages a
@@ -162,24 +178,22 @@ struct BalancedPlan {
     const int max_pages = pages_of_len(a.max_seq_len);
     const int first_pages = uni(pages0);
     if (__builtin_amdgcn_ballot_w64(lane < n_seqs && pages0 != first_pages) == 0) {
-      kind = kAlike;
-      len.big = a.pages_per_chunk;
-      len.small = a.pages_small;
-      len.n_big = a.n_big;
-      if (first_pages != max_pages) {                                  // shorter ones: as many chunks as there are places
-        const int n = a.fit_chunks / n_seqs;
-        len.big = len.small = max(kWaveRound, whole_rounds((first_pages + n - 1) / n));
-        len.n_big = max_pages;
-      }
+      if (first_pages == max_pages) return cut_as_host(a);
+      // Shorter ones: as many chunks as there are places -- unless, with one chunk each, a unit has two sequences and most have one
+      // (33 x 8000 tokens with a max_seq_len of 8200: 144 us, the host's 44 pages a chunk 129; 36 x 3000 60 and 55; 44 sequences 1 % the other
+      // way, and up to 12 pages 33 x 1500 31.0 and 31.4, with 4-bit values 22.5 and 26.1), or chunks are too long (44 x 12000 227 and 208).
+      const int n = a.fit_chunks / n_seqs, c = max(kWaveRound, whole_rounds((first_pages + n - 1) / n));
+      if ((n == 1 && c > kShort && 3 * n_seqs < 2 * a.fit_chunks) || c > kLongest) return 0;
+      kind = kGrid;
+      len.big = len.small = c;
+      len.n_big = max_pages;
       find_chunks();
+      others0 = (lane + 1) * (n0 - 1);
       return n_seqs * uni(n0);
     }
     // (at most kBalancedFan chunks of the longest sequence there is: by max_seq_len, 8 x 1K .. 8K tokens with one of 128K had chunks of
     // 32 pages where 8 do, 42.5 us instead of 25.5)
     const int total = wave_sum(pages0), longest = static_cast<int>(wave_max_u32(static_cast<uint32_t>(pages0)));
-    // As long as the longest of the host's; with longer ones, work-groups that come as others go are the better balance: 48 x 3K .. 12K
-    // tokens in chunks of 68 pages 155 us, by the general rule 143.
-    constexpr int kLongest = 64;
 #pragma unroll 1
     for (int c = whole_rounds(max((total + a.fit_chunks - 1) / a.fit_chunks, (longest + kBalancedFan - 1) / kBalancedFan)); c <= kLongest; c += 2 * kWaveRound) {
       // two lengths at a time, their counts in the halves of a word
@@ -239,11 +253,11 @@ struct BalancedPlan {
   // sequence and chunk of slot u >= n_seqs, u < what the cut returned; false: it has none
   __device__ __forceinline__ bool locate(int u, int& seq, int& chunk) const {
     if (kind == kFitted) return locate_fitted(u, seq, chunk);
-    if (kind == kAlike) {
+    if (kind == kGrid) {
       chunk = uni(static_cast<int>(static_cast<float>(u) * __builtin_amdgcn_rcpf(static_cast<float>(n_seqs))));   // off by one at most
       chunk += u - chunk * n_seqs >= n_seqs ? 1 : (u - chunk * n_seqs < 0 ? -1 : 0);
       seq = u - chunk * n_seqs;
-      return true;
+      return chunk < __builtin_amdgcn_readlane(n0, seq);
     }
     // most chunk numbers c below which at most u slots lie: sum of min(n, c) over the sequences
     int lo = 1, before = n_seqs, hi = kBalancedFan;
@@ -291,7 +305,7 @@ struct BalancedPlan {
     if (kind != kGeneral) {
       n_pages = __builtin_amdgcn_readlane(pages0, seq);
       n_chunks = __builtin_amdgcn_readlane(n0, seq);
-      chunks_before = kind == kAlike ? seq * n_chunks : seq + __builtin_amdgcn_readlane(others0, seq) - (n_chunks - 1);
+      chunks_before = seq + __builtin_amdgcn_readlane(others0, seq) - (n_chunks - 1);
       return;
     }
     int sum = 0;

@@ -22,7 +22,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TB == 5 ? 2
 
 template <int RB, int TB, int NH>
 void launch_heads(const DecodeArgs& a, dim3 grid, hipStream_t st) {
-  if (a.spare_chunks > 0) hipLaunchKernelGGL((pq_decode_partials_kernel<RB, TB, PQ_GROUPED_VB, NH, true>), grid, dim3(256), 0, st, a);
+  if (a.cut_places > 0) hipLaunchKernelGGL((pq_decode_partials_kernel<RB, TB, PQ_GROUPED_VB, NH, true>), grid, dim3(256), 0, st, a);
   else hipLaunchKernelGGL((pq_decode_partials_kernel<RB, TB, PQ_GROUPED_VB, NH, false>), grid, dim3(256), 0, st, a);
 }
 template <int RB, int TB>

@@ -85,8 +85,9 @@ struct DecodeArgs {
   int32_t n_big;            // chunks from here on are pages_small long (pq_decode_matrix.hpp)
   int32_t pages_small;
   int32_t wide_groups;      // work-groups of 8 wavefronts instead of 4 (pq_decode_matrix.hip)
-  int32_t spare_chunks;     // > 0: chunks are cut on the device (pq_decode_sched.hpp), n_seqs + this many per KV head at most
-  int32_t fit_chunks;       // ... which of a medium launch are to be this many per KV head if lengths differ; 0: a large launch
+  int32_t cut_places;       // > 0: the chunks are cut on the device (pq_decode_cut.hpp); this and the next two as in DeviceCut
+  int32_t spare_chunks;
+  int32_t fit_chunks;
   float scale_log2;         // sm_scale * log2(e)
   float cos_tab[kMaxAngleBins];
   float sin_tab[kMaxAngleBins];

@@ -30,7 +30,7 @@ void launch_named(bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st) {
 }
 template <int W, int VB, int NH, bool Q32>
 void launch_one(bool roles, const DecodeArgs& a, dim3 grid, hipStream_t st) {
-  if (a.spare_chunks > 0) launch_named<W, VB, NH, Q32, true>(roles, a, grid, st);
+  if (a.cut_places > 0) launch_named<W, VB, NH, Q32, true>(roles, a, grid, st);
   else if (a.wide_groups && !roles) hipLaunchKernelGGL((pq_decode_partials_kernel<W, VB, NH, Q32, false, 8>), grid, dim3(512), 0, st, a);
   else launch_named<W, VB, NH, Q32, false>(roles, a, grid, st);
 }

@@ -1004,7 +1004,7 @@ __device__ __forceinline__ void grouped_scores_body(const DecodeArgs& a) {
 }
 
 // ---- attention ----------------------------------------------------------------------------------
-// kCut: the chunks are cut on the device (a.spare_chunks > 0).  kMatWaves: wavefronts of the work-group, 4 or 8.
+// kCut: the chunks are cut on the device (a.cut_places > 0).  kMatWaves: wavefronts of the work-group, 4 or 8.
 // kGroupedRadius: 0 on the uniform grid; with the grouped angle quantizer the radius bits (queries of either type are
 // taken as fp32 there, so that Q32 is true).
 template <int W, int VB, int NH, bool Q32, bool kCut, int kMatWaves, int kGroupedRadius = 0>

@@ -161,18 +161,19 @@ inline ChunkPlan plan_attention(const pq_layout* l, int32_t v_bits, int32_t n_se
                                                 : plan_chunks(n_seqs, l->n_kv_heads, max_seq_len);
 }
 
-// How a launch is cut into chunks on the device by the sequences' real lengths (BalancedPlan); spare_chunks 0: it is cut on the
-// host.  The grid has n_seqs + spare_chunks places per KV head.  fit_chunks: how many chunks per KV head are resident at once, if
-// that cut (BalancedPlan::cut_resident) is tried.
+// How a launch is cut into chunks on the device by the sequences' real lengths (BalancedPlan).  places: of the grid, per KV head; 0:
+// the launch is cut on the host.  fit_chunks: how many chunks per KV head are resident at once, if that cut
+// (BalancedPlan::cut_resident) is tried; spare_chunks: chunks per KV head beyond one a sequence that the general rule may make, 0 if the
+// launch has the host's chunks where the other cut will not do.
 // Three kinds of launches: sequences of at least two chunks that leave places on the compute units (fit_chunks > 0), from four pages a
-// resident work-group on (below, chunks are one round long); launches where a resident work-group may have kCutShare pages or more, up to three
-// work-groups a resident one or as many as the workspace has partials for; and the others, cut as if every sequence had max_seq_len
-// tokens.  With fewer than 16 units the host's cut has more chunks per unit than are combined in the kernel (but for launches
+// resident work-group on (below, chunks are one round long); launches where a resident work-group may have kCutShare pages or more, for the general
+// rule, up to three work-groups a resident one or as many as the workspace has partials for (a launch may be of both kinds); and the
+// others, cut as if every sequence had max_seq_len tokens.  With fewer than 16 units the host's cut has more chunks per unit than are combined in the kernel (but for launches
 // of kCutShare pages, whose chunks may be 32 of a unit); above 512 sequences reading all lengths in every work-group costs more
 // than uneven chunks do among so many.  The grouped quantizer's matrix kernels have the first kind and the last one.
 constexpr int64_t kCutShare = 48;
 struct DeviceCut {
-  int32_t spare_chunks, fit_chunks;
+  int32_t places, spare_chunks, fit_chunks;
 };
 inline DeviceCut device_cut(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
   const int64_t units = static_cast<int64_t>(n_seqs) * l->n_kv_heads;
@@ -180,7 +181,7 @@ inline DeviceCut device_cut(const pq_layout* l, int32_t v_bits, int32_t n_seqs, 
   const bool uniform = l->angle_quantizer == PQ_ANGLE_UNIFORM;
   if (!(uniform || grouped_on_matrix(l, n_q_heads / l->n_kv_heads)) || !large_launch(l, n_seqs, max_seq_len) || units < kResidentGroups / kBalancedFan || n_seqs > kBalancedSeqs ||
       l->n_kv_heads > kComputeUnits || units * max_pages >= (int64_t{1} << 30))
-    return {0, 0};
+    return {0, 0, 0};
   const bool large = units * max_pages >= kCutShare * kResidentGroups;
   const int resident = 2 * (kComputeUnits / l->n_kv_heads);
   const int n_chunks = plan_attention(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
@@ -188,10 +189,12 @@ inline DeviceCut device_cut(const pq_layout* l, int32_t v_bits, int32_t n_seqs, 
                    units * max_pages > kWaveRound * kResidentGroups;
   // (the workspace has room for the host's chunks, and at this size for one partial of each resident work-group; more places than
   // that cost time: 16 sequences of 2K tokens with a max_seq_len of 32K 21.7 us with three work-groups a resident one)
-  if (fit) return {std::max(n_seqs * n_chunks, resident) - n_seqs, resident};
-  if (!large || !uniform) return {0, 0};
+  const int places = fit ? std::max(n_seqs * n_chunks, resident) : 0;
+  if (!large || !uniform) return {places, 0, fit ? resident : 0};
   const int64_t partials = workspace_slots(l, n_seqs, l->n_kv_heads, max_seq_len) - units;     // (one query head per KV head)
-  return {static_cast<int32_t>(std::min<int64_t>(3 * kResidentGroups, partials) / l->n_kv_heads), 0};
+  const int spare = static_cast<int>(std::min<int64_t>(3 * kResidentGroups, partials) / l->n_kv_heads);
+  if (fit) return {places, std::min(spare, places - n_seqs), resident};
+  return {n_seqs + spare, spare, 0};
 }
 
 // Whether one kernel does all of pq_decode_attention (true), or the merge kernel follows: the
@@ -200,7 +203,7 @@ inline DeviceCut device_cut(const pq_layout* l, int32_t v_bits, int32_t n_seqs, 
 // leaves partials only.)
 inline bool merges_in_kernel(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
   if (l->angle_quantizer != PQ_ANGLE_UNIFORM && !grouped_on_matrix(l, n_q_heads / l->n_kv_heads)) return false;
-  if (device_cut(l, v_bits, n_seqs, n_q_heads, max_seq_len).spare_chunks > 0) return true;
+  if (device_cut(l, v_bits, n_seqs, n_q_heads, max_seq_len).places > 0) return true;
   const int n_chunks = plan_attention(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
   return n_chunks == 1 || (n_chunks <= kMergeFan && large_launch(l, n_seqs, max_seq_len));
 }

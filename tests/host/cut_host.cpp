@@ -162,7 +162,7 @@ using std::max;
 using std::min;
 struct DecodeArgs {
   const int32_t* seq_lens;
-  int32_t n_seqs, n_kv_heads, max_seq_len, pages_per_chunk, n_big, pages_small, spare_chunks, fit_chunks;
+  int32_t n_seqs, n_kv_heads, max_seq_len, pages_per_chunk, n_chunks, n_big, pages_small, spare_chunks, fit_chunks;
 };
 }  // namespace pq
 
@@ -186,7 +186,7 @@ extern "C" int cut_host(int n_seqs, int n_kv_heads, int n_q_heads, int grouped, 
   layout.angle_quantizer = grouped ? PQ_ANGLE_GROUPED : PQ_ANGLE_UNIFORM;
   const ChunkPlan host = plan_attention(&layout, v_bits, n_seqs, n_q_heads, max_seq_len);
   const DeviceCut cut = device_cut(&layout, v_bits, n_seqs, n_q_heads, max_seq_len);
-  plan[0] = cut.spare_chunks > 0 ? n_seqs + cut.spare_chunks : static_cast<int64_t>(n_seqs) * host.n_chunks;
+  plan[0] = cut.places > 0 ? cut.places : static_cast<int64_t>(n_seqs) * host.n_chunks;
   plan[1] = cut.fit_chunks;
   plan[2] = merges_in_kernel(&layout, v_bits, n_seqs, n_q_heads, max_seq_len);
   plan[3] = host.pages_per_chunk;
@@ -194,8 +194,8 @@ extern "C" int cut_host(int n_seqs, int n_kv_heads, int n_q_heads, int grouped, 
   plan[5] = static_cast<int64_t>(workspace_slots(&layout, n_seqs, n_q_heads, max_seq_len)) / (n_q_heads / n_kv_heads);
   plan[6] = -1;
   plan[7] = 0;
-  if (cut.spare_chunks == 0) return 0;
-  const DecodeArgs a = {lens, n_seqs, n_kv_heads, max_seq_len, host.pages_per_chunk, host.n_big, host.pages_small, cut.spare_chunks, cut.fit_chunks};
+  if (cut.places == 0) return 0;
+  const DecodeArgs a = {lens, n_seqs, n_kv_heads, max_seq_len, host.pages_per_chunk, host.n_chunks, host.n_big, host.pages_small, cut.spare_chunks, cut.fit_chunks};
   std::vector<int32_t> others(kBalancedSeqs);
   for (int s = 0; s < n_seqs; ++s) others[s] = pages_of_len(clamped_len(a, s));   // (the other wavefronts of the work-group)
   lanes::run([&](int id) {

@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-ON_HOST, GENERAL, ALIKE, FITTED = -1, 0, 1, 2
+ON_HOST, GENERAL, GRID, FITTED = -1, 0, 1, 2
 FAN = 32
 
 
@@ -116,13 +116,13 @@ def test_every_chunk_has_one_place(lib, seed):
             except AssertionError:
                 print(case)
                 raise
-    assert {GENERAL, ALIKE, FITTED} <= seen or len(seen) >= 3, seen
+    assert {GENERAL, GRID, FITTED} <= seen or len(seen) >= 3, seen
 
 
 LAUNCHES = [
     # lengths, KV heads, bound, the cut on the uniform grid and with the grouped quantizer
-    ([16 * 128] * 17, 8, None, ALIKE, ALIKE),
-    ([700] * 20, 4, 6000, ALIKE, ALIKE),
+    ([16 * 128] * 17, 8, None, GRID, GRID),
+    ([700] * 20, 4, 6000, GRID, GRID),
     (spread(20, 1, 3400), 4, 3400, FITTED, FITTED),
     (spread(40, 1, 1300), 8, 1500, FITTED, FITTED),                      # more sequences than units
     ([6000] + [1 + i for i in range(40)], 2, None, FITTED, FITTED),      # units with nothing but a one-page first chunk
@@ -130,7 +130,7 @@ LAUNCHES = [
     ([0, 2900, 5, 0, 128, 129, 1000, 2432, 2433], 7, 4500, FITTED, FITTED),
     ([2300, 400], 16, 9000, FITTED, ON_HOST),                            # units without a first chunk
     (spread(63, 0, 800) + [2100], 2, 2500, FITTED, FITTED),
-    (spread(48, 1000, 16000), 8, None, GENERAL, GENERAL),                # chunks of 64 pages are too many to be resident together
+    (spread(48, 1000, 16000), 8, None, GENERAL, GRID),                   # chunks of 64 pages are too many to be resident together
     (spread(31, 200, 3000), 8, None, FITTED, FITTED),
     (spread(64, 1024, 16384), 8, None, GENERAL, ON_HOST),                # no places are left
     ([260] * 16, 4, 400 * 1024, GENERAL, ON_HOST),                       # the bound would have more chunks than are combined
@@ -171,3 +171,14 @@ def test_no_round_is_lost_to_even_chunks(lib, lens, kv_heads):
 def test_chunks_that_start_together_are_64_pages_at_most(lib, lens):
     cut = Cut(lib, lens, 8).check()
     assert max(cut.sizes()) <= 64, (cut.kind, cut.sizes())
+
+
+@pytest.mark.parametrize("lens,kv_heads,bound", [([8000] * 33, 8, 8200), ([3000] * 36, 8, 3200), ([12000] * 40, 8, 12200), ([8000] * 9, 32, 8200), ([12000] * 44, 8, 12200),
+                                                 ([1500] * 33, 8, 1700), ([8000] * 48, 8, 8200), ([30000] * 24, 8, 30200)])
+@pytest.mark.parametrize("grouped", [False, True])
+def test_places_are_not_left_empty_by_equal_sequences(lib, lens, kv_heads, bound, grouped):
+    """Sequences a little shorter than the bound, a few more than compute units: not one chunk each, two of them on some units."""
+    cut = Cut(lib, lens, kv_heads, bound, grouped=grouped).check()
+    fullest, mean = cut.rounds()
+    assert cut.kind != FITTED and max(cut.sizes()) <= 64
+    assert len(cut.sizes()) > 2 * (256 // kv_heads) * 2 // 3 or max(cut.sizes()) <= 12, (cut.kind, cut.sizes())
