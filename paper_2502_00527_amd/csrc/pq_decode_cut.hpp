@@ -96,9 +96,10 @@ struct BalancedPlan {
       f(s0, p, chunks_of(s0 + lane, p));
     }
   }
-  // ceil(x / d) for 0 <= x <= 2^24 (every page count), by the reciprocal of d; d >= 4, or x < 8
+  // ceil(x / d) for 0 <= x <= 2^24 (every page count) and d >= 1, by the reciprocal of d; x / d <= 2^22, so that the quotient is
+  // off by one at most
   static __device__ __forceinline__ int div_up(int x, int d, float inverse) {
-    const int q = static_cast<int>(static_cast<float>(x) * inverse);   // off by one at most
+    const int q = static_cast<int>(static_cast<float>(x) * inverse);
     const int rest = x - q * d;
     return q + (rest > 0 ? 1 : 0) + (rest > d ? 1 : 0) - (rest <= -d ? 1 : 0);
   }
@@ -205,7 +206,8 @@ struct BalancedPlan {
         kind = kFitted;
         n0 = first ? n : m;
         units = kComputeUnits / a.n_kv_heads;
-        size0 = div_up(pages0, n0, __builtin_amdgcn_rcpf(static_cast<float>(n0)));
+        const int chunks0 = max(n0, 1);                                // (no chunks past the last sequence)
+        size0 = div_up(pages0, chunks0, __builtin_amdgcn_rcpf(static_cast<float>(chunks0)));
         // Alike to the page, not in whole rounds: the places are done together (36 x 400 .. 1500 tokens 23.6 us against 25.6, 20 x 11K .. 12K 95.9
         // against 102).  But where no sequence has more than three rounds and no unit two first chunks, rounds of 2 + 1 are three a unit and
         // 6 + 6 pages are four: 28 x 750 .. 1500 tokens 23.6 -> 22.1, with 4-bit values 20.5 -> 18.6, grouped quantizer 29.9 -> 26.7.
