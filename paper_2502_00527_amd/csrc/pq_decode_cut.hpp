@@ -121,11 +121,11 @@ struct BalancedPlan {
     return wave_sum(sum);
   }
   // after load() and store_others(); returns the chunks per KV head
-  __device__ __forceinline__ int cut(const DecodeArgs& a, bool fp16_values) {
+  __device__ __forceinline__ int cut(const DecodeArgs& a, bool fp16_values, bool grouped) {
     pages0 = lane < n_seqs ? pages_of_len(min(pages0, a.max_seq_len)) : 0;
     kind = kGeneral;
     if (a.fit_chunks > 0) {
-      const int slots = cut_resident(a);
+      const int slots = cut_resident(a, fp16_values ? kPairedFp16 : (grouped ? kPairedGrouped : kPairedQuantized));
       if (slots > 0) return slots;
       if (a.spare_chunks == 0) return cut_as_host(a);
     }
@@ -164,6 +164,20 @@ struct BalancedPlan {
   // the better balance (48 x 3K .. 12K tokens in chunks of 68 pages 155 us, by the general rule 143).  Up to kShort pages, a chunk's start
   // and end are worth an empty place.
   static constexpr int kLongest = 64, kShort = 12;
+  // Whether more chunks than units, but by less than a third, are above half of the longest one (n0, size0): those few units with two
+  // of them end last, at twice the time of the others.  Above kPaired* pages chunks cut without a look at the places are the better ones
+  // then; shorter ones, and more units with two, are no slower.  Microseconds, 8 KV heads, as the host or the general rule cuts ->
+  // resident together:
+  //   fp16 values: 33 x 7700 .. 8200 tokens 127 -> 151;  20 x 8192 + 13 x 600 77 -> 86;  36 x 3700 .. 4100 74 -> 80;  20 x 3584 + 15 x 600
+  //     (chunks of 14 pages) 41.5 -> 43.8;  36 x 1350 .. 1500 32.6 -> 33.0;  35 x 900 .. 1800 34 -> 30;  44 x 7700 .. 8200, a third, 166 -> 158
+  //   4-bit values: 33 x 7700 .. 8200 75 -> 83;  36 x 3700 .. 4100 47.0 -> 47.0;  36 x 2700 .. 3000 37.9 -> 37.6;  20 x 4096 + 15 x 600 37.5 -> 31.8
+  //   grouped quantizer, 4-bit values: 36 x 2170 .. 2300 45 -> 50;  40 x 1920 .. 2048 43.4 -> 41.4
+  static constexpr int kPairedFp16 = 12, kPairedGrouped = 16, kPairedQuantized = 28;   // (the two latter: quantized values)
+  __device__ __forceinline__ bool pairs_up_few() const {
+    const int top = static_cast<int>(wave_max_u32(static_cast<uint32_t>(n0 > 0 ? size0 : 0)));
+    const int over = wave_sum(2 * size0 > top ? n0 : 0);
+    return over > units && 3 * over < 4 * units;
+  }
   // The cut of a launch of at most 64 sequences that leaves places on the compute units when every sequence has one work-group.
   // If all sequences are equally long nothing has to be counted, and if they are as long as the host was told its chunk
   // lengths are the measured ones.  If lengths differ, what matters is that all chunks start at once and that the two work-groups of a compute unit
@@ -175,7 +189,7 @@ struct BalancedPlan {
   //   grouped quantizer: 12 x 1K .. 16K 80.8 -> 52.9, 8 heads and 4-bit values 81.2 -> 47.2;  20 x 5K .. 10K, 2-bit values 50.8 -> 39.7
   //   6 x 500 .. 12K 36.4 -> 27.1;  30 x 300 .. 2500 29.3 -> 25.2;  16 x 4K .. 32K 142.8 -> 114.3;  8 x 4K .. 8K, 32 KV heads 82.1 -> 77.0
   //   alike: 16 x 2K with a max_seq_len of 32K 20.7 -> 20.8, 16 x 8K 60.0 -> 59.4, 31 x 3000 43.5 -> 43.5;  8 x 8K, 32 KV heads 109.4 -> 109.0
-  __device__ __forceinline__ int cut_resident(const DecodeArgs& a) {
+  __device__ __forceinline__ int cut_resident(const DecodeArgs& a, int paired_long) {
     const int max_pages = pages_of_len(a.max_seq_len);
     const int first_pages = uni(pages0);
     if (__builtin_amdgcn_ballot_w64(lane < n_seqs && pages0 != first_pages) == 0) {
@@ -212,6 +226,7 @@ struct BalancedPlan {
         // against 102).  But where no sequence has more than three rounds and no unit two first chunks, rounds of 2 + 1 are three a unit and
         // 6 + 6 pages are four: 28 x 750 .. 1500 tokens 23.6 -> 22.1, with 4-bit values 20.5 -> 18.6, grouped quantizer 29.9 -> 26.7.
         if ((first ? c : c + kWaveRound) == 2 * kWaveRound && longest <= 3 * kWaveRound && n_seqs <= units) size0 = whole_rounds(size0);
+        if ((first ? c : c + kWaveRound) > paired_long && pairs_up_few()) return 0;
         others0 = wave_prefix(max(n0 - 1, 0));
         return 2 * units;
       }

@@ -1063,7 +1063,7 @@ __device__ __forceinline__ void attention_body(const DecodeArgs& a) {
   BalancedPlan plan;
   auto take_cut = [&] {
     plan.store_others(a, sh.pages, tid);
-    const int chunks = plan.cut(a, VB == 16);
+    const int chunks = plan.cut(a, VB == 16, kGrouped);
     if (slot >= chunks) return false;
     if (slot >= a.n_seqs && !plan.locate(slot, seq, chunk)) return false;
     int before;

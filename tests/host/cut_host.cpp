@@ -202,7 +202,7 @@ extern "C" int cut_host(int n_seqs, int n_kv_heads, int n_q_heads, int grouped, 
     BalancedPlan p = {};
     p.load(a, id);
     p.store_others(a, others.data(), id);
-    const int chunks = p.cut(a, v_bits == 16);
+    const int chunks = p.cut(a, v_bits == 16, grouped != 0);
     if (id == 0) plan[6] = p.kind, plan[7] = chunks;
     if (p.kind == BalancedPlan::kFitted && (p.size0 < 0 || p.size0 > p.pages0 + kWaveRound)) lanes::fail("a lane's pages a chunk are not a number of pages");
     for (int u = 0; u < plan[0]; ++u) {

@@ -182,3 +182,25 @@ def test_places_are_not_left_empty_by_equal_sequences(lib, lens, kv_heads, bound
     fullest, mean = cut.rounds()
     assert cut.kind != FITTED and max(cut.sizes()) <= 64
     assert len(cut.sizes()) > 2 * (256 // kv_heads) * 2 // 3 or max(cut.sizes()) <= 12, (cut.kind, cut.sizes())
+
+
+# sequences of about the same length, a few more than compute units, or chunks of 64-page sequences that are
+PAIRED = [(spread(33, 7700, 8192), 8), (spread(36, 7700, 8192), 8), (spread(40, 5800, 6100), 8), (spread(17, 7700, 8192), 16), (spread(9, 7700, 8192), 32), ([8192] * 35 + [100], 8),
+          ([8192] * 20 + [600] * 13, 8), (spread(20, 7700, 8192) + spread(16, 300, 900), 8)]
+
+
+@pytest.mark.parametrize("lens,kv_heads", PAIRED)
+@pytest.mark.parametrize("v_bits,grouped", [(16, False), (4, False), (2, True)])
+def test_no_few_units_have_two_long_chunks(lib, lens, kv_heads, v_bits, grouped):
+    """More long chunks than compute units, but by less than a third: the few units with two of them would be waited for."""
+    cut = Cut(lib, lens, kv_heads, v_bits=v_bits, grouped=grouped).check()
+    long = sum(2 * size > max(cut.sizes()) for size in cut.sizes())
+    units = 256 // kv_heads
+    assert cut.kind != FITTED, (cut.sizes(), cut.rounds())
+    assert len(cut.sizes()) > 2 * units * 2 // 3, (long, cut.sizes())
+
+
+@pytest.mark.parametrize("lens,kv_heads,v_bits,grouped", [(spread(44, 7700, 8192), 8, 16, False), (spread(32, 512, 8192), 8, 2, False), (spread(36, 2700, 3000), 8, 4, False),
+                                                          (spread(36, 1350, 1500), 8, 16, False), (spread(40, 1900, 2048), 8, 4, True), (spread(24, 7700, 8192), 8, 16, False)])
+def test_all_chunks_start_at_once_where_that_is_no_slower(lib, lens, kv_heads, v_bits, grouped):
+    assert Cut(lib, lens, kv_heads, v_bits=v_bits, grouped=grouped).check().kind == FITTED
