@@ -217,7 +217,6 @@ struct BalancedPlan {
       const int both = wave_sum(n | (m << 16));
       const bool first = (both & 0xffff) <= a.fit_chunks;
       if (first || (c < kLongest && (both >> 16) <= a.fit_chunks)) {
-        kind = kFitted;
         n0 = first ? n : m;
         units = kComputeUnits / a.n_kv_heads;
         const int chunks0 = max(n0, 1);                                // (no chunks past the last sequence)
@@ -227,6 +226,7 @@ struct BalancedPlan {
         // 6 + 6 pages are four: 28 x 750 .. 1500 tokens 23.6 -> 22.1, with 4-bit values 20.5 -> 18.6, grouped quantizer 29.9 -> 26.7.
         if ((first ? c : c + kWaveRound) == 2 * kWaveRound && longest <= 3 * kWaveRound && n_seqs <= units) size0 = whole_rounds(size0);
         if ((first ? c : c + kWaveRound) > paired_long && pairs_up_few()) return 0;
+        kind = kFitted;
         others0 = wave_prefix(max(n0 - 1, 0));
         return 2 * units;
       }

@@ -204,3 +204,27 @@ def test_no_few_units_have_two_long_chunks(lib, lens, kv_heads, v_bits, grouped)
                                                           (spread(36, 1350, 1500), 8, 16, False), (spread(40, 1900, 2048), 8, 4, True), (spread(24, 7700, 8192), 8, 16, False)])
 def test_all_chunks_start_at_once_where_that_is_no_slower(lib, lens, kv_heads, v_bits, grouped):
     assert Cut(lib, lens, kv_heads, v_bits=v_bits, grouped=grouped).check().kind == FITTED
+
+
+# Launches to which the device's first cut does not apply; tests/test_gpu_cut_fallbacks.py runs them.
+# lengths, KV heads, query heads per KV head, max_seq_len, value bits, grouped quantizer, the cut
+FALLBACKS = [
+    (spread(33, 1690, 1790), 8, 4, 1800, 16, False, GRID),               # pairs on few units: the host's chunks
+    (spread(33, 1690, 1790), 8, 1, 12100, 16, False, GENERAL),           # the same from 48 pages a resident work-group on
+    (spread(17, 3700, 4090), 16, 2, 4096, 4, False, GRID),
+    (spread(17, 3700, 4090), 16, 4, 12400, 2, False, GENERAL),
+    (spread(9, 2200, 2430), 32, 3, 2500, 16, True, GRID),
+    (spread(33, 2200, 2430), 8, 4, 12100, 4, True, GRID),                # the grouped quantizer has no general rule
+    ([1700] * 33, 8, 4, 1800, 16, False, GRID),                          # equal ones below the bound
+    ([1700] * 33, 8, 4, 12100, 2, False, GENERAL),
+    ([1700] * 33, 8, 8, 1800, 16, True, GRID),
+    ([1, 1, 1] + [1700] * 33, 8, 6, 12100, 16, False, GENERAL),
+    (spread(2, 8500, 17000) + [17000], 128, 1, 17000, 4, False, GENERAL),   # chunks of 64 pages are too many
+    (spread(2, 8500, 17000) + [17000], 128, 3, 17000, 2, True, GRID),
+]
+
+
+@pytest.mark.parametrize("lens,kv_heads,group,bound,v_bits,grouped,kind", FALLBACKS)
+def test_launches_the_first_cut_does_not_apply_to(lib, lens, kv_heads, group, bound, v_bits, grouped, kind):
+    cut = Cut(lib, lens, kv_heads, bound, group, v_bits, grouped).check()
+    assert cut.kind == kind and cut.resident > 0, (cut.kind, cut.resident, cut.sizes())
