@@ -189,12 +189,18 @@ inline DeviceCut device_cut(const pq_layout* l, int32_t v_bits, int32_t n_seqs, 
                    units * max_pages > kWaveRound * kResidentGroups;
   // (the workspace has room for the host's chunks, and at this size for one partial of each resident work-group; more places than
   // that cost time: 16 sequences of 2K tokens with a max_seq_len of 32K 21.7 us with three work-groups a resident one)
-  const int places = fit ? std::max(n_seqs * n_chunks, resident) : 0;
+  int places = fit ? std::max(n_seqs * n_chunks, resident) : 0;
   if (!large || !uniform) return {places, 0, fit ? resident : 0};
   const int64_t partials = workspace_slots(l, n_seqs, l->n_kv_heads, max_seq_len) - units;     // (one query head per KV head)
   const int spare = static_cast<int>(std::min<int64_t>(3 * kResidentGroups, partials) / l->n_kv_heads);
-  if (fit) return {places, std::min(spare, places - n_seqs), resident};
-  return {n_seqs + spare, spare, 0};
+  if (!fit) return {n_seqs + spare, spare, 0};
+  // as many as the general rule would make of sequences of max_seq_len tokens, as far as there is room: with a shorter last part
+  // they may be more than the host's (33 x 12000 tokens, 4-bit values: 99 chunks of 32 pages 112 us, 66 of 48 127)
+  const ChunkLengths len = chunk_lengths(static_cast<int>(std::min<int64_t>(1 << 20, (units * max_pages + kResidentGroups - 1) / kResidentGroups)),
+                                         static_cast<int>(max_pages), v_bits == 16);
+  const int64_t first = std::min<int64_t>(len.n_big, (max_pages + len.big - 1) / len.big), rest = std::max<int64_t>(0, max_pages - first * len.big);
+  places = static_cast<int>(std::max<int64_t>(places, std::min<int64_t>(n_seqs * (first + (rest + len.small - 1) / len.small), n_seqs + spare)));
+  return {places, std::min(spare, places - n_seqs), resident};
 }
 
 // Whether one kernel does all of pq_decode_attention (true), or the merge kernel follows: the

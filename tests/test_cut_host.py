@@ -206,6 +206,14 @@ def test_all_chunks_start_at_once_where_that_is_no_slower(lib, lens, kv_heads, v
     assert Cut(lib, lens, kv_heads, v_bits=v_bits, grouped=grouped).check().kind == FITTED
 
 
+@pytest.mark.parametrize("lens,v_bits", [(spread(33, 11500, 12000), 4), (spread(36, 11500, 12000), 2), (spread(33, 11500, 12000), 2), ([12000] * 34 + [12100], 4)])
+def test_the_general_rule_has_the_places_it_needs(lib, lens, v_bits):
+    """Quantized values, from 48 pages a resident work-group on: chunks of three quarters of a work-group's part at most."""
+    cut = Cut(lib, lens, 8, v_bits=v_bits).check()
+    share = (len(lens) * 8 * max(cut.pages) + 511) // 512
+    assert cut.kind == GENERAL and max(cut.sizes()) <= (share * 3 // 4 + 3) // 4 * 4, (share, cut.sizes())
+
+
 # Launches to which the device's first cut does not apply; tests/test_gpu_cut_fallbacks.py runs them.
 # lengths, KV heads, query heads per KV head, max_seq_len, value bits, grouped quantizer, the cut
 FALLBACKS = [
