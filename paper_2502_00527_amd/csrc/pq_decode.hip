@@ -362,9 +362,9 @@ int decode_launch(const pq_layout* layout, const void* q, pq_dtype q_dtype, int3
   const int group_total = n_q_heads / layout->n_kv_heads;
   a.group_total = group_total;
   const bool roles = choose_attention_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len) == AttentionKernel::kRoles;
-  const bool merged = out != nullptr && merges_in_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len);
+  const DeviceCut cut = out != nullptr ? device_cut(layout, plan, v_bits, n_seqs, n_q_heads, max_seq_len) : DeviceCut{0, 0, 0};
+  const bool merged = out != nullptr && merges_in_kernel(layout, plan, cut, n_seqs, n_q_heads, max_seq_len);
   a.merge_in_kernel = merged ? 1 : 0;
-  const DeviceCut cut = out != nullptr ? device_cut(layout, v_bits, n_seqs, n_q_heads, max_seq_len) : DeviceCut{0, 0, 0};
   a.cut_places = cut.places;
   a.spare_chunks = cut.spare_chunks;
   a.fit_chunks = cut.fit_chunks;
@@ -429,7 +429,8 @@ extern "C" int pq_decode_merges_in_kernel(const pq_layout* layout, int32_t n_seq
                                           int32_t max_seq_len, int32_t v_bits) {
   const int st = check_decode_shape(layout, n_seqs, n_q_heads, max_seq_len);
   if (st != PQ_OK) return st;
-  return merges_in_kernel(layout, v_bits, n_seqs, n_q_heads, max_seq_len) ? 1 : 0;
+  const ChunkPlan plan = plan_attention(layout, v_bits, n_seqs, n_q_heads, max_seq_len);
+  return merges_in_kernel(layout, plan, device_cut(layout, plan, v_bits, n_seqs, n_q_heads, max_seq_len), n_seqs, n_q_heads, max_seq_len) ? 1 : 0;
 }
 
 extern "C" int pq_decode_merge(const pq_layout* layout, int32_t n_seqs, int32_t n_q_heads,

@@ -175,7 +175,8 @@ constexpr int64_t kCutShare = 48;
 struct DeviceCut {
   int32_t places, spare_chunks, fit_chunks;
 };
-inline DeviceCut device_cut(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
+// `host`: what plan_attention() gives for the launch.
+inline DeviceCut device_cut(const pq_layout* l, const ChunkPlan& host, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
   const int64_t units = static_cast<int64_t>(n_seqs) * l->n_kv_heads;
   const int64_t max_pages = (static_cast<int64_t>(max_seq_len) + kGroup - 1) / kGroup;
   const bool uniform = l->angle_quantizer == PQ_ANGLE_UNIFORM;
@@ -184,7 +185,7 @@ inline DeviceCut device_cut(const pq_layout* l, int32_t v_bits, int32_t n_seqs, 
     return {0, 0, 0};
   const bool large = units * max_pages >= kCutShare * kResidentGroups;
   const int resident = 2 * (kComputeUnits / l->n_kv_heads);
-  const int n_chunks = plan_attention(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
+  const int n_chunks = host.n_chunks;
   const bool fit = n_seqs <= 64 && n_seqs < resident && n_chunks >= 2 && n_chunks <= (large && uniform ? kBalancedFan : kMergeFan) &&
                    units * max_pages > kWaveRound * kResidentGroups;
   // (the workspace has room for the host's chunks, and at this size for one partial of each resident work-group; more places than
@@ -207,11 +208,9 @@ inline DeviceCut device_cut(const pq_layout* l, int32_t v_bits, int32_t n_seqs, 
 // sequences are one chunk long, the launch is cut on the device, or a large one has few enough chunks per
 // unit.  (Grouped quantizer, 16 x 16K tokens: 115.6 -> 114.7 us without the launch, 4 x 8K 23.7 -> 22.7.  Its vector-unit kernel
 // leaves partials only.)
-inline bool merges_in_kernel(const pq_layout* l, int32_t v_bits, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
+inline bool merges_in_kernel(const pq_layout* l, const ChunkPlan& host, const DeviceCut& cut, int32_t n_seqs, int32_t n_q_heads, int32_t max_seq_len) {
   if (l->angle_quantizer != PQ_ANGLE_UNIFORM && !grouped_on_matrix(l, n_q_heads / l->n_kv_heads)) return false;
-  if (device_cut(l, v_bits, n_seqs, n_q_heads, max_seq_len).places > 0) return true;
-  const int n_chunks = plan_attention(l, v_bits, n_seqs, n_q_heads, max_seq_len).n_chunks;
-  return n_chunks == 1 || (n_chunks <= kMergeFan && large_launch(l, n_seqs, max_seq_len));
+  return cut.places > 0 || host.n_chunks == 1 || (host.n_chunks <= kMergeFan && large_launch(l, n_seqs, max_seq_len));
 }
 
 // Work-groups of 8 wavefronts: sequences of one chunk with more pages than 4 wavefronts take at once, and no more

@@ -185,10 +185,10 @@ extern "C" int cut_host(int n_seqs, int n_kv_heads, int n_q_heads, int grouped, 
   layout.n_kv_heads = n_kv_heads;
   layout.angle_quantizer = grouped ? PQ_ANGLE_GROUPED : PQ_ANGLE_UNIFORM;
   const ChunkPlan host = plan_attention(&layout, v_bits, n_seqs, n_q_heads, max_seq_len);
-  const DeviceCut cut = device_cut(&layout, v_bits, n_seqs, n_q_heads, max_seq_len);
+  const DeviceCut cut = device_cut(&layout, host, v_bits, n_seqs, n_q_heads, max_seq_len);
   plan[0] = cut.places > 0 ? cut.places : static_cast<int64_t>(n_seqs) * host.n_chunks;
   plan[1] = cut.fit_chunks;
-  plan[2] = merges_in_kernel(&layout, v_bits, n_seqs, n_q_heads, max_seq_len);
+  plan[2] = merges_in_kernel(&layout, host, cut, n_seqs, n_q_heads, max_seq_len);
   plan[3] = host.pages_per_chunk;
   plan[4] = host.n_chunks;
   plan[5] = static_cast<int64_t>(workspace_slots(&layout, n_seqs, n_q_heads, max_seq_len)) / (n_q_heads / n_kv_heads);
