@@ -151,7 +151,7 @@ int key_table_index(const pq_layout* l) {
 
 // The caller's workspace: the chunks' partials and the units' arrival words.  Its size is that of
 // the chunk plan of plan_chunks() or of one partial for each of four_page_groups() + units, whichever
-// is larger; plan_uniform() and spare_chunks() keep within it.  (Of the words only `units` are used.
+// is larger; plan_uniform() and device_cut() keep within it.  (Of the words only `units` are used.
 // The size is what callers have been told, and the limit of the static scratch follows from it.)
 struct Workspace {
   float* acc;

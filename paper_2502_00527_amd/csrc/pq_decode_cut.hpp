@@ -58,9 +58,10 @@ __device__ __forceinline__ int wave_sum(int v) {
   return uni(static_cast<int>(s[0] + s[1]));
 }
 
-// The cut of a launch into chunks, made alike by every wavefront of it.  Slot u of a KV head: chunk 0
-// of sequence u for the first n_seqs, then the second chunks of the sequences that have one, and so on.
-// Sequences 0 .. 63 sit in a register, the others in LDS.
+// The cut of a launch into chunks, made alike by every wavefront of it.  Slot u of a KV head is chunk 0
+// of sequence u for the first n_seqs; the others have, by the kind of the cut, the second chunks of the sequences that have one, then
+// the third ones and so on (kGeneral), chunk u / n_seqs of sequence u % n_seqs or nothing (kGrid), or the chunk that suits
+// the compute unit (kFitted, locate_fitted()).  Sequences 0 .. 63 sit in a register, the others in LDS.
 struct BalancedPlan {
   int pages0, n0;                              // sequence `lane`: pages; chunks (0 past the last sequence, 1 if it is empty)
   const int32_t* others;                       // LDS: pages of sequences 64 ..
@@ -234,7 +235,9 @@ struct BalancedPlan {
     return 0;
   }
   // Slot u takes its place on compute unit u % units of its KV head, if work-groups are handed out in order (which they are:
-  // of 512 work-groups i and i + 256 shared a unit, 256 times of 256; nothing but time hangs on it).  The first slots have the sequences' first chunks; of the others, the longest chunk goes to the unit
+  // of 512 work-groups i and i + 256 shared a unit, 256 times of 256; nothing but time hangs on it; with KV heads that do not divide
+  // 256 the partner is a neighbour's: 5, 6, 7, 12 and 24 heads, 500 .. 8K tokens, fp16 values 64 -> 56, 67 -> 54, 68 -> 51 us and the like,
+  // 6 % faster at least).  The first slots have the sequences' first chunks; of the others, the longest chunk goes to the unit
   // with the least to do, the next one to the next.  False: there are no more.
   __device__ __forceinline__ bool locate_fitted(int u, int& seq, int& chunk) const {
     const int alone = max(0, units - n_seqs);                          // units without a first chunk

@@ -26,12 +26,18 @@
 // values; one multiply-add per (head, pair, token) and (head, dim, token) on the vector unit took 2200.
 // With fp16 values a page is 41 KB, 3600 cycles of a compute unit's share of HBM: memory-bound
 // (16 x 32K tokens, 4 query heads per KV head: 209 - 210 us, 6.5 TB/s; 217 on the vector unit).  With
-// quantized values the page is 11 - 17 KB and issue slots are the longer side, with the clock: a wavefront takes 10700 cycles a
-// page beside another one (8400 alone), the same when every page comes from the caches, but at 1.5 - 1.6 GHz from memory and at 2.0 GHz
-// from the caches -- power.  What helps is less to issue: one wait for four operands instead of four, two steps' queries in
-// one LDS read, lane constants kept where the registers allow it, denominators and zero-point sums by one multiply-add a token,
-// the next page's scales found among the values: 796 -> 690 vector instructions, 10700 -> 9600 cycles, and for 16 x 32K tokens
-// with 4-bit values 124 -> 120 us, 32 ragged ones with 2-bit values 42.7 -> 41.6.  (The values of one page beside the scores of
+// quantized values the page is 11 - 17 KB and its instructions are the longer side, with the clock: a wavefront takes as many cycles a
+// page when every page comes from the caches as from memory, but the clock falls from 2.0 GHz to 1.4 - 1.6 -- power.  Read from the
+// shader clock in the kernel, 16 x 32K tokens with 4-bit values, 4 heads, cycles a page of a wavefront beside one other:
+//   scores   5650   322 vector, 128 matrix and 144 LDS instructions
+//   softmax  1730   about 140 vector
+//   values   2340   264 vector, 32 matrix (230 of the former bring codes to their fields)
+// 9700 in all, 4850 a SIMD; with 10000 at the start of each of four chunks a SIMD, 176000 cycles a launch, 1.37 GHz in that run.  Of
+// those, vector and matrix instructions take 69 % of a SIMD's issue slots, the matrix pipe is busy for 46 %, LDS for 51 %: none
+// is full, and two wavefronts do not hide one another's chains (alone on its SIMD, a wavefront took 8400 cycles when two took 10700).
+// What helped is less to issue: one wait for four operands instead of four, two steps' queries in one LDS read, lane constants kept
+// where the registers allow it, denominators and zero-point sums by one multiply-add a token, the next page's scales found among
+// the values: 106 vector instructions, 10700 -> 9600 cycles, 124 -> 120 us.  (The values of one page beside the scores of
 // the next one, in one instruction stream: the same issue slots, 11200 cycles, +2 %.)
 //
 // The table is kept 16 times in LDS, copy l in the 16-byte column l of a 256-byte row, and lane l
