@@ -186,7 +186,7 @@ struct BalancedPlan {
   // chunks alike, and locate_fitted() says who takes which.  Returns the slots that may have a chunk, 0 if neither will do.
   // Measured (8 KV heads, 4 query heads each, microseconds: chunks cut on the host, or here by chunk_lengths() from 48 pages a
   // share on, and dealt out chunk by chunk -> this):
-  //   32 x 512 .. 8K tokens 70.9 -> 61.4, 3+3-bit keys and 2-bit values 42.4 -> 38.7;  8 x 2K .. 30K, 4-bit values 54.1 -> 41.8
+  //   32 x 512 .. 8K tokens 70.9 -> 61.4, 3+3-bit keys and 2-bit values 41.6 -> 35.1 (with fewer instructions a page);  8 x 2K .. 30K, 4-bit values 54.1 -> 41.8
   //   grouped quantizer: 12 x 1K .. 16K 80.8 -> 52.9, 8 heads and 4-bit values 81.2 -> 47.2;  20 x 5K .. 10K, 2-bit values 50.8 -> 39.7
   //   6 x 500 .. 12K 36.4 -> 27.1;  30 x 300 .. 2500 29.3 -> 25.2;  16 x 4K .. 32K 142.8 -> 114.3;  8 x 4K .. 8K, 32 KV heads 82.1 -> 77.0
   //   alike: 16 x 2K with a max_seq_len of 32K 20.7 -> 20.8, 16 x 8K 60.0 -> 59.4, 31 x 3000 43.5 -> 43.5;  8 x 8K, 32 KV heads 109.4 -> 109.0
